@@ -81,6 +81,8 @@ static int validate_lcg(const mcrng_lcg* L, uint32_t min_m, LcgDev* out) {
     out->c = L->c & out->mask;
     out->m = L->m;
     out->shift53 = L->m >= 53 ? L->m - 53 : 0;
+    out->up = 64 - L->m;
+    out->cz = out->c << out->up;
     return MCRNG_OK;
 }
 
@@ -378,6 +380,7 @@ struct mcrng_ctx {
     uint32_t n_problems = 0;
     uint32_t max_cells = 0, max_tedges = 0, max_slice = 0;
     bool any_timed = false;
+    bool one_region = false;      // every problem has one region
     uint64_t partial_words = 0;
 
     std::map<uint64_t, hipGraphExec_t> graphs;          // (tables, opts) -> executable
@@ -597,6 +600,7 @@ static bool chain_planned(const mcrng_problem* P, uint32_t n, const mcrng_run_op
     a.max_cells = P[0].n_regions + P[0].n_space_bins;
     a.max_tedges = P[0].n_time_bins ? P[0].n_time_bins + 1 : 0;
     a.tally_copies = 1;
+    a.one_region = P[0].n_regions == 1;
     TransportParams b = a;
     b.tally_copies = 2;
     LaunchShape s{};
@@ -637,6 +641,7 @@ static int build_tables(mcrng_ctx* ctx, const LcgDev& L, const mcrng_problem* P,
     ctx->h_pu_begin.assign(n + 1, 0);
     ctx->max_cells = ctx->max_tedges = ctx->max_slice = 0;
     ctx->any_timed = false;
+    ctx->one_region = true;
     uint64_t slot = 0, out_off = 0;
     *warn = MCRNG_OK;
     for (uint32_t p = 0; p < n; ++p) {
@@ -663,6 +668,7 @@ static int build_tables(mcrng_ctx* ctx, const LcgDev& L, const mcrng_problem* P,
         D.cell_off = static_cast<uint32_t>(ctx->h_sig64.size());
         D.edge_off = static_cast<uint32_t>(ctx->h_edges64.size());
         D.n_cells = nc;
+        if (Q.n_regions != 1) ctx->one_region = false;
         uint32_t reg = 0, sb = 0;
         for (uint32_t c = 0; c < nc; ++c) {
             while (reg + 1 < Q.n_regions && Q.region_edges[reg + 1] <= E[c]) ++reg;
@@ -920,6 +926,7 @@ extern "C" int mcrng_run_histories(mcrng_ctx* ctx, const mcrng_lcg* lcg, const m
 static int enqueue_run(mcrng_ctx* ctx, const LcgDev& L, const mcrng_run_opts& o, hipStream_t st) {
     TransportParams tp = make_params(ctx, L, o.tally_copies == 2 ? std::max<uint32_t>(o.block / 64, 1) : 1);
     tp.coll_batch = o.coll_batch;
+    tp.one_region = ctx->one_region && o.hist_per_lane == 1;
     LaunchShape sh;
     sh.block = static_cast<int>(o.block);
     sh.hist_per_lane = static_cast<int>(o.hist_per_lane);
@@ -1475,9 +1482,10 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     pp.hash = hash ? 1u : 0u;
     const double nu_floor = std::floor(P->multiplicity);
     pp.n_floor = static_cast<uint32_t>(nu_floor);
-    pp.nu_frac = P->multiplicity - nu_floor;
+    const double nu_frac = P->multiplicity - nu_floor;
+    pp.frac_below = uniform_below(nu_frac);
     pp.sigma_t = P->sigma_t;
-    pp.scatter = P->scatter;
+    pp.scatter_below = uniform_below(P->scatter);
     pp.x_lo = P->x_lo;
     pp.x_hi = P->x_hi;
     pp.t_end = P->time_edges[P->n_time_bins];
@@ -1495,7 +1503,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
         warn = rc;
         pp.stride_q = P->seeding.stride;
     }
-    const uint32_t n_max = pp.n_floor + (pp.nu_frac > 0.0 ? 1u : 0u);
+    const uint32_t n_max = pp.n_floor + (nu_frac > 0.0 ? 1u : 0u);
 
     ctx->h_pulse_tedges.assign(P->time_edges, P->time_edges + P->n_time_bins + 1);
     if ((rc = upload(ctx->pulse_tedges, ctx->h_pulse_tedges, st)) < 0) return rc;

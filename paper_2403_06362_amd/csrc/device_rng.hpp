@@ -23,16 +23,12 @@ struct LcgDev {
     uint64_t mask;      // 2^m - 1 (all ones for m = 64)
     uint32_t shift53;   // m - 53: right shift that keeps the top 53 state bits
     uint32_t m;
+    uint64_t cz;        // c << up: the increment of the top-aligned state
+    uint32_t up;        // 64 - m: the top-aligned state is Z = X << up
 };
 
 __device__ __forceinline__ uint64_t lcg_next(const LcgDev& L, uint64_t x) {
     return (L.g * x + L.c) & L.mask;
-}
-
-// The same step for m >= 32, where the mask leaves the low word alone (one
-// AND on the high word instead of two).
-__device__ __forceinline__ uint64_t lcg_next_wide(const LcgDev& L, uint64_t x) {
-    return (L.g * x + L.c) & (L.mask | 0xffffffffull);
 }
 
 __device__ __forceinline__ uint64_t affine_apply(uint64_t G, uint64_t C, uint64_t mask, uint64_t x) {
@@ -64,15 +60,109 @@ __host__ __device__ __forceinline__ uint64_t murmur_hash(uint64_t k, uint64_t s)
     return murmur_with_seed_part(k, murmur_seed_part(s));
 }
 
-// u = ((X >> (m - 53)) + 1) * 2^-53.  The integer is at most 2^53, so the
-// conversion to double is exact.
-// The integer's halves are converted separately and joined by one fused
-// multiply-add, hi 2^32 + lo, exact (as the plain conversion is) below 2^53.
-__device__ __forceinline__ double to_uniform(const LcgDev& L, uint64_t x) {
-    const uint64_t top = (x >> L.shift53) + 1ull;
-    const double hi = static_cast<double>(static_cast<uint32_t>(top >> 32));
-    const double lo = static_cast<double>(static_cast<uint32_t>(top));
-    return __builtin_fma(hi, 0x1p32, lo) * 0x1p-53;
+// ------------------------------------------------------------ top-aligned states
+// The transport and pulse kernels carry the state as Z = X << (64 - m).  One
+// step is Z <- g Z + (c << (64 - m)) modulo 2^64, which is eq. (1) shifted, so
+// no mask is left in the chain, and the 53 bits of the uniform sit in Z's top
+// bits whatever m is, so every shift is a constant.
+__device__ __forceinline__ uint64_t lcg_next_z(const LcgDev& L, uint64_t z) { return L.g * z + L.cz; }
+
+// u = ((Z >> 11) + 1) 2^-53 = (hi 2^32 + (lo | 0x7ff) + 1) 2^-64: the low
+// word goes into the mantissa of 2^-12 + lo 2^-64 (no conversion), the high
+// word is converted; both sums are exact, u has 53 bits.  Five instructions
+// (shift, 64-bit add, two conversions, multiply-add and scaling take seven).
+__device__ __forceinline__ double uniform_z(uint64_t z) {
+    const uint32_t lo = static_cast<uint32_t>(z) | 0x7ffu;
+    const double a = __longlong_as_double(static_cast<long long>(0x3f30000000000000ull | lo));
+    const double hi = static_cast<double>(static_cast<uint32_t>(z >> 32));
+    return __builtin_fma(hi, 0x1p-32, a + (0x1p-64 - 0x1p-12));
+}
+
+// u < c for the uniform of state Z is Z < uniform_below(c): (T + 1) 2^-53 < c
+// with T = Z >> 11 is T + 1 < ceil(c 2^53) (c 2^53 is exact).  0 <= c <= 1.
+__host__ __device__ __forceinline__ uint64_t uniform_below(double c) {
+    const uint64_t t = static_cast<uint64_t>(__builtin_ceil(c * 0x1p53));
+    return t == 0 ? 0ull : (t - 1ull) << 11;
+}
+
+// ------------------------------------------------------------ lane masks and selects
+// Wave masks live in scalar registers; a lane's bit is a condition again.
+__device__ __forceinline__ uint64_t wave_mask(bool c) { return __builtin_amdgcn_ballot_w64(c); }
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// A value that is the same on every lane, in scalar registers.
+__device__ __forceinline__ uint64_t uniform_value(uint64_t v) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+__device__ __forceinline__ double uniform_value(double v) {
+    return __longlong_as_double(static_cast<long long>(uniform_value(static_cast<uint64_t>(__double_as_longlong(v)))));
+}
+__device__ __forceinline__ float uniform_value(float v) {
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
+}
+
+// mask bit ? a : b, in the three-operand encoding.  The compiler selects with
+// the short encoding through vcc, and on this chip two of those back to back
+// (the halves of a 64-bit select) take 28 issue cycles, against 9 for the
+// long encoding (measured at 8 waves per SIMD).  A mask that a vector
+// compare has just written may be read as an operand two wait states later.
+__device__ __forceinline__ uint32_t sel(uint64_t m, uint32_t a, uint32_t b) {
+    uint32_t r;
+    asm("s_nop 1\n\tv_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(uniform_value(m)));
+    return r;
+}
+__device__ __forceinline__ float sel(uint64_t m, float a, float b) {
+    return __uint_as_float(sel(m, __float_as_uint(a), __float_as_uint(b)));
+}
+__device__ __forceinline__ uint64_t sel(uint64_t m, uint64_t a, uint64_t b) {
+    uint32_t lo, hi;
+    asm("s_nop 1\n\tv_cndmask_b32_e64 %0, %2, %3, %6\n\tv_cndmask_b32_e64 %1, %4, %5, %6"
+        : "=&v"(lo), "=v"(hi)
+        : "v"(static_cast<uint32_t>(b)), "v"(static_cast<uint32_t>(a)), "v"(static_cast<uint32_t>(b >> 32)),
+          "v"(static_cast<uint32_t>(a >> 32)), "s"(uniform_value(m)));
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+__device__ __forceinline__ double sel(uint64_t m, double a, double b) {
+    return __longlong_as_double(static_cast<long long>(sel(m, static_cast<uint64_t>(__double_as_longlong(a)),
+                                                           static_cast<uint64_t>(__double_as_longlong(b)))));
+}
+// mask bit ? A : B with small constants (-16 .. 64).
+template <int A, int B>
+__device__ __forceinline__ uint32_t sel_const(uint64_t m) {
+    uint32_t r;
+    asm("s_nop 1\n\tv_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "n"(B), "n"(A), "s"(uniform_value(m)));
+    return r;
+}
+// mask bit ? v : 0
+__device__ __forceinline__ uint32_t sel_or_zero(uint64_t m, uint32_t v) {
+    uint32_t r;
+    asm("s_nop 1\n\tv_cndmask_b32_e64 %0, 0, %1, %2" : "=v"(r) : "v"(v), "s"(uniform_value(m)));
+    return r;
+}
+
+// Minima and maxima of numbers (never NaN), one instruction each: fmin and
+// fmax of a loaded value first quiet it with another.
+__device__ __forceinline__ double min_num(double a, double b) {
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double max_num(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float min_num(float a, float b) {
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float max_num(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
 }
 
 // ------------------------------------------------------------ division
@@ -84,10 +174,13 @@ __device__ __forceinline__ double to_uniform(const LcgDev& L, uint64_t x) {
 // the exponent range.  The refined reciprocal depends on b alone, so a
 // divisor used many times (a cell's sigma_t, a flight's direction cosine)
 // has it computed once.  quot(a, b, recip_refined(b)) then equals a / b bit
-// for bit wherever the scaling does not act, which holds when |a| is at
-// least 2^-900 (single: 2^-60), b is nonzero with |b| in [2^-64, 2^64] and
-// |a| is at most 2^42: what the transport's validated geometry allows.  A
-// smaller |a| (zero included) takes the plain division.
+// for bit wherever the scaling does not act and no intermediate leaves the
+// normal range, which holds when |a| is at least 2^-900 (single: 2^-100), the
+// quotient is at least 2^-700 (single: 2^-36), b is nonzero with |b| in
+// [2^-64, 2^64] and |a| is at most 2^42: what the transport's validated
+// geometry allows above a smallest quotient (kQuotMin).  The callers take
+// the plain division for a smaller quotient.  a = 0 gives 0 (its sign never
+// matters); b = 0 gives NaN.
 __device__ __forceinline__ double recip_refined(double b) {
     double r = __builtin_amdgcn_rcp(b);
     r = __builtin_fma(r, __builtin_fma(-b, r, 1.0), r);
@@ -96,7 +189,6 @@ __device__ __forceinline__ double recip_refined(double b) {
 }
 
 __device__ __forceinline__ double quot(double a, double b, double r) {
-    if (!(__builtin_fabs(a) >= 0x1p-900)) return a / b;
     const double q = a * r;
     return __builtin_fma(__builtin_fma(-b, q, a), r, q);
 }
@@ -107,11 +199,21 @@ __device__ __forceinline__ float recip_refined(float b) {
 }
 
 __device__ __forceinline__ float quot(float a, float b, float r) {
-    if (!(__builtin_fabsf(a) >= 0x1p-60f)) return a / b;
     float q = a * r;
     q = __builtin_fmaf(__builtin_fmaf(-b, q, a), r, q);
     return __builtin_fmaf(__builtin_fmaf(-b, q, a), r, q);
 }
+
+// With b a cross section in [2^-64, 2^64] or a direction cosine (a multiple
+// of 2^-52, at most 1), a quotient of at least kQuotMin has |a| >= 2^-764
+// (single: 2^-100), so one comparison of the smaller of a flight's two
+// distances covers both divisions.
+template <class R>
+struct QuotMin;
+template <>
+struct QuotMin<double> { static constexpr double v = 0x1p-700; };
+template <>
+struct QuotMin<float> { static constexpr float v = 0x1p-36f; };
 
 // Natural logarithm of u in (0, 1] (any positive normal double works).
 // Fixed sequence of IEEE double operations, each rounded to nearest, no
@@ -129,14 +231,11 @@ __device__ __forceinline__ double fixed_log(double u) {
     constexpr double kC[12] = {0.0,        2.0 / 3.0,  2.0 / 5.0,  2.0 / 7.0,
                                2.0 / 9.0,  2.0 / 11.0, 2.0 / 13.0, 2.0 / 15.0,
                                2.0 / 17.0, 2.0 / 19.0, 2.0 / 21.0, 2.0 / 23.0};
-    const uint64_t bits = __double_as_longlong(u);
-    int e = static_cast<int>((bits >> 52) & 0x7ff) - 1023;
-    double f = __longlong_as_double(static_cast<long long>((bits & 0x000fffffffffffffull) |
-                                                           0x3ff0000000000000ull));
-    if (f >= 1.5) {
-        f = f * 0.5;
-        e = e + 1;
-    }
+    // u = m 2^E, m in [1/2, 1): m < 3/4 gives f = 2m, e = E - 1, else f = m, e = E
+    const double m = __builtin_amdgcn_frexp_mant(u);
+    const uint32_t i = sel_const<1, 0>(wave_mask(m < 0.75));
+    const int e = __builtin_amdgcn_frexp_exp(u) - static_cast<int>(i);
+    const double f = __builtin_amdgcn_ldexp(m, static_cast<int>(i));
     const double a = f - 1.0;
     const double b = 2.0 + a;
     const double s = quot(a, b, recip_refined(b));   // a in {0} or [2^-53, 1/2), b in [7/4, 5/2)
@@ -159,6 +258,25 @@ __device__ __forceinline__ double fixed_log(double u) {
 // Quantised track length: q = round-half-even(s * 2^56) for 0 <= s < 2^7.
 __device__ __forceinline__ uint64_t quantise(double s) {
     return static_cast<uint64_t>(__builtin_rint(s * 0x1p56));
+}
+
+// q as two limbs, q = lo + 2^32 hi, 0 <= hi < 2^31, |lo| <= 2^31, each a
+// 64-bit word (lo signed).  Adding 1.5 x 2^28 rounds s to a multiple of 2^-24
+// and leaves that multiple in the sum's low word; the exact rest (at most
+// 2^-25) plus 1.5 x 2^-4 rounds half-even to a multiple of 2^-56 (2^32 hi is
+// even, so ties go the same way as in one rounding of s), left in the low
+// word with its sign borrowed from the high word.
+struct Limbs {
+    uint64_t lo, hi;
+};
+__device__ __forceinline__ Limbs quantise_limbs(double s) {
+    const double t = s + 0x1.8p28;
+    const double rest = s - (t - 0x1.8p28);
+    const uint64_t u = static_cast<uint64_t>(__double_as_longlong(rest + 0x1.8p-4));
+    Limbs q;
+    q.lo = (static_cast<uint64_t>(static_cast<uint32_t>(u >> 32) - 0x3fb80000u) << 32) | static_cast<uint32_t>(u);
+    q.hi = static_cast<uint32_t>(static_cast<uint64_t>(__double_as_longlong(t)));
+    return q;
 }
 
 }  // namespace mcrng

@@ -45,24 +45,56 @@ __device__ __forceinline__ BankView<F32> view(const EventBank& b) {
 }
 
 template <bool F32>
-__device__ __forceinline__ CellsLds<F32> global_cells(const TransportParams& P, const DevProblem& PR) {
-    CellsLds<F32> C;
+__device__ __forceinline__ GlobalCells<F32> global_cells(const TransportParams& P, const DevProblem& PR) {
+    GlobalCells<F32> C;
     if constexpr (F32) {
-        C.edge = P.edges32 + PR.edge_off;
-        C.sig = P.sig32 + PR.cell_off;
+        C.edges = P.edges32 + PR.edge_off;
+        C.sigs = P.sig32 + PR.cell_off;
         C.tedge = P.tedges32 + PR.tedge_off;
     } else {
-        C.edge = P.edges64 + PR.edge_off;
-        C.sig = P.sig64 + PR.cell_off;
+        C.edges = P.edges64 + PR.edge_off;
+        C.sigs = P.sig64 + PR.cell_off;
         C.tedge = P.tedges64 + PR.tedge_off;
     }
-    C.rsig = nullptr;   // each event refines its cell's reciprocal
     C.scat = P.scat64 + PR.cell_off;
-    C.bin = P.cbin + PR.cell_off;
-    C.n_cells = static_cast<int32_t>(PR.n_cells);
+    C.bins = P.cbin + PR.cell_off;
+    C.n_off = PR.n_cells * static_cast<uint32_t>(sizeof(typename GlobalCells<F32>::R));
     C.n_time_bins = static_cast<int32_t>(PR.n_time_bins);
     C.n_space_bins = static_cast<int32_t>(PR.n_space_bins);
     return C;
+}
+
+// A live particle of the bank with the counts of its history.
+template <bool F32>
+struct EventParticle {
+    Particle<F32> p;
+    bool need_tau;          // the next event starts by sampling a flight
+    uint32_t draws, events, colls;
+};
+
+// One whole event (the schedule's unit of work), counted.  Lanes of a wave
+// call it together; each lane's outcome is END_NONE or its history's end.
+template <bool F32, bool TIMED, class Tally>
+__device__ __forceinline__ int step_particle(EventParticle<F32>& e, const GlobalCells<F32>& C, const LcgDev& L,
+                                             const Tally& tally) {
+    if (e.need_tau) {
+        sample_tau<F32>(e.p, L);
+        e.draws++;
+        e.need_tau = false;
+    }
+    e.events++;
+    const GeomOut o = geom_pass<F32, TIMED>(e.p, C, wave_mask(true), tally);
+    const uint64_t absorbed = collide_pass<F32>(e.p, C, L, o.coll);
+    int end = END_NONE;
+    if (in_mask(o.coll)) {
+        e.colls++;
+        e.draws += in_mask(absorbed) ? 1u : 2u;
+        e.need_tau = !in_mask(absorbed);
+    }
+    if (in_mask(absorbed)) end = END_ABSORBED;
+    if (in_mask(o.leak)) end = in_mask(o.right) ? END_LEAK_RIGHT : END_LEAK_LEFT;
+    if (TIMED && in_mask(o.census)) end = END_CENSUS;
+    return end;
 }
 
 // A bank particle's cell word carries its need-a-flight flag in bit 31
@@ -70,31 +102,53 @@ __device__ __forceinline__ CellsLds<F32> global_cells(const TransportParams& P, 
 // per event.
 constexpr uint32_t kNeedTauBit = 0x80000000u;
 
-template <bool F32>
-__device__ __forceinline__ void load_cell(const EventBank& b, uint32_t i, Particle<F32>& p) {
-    const uint32_t w = static_cast<uint32_t>(b.cell[i]);
-    p.cell = static_cast<int32_t>(w & ~kNeedTauBit);
-    p.need_tau = (w & kNeedTauBit) != 0;
-}
-
 // TIMED false: no problem of the set is timed, so a particle's time is never
 // read and is not stored.
 template <bool F32, bool TIMED>
-__device__ __forceinline__ void store_particle(const EventBank& b, uint32_t i, const Particle<F32>& p, uint32_t ev,
-                                               uint32_t co, uint32_t unit, uint32_t rec) {
+__device__ __forceinline__ void load_particle(const EventBank& b, uint32_t i, EventParticle<F32>& e) {
     BankView<F32> v = view<F32>(b);
-    v.x[i] = p.x;
-    v.mu[i] = p.mu;
-    if (TIMED) v.t[i] = p.t;
-    v.tau[i] = p.tau;
-    b.X[i] = p.X;
-    b.cell[i] = static_cast<int32_t>(static_cast<uint32_t>(p.cell) | (p.need_tau ? kNeedTauBit : 0u));
-    b.tb[i] = p.tb;
-    b.hdraws[i] = p.hdraws;
-    b.events[i] = ev;
-    b.colls[i] = co;
+    e.p.x = v.x[i];
+    e.p.mu = v.mu[i];
+    e.p.rmu = recip_refined(e.p.mu);
+    e.p.t = TIMED ? v.t[i] : 0;
+    e.p.tau = v.tau[i];
+    e.p.Z = b.X[i];
+    const uint32_t w = static_cast<uint32_t>(b.cell[i]);
+    e.p.off = (w & ~kNeedTauBit) * static_cast<uint32_t>(sizeof(typename Particle<F32>::R));
+    e.need_tau = (w & kNeedTauBit) != 0;
+    e.p.tb = b.tb[i];
+    e.draws = b.hdraws[i];
+    e.events = b.events[i];
+    e.colls = b.colls[i];
+}
+
+template <bool F32, bool TIMED>
+__device__ __forceinline__ void store_particle(const EventBank& b, uint32_t i, const EventParticle<F32>& e,
+                                               uint32_t unit, uint32_t rec) {
+    BankView<F32> v = view<F32>(b);
+    v.x[i] = e.p.x;
+    v.mu[i] = e.p.mu;
+    if (TIMED) v.t[i] = e.p.t;
+    v.tau[i] = e.p.tau;
+    b.X[i] = e.p.Z;
+    const uint32_t cell = e.p.off / static_cast<uint32_t>(sizeof(typename Particle<F32>::R));
+    b.cell[i] = static_cast<int32_t>(cell | (e.need_tau ? kNeedTauBit : 0u));
+    b.tb[i] = e.p.tb;
+    b.hdraws[i] = e.draws;
+    b.events[i] = e.events;
+    b.colls[i] = e.colls;
     b.unit[i] = unit;
     b.rec[i] = rec;
+}
+
+template <bool F32>
+__device__ __forceinline__ void store_record(HistoryRecord* records, uint32_t rec, const EventParticle<F32>& e, int end) {
+    HistoryRecord h;
+    h.events = e.events;
+    h.collisions = e.colls;
+    h.draws = e.draws;
+    h.end = static_cast<uint32_t>(end);
+    records[rec] = h;
 }
 
 // Particle i of the slice [unit_begin, unit_end): the unit is found by binary
@@ -111,7 +165,7 @@ __global__ void __launch_bounds__(256) k_event_init(EventParams E) {
     }
     const WorkUnit U = E.tp.units[lo];
     const DevProblem PR = E.tp.problems[U.problem];
-    const CellsLds<F32> C = global_cells<F32>(E.tp, PR);
+    const GlobalCells<F32> C = global_cells<F32>(E.tp, PR);
     const uint32_t su = E.one_group ? E.unit_begin : lo;   // score unit
     SeedDev S;
     S.kind = static_cast<int>(PR.seed_kind);
@@ -119,9 +173,10 @@ __global__ void __launch_bounds__(256) k_event_init(EventParams E) {
     S.base = PR.seed_base;
     S.first_index = PR.first_index;
     S.table = PR.table;
-    Particle<F32> p;
-    init_particle<F32, TIMED>(p, C, E.tp.lcg, S, U.j0 + (r - E.rec_begin[lo]));
-    store_particle<F32, TIMED>(E.in, i, p, 0u, 0u, su, static_cast<uint32_t>(r));
+    EventParticle<F32> e{};
+    init_particle_at<F32, TIMED>(e.p, C, stream_start_z(E.tp.lcg, S, U.j0 + (r - E.rec_begin[lo])));
+    e.need_tau = true;
+    store_particle<F32, TIMED>(E.in, i, e, su, static_cast<uint32_t>(r));
 }
 
 constexpr int kEventStepBlock = 1024;
@@ -168,41 +223,23 @@ __global__ void __launch_bounds__(kEventStepBlock) k_event_step(EventParams E) {
     for (int k = 0; k < kEventStepPer; ++k) {
         const uint32_t i = b0 + static_cast<uint32_t>(k) * kEventStepBlock + threadIdx.x;
         bool alive = false;
-        Particle<F32> p;
+        EventParticle<F32> e{};
         uint32_t unit = 0, rec = 0;
-        LaneCounters cnt;
         if (i < n_in) {
-            BankView<F32> v = view<F32>(E.in);
-            p.x = v.x[i];
-            p.mu = v.mu[i];
-        set_direction<F32>(p);
-            set_direction<F32>(p);
-            p.t = TIMED ? v.t[i] : 0;
-            p.tau = v.tau[i];
-            p.X = E.in.X[i];
-            load_cell<F32>(E.in, i, p);
-            p.tb = E.in.tb[i];
-            p.hdraws = E.in.hdraws[i];
-            cnt.events = E.in.events[i];
-            cnt.collisions = E.in.colls[i];
+            load_particle<F32, TIMED>(E.in, i, e);
             unit = E.in.unit[i];
             rec = E.in.rec[i];
             const WorkUnit U = E.tp.units[unit];
             const DevProblem PR = E.tp.problems[U.problem];
-            const CellsLds<F32> C = global_cells<F32>(E.tp, PR);
-            const int end = (unit == home)  ? step_particle<F32, TIMED>(p, C, E.tp.lcg, reinterpret_cast<uint64_t*>(s_tally), cnt)
-                            : E.one_group   ? step_particle<F32, TIMED, true>(p, C, E.tp.lcg, E.tp.partial + U.slot, cnt)
-                                            : step_particle<F32, TIMED>(p, C, E.tp.lcg, E.tp.partial + U.slot, cnt);
-            if (end != END_NONE) {
-                HistoryRecord h;
-                h.events = static_cast<uint32_t>(cnt.events);
-                h.collisions = static_cast<uint32_t>(cnt.collisions);
-                h.draws = p.hdraws;
-                h.end = static_cast<uint32_t>(end);
-                E.records[rec] = h;
-            } else {
+            const GlobalCells<F32> C = global_cells<F32>(E.tp, PR);
+            const int end = (unit == home) ? step_particle<F32, TIMED>(e, C, E.tp.lcg,
+                                                                      PairTally<false>{reinterpret_cast<uint64_t*>(s_tally)})
+                            : E.one_group  ? step_particle<F32, TIMED>(e, C, E.tp.lcg, PairTally<true>{E.tp.partial + U.slot})
+                                           : step_particle<F32, TIMED>(e, C, E.tp.lcg, PairTally<false>{E.tp.partial + U.slot});
+            if (end != END_NONE)
+                store_record(E.records, rec, e, end);
+            else
                 alive = true;
-            }
         }
         // compaction: the block's survivors go to consecutive slots of `out`
         // through one atomic per block and pass (a single counter hit once
@@ -222,8 +259,7 @@ __global__ void __launch_bounds__(kEventStepBlock) k_event_step(EventParams E) {
         __syncthreads();
         if (alive) {
             const uint32_t lt = static_cast<uint32_t>(__popcll(mask & ((lane == 0) ? 0ull : (~0ull >> (64 - lane)))));
-            store_particle<F32, TIMED>(E.out, s_base + s_wave_count[wid] + lt, p, static_cast<uint32_t>(cnt.events),
-                                static_cast<uint32_t>(cnt.collisions), unit, rec);
+            store_particle<F32, TIMED>(E.out, s_base + s_wave_count[wid] + lt, e, unit, rec);
         }
         __syncthreads();   // s_wave_count and s_base are reused by the next pass
     }
@@ -248,40 +284,23 @@ __global__ void __launch_bounds__(256) k_event_finish(EventParams E) {
     for (uint32_t w = threadIdx.x; w < words; w += 256) s_tally[w] = 0;
     __syncthreads();
     if (i < n_in) {
-        BankView<F32> v = view<F32>(E.in);
-        Particle<F32> p;
-        LaneCounters cnt;
-        p.x = v.x[i];
-        p.mu = v.mu[i];
-        set_direction<F32>(p);
-        p.t = TIMED ? v.t[i] : 0;
-        p.tau = v.tau[i];
-        p.X = E.in.X[i];
-        load_cell<F32>(E.in, i, p);
-        p.tb = E.in.tb[i];
-        p.hdraws = E.in.hdraws[i];
-        cnt.events = E.in.events[i];
-        cnt.collisions = E.in.colls[i];
+        EventParticle<F32> e;
+        load_particle<F32, TIMED>(E.in, i, e);
         const uint32_t unit = E.in.unit[i];
         const uint32_t rec = E.in.rec[i];
         const WorkUnit U = E.tp.units[unit];
         const DevProblem PR = E.tp.problems[U.problem];
-        const CellsLds<F32> C = global_cells<F32>(E.tp, PR);
+        const GlobalCells<F32> C = global_cells<F32>(E.tp, PR);
         uint64_t* tally = E.tp.partial + U.slot;
         int end = END_NONE;
         if (words != 0)
             while (end == END_NONE)
-                end = step_particle<F32, TIMED>(p, C, E.tp.lcg, reinterpret_cast<uint64_t*>(s_tally), cnt);
+                end = step_particle<F32, TIMED>(e, C, E.tp.lcg, PairTally<false>{reinterpret_cast<uint64_t*>(s_tally)});
         else if (E.one_group)
-            while (end == END_NONE) end = step_particle<F32, TIMED, true>(p, C, E.tp.lcg, tally, cnt);
+            while (end == END_NONE) end = step_particle<F32, TIMED>(e, C, E.tp.lcg, PairTally<true>{tally});
         else
-            while (end == END_NONE) end = step_particle<F32, TIMED>(p, C, E.tp.lcg, tally, cnt);
-        HistoryRecord h;
-        h.events = static_cast<uint32_t>(cnt.events);
-        h.collisions = static_cast<uint32_t>(cnt.collisions);
-        h.draws = p.hdraws;
-        h.end = static_cast<uint32_t>(end);
-        E.records[rec] = h;
+            while (end == END_NONE) end = step_particle<F32, TIMED>(e, C, E.tp.lcg, PairTally<false>{tally});
+        store_record(E.records, rec, e, end);
     }
     __syncthreads();
     for (uint32_t w = 2 * threadIdx.x; w < words; w += 2 * 256)

@@ -44,6 +44,20 @@ __device__ __forceinline__ uint64_t stream_start(const LcgDev& L, const SeedDev&
     return x;
 }
 
+// The same state top-aligned (Z = X << (64 - m)): the shift drops what a mask
+// would, and the affine maps need none on the way (they hold modulo 2^m).
+__device__ __forceinline__ uint64_t stream_start_z(const LcgDev& L, const SeedDev& S, uint64_t i) {
+    const uint64_t idx = S.first_index + i;
+    if (S.kind == SEED_HASH) return murmur_with_seed_part(idx + 1ull, S.base) << L.up;
+    uint64_t x = S.base;
+    for (uint32_t d = 0; d < S.stride_digits; ++d) {
+        const uint32_t v = static_cast<uint32_t>(idx >> (kStrideRadixBits * d)) & (kStrideRadix - 1);
+        const uint64_t* e = S.table + 2 * (d * kStrideRadix + v);
+        x = e[0] * x + e[1];
+    }
+    return x << L.up;
+}
+
 // ------------------------------------------------------------ draw kernels
 
 // Round alignment of a stream (the draw kernel for m = 63 and 64 with an odd
@@ -116,6 +130,7 @@ struct TransportParams {
     uint32_t max_slice;          // largest slice_bins
     uint32_t tally_copies;       // 1 or waves per block
     uint32_t coll_batch;         // run a wave's collision phase once this many of its lanes wait (>= 1)
+    uint32_t one_region;         // every problem has one region (its cells are its space bins)
     const double* edges64;       // flat cell arrays
     const double* sig64;
     const double* scat64;

@@ -4,12 +4,16 @@
 //
 // An event is split in three parts that a schedule may run at different
 // times for one particle (never reordered, never skipped):
-//   sample_tau   X = lcg(X); tau = -ln(uniform(X))                 (the flight)
-//   geom_*       distances to collision / edge / time, choice, score,
-//                move; returns END_*, END_NONE (edge or time step) or
-//                STEP_COLLIDE (the particle stands at its collision site)
-//   collide      X = lcg(X), absorbed unless uniform < c; X = lcg(X),
-//                mu = R(2 u - 1); the next part is sample_tau
+//   sample_tau    X = lcg(X); tau = -ln(uniform(X))                 (the flight)
+//   geom_pass     distances to collision / edge / time, choice, score, move
+//   collide_pass  X = lcg(X), absorbed unless uniform < c; X = lcg(X),
+//                 mu = R(2 u - 1); the next part is sample_tau
+// The passes work on a whole wave: the lanes to advance come as a wave mask in
+// scalar registers and the outcomes go out as wave masks, so that a lane's
+// phase costs no vector instruction and both halves of a choice are
+// straight-line selects.  (The slab kernels are bound by vector issue: with
+// the phases in vector registers and a branch per outcome the long-chain slab
+// took 173 vector instructions per event.)
 // Every floating-point result is the IEEE operation's, rounded to nearest,
 // with no fused multiply-add where the operation is a separate multiply and
 // add (the library is built with -ffp-contract=off).  Divisions by a
@@ -31,59 +35,79 @@ struct Particle {
     using R = typename std::conditional<F32, float, double>::type;
     R x, mu, t;         // FP64: global x, t; FP32: x from the cell's left edge, t from the time bin start
     double tau;         // remaining optical depth of the flight (double in both modes)
-    R rmu;              // refined reciprocal of mu (set_direction)
-    R far;              // +inf when mu == 0 (the flight meets no edge), else 0
-    uint64_t X;         // LCG state
-    int32_t cell, tb;
-    uint32_t hdraws;    // numbers drawn by this history
-    bool need_tau;      // the next event starts by sampling a flight
+    R rmu;              // refined reciprocal of mu; NaN when mu == 0 (no edge distance compares below a flight's)
+    uint64_t Z;         // top-aligned LCG state
+    uint32_t off;       // cell index times sizeof(R)
+    int32_t tb;
 };
 
-// Derived direction values, after every change of mu.
-template <bool F32>
-__device__ __forceinline__ void set_direction(Particle<F32>& p) {
-    using R = typename Particle<F32>::R;
-    p.rmu = recip_refined(p.mu);
-    p.far = (p.mu == R(0)) ? static_cast<R>(__builtin_huge_val()) : R(0);
-}
-
-// Cell data of the current problem (LDS-staged or global).  FP64: edge[c]
-// is the position of edge c (n_cells + 1), tedge[t] the time edges.  FP32:
-// edge[c] is the width of cell c, tedge[t] the duration of time bin t.
-// rsig[c] is recip_refined(sig[c]) (staged with the cells), or null: then
-// it is computed per event.
-template <bool F32>
-struct CellsLds {
+// Cell data of the current problem.  FP64: edge c is the position of edge c
+// (n_cells + 1), tedge[t] the time edges.  FP32: entry c + 1 of the edge
+// array is the width of cell c (entry 0 is unused), tedge[t] the duration of
+// time bin t.  Offsets are cell indices times sizeof(R).
+// ONE: one region, so cells are the space bins and sigma_t and c are the
+// same in all of them (kept in registers).
+template <bool F32, bool ONE>
+struct LdsCells {
     using R = typename std::conditional<F32, float, double>::type;
-    const R* edge;
-    const R* sig;       // n_cells
-    const R* rsig;      // n_cells, or null
-    const double* scat; // n_cells (the absorption test stays in double)
-    const int32_t* bin; // n_cells
+    const char* edge_base;
+    const char* sig_base;
+    const char* rsig_base;
+    const char* below_base;
+    const char* bin_base;
     const R* tedge;
-    int32_t n_cells;
+    R sig1, rsig1;
+    uint64_t below1;
+    uint32_t n_off;        // n_cells * sizeof(R)
     int32_t n_time_bins;
     int32_t n_space_bins;
+    __device__ __forceinline__ const R* edge(uint32_t off) const { return reinterpret_cast<const R*>(edge_base + off); }
+    __device__ __forceinline__ R sig(uint32_t off) const {
+        if constexpr (ONE) return sig1;
+        return *reinterpret_cast<const R*>(sig_base + off);
+    }
+    __device__ __forceinline__ R rsig(uint32_t off, R) const {
+        if constexpr (ONE) return rsig1;
+        return *reinterpret_cast<const R*>(rsig_base + off);
+    }
+    // the state bound of the absorption test (uniform_below of the cell's c)
+    __device__ __forceinline__ uint64_t below(uint32_t off) const {
+        if constexpr (ONE) return below1;
+        return *reinterpret_cast<const uint64_t*>(below_base + (F32 ? 2u * off : off));
+    }
+    // 8 x the cell's space bin
+    __device__ __forceinline__ uint32_t bin8(uint32_t off) const {
+        if constexpr (ONE) return F32 ? 2u * off : off;
+        return *reinterpret_cast<const uint32_t*>(bin_base + (F32 ? off : off >> 1));
+    }
 };
 
+// The same from the problem's tables in HBM (edges as LdsCells; FP32 widths
+// start at entry 0, so the entry before cell 0's must not be read).
 template <bool F32>
-__device__ __forceinline__ typename CellsLds<F32>::R cell_recip(const CellsLds<F32>& C, int c,
-                                                               typename CellsLds<F32>::R sig) {
-    return C.rsig ? C.rsig[c] : recip_refined(sig);
-}
-
-enum : int { STEP_COLLIDE = -1, END_NONE = 0, END_LEAK_LEFT, END_LEAK_RIGHT, END_ABSORBED, END_CENSUS };
-
-struct LaneCounters {
-    uint64_t events = 0, draws = 0, collisions = 0;
-    uint32_t histories = 0, leak_left = 0, leak_right = 0, absorbed = 0, census = 0;
-    uint32_t max_draws = 0, over_stride = 0;
+struct GlobalCells {
+    using R = typename std::conditional<F32, float, double>::type;
+    const R* edges;
+    const R* sigs;
+    const double* scat;
+    const int32_t* bins;
+    const R* tedge;
+    uint32_t n_off;
+    int32_t n_time_bins;
+    int32_t n_space_bins;
+    __device__ __forceinline__ const R* edge(uint32_t off) const { return edges + off / sizeof(R) - (F32 ? 1 : 0); }
+    __device__ __forceinline__ R sig(uint32_t off) const { return sigs[off / sizeof(R)]; }
+    __device__ __forceinline__ R rsig(uint32_t, R sig) const { return recip_refined(sig); }
+    __device__ __forceinline__ uint64_t below(uint32_t off) const { return uniform_below(scat[off / sizeof(R)]); }
+    __device__ __forceinline__ uint32_t bin8(uint32_t off) const { return 8u * static_cast<uint32_t>(bins[off / sizeof(R)]); }
 };
+
+enum : int { END_NONE = 0, END_LEAK_LEFT, END_LEAK_RIGHT, END_ABSORBED, END_CENSUS };
 
 // Adds q to a tally word pair: the low and the high 32-bit halves of q are
 // summed into separate 64-bit words (LDS or global memory); the pair holds
 // low + 2^32 high.
-__device__ __forceinline__ void lds_score(uint64_t* slot, uint64_t q) {
+__device__ __forceinline__ void pair_score(uint64_t* slot, uint64_t q) {
     atomicAdd(reinterpret_cast<unsigned long long*>(slot), static_cast<unsigned long long>(q & 0xffffffffull));
     atomicAdd(reinterpret_cast<unsigned long long*>(slot + 1), static_cast<unsigned long long>(q >> 32));
 }
@@ -97,24 +121,48 @@ __device__ __forceinline__ void carry_add(uint64_t* slot, uint64_t lo, uint64_t 
     if (hi != 0) atomicAdd(reinterpret_cast<unsigned long long*>(slot + 1), static_cast<unsigned long long>(hi));
 }
 
-// A score: lds_score, or (CARRY) carry_add into a global pair.
+// Tally of an event schedule's particle: word pairs, added plainly or (CARRY)
+// with carry_add.
 template <bool CARRY>
-__device__ __forceinline__ void add_score(uint64_t* slot, uint64_t q) {
-    if constexpr (CARRY)
-        carry_add(slot, q & 0xffffffffull, q >> 32);
-    else
-        lds_score(slot, q);
-}
+struct PairTally {
+    uint64_t* tally;
+    __device__ __forceinline__ void add(uint32_t bin8, double s) const {
+        const uint64_t q = quantise(s);
+        if constexpr (CARRY)
+            carry_add(tally + bin8 / 4, q & 0xffffffffull, q >> 32);
+        else
+            pair_score(tally + bin8 / 4, q);
+    }
+};
+
+// A unit's tally slice in LDS: the low limbs of all bins, then (hi_off bytes
+// on) the high limbs.  Words of one limb lie next to each other, so lanes in
+// neighbouring bins use all banks (as pairs, half of them per add).
+struct LimbTally {
+    char* lo;
+    uint32_t hi_off;
+    __device__ __forceinline__ void add(uint32_t bin8, double s) const {
+        const Limbs q = quantise_limbs(s);
+        char* const w = lo + bin8;
+        atomicAdd(reinterpret_cast<unsigned long long*>(w), static_cast<unsigned long long>(q.lo));
+        atomicAdd(reinterpret_cast<unsigned long long*>(w + hi_off), static_cast<unsigned long long>(q.hi));
+    }
+};
 
 template <bool F32>
 __device__ __forceinline__ void sample_tau(Particle<F32>& p, const LcgDev& L) {
-    p.X = lcg_next_wide(L, p.X);
-    p.hdraws++;
-    p.tau = -fixed_log(to_uniform(L, p.X));
-    p.need_tau = false;
+    p.Z = lcg_next_z(L, p.Z);
+    p.tau = -fixed_log(uniform_z(p.Z));
 }
 
-// FP64 geometry in global coordinates:
+// Outcomes of a geometry pass, subsets of the lanes it advanced: at a
+// collision site; out of the slab (right: of those, past the right face);
+// past the last time edge.  The others go on with their flight.
+struct GeomOut {
+    uint64_t coll, leak, right, census;
+};
+
+// One geometry step of the lanes in G.  FP64, global coordinates:
 //   s = tau / sig[c]                                          -> collision
 //   se = (E[c+1] - x) / mu if mu > 0, (E[c] - x) / mu if mu < 0, +inf if
 //   mu == 0;  if se < s: s = se                               -> edge
@@ -125,187 +173,131 @@ __device__ __forceinline__ void sample_tau(Particle<F32>& p, const LcgDev& L) {
 //          mu < 0: x = E[c], c - 1 (leak left past the first)
 //   other: x = x + mu * s, clamped to [E[c], E[c+1]]
 //   time:  tb + 1, t = T[tb+1]; census past the last time edge
-// (far turns the mu == 0 edge distance into +inf or NaN, which loses the
-// strict comparison as +inf does.)
-template <bool TIMED, bool CARRY = false>
-__device__ __forceinline__ int geom_f64(Particle<false>& p, const CellsLds<false>& C, uint64_t* tally) {
-    const int c = p.cell;
-    const double sig = C.sig[c];
-    const double e_lo = C.edge[c], e_hi = C.edge[c + 1];
-    double s = quot(p.tau, sig, cell_recip<false>(C, c, sig));
-    int ev = 0;   // 0 collision, 1 edge, 2 time
-    const bool up = p.mu > 0.0;
-    const double e_to = up ? e_hi : e_lo;
-    const double se = quot(e_to - p.x, p.mu, p.rmu) + p.far;
-    if (se < s) {
-        s = se;
-        ev = 1;
-    }
-    double tnext = 0.0;
-    const bool timed = TIMED && C.n_time_bins > 0;   // a set may mix steady and timed problems
-    if (timed) {
-        tnext = C.tedge[p.tb + 1];
-        const double st = tnext - p.t;
-        if (st < s) {
-            s = st;
-            ev = 2;
-        }
-    }
-    add_score<CARRY>(tally + 2 * (static_cast<uint32_t>(p.tb) * C.n_space_bins + C.bin[c]), quantise(s));
-    if (timed) p.t = __builtin_fmin(p.t + s, tnext);
-    p.tau = __builtin_fmax(p.tau - sig * s, 0.0);
-    if (ev == 1) {
-        const int nc = up ? c + 1 : c - 1;
-        if (nc < 0) return END_LEAK_LEFT;
-        if (nc == C.n_cells) return END_LEAK_RIGHT;
-        p.cell = nc;
-        p.x = e_to;
-        return END_NONE;
-    }
-    p.x = __builtin_fmin(__builtin_fmax(p.x + p.mu * s, e_lo), e_hi);
-    if (timed && ev == 2) {
-        const int ntb = p.tb + 1;
-        p.tb = ntb;
-        p.t = tnext;
-        if (ntb == C.n_time_bins) return END_CENSUS;
-        return END_NONE;
-    }
-    return STEP_COLLIDE;
-}
-
-// FP32 geometry with the position measured from the cell's left edge and
-// the time from the time bin's start (W = cell width, DT = bin duration);
-// the remaining optical depth tau stays double (a float tau would lose
-// absolute precision over a flight's many subtractions, and the flight's
-// last segment, their small remainder, would carry it):
+// FP32, position measured from the cell's left edge and time from the time
+// bin's start (W = cell width, DT = bin duration); the remaining optical
+// depth tau stays double (a float tau would lose absolute precision over a
+// flight's many subtractions, and the flight's last segment, their small
+// remainder, would carry it):
 //   s = R(tau) / sig[c];  se = (W[c] - x)/mu (mu > 0), (0 - x)/mu (mu < 0),
 //   +inf (mu == 0);  timed: st = DT[tb] - t;  strict-less order as in FP64
 //   score q(double(s));  timed: t = t + s, clamped to DT[tb]
 //   tau = tau - double(sig) double(s) (exact product), clamped at 0
 //   edge: mu > 0: c + 1, x = 0;  mu < 0: c - 1, x = W[c - 1]
 //   other: x = x + mu s clamped to [0, W[c]];  time: tb + 1, t = 0
-template <bool TIMED, bool CARRY = false>
-__device__ __forceinline__ int geom_f32(Particle<true>& p, const CellsLds<true>& C, uint64_t* tally) {
-    const int c = p.cell;
-    const float sig = C.sig[c];
-    const float w = C.edge[c];
-    float s = quot(static_cast<float>(p.tau), sig, cell_recip<true>(C, c, sig));
-    int ev = 0;
-    const bool up = p.mu > 0.0f;
-    const float e_to = up ? w : 0.0f;
-    const float se = quot(e_to - p.x, p.mu, p.rmu) + p.far;
-    if (se < s) {
-        s = se;
-        ev = 1;
-    }
-    float dtb = 0.0f;
-    const bool timed = TIMED && C.n_time_bins > 0;
-    if (timed) {
-        dtb = C.tedge[p.tb];
-        const float st = dtb - p.t;
-        if (st < s) {
-            s = st;
-            ev = 2;
-        }
-    }
-    add_score<CARRY>(tally + 2 * (static_cast<uint32_t>(p.tb) * C.n_space_bins + C.bin[c]),
-                     quantise(static_cast<double>(s)));
-    if (timed) p.t = __builtin_fminf(p.t + s, dtb);
-    p.tau = __builtin_fmax(p.tau - static_cast<double>(sig) * static_cast<double>(s), 0.0);
-    if (ev == 1) {
-        if (up) {
-            const int nc = c + 1;
-            if (nc == C.n_cells) return END_LEAK_RIGHT;
-            p.cell = nc;
-            p.x = 0.0f;
-        } else {
-            if (c == 0) return END_LEAK_LEFT;
-            p.cell = c - 1;
-            p.x = C.edge[c - 1];
-        }
-        return END_NONE;
-    }
-    p.x = __builtin_fminf(__builtin_fmaxf(p.x + p.mu * s, 0.0f), w);
-    if (timed && ev == 2) {
-        const int ntb = p.tb + 1;
-        p.tb = ntb;
-        p.t = 0.0f;
-        if (ntb == C.n_time_bins) return END_CENSUS;
-        return END_NONE;
-    }
-    return STEP_COLLIDE;
-}
-
-// CARRY: the tally is a global pair array scored with carry_add.
-template <bool F32, bool TIMED, bool CARRY = false>
-__device__ __forceinline__ int geom_step(Particle<F32>& p, const CellsLds<F32>& C, uint64_t* tally) {
-    if constexpr (F32)
-        return geom_f32<TIMED, CARRY>(p, C, tally);
-    else
-        return geom_f64<TIMED, CARRY>(p, C, tally);
-}
-
-// Collision at the current site: u1 decides absorption (double compare with
-// the cell's scattering ratio), u2 the new direction mu = R(2 u2 - 1)
-// (computed in double, exact, then rounded once).  The next flight is
-// sampled by sample_tau.
-template <bool F32>
-__device__ __forceinline__ int collide(Particle<F32>& p, const CellsLds<F32>& C, const LcgDev& L) {
+// Every lane computes (lanes outside G on whatever their registers hold: any
+// offset in them is a cell's); only the lanes in G score and change state.
+template <bool F32, bool TIMED, class Cells, class Tally>
+__device__ __forceinline__ GeomOut geom_pass(Particle<F32>& p, const Cells& C, uint64_t G, const Tally& tally) {
     using R = typename Particle<F32>::R;
-    p.X = lcg_next_wide(L, p.X);
-    p.hdraws++;
-    const double u1 = to_uniform(L, p.X);
-    if (!(u1 < C.scat[p.cell])) return END_ABSORBED;
-    p.X = lcg_next_wide(L, p.X);
-    p.hdraws++;
-    const double u2 = to_uniform(L, p.X);
-    p.mu = static_cast<R>(2.0 * u2 - 1.0);
-    set_direction<F32>(p);
-    p.need_tau = true;
-    return END_NONE;
+    constexpr int kStep = static_cast<int>(sizeof(R));
+    const uint32_t off = p.off;
+    const R* const ed = C.edge(off);
+    // FP64: the cell's edges; FP32: the widths of the cell before and of the cell
+    R e0, e1;
+    if constexpr (F32 && !std::is_same<Cells, GlobalCells<true>>::value) {
+        e0 = ed[0];
+        e1 = ed[1];
+    } else if constexpr (F32) {
+        e0 = off != 0 ? ed[0] : R(0);
+        e1 = ed[1];
+    } else {
+        e0 = ed[0];
+        e1 = ed[1];
+    }
+    const R e_lo = F32 ? R(0) : e0, e_hi = e1;
+    const R sig = C.sig(off);
+    const R depth = static_cast<R>(p.tau);
+    const uint64_t up = wave_mask(p.mu > R(0));
+    const R e_to = F32 ? static_cast<R>(sel(up, e_hi, R(0))) : sel(up, e_hi, e_lo);
+    const R num = e_to - p.x;
+    const R sc = quot(depth, sig, C.rsig(off, sig));
+    const R se = quot(num, p.mu, p.rmu);
+    uint64_t edge = wave_mask(se < sc);
+    R s = sel(edge, se, sc);
+    if ((wave_mask(!(s >= QuotMin<R>::v)) & G) != 0) {
+        // a distance below the refined quotients' range: plain divisions
+        const R pc = depth / sig;
+        const R pe = p.mu == R(0) ? static_cast<R>(__builtin_huge_val()) : num / p.mu;
+        edge = wave_mask(pe < pc);
+        s = sel(edge, pe, pc);
+    }
+    // a set may mix steady and timed problems, an event schedule's wave too
+    const uint64_t timed = TIMED ? wave_mask(C.n_time_bins > 0) : 0ull;
+    uint64_t time = 0;
+    R tnext = R(0);
+    if (timed != 0) {
+        if (C.n_time_bins > 0) tnext = F32 ? C.tedge[p.tb] : C.tedge[p.tb + 1];
+        const R st = tnext - p.t;
+        time = timed & wave_mask(st < s);
+        s = sel(time, st, s);
+        edge &= ~time;
+    }
+    const uint32_t noff = off + sel_or_zero(edge, sel_const<kStep, -kStep>(up));
+    const uint64_t out = edge & wave_mask(noff >= C.n_off);   // -1 wraps past n_off
+    GeomOut o;
+    o.coll = G & ~(edge | time);
+    o.leak = G & out;
+    o.right = o.leak & up;
+    o.census = 0;
+    uint64_t last = 0;
+    if (timed != 0) {
+        last = wave_mask(p.tb + 1 == C.n_time_bins);
+        o.census = G & time & last;
+    }
+    const uint64_t stay = ~out;
+    if (in_mask(G)) {
+        tally.add((TIMED ? __umul24(static_cast<uint32_t>(p.tb), 8u * static_cast<uint32_t>(C.n_space_bins)) : 0u) +
+                      C.bin8(off),
+                  static_cast<double>(s));
+        p.tau = __builtin_fmax(p.tau - static_cast<double>(sig) * static_cast<double>(s), 0.0);
+        const R moved = min_num(max_num(p.x + p.mu * s, e_lo), e_hi);
+        const R entry = F32 ? sel(up, R(0), e0) : e_to;
+        p.x = sel(edge, entry, moved);
+        p.off = sel(stay, noff, off);
+        if (timed != 0) {
+            p.t = sel(time, F32 ? R(0) : tnext, min_num(p.t + s, tnext));
+            p.tb += static_cast<int32_t>(sel_const<1, 0>(time & ~last));
+        }
+    }
+    return o;
 }
 
-// One whole event (the event-sorted schedule's unit of work), counted.
-template <bool F32, bool TIMED, bool CARRY = false>
-__device__ __forceinline__ int step_particle(Particle<F32>& p, const CellsLds<F32>& C, const LcgDev& L,
-                                             uint64_t* tally, LaneCounters& cnt) {
-    if (p.need_tau) sample_tau<F32>(p, L);
-    cnt.events++;
-    const int r = geom_step<F32, TIMED, CARRY>(p, C, tally);
-    if (r != STEP_COLLIDE) return r;
-    cnt.collisions++;
-    return collide<F32>(p, C, L);
+// Collision of the lanes in W at their sites: u1 decides absorption (the
+// state against the cell's bound), u2 the new direction mu = R(2 u2 - 1)
+// (computed in double, exact, then rounded once).  Returns the absorbed
+// lanes; the others sample their next flight with sample_tau.
+template <bool F32, class Cells>
+__device__ __forceinline__ uint64_t collide_pass(Particle<F32>& p, const Cells& C, const LcgDev& L, uint64_t W) {
+    using R = typename Particle<F32>::R;
+    const uint64_t z1 = lcg_next_z(L, p.Z);
+    const uint64_t go = wave_mask(z1 < C.below(p.off)) & W;
+    if (in_mask(go)) {
+        p.Z = lcg_next_z(L, z1);
+        p.mu = static_cast<R>(__builtin_fma(uniform_z(p.Z), 2.0, -1.0));
+        p.rmu = recip_refined(p.mu);
+    }
+    return W & ~go;
 }
 
-// A new history whose stream starts at state X: source at the left face
+// A new history whose stream starts at state Z: source at the left face
 // moving right, at the first time edge; its first flight is sampled before
 // its first geometry step.
-template <bool F32, bool TIMED>
-__device__ __forceinline__ void init_particle_at(Particle<F32>& p, const CellsLds<F32>& C, uint64_t X) {
+template <bool F32, bool TIMED, class Cells>
+__device__ __forceinline__ void init_particle_at(Particle<F32>& p, const Cells& C, uint64_t Z) {
     using R = typename Particle<F32>::R;
-    p.X = X;
+    p.Z = Z;
     if constexpr (F32) {
         p.x = 0.0f;
         p.t = 0.0f;
     } else {
-        p.x = C.edge[0];
+        p.x = *C.edge(0);
         p.t = (TIMED && C.n_time_bins > 0) ? C.tedge[0] : 0.0;
     }
     p.mu = R(1);
     p.rmu = R(1);   // recip_refined(1) is exactly 1
-    p.far = R(0);
     p.tau = 0.0;
-    p.cell = 0;
+    p.off = 0;
     p.tb = 0;
-    p.hdraws = 0;
-    p.need_tau = true;
-}
-
-// History j (global index) of a problem with seeding S.
-template <bool F32, bool TIMED>
-__device__ __forceinline__ void init_particle(Particle<F32>& p, const CellsLds<F32>& C, const LcgDev& L,
-                                              const SeedDev& S, uint64_t j) {
-    init_particle_at<F32, TIMED>(p, C, stream_start(L, S, j));
 }
 
 }  // namespace mcrng

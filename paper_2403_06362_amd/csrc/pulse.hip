@@ -63,7 +63,7 @@ struct PulseLane {
 
 struct PParticle {
     double x, t;
-    uint64_t X;        // stream state
+    uint64_t Z;        // stream state, top-aligned (X << (64 - m))
     int32_t tb;        // time bin of t (-1 before the first time edge)
     uint32_t batch;
     double mu;         // direction: a census copy's, or the last flight's
@@ -88,12 +88,12 @@ __device__ __forceinline__ uint32_t pulse_flight(const PulseParams& P, PParticle
     if (DIR && p.has_mu) {
         mu = p.mu;
     } else {
-        p.X = lcg_next_wide(L, p.X);
-        mu = 2.0 * to_uniform(L, p.X) - 1.0;
+        p.Z = lcg_next_z(L, p.Z);
+        mu = __builtin_fma(uniform_z(p.Z), 2.0, -1.0);   // exact
         *draws += 1;
     }
-    p.X = lcg_next_wide(L, p.X);
-    const double tau = -fixed_log(to_uniform(L, p.X));
+    p.Z = lcg_next_z(L, p.Z);
+    const double tau = -fixed_log(uniform_z(p.Z));
     *draws += 1;
     const double s = quot(tau, P.sigma_t, recip_refined(P.sigma_t));   // the reciprocal is loop-invariant
     const double tn = p.t + s;
@@ -110,12 +110,12 @@ __device__ __forceinline__ uint32_t pulse_flight(const PulseParams& P, PParticle
         *tally = static_cast<int64_t>(p.batch) * P.n_time_bins + p.tb;
         c.tallied++;
     }
-    p.X = lcg_next_wide(L, p.X);
+    p.Z = lcg_next_z(L, p.Z);
     *draws += 1;
-    if (!(to_uniform(L, p.X) < P.scatter)) return PULSE_ABSORBED;
-    p.X = lcg_next_wide(L, p.X);
+    if (!(p.Z < P.scatter_below)) return PULSE_ABSORBED;
+    p.Z = lcg_next_z(L, p.Z);
     *draws += 1;
-    *n = P.n_floor + (to_uniform(L, p.X) < P.nu_frac ? 1u : 0u);
+    *n = P.n_floor + (p.Z < P.frac_below ? 1u : 0u);
     return PULSE_SCATTERED;
 }
 
@@ -135,16 +135,16 @@ __device__ __forceinline__ uint32_t pulse_particle(const PulseParams& P, PPartic
     return n;
 }
 
-// Start state of source i of the run (0-based over all batches).
+// Start state (top-aligned) of source i of the run (0-based over all batches).
 __device__ __forceinline__ uint64_t pulse_source_state(const PulseParams& P, uint64_t j, uint32_t* batch) {
     const uint64_t b = j / P.per_batch;
     const uint64_t i = j - b * P.per_batch;
     *batch = static_cast<uint32_t>(b);
     if (P.hash) {
         const uint64_t parent = murmur_hash(P.first_batch + b + 1ull, P.seed.base);
-        return murmur_hash(i + 1ull, parent) & P.lcg.mask;
+        return murmur_hash(i + 1ull, parent) << P.lcg.up;
     }
-    return stream_start(P.lcg, P.seed, j);
+    return stream_start_z(P.lcg, P.seed, j);
 }
 
 __device__ __forceinline__ void note_stream(const PulseParams& P, PulseLane& c, uint64_t draws) {
@@ -348,7 +348,7 @@ __device__ __forceinline__ void census_stage(const PulseParams& P, CensusStage& 
         const double step = p.mu * rest;
         CS.x[e] = p.x + step;
         CS.mu[e] = p.mu;
-        CS.X[e] = p.X;
+        CS.X[e] = p.Z >> P.lcg.up;
         CS.batch[e] = p.batch;
     }
     cstaged += cnt;
@@ -362,14 +362,14 @@ __device__ __forceinline__ void load_item(const PulseParams& P, uint64_t j, PPar
         p.x = e.x;
         p.mu = e.mu;
         p.has_mu = true;
-        p.X = e.X;
+        p.Z = e.X;
         p.batch = e.batch;
         p.t = P.t_start;
         p.tb = P.tb_start;
     } else {
         p.x = P.in.x[j];
         p.t = P.in.t[j];
-        p.X = P.in.X[j];
+        p.Z = P.in.X[j];
         p.batch = P.in.batch[j];
         p.tb = P.in.tb[j];
         p.has_mu = false;
@@ -402,7 +402,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_bank(PulseParams P) {
     uint64_t seen = 0;                 // wave-uniform: output count after this wave's last flush
     PParticle p;
     p.x = p.t = 0.0;
-    p.X = 0;
+    p.Z = 0;
     p.tb = -1;
     p.batch = 0;
     p.mu = 0.0;
@@ -427,7 +427,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_bank(PulseParams P) {
         if (!active && rank < take) {
             const uint64_t j = mine;
             if (SOURCES) {
-                p.X = pulse_source_state(P, P.src_begin + j, &p.batch);
+                p.Z = pulse_source_state(P, P.src_begin + j, &p.batch);
                 p.x = 0.0;
                 p.t = 0.0;
                 p.tb = P.tb0;
@@ -470,7 +470,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_bank(PulseParams P) {
                     const uint32_t e = staged + off + (k - k0);
                     S.x[e] = p.x;
                     S.t[e] = p.t;
-                    S.X[e] = murmur_hash(k, p.X) & P.lcg.mask;
+                    S.X[e] = murmur_hash(k, p.Z >> P.lcg.up) << P.lcg.up;
                     S.batch[e] = p.batch;
                     S.tb[e] = p.tb;
                 }
@@ -481,13 +481,13 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_bank(PulseParams P) {
                 if (lane == 0) base = atomicAdd(reinterpret_cast<unsigned long long*>(P.out_count), total);
                 base = lane_value(base, 0);
                 for (uint32_t k = k0; k <= n; ++k)
-                    bank_store(P, base + off + (k - k0), p.x, p.t, murmur_hash(k, p.X) & P.lcg.mask, p.batch, p.tb);
+                    bank_store(P, base + off + (k - k0), p.x, p.t, murmur_hash(k, p.Z >> P.lcg.up) << P.lcg.up, p.batch, p.tb);
                 seen = base + total;
             }
         }
         if (n > 0) {
             if (keep) {
-                p.X = murmur_hash(1ull, p.X) & P.lcg.mask;   // the first emerging particle runs on here
+                p.Z = murmur_hash(1ull, p.Z >> P.lcg.up) << P.lcg.up;   // the first emerging particle runs on here
                 p.has_mu = false;
             } else {
                 active = false;
@@ -510,7 +510,7 @@ __device__ __forceinline__ void spill(const PulseParams& P, double x, double t, 
     const uint64_t base = atomicAdd(reinterpret_cast<unsigned long long*>(P.out_count),
                                     static_cast<unsigned long long>(k1 - k0 + 1));
     for (uint32_t k = k0; k <= k1; ++k)
-        bank_store(P, base + (k - k0), x, t, murmur_hash(k, key) & P.lcg.mask, batch, tb);
+        bank_store(P, base + (k - k0), x, t, murmur_hash(k, key) << P.lcg.up, batch, tb);
 }
 
 // ITEMS = sources: the family schedule.  ITEMS = a generation bank (hash
@@ -606,7 +606,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
 
     PParticle p;
     p.x = p.t = 0.0;
-    p.X = 0;
+    p.Z = 0;
     p.tb = -1;
     p.batch = 0;
     p.mu = 0.0;
@@ -683,7 +683,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
                 const uint64_t j = wbase + rank;
                 if (SOURCES) {
                     const FamilySource e = ring[j - cbase];
-                    p.X = e.X;
+                    p.Z = e.X;
                     p.batch = e.batch;
                     if (SL)
                         lsl = cur_slot >= 0 ? (cur_slot << 16) | static_cast<int32_t>(static_cast<uint32_t>(cur_slot) * 2u * nt +
@@ -727,7 +727,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
             if (n > 1) {
                 if (sp + (has_top ? 1u : 0u) == P.stack_depth) {   // has_top is false unless DEEP
                     if (SPILL) {
-                        spill(P, p.x, p.t, p.tb, p.batch, p.X, 2, n);
+                        spill(P, p.x, p.t, p.tb, p.batch, p.Z >> P.lcg.up, 2, n);
                     } else {
                         atomicOr(P.overflow, 1u);
                         active = false;   // the family is abandoned; the run reports an error
@@ -738,7 +738,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
                     PulseStackEntry e;
                     e.x = p.x;
                     e.t = p.t;
-                    e.key = p.X;
+                    e.key = p.Z >> P.lcg.up;
                     e.tb = p.tb;
                     e.next = 2;
                     e.n = static_cast<uint16_t>(n);
@@ -753,14 +753,14 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
             }
             if (SPILL && budget == 0) {
                 // out of budget: the first emerging particle and the stack go to the bank
-                spill(P, p.x, p.t, p.tb, p.batch, p.X, 1, 1);
+                spill(P, p.x, p.t, p.tb, p.batch, p.Z >> P.lcg.up, 1, 1);
                 spill_stack(P, stack, sstride, sp, top, has_top, p.batch);
                 sp = 0;
                 has_top = false;
                 active = false;
                 continue;
             }
-            if (HASH) p.X = murmur_hash(1ull, p.X) & P.lcg.mask;
+            if (HASH) p.Z = murmur_hash(1ull, p.Z >> P.lcg.up) << P.lcg.up;
             p.has_mu = false;
             continue;   // the first emerging particle starts at once
         }
@@ -782,7 +782,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
         p.t = e.t;
         p.tb = e.tb;
         p.has_mu = false;
-        if (HASH) p.X = murmur_hash(e.next, e.key) & P.lcg.mask;
+        if (HASH) p.Z = murmur_hash(e.next, e.key) << P.lcg.up;
         if (e.next != e.n) {
             e.next++;
         } else if (!DEEP) {
@@ -895,7 +895,7 @@ __global__ void __launch_bounds__(256) k_pulse_split(PulseParams P, uint64_t n) 
                     PulseCensusEntry e;
                     e.x = a.x;
                     e.mu = a.mu;
-                    e.X = murmur_hash(k, a.X) & P.lcg.mask;
+                    e.X = murmur_hash(k, a.X) << P.lcg.up;
                     e.batch = a.batch;
                     e.pad = 0;
                     P.copies_out[o] = e;

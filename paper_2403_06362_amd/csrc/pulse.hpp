@@ -16,7 +16,7 @@ enum PulseDiagWord {
 struct PulseBankView {
     double* x;
     double* t;
-    uint64_t* X;         // start state of the particle's stream
+    uint64_t* X;         // start state of the particle's stream, top-aligned (X << (64 - m))
     uint32_t* batch;
     int32_t* tb;
 };
@@ -33,7 +33,7 @@ struct PulseStackEntry {
 // A census arrival, or a census copy, of a population-controlled run (32 B).
 struct PulseCensusEntry {
     double x, mu;        // census point and direction
-    uint64_t X;          // arrival: stream state after its draws; copy: its start state
+    uint64_t X;          // arrival: stream state after its draws; copy: its start state, top-aligned
     uint32_t batch;      // batch of the run (0-based)
     uint32_t pad;
 };
@@ -47,8 +47,9 @@ struct PulseParams {
     uint32_t n_time_bins;
     uint32_t hash;           // 1: hash seeding (secondaries seeded by eq. 5)
     uint32_t n_floor;        // floor(nu)
-    double nu_frac;          // nu - floor(nu)
-    double sigma_t, scatter, x_lo, x_hi, t_end;
+    uint64_t frac_below;     // uniform_below(nu - floor(nu)): one more particle below it
+    uint64_t scatter_below;  // uniform_below(scatter)
+    double sigma_t, x_lo, x_hi, t_end;
     int32_t tb0;             // time bin of t = 0
     uint32_t stack_depth;    // family schedule: entries per lane
     const double* t_edges;   // device, n_time_bins + 1

@@ -54,17 +54,21 @@ hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t st) 
     return hipGetLastError();
 }
 
-// LDS layout: [tally: copies x max_slice x 2 u64][edges][sig][rsig][scat f64][bin i32][tedges]
+// LDS layout: [tally: copies x (low limbs, high limbs) x max_slice u64][edges]
+// [sig][rsig][below u64][bin i32][tedges]; with one region per problem the
+// four per-cell arrays after the edges are left out (registers hold them).
 __host__ __device__ inline size_t align16(size_t v) { return (v + 15) & ~static_cast<size_t>(15); }
 
 size_t transport_lds_bytes(const TransportParams& p, int f32) {
     const size_t rs = f32 ? sizeof(float) : sizeof(double);
     size_t b = align16(static_cast<size_t>(p.tally_copies) * p.max_slice * 2 * sizeof(uint64_t));
     b += align16((p.max_cells + 1) * rs);
-    b += align16(p.max_cells * rs);
-    b += align16(p.max_cells * rs);
-    b += align16(p.max_cells * sizeof(double));
-    b += align16(p.max_cells * sizeof(int32_t));
+    if (!p.one_region) {
+        b += align16(p.max_cells * rs);
+        b += align16(p.max_cells * rs);
+        b += align16(p.max_cells * sizeof(uint64_t));
+        b += align16(p.max_cells * sizeof(int32_t));
+    }
     b += align16((p.max_tedges > 0 ? p.max_tedges : 1) * rs);
     return b;
 }
@@ -75,24 +79,125 @@ size_t transport_static_lds_bytes(int block) {
            static_cast<size_t>(block / 64) * 128 * (sizeof(uint64_t) + 1) + 512;
 }
 
-// Phase of a lane's history slot.
-enum : int {
-    PH_EMPTY = 0,   // no history: refilled at the next collision pass
-    PH_GEOM = 1,    // has a flight: takes geometry steps
-    PH_COLL = 2,    // stands at a collision site
-    PH_NEW = 3      // a new history or a scattered particle: samples its next flight
+// The block's LDS arrays after the tally slices.
+template <bool F32, bool ONE>
+struct CellArrays {
+    using R = typename Particle<F32>::R;
+    R *edge, *sig, *rsig, *tedge;
+    uint64_t* below;
+    int32_t* bin8;
+    __device__ __forceinline__ CellArrays(const TransportParams& P, unsigned char* smem) {
+        size_t off = align16(static_cast<size_t>(P.tally_copies) * P.max_slice * 2 * sizeof(uint64_t));
+        edge = reinterpret_cast<R*>(smem + off);
+        off += align16((P.max_cells + 1) * sizeof(R));
+        sig = rsig = nullptr;
+        below = nullptr;
+        bin8 = nullptr;
+        if constexpr (!ONE) {
+            sig = reinterpret_cast<R*>(smem + off);
+            off += align16(P.max_cells * sizeof(R));
+            rsig = reinterpret_cast<R*>(smem + off);
+            off += align16(P.max_cells * sizeof(R));
+            below = reinterpret_cast<uint64_t*>(smem + off);
+            off += align16(P.max_cells * sizeof(uint64_t));
+            bin8 = reinterpret_cast<int32_t*>(smem + off);
+            off += align16(P.max_cells * sizeof(int32_t));
+        }
+        tedge = reinterpret_cast<R*>(smem + off);
+    }
 };
 
-__device__ __forceinline__ uint32_t wave_count(bool c) {
-    return static_cast<uint32_t>(__popcll(__builtin_amdgcn_ballot_w64(c)));
+// Stages problem PR's cells, time edges and stride skip table (all threads of
+// the block; the caller synchronises).
+template <bool F32, bool TIMED, bool ONE, int BLOCK>
+__device__ __forceinline__ void stage_problem(const TransportParams& P, const DevProblem& PR,
+                                              const CellArrays<F32, ONE>& A, uint64_t* skip, uint32_t tid) {
+    using R = typename Particle<F32>::R;
+    const R *g_edge, *g_sig, *g_tedge;
+    if constexpr (F32) {
+        g_edge = P.edges32;
+        g_sig = P.sig32;
+        g_tedge = P.tedges32;
+    } else {
+        g_edge = P.edges64;
+        g_sig = P.sig64;
+        g_tedge = P.tedges64;
+    }
+    // FP32: widths from entry 1 on
+    for (uint32_t i = tid; i <= PR.n_cells; i += BLOCK)
+        A.edge[i] = F32 ? (i == 0 ? R(0) : g_edge[PR.edge_off + i - 1]) : g_edge[PR.edge_off + i];
+    if constexpr (!ONE)
+        for (uint32_t i = tid; i < PR.n_cells; i += BLOCK) {
+            const R sg = g_sig[PR.cell_off + i];
+            A.sig[i] = sg;
+            A.rsig[i] = recip_refined(sg);
+            A.below[i] = uniform_below(P.scat64[PR.cell_off + i]);
+            A.bin8[i] = 8 * P.cbin[PR.cell_off + i];
+        }
+    if (TIMED)
+        for (uint32_t i = tid; i <= PR.n_time_bins; i += BLOCK) A.tedge[i] = g_tedge[PR.tedge_off + i];
+    if (PR.seed_kind == SEED_STRIDE)
+        for (uint32_t i = tid; i < PR.stride_digits * kStrideRadix * 2u; i += BLOCK) skip[i] = PR.table[i];
 }
 
-// One history per lane: seven waves per SIMD (72 VGPRs, a few spilled)
-// measured faster than five (FP64) or six (FP32) without spills, except
-// FP64 with time bins, where six (80 VGPRs) is best.
-template <bool F32, bool TIMED, int H, int BLOCK>
-__global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 1) k_transport(TransportParams P) {
+template <bool F32, bool ONE>
+__device__ __forceinline__ LdsCells<F32, ONE> staged_cells(const TransportParams& P, const DevProblem& PR,
+                                                           const CellArrays<F32, ONE>& A) {
     using R = typename Particle<F32>::R;
+    LdsCells<F32, ONE> C;
+    C.edge_base = reinterpret_cast<const char*>(A.edge);
+    C.sig_base = reinterpret_cast<const char*>(A.sig);
+    C.rsig_base = reinterpret_cast<const char*>(A.rsig);
+    C.below_base = reinterpret_cast<const char*>(A.below);
+    C.bin_base = reinterpret_cast<const char*>(A.bin8);
+    C.tedge = A.tedge;
+    C.sig1 = C.rsig1 = R(0);
+    C.below1 = 0;
+    if constexpr (ONE) {
+        R sg;
+        if constexpr (F32)
+            sg = P.sig32[PR.cell_off];
+        else
+            sg = P.sig64[PR.cell_off];
+        C.sig1 = uniform_value(sg);
+        C.rsig1 = uniform_value(recip_refined(sg));
+        C.below1 = uniform_value(uniform_below(P.scat64[PR.cell_off]));
+    }
+    C.n_off = PR.n_cells * static_cast<uint32_t>(sizeof(R));
+    C.n_time_bins = static_cast<int32_t>(PR.n_time_bins);
+    C.n_space_bins = static_cast<int32_t>(PR.n_space_bins);
+    return C;
+}
+
+__device__ __forceinline__ SeedDev problem_seed(const DevProblem& PR, const uint64_t* skip) {
+    SeedDev S;
+    S.kind = static_cast<int>(PR.seed_kind);
+    S.stride_digits = PR.stride_digits;
+    S.base = PR.seed_base;
+    S.first_index = PR.first_index;
+    S.table = skip;
+    return S;
+}
+
+// The limbs of one LDS tally bin as a word pair low + 2^32 high, 0 <= low < 2^32
+// (the low limbs' sum is signed; the bin's total is not negative).
+__device__ __forceinline__ void add_limbs(uint64_t lo, uint64_t hi, uint64_t* plo, uint64_t* phi) {
+    *plo += lo & 0xffffffffull;
+    *phi += hi + static_cast<uint64_t>(static_cast<int64_t>(lo) >> 32);
+}
+
+__device__ __forceinline__ uint32_t mask_count(uint64_t m) { return static_cast<uint32_t>(__popcll(m)); }
+
+// A lane's rank among the lanes of a mask.
+__device__ __forceinline__ uint32_t mask_rank(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+}
+
+// A lane's history slot is flying (its bit in G: takes geometry steps),
+// waiting at a collision site (W), or empty.
+template <bool F32, bool TIMED, bool ONE, int H, int BLOCK>
+__global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 1) k_transport(TransportParams P) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_unit;
     __shared__ uint32_t s_next;
@@ -105,36 +210,13 @@ __global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 
 
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & 63u;
-    const uint32_t wid = tid >> 6;
-
-    uint64_t* tally_all = reinterpret_cast<uint64_t*>(smem);
-    size_t off = align16(static_cast<size_t>(P.tally_copies) * P.max_slice * 2 * sizeof(uint64_t));
-    R* l_edge = reinterpret_cast<R*>(smem + off);
-    off += align16((P.max_cells + 1) * sizeof(R));
-    R* l_sig = reinterpret_cast<R*>(smem + off);
-    off += align16(P.max_cells * sizeof(R));
-    R* l_rsig = reinterpret_cast<R*>(smem + off);
-    off += align16(P.max_cells * sizeof(R));
-    double* l_scat = reinterpret_cast<double*>(smem + off);
-    off += align16(P.max_cells * sizeof(double));
-    int32_t* l_bin = reinterpret_cast<int32_t*>(smem + off);
-    off += align16(P.max_cells * sizeof(int32_t));
-    R* l_tedge = reinterpret_cast<R*>(smem + off);
-
-    const R* g_edge;
-    const R* g_sig;
-    const R* g_tedge;
-    if constexpr (F32) {
-        g_edge = P.edges32;
-        g_sig = P.sig32;
-        g_tedge = P.tedges32;
-    } else {
-        g_edge = P.edges64;
-        g_sig = P.sig64;
-        g_tedge = P.tedges64;
-    }
-
+    const uint32_t wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const CellArrays<F32, ONE> A(P, smem);
     const uint32_t copy = (P.tally_copies > 1) ? (wid % P.tally_copies) : 0u;
+    const uint32_t copy_bytes = P.max_slice * 16u;
+    LimbTally tally;
+    tally.lo = reinterpret_cast<char*>(smem) + static_cast<size_t>(copy) * copy_bytes;
+    tally.hi_off = P.max_slice * 8u;
     int32_t cur_problem = -1;
 
     for (;;) {
@@ -144,67 +226,56 @@ __global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 
         }
         if (tid < kNDiag) s_diag[tid] = 0;
         __syncthreads();
-        const uint32_t pos = s_unit;
+        const uint32_t pos = __builtin_amdgcn_readfirstlane(s_unit);
         if (pos >= P.n_units) break;
         const uint32_t ui = P.order[pos];
         const WorkUnit U = P.units[ui];
         const DevProblem PR = P.problems[U.problem];
         const uint32_t slice = PR.slice_bins;
 
-        for (uint32_t c = 0; c < P.tally_copies; ++c)
-            for (uint32_t i = tid; i < 2 * slice; i += BLOCK) tally_all[static_cast<size_t>(c) * P.max_slice * 2 + i] = 0;
-        if (static_cast<int32_t>(U.problem) != cur_problem) {
-            for (uint32_t i = tid; i <= PR.n_cells; i += BLOCK) l_edge[i] = g_edge[PR.edge_off + i];
-            for (uint32_t i = tid; i < PR.n_cells; i += BLOCK) {
-                const R sg = g_sig[PR.cell_off + i];
-                l_sig[i] = sg;
-                l_rsig[i] = recip_refined(sg);
-                l_scat[i] = P.scat64[PR.cell_off + i];
-                l_bin[i] = P.cbin[PR.cell_off + i];
+        for (uint32_t c = 0; c < P.tally_copies; ++c) {
+            uint64_t* const t = reinterpret_cast<uint64_t*>(smem) + static_cast<size_t>(c) * P.max_slice * 2;
+            for (uint32_t i = tid; i < slice; i += BLOCK) {
+                t[i] = 0;
+                t[P.max_slice + i] = 0;
             }
-            if (TIMED)
-                for (uint32_t i = tid; i <= PR.n_time_bins; i += BLOCK) l_tedge[i] = g_tedge[PR.tedge_off + i];
-            if (PR.seed_kind == SEED_STRIDE)
-                for (uint32_t i = tid; i < PR.stride_digits * kStrideRadix * 2u; i += BLOCK) s_skip[i] = PR.table[i];
+        }
+        if (static_cast<int32_t>(U.problem) != cur_problem) {
+            stage_problem<F32, TIMED, ONE, BLOCK>(P, PR, A, s_skip, tid);
             cur_problem = static_cast<int32_t>(U.problem);
         }
         __syncthreads();
-
-        CellsLds<F32> C;
-        C.edge = l_edge;
-        C.sig = l_sig;
-        C.rsig = l_rsig;
-        C.scat = l_scat;
-        C.bin = l_bin;
-        C.tedge = l_tedge;
-        C.n_cells = static_cast<int32_t>(PR.n_cells);
-        C.n_time_bins = static_cast<int32_t>(PR.n_time_bins);
-        C.n_space_bins = static_cast<int32_t>(PR.n_space_bins);
-        SeedDev S;
-        S.kind = static_cast<int>(PR.seed_kind);
-        S.stride_digits = PR.stride_digits;
-        S.base = PR.seed_base;
-        S.first_index = PR.first_index;
-        S.table = s_skip;
-        uint64_t* tally = tally_all + static_cast<size_t>(copy) * P.max_slice * 2;
+        const LdsCells<F32, ONE> C = staged_cells<F32, ONE>(P, PR, A);
+        const SeedDev S = problem_seed(PR, s_skip);
         const uint64_t stride_q = PR.stride_q;
 
         Particle<F32> p[H];
-        int ph[H];
+        uint32_t draws[H];   // numbers drawn by the lane's history, before an absorption's one
+        uint64_t G[H], W[H];
 #pragma unroll
-        for (int h = 0; h < H; ++h) ph[h] = PH_EMPTY;
+        for (int h = 0; h < H; ++h) {
+            init_particle_at<F32, TIMED>(p[h], C, 0ull);
+            draws[h] = 0;
+            G[h] = W[h] = 0;
+        }
         // wave-uniform counts of the unit (scalar registers)
         uint64_t w_events = 0, w_colls = 0;
-        uint32_t w_ll = 0, w_lr = 0, w_abs = 0, w_cen = 0;
+        uint32_t w_leak = 0, w_lr = 0, w_abs = 0, w_cen = 0;
         // per lane, over the histories this lane ended (their total draws
         // follow from the wave counts: one for each history's first flight,
         // one per collision for the absorption test and two more per scatter)
         uint32_t l_maxd = 0, l_over = 0;
         bool exhausted = false;   // wave-uniform: no history of the unit left for this wave
         // the wave's ring of seeded histories (positions & 127): [r_next, r_filled)
-        uint64_t* ring = s_ring[__builtin_amdgcn_readfirstlane(wid)];
+        uint64_t* ring = s_ring[wid];
         uint32_t r_next = 0, r_filled = 0;   // wave-uniform
         bool unit_taken = false;             // wave-uniform: s_next has passed the unit's end
+        auto ended = [&](uint64_t m, uint32_t d) {
+            if (in_mask(m)) {
+                l_maxd = d > l_maxd ? d : l_maxd;
+                if (stride_q != 0 && d > stride_q) l_over++;
+            }
+        };
 
         // Each iteration: one geometry step for every lane with a flight;
         // then, once enough lanes wait at a collision site (or stand empty
@@ -213,102 +284,86 @@ __global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 
         // collision draws and samples its next flight.  Every particle still
         // runs its own operations in its own order.
         for (;;) {
+            uint32_t nwait = 0;
+            uint64_t flying = 0;
 #pragma unroll
             for (int h = 0; h < H; ++h) {
-                const bool g = ph[h] == PH_GEOM;
-                w_events += wave_count(g);
-                int r = END_NONE;
-                if (g) {
-                    r = geom_step<F32, TIMED>(p[h], C, tally);
-                    if (r == STEP_COLLIDE) {
-                        ph[h] = PH_COLL;
-                    } else if (r != END_NONE) {
-                        ph[h] = PH_EMPTY;
-                        const uint32_t d = p[h].hdraws;
-                        l_maxd = d > l_maxd ? d : l_maxd;
-                        if (stride_q != 0 && d > stride_q) l_over++;
+                if (G[h] != 0) {
+                    w_events += mask_count(G[h]);
+                    const GeomOut o = geom_pass<F32, TIMED>(p[h], C, G[h], tally);
+                    const uint64_t end = o.leak | o.census;
+                    G[h] &= ~(o.coll | end);
+                    W[h] |= o.coll;
+                    if (end != 0) {
+                        w_leak += mask_count(o.leak);
+                        w_lr += mask_count(o.right);
+                        if (TIMED) w_cen += mask_count(o.census);
+                        ended(end, draws[h]);
                     }
                 }
-                if (__builtin_amdgcn_ballot_w64(r > END_NONE) != 0) {
-                    w_ll += wave_count(r == END_LEAK_LEFT);
-                    w_lr += wave_count(r == END_LEAK_RIGHT);
-                    if (TIMED) w_cen += wave_count(r == END_CENSUS);
-                }
+                flying |= G[h];
+                nwait += mask_count(exhausted ? W[h] : ~G[h]);
             }
-            uint32_t nwait = 0, ngeom = 0;
-#pragma unroll
-            for (int h = 0; h < H; ++h) {
-                nwait += wave_count(ph[h] == PH_COLL || (ph[h] == PH_EMPTY && !exhausted));
-                ngeom += wave_count(ph[h] == PH_GEOM);
-            }
-            if (nwait < P.coll_batch && ngeom != 0) continue;
+            if (nwait < P.coll_batch && flying != 0) continue;
 
             // collision pass: refill the empty lanes first
+            uint64_t fresh[H], live = 0;
 #pragma unroll
             for (int h = 0; h < H; ++h) {
-                if (exhausted) continue;
-                const uint64_t need = __builtin_amdgcn_ballot_w64(ph[h] == PH_EMPTY);
-                if (need == 0) continue;
-                const uint32_t nneed = static_cast<uint32_t>(__popcll(need));
-                if (r_filled - r_next < nneed && !unit_taken) {
-                    // seed the next 64 histories of the unit at once (one per
-                    // lane), so that a refill is an LDS read
-                    uint32_t base = 0;
-                    if (lane == 0) base = atomicAdd(&s_next, 64u);
-                    base = __builtin_amdgcn_readfirstlane(base);
-                    if (base + 64u >= U.count) unit_taken = true;
-                    const uint32_t got = base < U.count ? (U.count - base < 64u ? U.count - base : 64u) : 0u;
-                    if (lane < got) ring[(r_filled + lane) & 127u] = stream_start(P.lcg, S, U.j0 + base + lane);
-                    r_filled += got;
+                fresh[h] = 0;
+                const uint64_t need = ~(G[h] | W[h]);
+                if (!exhausted && need != 0) {
+                    const uint32_t nneed = mask_count(need);
+                    if (r_filled - r_next < nneed && !unit_taken) {
+                        // seed the next 64 histories of the unit at once (one per
+                        // lane), so that a refill is an LDS read
+                        uint32_t base = 0;
+                        if (lane == 0) base = atomicAdd(&s_next, 64u);
+                        base = __builtin_amdgcn_readfirstlane(base);
+                        if (base + 64u >= U.count) unit_taken = true;
+                        const uint32_t got = base < U.count ? (U.count - base < 64u ? U.count - base : 64u) : 0u;
+                        if (lane < got) ring[(r_filled + lane) & 127u] = stream_start_z(P.lcg, S, U.j0 + base + lane);
+                        r_filled += got;
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                    const uint32_t avail = r_filled - r_next;
+                    const uint32_t take = avail < nneed ? avail : nneed;
+                    const uint32_t rank = mask_rank(need);
+                    fresh[h] = need & wave_mask(rank < take);
+                    if (in_mask(fresh[h])) {
+                        init_particle_at<F32, TIMED>(p[h], C, ring[(r_next + rank) & 127u]);
+                        draws[h] = 1;
+                    }
+                    r_next += take;
+                    if (unit_taken && r_next == r_filled) exhausted = true;
                     __builtin_amdgcn_wave_barrier();
                 }
-                const uint32_t avail = r_filled - r_next;
-                const uint32_t take = avail < nneed ? avail : nneed;
-                if (ph[h] == PH_EMPTY) {
-                    const uint32_t rank = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(need >> 32),
-                                                                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(need), 0u));
-                    if (rank < take) {
-                        init_particle_at<F32, TIMED>(p[h], C, ring[(r_next + rank) & 127u]);
-                        ph[h] = PH_NEW;
-                    }
-                }
-                r_next += take;
-                if (unit_taken && r_next == r_filled) exhausted = true;
-                __builtin_amdgcn_wave_barrier();
+                live |= G[h] | W[h] | fresh[h];
             }
-            uint32_t nlive = 0;
-#pragma unroll
-            for (int h = 0; h < H; ++h) nlive += wave_count(ph[h] != PH_EMPTY);
-            if (nlive == 0) break;
+            if (live == 0) break;
 #pragma unroll
             for (int h = 0; h < H; ++h) {
-                const bool cl = ph[h] == PH_COLL;
-                w_colls += wave_count(cl);
-                bool absorbed = false;
-                if (cl) {
-                    if (collide<F32>(p[h], C, P.lcg) != END_NONE) {
-                        absorbed = true;
-                        ph[h] = PH_EMPTY;
-                        const uint32_t d = p[h].hdraws;
-                        l_maxd = d > l_maxd ? d : l_maxd;
-                        if (stride_q != 0 && d > stride_q) l_over++;
-                    } else {
-                        ph[h] = PH_NEW;
-                    }
+                uint64_t fly = fresh[h];
+                if (W[h] != 0) {
+                    w_colls += mask_count(W[h]);
+                    const uint64_t absorbed = collide_pass<F32>(p[h], C, P.lcg, W[h]);
+                    w_abs += mask_count(absorbed);
+                    ended(absorbed, draws[h] + 1u);
+                    const uint64_t scat = W[h] & ~absorbed;
+                    draws[h] += sel_const<3, 0>(scat);
+                    fly |= scat;
+                    W[h] = 0;
                 }
-                w_abs += wave_count(absorbed);
-                if (ph[h] == PH_NEW) {
-                    sample_tau<F32>(p[h], P.lcg);
-                    ph[h] = PH_GEOM;
-                }
+                if (in_mask(fly)) sample_tau<F32>(p[h], P.lcg);
+                G[h] |= fly;
             }
         }
 
         // unit diagnostics: the wave's counts and the lanes' into LDS
         if (lane == 0) {
-            const unsigned long long ends = static_cast<unsigned long long>(w_ll) + w_lr + w_abs + w_cen;
+            const unsigned long long ends = static_cast<unsigned long long>(w_leak) + w_abs + w_cen;
             atomicAdd(&s_diag[D_HISTORIES], ends);
-            atomicAdd(&s_diag[D_LEAK_LEFT], static_cast<unsigned long long>(w_ll));
+            atomicAdd(&s_diag[D_LEAK_LEFT], static_cast<unsigned long long>(w_leak - w_lr));
             atomicAdd(&s_diag[D_LEAK_RIGHT], static_cast<unsigned long long>(w_lr));
             atomicAdd(&s_diag[D_ABSORBED], static_cast<unsigned long long>(w_abs));
             atomicAdd(&s_diag[D_CENSUS], static_cast<unsigned long long>(w_cen));
@@ -324,10 +379,8 @@ __global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 
         for (uint32_t i = tid; i < slice; i += BLOCK) {
             uint64_t lo = 0, hi = 0;
             for (uint32_t c = 0; c < P.tally_copies; ++c) {
-                const uint64_t l = tally_all[(static_cast<size_t>(c) * P.max_slice + i) * 2];
-                hi += tally_all[(static_cast<size_t>(c) * P.max_slice + i) * 2 + 1];
-                if (lo + l < lo) hi += 1ull << 32;   // a wrap of the low word: 2^64 = 2^32 x 2^32
-                lo += l;
+                const uint64_t* t = reinterpret_cast<uint64_t*>(smem) + static_cast<size_t>(c) * P.max_slice * 2;
+                add_limbs(t[i], t[P.max_slice + i], &lo, &hi);
             }
             dst[2 * i] = lo;
             dst[2 * i + 1] = hi;
@@ -393,9 +446,8 @@ struct Slot {
 
 #define CH_ACQ_REL(op, p, v) __hip_atomic_##op((p), (v), __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP)
 
-template <bool F32, bool TIMED, int BLOCK>
+template <bool F32, bool TIMED, bool ONE, int BLOCK>
 __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_chain(TransportParams P) {
-    using R = typename Particle<F32>::R;
     using chain::kNone;
     using chain::kNoMore;
     using chain::kWant;
@@ -410,54 +462,12 @@ __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_ch
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & 63u;
     const uint32_t wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-
-    uint64_t* tally_all = reinterpret_cast<uint64_t*>(smem);
-    size_t off = align16(static_cast<size_t>(P.tally_copies) * P.max_slice * 2 * sizeof(uint64_t));
-    R* l_edge = reinterpret_cast<R*>(smem + off);
-    off += align16((P.max_cells + 1) * sizeof(R));
-    R* l_sig = reinterpret_cast<R*>(smem + off);
-    off += align16(P.max_cells * sizeof(R));
-    R* l_rsig = reinterpret_cast<R*>(smem + off);
-    off += align16(P.max_cells * sizeof(R));
-    double* l_scat = reinterpret_cast<double*>(smem + off);
-    off += align16(P.max_cells * sizeof(double));
-    int32_t* l_bin = reinterpret_cast<int32_t*>(smem + off);
-    off += align16(P.max_cells * sizeof(int32_t));
-    R* l_tedge = reinterpret_cast<R*>(smem + off);
-
-    const R* g_edge;
-    const R* g_sig;
-    const R* g_tedge;
-    if constexpr (F32) {
-        g_edge = P.edges32;
-        g_sig = P.sig32;
-        g_tedge = P.tedges32;
-    } else {
-        g_edge = P.edges64;
-        g_sig = P.sig64;
-        g_tedge = P.tedges64;
-    }
-
+    const CellArrays<F32, ONE> A(P, smem);
     const DevProblem PR = P.problems[0];
     const uint32_t slice = PR.slice_bins;
-    uint64_t* const tsl0 = tally_all;
-    uint64_t* const tsl1 = tally_all + static_cast<size_t>(P.max_slice) * 2;
-    for (uint32_t i = tid; i <= PR.n_cells; i += BLOCK) l_edge[i] = g_edge[PR.edge_off + i];
-    for (uint32_t i = tid; i < PR.n_cells; i += BLOCK) {
-        const R sg = g_sig[PR.cell_off + i];
-        l_sig[i] = sg;
-        l_rsig[i] = recip_refined(sg);
-        l_scat[i] = P.scat64[PR.cell_off + i];
-        l_bin[i] = P.cbin[PR.cell_off + i];
-    }
-    if (TIMED)
-        for (uint32_t i = tid; i <= PR.n_time_bins; i += BLOCK) l_tedge[i] = g_tedge[PR.tedge_off + i];
-    if (PR.seed_kind == SEED_STRIDE)
-        for (uint32_t i = tid; i < PR.stride_digits * kStrideRadix * 2u; i += BLOCK) s_skip[i] = PR.table[i];
-    for (uint32_t i = tid; i < 2u * slice; i += BLOCK) {
-        tsl0[i] = 0ull;
-        tsl1[i] = 0ull;
-    }
+    const uint32_t slice1_off = P.max_slice * 16u;   // bytes from slice 0 to slice 1
+    stage_problem<F32, TIMED, ONE, BLOCK>(P, PR, A, s_skip, tid);
+    for (uint32_t i = tid; i < 4u * P.max_slice; i += BLOCK) reinterpret_cast<uint64_t*>(smem)[i] = 0ull;
     if (tid < kNDiag) s_diag[tid] = 0;
 
     // lane 0 of a wave: puts the launch's next unit into free slice f
@@ -505,22 +515,8 @@ __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_ch
     }
     __syncthreads();
 
-    CellsLds<F32> C;
-    C.edge = l_edge;
-    C.sig = l_sig;
-    C.rsig = l_rsig;
-    C.scat = l_scat;
-    C.bin = l_bin;
-    C.tedge = l_tedge;
-    C.n_cells = static_cast<int32_t>(PR.n_cells);
-    C.n_time_bins = static_cast<int32_t>(PR.n_time_bins);
-    C.n_space_bins = static_cast<int32_t>(PR.n_space_bins);
-    SeedDev S;
-    S.kind = static_cast<int>(PR.seed_kind);
-    S.stride_digits = PR.stride_digits;
-    S.base = PR.seed_base;
-    S.first_index = PR.first_index;
-    S.table = s_skip;
+    const LdsCells<F32, ONE> C = staged_cells<F32, ONE>(P, PR, A);
+    const SeedDev S = problem_seed(PR, s_skip);
     const uint64_t stride_q = PR.stride_q;
     uint64_t* const ring = s_ring[wid];
     uint8_t* const rsl = s_rslice[wid];
@@ -538,11 +534,15 @@ __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_ch
         if (lane == 0) old = CH_ACQ_REL(fetch_sub, &s_cs[sl].alive, n);
         old = __builtin_amdgcn_readfirstlane(old);
         if (old != n) return;
-        uint64_t* t = sl ? tsl1 : tsl0;
+        uint64_t* t = reinterpret_cast<uint64_t*>(smem) + (sl ? static_cast<size_t>(P.max_slice) * 2 : 0);
         uint64_t* dst = P.partial + s_cs[sl].hslot;
-        for (uint32_t i = lane; i < 2u * slice; i += 64u) {
-            dst[i] = t[i];
+        for (uint32_t i = lane; i < slice; i += 64u) {
+            uint64_t lo = 0, hi = 0;
+            add_limbs(t[i], t[P.max_slice + i], &lo, &hi);
+            dst[2 * i] = lo;
+            dst[2 * i + 1] = hi;
             t[i] = 0ull;
+            t[P.max_slice + i] = 0ull;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         if (lane == 0) {
@@ -601,7 +601,7 @@ __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_ch
         cnt = __builtin_amdgcn_readfirstlane(cnt);
         const uint32_t got = cnt - base < 64u ? cnt - base : 64u;
         if (lane < got) {
-            ring[(r_filled + lane) & 127u] = stream_start(P.lcg, S, s_cs[f].j0 + base + lane);
+            ring[(r_filled + lane) & 127u] = stream_start_z(P.lcg, S, s_cs[f].j0 + base + lane);
             rsl[(r_filled + lane) & 127u] = static_cast<uint8_t>(f);
         }
         r_filled += got;
@@ -616,45 +616,47 @@ __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_ch
     };
 
     Particle<F32> p;
-    int ph = PH_EMPTY;
-    uint64_t* tl = tsl0;   // the slice of the lane's history
+    init_particle_at<F32, TIMED>(p, C, 0ull);
+    uint32_t draws = 0;         // numbers drawn by the lane's history, before an absorption's one
+    uint64_t G = 0, W = 0;      // flying, waiting (`live` also covers them)
+    uint32_t tl = 0;            // byte offset of the slice of the lane's history
     uint64_t w_events = 0, w_colls = 0;
-    uint32_t w_ll = 0, w_lr = 0, w_abs = 0, w_cen = 0;
+    uint32_t w_leak = 0, w_lr = 0, w_abs = 0, w_cen = 0;
     uint32_t l_maxd = 0, l_over = 0;
     bool starved = false;   // wave-uniform: the last refill found no history to take
+    auto note_end = [&](uint64_t m, uint32_t d) {
+        if (in_mask(m)) {
+            l_maxd = d > l_maxd ? d : l_maxd;
+            if (stride_q != 0 && d > stride_q) l_over++;
+        }
+    };
 
     for (;;) {
-        {
-            const bool g = ph == PH_GEOM;
-            w_events += wave_count(g);
-            int r = END_NONE;
-            if (g) {
-                r = geom_step<F32, TIMED>(p, C, tl);
-                if (r == STEP_COLLIDE) {
-                    ph = PH_COLL;
-                } else if (r != END_NONE) {
-                    ph = PH_EMPTY;
-                    const uint32_t d = p.hdraws;
-                    l_maxd = d > l_maxd ? d : l_maxd;
-                    if (stride_q != 0 && d > stride_q) l_over++;
-                }
-            }
-            const uint64_t ended = __builtin_amdgcn_ballot_w64(r > END_NONE);
-            if (ended != 0) {
-                w_ll += wave_count(r == END_LEAK_LEFT);
-                w_lr += wave_count(r == END_LEAK_RIGHT);
-                if (TIMED) w_cen += wave_count(r == END_CENSUS);
-                ends(ended);
+        if (G != 0) {
+            w_events += mask_count(G);
+            LimbTally tally;
+            tally.lo = reinterpret_cast<char*>(smem) + tl;
+            tally.hi_off = P.max_slice * 8u;
+            const GeomOut o = geom_pass<F32, TIMED>(p, C, G, tally);
+            const uint64_t end = o.leak | o.census;
+            G &= ~(o.coll | end);
+            W |= o.coll;
+            if (end != 0) {
+                w_leak += mask_count(o.leak);
+                w_lr += mask_count(o.right);
+                if (TIMED) w_cen += mask_count(o.census);
+                note_end(end, draws);
+                ends(end);
             }
         }
-        const uint32_t nwait = wave_count(ph == PH_COLL || (ph == PH_EMPTY && !starved));
-        const uint32_t ngeom = wave_count(ph == PH_GEOM);
-        if (nwait < P.coll_batch && ngeom != 0) continue;
+        const uint32_t nwait = mask_count(starved ? W : ~G);
+        if (nwait < P.coll_batch && G != 0) continue;
 
         // collision pass: refill the empty lanes first
-        const uint64_t need = __builtin_amdgcn_ballot_w64(ph == PH_EMPTY);
+        uint64_t fresh = 0;
+        const uint64_t need = ~(G | W);
         if (need != 0) {
-            const uint32_t nneed = static_cast<uint32_t>(__popcll(need));
+            const uint32_t nneed = mask_count(need);
             starved = false;
             while (r_filled - r_next < nneed) {
                 if (!fetch()) {
@@ -664,20 +666,17 @@ __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_ch
             }
             const uint32_t avail = r_filled - r_next;
             const uint32_t take = avail < nneed ? avail : nneed;
-            bool in1 = false;
-            if (ph == PH_EMPTY) {
-                const uint32_t rank = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(need >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(need), 0u));
-                if (rank < take) {
-                    const uint32_t e = (r_next + rank) & 127u;
-                    init_particle_at<F32, TIMED>(p, C, ring[e]);
-                    in1 = rsl[e] != 0;
-                    tl = in1 ? tsl1 : tsl0;
-                    ph = PH_NEW;
-                }
+            const uint32_t rank = mask_rank(need);
+            fresh = need & wave_mask(rank < take);
+            const uint32_t e = (r_next + rank) & 127u;
+            const uint64_t in1 = fresh & wave_mask(rsl[e] != 0);
+            if (in_mask(fresh)) {
+                init_particle_at<F32, TIMED>(p, C, ring[e]);
+                tl = sel_or_zero(in1, slice1_off);
+                draws = 1;
             }
-            s1mask |= __builtin_amdgcn_ballot_w64(in1);
-            live = __builtin_amdgcn_ballot_w64(ph != PH_EMPTY);
+            s1mask |= in1;
+            live = G | W | fresh;
             r_next += take;
             __builtin_amdgcn_wave_barrier();
         }
@@ -690,38 +689,29 @@ __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_ch
             if ((w & kNoMore) && r_next == r_filled) break;
             __builtin_amdgcn_s_sleep(4);
         }
-        {
-            const bool cl = ph == PH_COLL;
-            w_colls += wave_count(cl);
-            bool absorbed = false;
-            if (cl) {
-                if (collide<F32>(p, C, P.lcg) != END_NONE) {
-                    absorbed = true;
-                    ph = PH_EMPTY;
-                    const uint32_t d = p.hdraws;
-                    l_maxd = d > l_maxd ? d : l_maxd;
-                    if (stride_q != 0 && d > stride_q) l_over++;
-                } else {
-                    ph = PH_NEW;
-                }
+        uint64_t fly = fresh;
+        if (W != 0) {
+            w_colls += mask_count(W);
+            const uint64_t absorbed = collide_pass<F32>(p, C, P.lcg, W);
+            const uint64_t scat = W & ~absorbed;
+            W = 0;
+            if (absorbed != 0) {
+                w_abs += mask_count(absorbed);
+                note_end(absorbed, draws + 1u);
+                ends(absorbed);
             }
-            const uint64_t ab = __builtin_amdgcn_ballot_w64(absorbed);
-            if (ab != 0) {
-                w_abs += static_cast<uint32_t>(__popcll(ab));
-                ends(ab);
-            }
-            if (ph == PH_NEW) {
-                sample_tau<F32>(p, P.lcg);
-                ph = PH_GEOM;
-            }
+            draws += sel_const<3, 0>(scat);
+            fly |= scat;
         }
+        if (in_mask(fly)) sample_tau<F32>(p, P.lcg);
+        G |= fly;
     }
 
     // the problem's diagnostics: the block's sums, into its last unit's words
     if (lane == 0) {
-        const unsigned long long nend = static_cast<unsigned long long>(w_ll) + w_lr + w_abs + w_cen;
+        const unsigned long long nend = static_cast<unsigned long long>(w_leak) + w_abs + w_cen;
         atomicAdd(&s_diag[D_HISTORIES], nend);
-        atomicAdd(&s_diag[D_LEAK_LEFT], static_cast<unsigned long long>(w_ll));
+        atomicAdd(&s_diag[D_LEAK_LEFT], static_cast<unsigned long long>(w_leak - w_lr));
         atomicAdd(&s_diag[D_LEAK_RIGHT], static_cast<unsigned long long>(w_lr));
         atomicAdd(&s_diag[D_ABSORBED], static_cast<unsigned long long>(w_abs));
         atomicAdd(&s_diag[D_CENSUS], static_cast<unsigned long long>(w_cen));
@@ -736,9 +726,9 @@ __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_ch
 }
 #undef CH_ACQ_REL
 
-template <bool F32, bool TIMED, int H, int BLOCK>
+template <bool F32, bool TIMED, bool ONE, int H, int BLOCK>
 static hipError_t launch_t(const TransportParams& p, int grid, size_t lds, hipStream_t st, int* used) {
-    auto kern = k_transport<F32, TIMED, H, BLOCK>;
+    auto kern = k_transport<F32, TIMED, ONE, H, BLOCK>;
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
@@ -762,23 +752,24 @@ static hipError_t launch_t(const TransportParams& p, int grid, size_t lds, hipSt
     return hipGetLastError();
 }
 
-template <bool F32, bool TIMED, int H>
+template <bool F32, bool TIMED, bool ONE, int H>
 static hipError_t launch_b(const TransportParams& p, int block, int grid, size_t lds, hipStream_t st, int* used) {
     switch (block) {
-        case 64: return launch_t<F32, TIMED, H, 64>(p, grid, lds, st, used);
-        case 128: return launch_t<F32, TIMED, H, 128>(p, grid, lds, st, used);
-        case 512: return launch_t<F32, TIMED, H, 512>(p, grid, lds, st, used);
-        case 1024: return launch_t<F32, TIMED, H, 1024>(p, grid, lds, st, used);
-        default: return launch_t<F32, TIMED, H, 256>(p, grid, lds, st, used);
+        case 64: return launch_t<F32, TIMED, ONE, H, 64>(p, grid, lds, st, used);
+        case 128: return launch_t<F32, TIMED, ONE, H, 128>(p, grid, lds, st, used);
+        case 512: return launch_t<F32, TIMED, ONE, H, 512>(p, grid, lds, st, used);
+        case 1024: return launch_t<F32, TIMED, ONE, H, 1024>(p, grid, lds, st, used);
+        default: return launch_t<F32, TIMED, ONE, H, 256>(p, grid, lds, st, used);
     }
 }
 
-template <bool F32, bool TIMED>
+template <bool F32, bool TIMED, bool ONE>
 static hipError_t launch_h(const TransportParams& p, const LaunchShape& s, size_t lds, hipStream_t st, int* used) {
     switch (s.hist_per_lane) {
-        case 2: return launch_b<F32, TIMED, 2>(p, s.block, s.grid, lds, st, used);
-        case 4: return launch_b<F32, TIMED, 4>(p, s.block, s.grid, lds, st, used);
-        default: return launch_b<F32, TIMED, 1>(p, s.block, s.grid, lds, st, used);
+        // (several histories per lane: only the general form is built)
+        case 2: return launch_b<F32, TIMED, false, 2>(p, s.block, s.grid, lds, st, used);
+        case 4: return launch_b<F32, TIMED, false, 4>(p, s.block, s.grid, lds, st, used);
+        default: return launch_b<F32, TIMED, ONE, 1>(p, s.block, s.grid, lds, st, used);
     }
 }
 
@@ -791,9 +782,9 @@ static hipError_t blocks_per_cu(const void* kern, int block, size_t lds, int* ou
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(out, kern, block, lds);
 }
 
-template <bool F32, bool TIMED, int BLOCK>
+template <bool F32, bool TIMED, bool ONE, int BLOCK>
 static hipError_t launch_chain_t(const TransportParams& p, int grid, size_t lds, hipStream_t st, int* used) {
-    auto kern = k_transport_chain<F32, TIMED, BLOCK>;
+    auto kern = k_transport_chain<F32, TIMED, ONE, BLOCK>;
     if (grid <= 0) {
         int dev = 0, cus = 0, per_cu = 0;
         hipError_t e = hipGetDevice(&dev);
@@ -816,68 +807,71 @@ static hipError_t launch_chain_t(const TransportParams& p, int grid, size_t lds,
     return hipGetLastError();
 }
 
-template <bool F32, bool TIMED>
+template <bool F32, bool TIMED, bool ONE>
 static hipError_t launch_chain_b(const TransportParams& p, const LaunchShape& s, size_t lds, hipStream_t st,
                                  int* used) {
     switch (s.block) {
-        case 64: return launch_chain_t<F32, TIMED, 64>(p, s.grid, lds, st, used);
-        case 128: return launch_chain_t<F32, TIMED, 128>(p, s.grid, lds, st, used);
-        case 512: return launch_chain_t<F32, TIMED, 512>(p, s.grid, lds, st, used);
-        case 1024: return launch_chain_t<F32, TIMED, 1024>(p, s.grid, lds, st, used);
-        default: return launch_chain_t<F32, TIMED, 256>(p, s.grid, lds, st, used);
+        case 64: return launch_chain_t<F32, TIMED, ONE, 64>(p, s.grid, lds, st, used);
+        case 128: return launch_chain_t<F32, TIMED, ONE, 128>(p, s.grid, lds, st, used);
+        case 512: return launch_chain_t<F32, TIMED, ONE, 512>(p, s.grid, lds, st, used);
+        case 1024: return launch_chain_t<F32, TIMED, ONE, 1024>(p, s.grid, lds, st, used);
+        default: return launch_chain_t<F32, TIMED, ONE, 256>(p, s.grid, lds, st, used);
     }
 }
 
-template <bool F32, bool TIMED, int BLOCK>
+template <bool F32, bool TIMED, bool ONE, int BLOCK>
 static hipError_t chain_fits_t(const TransportParams& a, const TransportParams& b, int f32, bool* fits) {
     int na = 0, nb = 0;
-    hipError_t e = blocks_per_cu(reinterpret_cast<const void*>(k_transport<F32, TIMED, 1, BLOCK>), BLOCK,
+    hipError_t e = blocks_per_cu(reinterpret_cast<const void*>(k_transport<F32, TIMED, ONE, 1, BLOCK>), BLOCK,
                                  transport_lds_bytes(a, f32), &na);
     if (e != hipSuccess) return e;
-    e = blocks_per_cu(reinterpret_cast<const void*>(k_transport_chain<F32, TIMED, BLOCK>), BLOCK,
+    e = blocks_per_cu(reinterpret_cast<const void*>(k_transport_chain<F32, TIMED, ONE, BLOCK>), BLOCK,
                       transport_lds_bytes(b, f32), &nb);
     if (e != hipSuccess) return e;
     *fits = nb >= 1 && nb >= na;
     return hipSuccess;
 }
 
-template <bool F32, bool TIMED>
+template <bool F32, bool TIMED, bool ONE>
 static hipError_t chain_fits_b(const TransportParams& a, const TransportParams& b, const LaunchShape& s, bool* fits) {
     switch (s.block) {
-        case 64: return chain_fits_t<F32, TIMED, 64>(a, b, s.f32, fits);
-        case 128: return chain_fits_t<F32, TIMED, 128>(a, b, s.f32, fits);
-        case 512: return chain_fits_t<F32, TIMED, 512>(a, b, s.f32, fits);
-        case 1024: return chain_fits_t<F32, TIMED, 1024>(a, b, s.f32, fits);
-        default: return chain_fits_t<F32, TIMED, 256>(a, b, s.f32, fits);
+        case 64: return chain_fits_t<F32, TIMED, ONE, 64>(a, b, s.f32, fits);
+        case 128: return chain_fits_t<F32, TIMED, ONE, 128>(a, b, s.f32, fits);
+        case 512: return chain_fits_t<F32, TIMED, ONE, 512>(a, b, s.f32, fits);
+        case 1024: return chain_fits_t<F32, TIMED, ONE, 1024>(a, b, s.f32, fits);
+        default: return chain_fits_t<F32, TIMED, ONE, 256>(a, b, s.f32, fits);
     }
+}
+
+// Calls f with the precision, time-dependence and one-region flags of a launch
+// as compile-time constants.
+template <class F>
+static hipError_t with_flags(int f32, int timed, int one, F f) {
+    using T = std::true_type;
+    using N = std::false_type;
+    if (f32) {
+        if (timed) return one ? f(T(), T(), T()) : f(T(), T(), N());
+        return one ? f(T(), N(), T()) : f(T(), N(), N());
+    }
+    if (timed) return one ? f(N(), T(), T()) : f(N(), T(), N());
+    return one ? f(N(), N(), T()) : f(N(), N(), N());
 }
 
 hipError_t transport_chain_fits(const TransportParams& single, const TransportParams& chained, const LaunchShape& s,
                                 bool* fits) {
     *fits = false;
-    if (s.f32)
-        return s.timed ? chain_fits_b<true, true>(single, chained, s, fits)
-                       : chain_fits_b<true, false>(single, chained, s, fits);
-    return s.timed ? chain_fits_b<false, true>(single, chained, s, fits)
-                   : chain_fits_b<false, false>(single, chained, s, fits);
+    return with_flags(s.f32, s.timed, static_cast<int>(single.one_region), [&](auto f, auto t, auto o) {
+        return chain_fits_b<f.value, t.value, o.value>(single, chained, s, fits);
+    });
 }
 
 hipError_t launch_transport(const TransportParams& p, const LaunchShape& s, hipStream_t st, int* grid_used) {
     if (p.n_units == 0) return hipSuccess;
     const size_t lds = transport_lds_bytes(p, s.f32);
-    if (s.chain) {
-        if (s.f32)
-            return s.timed ? launch_chain_b<true, true>(p, s, lds, st, grid_used)
-                           : launch_chain_b<true, false>(p, s, lds, st, grid_used);
-        return s.timed ? launch_chain_b<false, true>(p, s, lds, st, grid_used)
-                       : launch_chain_b<false, false>(p, s, lds, st, grid_used);
-    }
-    if (s.f32) {
-        return s.timed ? launch_h<true, true>(p, s, lds, st, grid_used)
-                       : launch_h<true, false>(p, s, lds, st, grid_used);
-    }
-    return s.timed ? launch_h<false, true>(p, s, lds, st, grid_used)
-                   : launch_h<false, false>(p, s, lds, st, grid_used);
+    return with_flags(s.f32, s.timed, static_cast<int>(p.one_region), [&](auto f, auto t, auto o) {
+        if (s.chain) return launch_chain_b<f.value, t.value, o.value>(p, s, lds, st, grid_used);
+        return launch_h<f.value, t.value, o.value>(p, s, lds, st, grid_used);
+    });
 }
 
 // ------------------------------------------------------------------ reduction

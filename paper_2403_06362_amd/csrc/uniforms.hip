@@ -34,7 +34,7 @@ __global__ void __launch_bounds__(256) k_uniforms(LcgDev L, SeedDev S, uint64_t 
         base = stream_start(L, S, b0);
     }
     for (uint64_t i = b0 + threadIdx.x; i < n; i += stride) {
-        uint64_t x;
+        uint64_t x;   // the state, top-aligned while it is stepped
         if (MODE == SEED_LOAD) {
             x = state[i];
         } else if (MODE == SEED_STRIDE) {
@@ -43,13 +43,14 @@ __global__ void __launch_bounds__(256) k_uniforms(LcgDev L, SeedDev S, uint64_t 
         } else {
             x = stream_start(L, S, i);
         }
+        x <<= L.up;
         double* out = u + i;
         for (uint32_t j = 0; j < k; ++j) {
-            x = lcg_next(L, x);
-            __builtin_nontemporal_store(to_uniform(L, x), out);
+            x = lcg_next_z(L, x);
+            __builtin_nontemporal_store(uniform_z(x), out);
             out += n;
         }
-        if (state) state[i] = x;
+        if (state) state[i] = x >> L.up;
     }
 }
 
