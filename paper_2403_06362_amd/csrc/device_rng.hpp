@@ -6,7 +6,7 @@
 //   affine_apply ... one factor of the skip-ahead of eq. (2): X <- G X + C mod 2^m
 //   murmur_hash .... Listing 1, hash(k, s) with wrapping 64-bit multiplies
 //   to_uniform ..... top 53 state bits, plus one, times 2^-53 (exact, in (0, 1])
-//   fixed_log ...... natural log with a fixed IEEE operation sequence
+//   fixed_neg_log .. natural log with a fixed IEEE operation sequence
 //
 // All 64-bit products are the low 64 bits of the full product; reduction
 // modulo 2^m is a mask because 2^m divides 2^64.
@@ -74,7 +74,8 @@ __device__ __forceinline__ uint64_t lcg_next_z(const LcgDev& L, uint64_t z) { re
 __device__ __forceinline__ double uniform_z(uint64_t z) {
     const uint32_t lo = static_cast<uint32_t>(z) | 0x7ffu;
     const double a = __longlong_as_double(static_cast<long long>(0x3f30000000000000ull | lo));
-    const double hi = static_cast<double>(static_cast<uint32_t>(z >> 32));
+    double hi;   // (a plain conversion of z >> 32 is widened to 64 bits: one more addition)
+    asm("v_cvt_f64_u32 %0, %1" : "=v"(hi) : "v"(static_cast<uint32_t>(z >> 32)));
     return __builtin_fma(hi, 0x1p-32, a + (0x1p-64 - 0x1p-12));
 }
 
@@ -178,8 +179,8 @@ __device__ __forceinline__ float max_num(float a, float b) {
 // normal range, which holds when |a| is at least 2^-900 (single: 2^-100), the
 // quotient is at least 2^-700 (single: 2^-36), b is nonzero with |b| in
 // [2^-64, 2^64] and |a| is at most 2^42: what the transport's validated
-// geometry allows above a smallest quotient (kQuotMin).  The callers take
-// the plain division for a smaller quotient.  a = 0 gives 0 (its sign never
+// geometry allows above the smallest quotient.  The callers take the plain
+// division for a smaller one (below_quot_min).  a = 0 gives 0 (its sign never
 // matters); b = 0 gives NaN.
 __device__ __forceinline__ double recip_refined(double b) {
     double r = __builtin_amdgcn_rcp(b);
@@ -205,15 +206,18 @@ __device__ __forceinline__ float quot(float a, float b, float r) {
 }
 
 // With b a cross section in [2^-64, 2^64] or a direction cosine (a multiple
-// of 2^-52, at most 1), a quotient of at least kQuotMin has |a| >= 2^-764
+// of 2^-52, at most 1), a quotient of at least 2^-700
+// (single: 2^-36) has |a| >= 2^-764
 // (single: 2^-100), so one comparison of the smaller of a flight's two
 // distances covers both divisions.
-template <class R>
-struct QuotMin;
-template <>
-struct QuotMin<double> { static constexpr double v = 0x1p-700; };
-template <>
-struct QuotMin<float> { static constexpr float v = 0x1p-36f; };
+// The comparison is on the bits (s >= 0; a -0 counts as large, and its
+// quotient is right), so that the bound is a literal.
+__device__ __forceinline__ bool below_quot_min(double s) {   // s < 2^-700
+    return static_cast<uint32_t>(static_cast<uint64_t>(__double_as_longlong(s)) >> 32) < 0x14300000u;
+}
+__device__ __forceinline__ bool below_quot_min(float s) {    // s < 2^-36
+    return __float_as_uint(s) < 0x2d800000u;
+}
 
 // Natural logarithm of u in (0, 1] (any positive normal double works).
 // Fixed sequence of IEEE double operations, each rounded to nearest, no
@@ -225,7 +229,8 @@ struct QuotMin<float> { static constexpr float v = 0x1p-36f; };
 // ln(1 + a) = 2 atanh(s) = 2s + sum_k 2 s^(2k+1)/(2k+1) and 2s = a - a s.
 // LN2_HI is ln 2 truncated to 40 fraction bits, LN2_LO the double nearest
 // to the rest.  Within 1.25 ulp of the exact logarithm.
-__device__ __forceinline__ double fixed_log(double u) {
+// Returns -ln u (the negation is exact).
+__device__ __forceinline__ double fixed_neg_log(double u) {
     constexpr double kLn2Hi = 0x1.62e42fefa2000p-1;
     constexpr double kLn2Lo = 0x1.9ef35793c7673p-41;
     constexpr double kC[12] = {0.0,        2.0 / 3.0,  2.0 / 5.0,  2.0 / 7.0,
@@ -252,7 +257,7 @@ __device__ __forceinline__ double fixed_log(double u) {
     const double l = a - c;
     const double ed = static_cast<double>(e);
     const double r = l + ed * kLn2Lo;
-    return ed * kLn2Hi + r;
+    return ed * -kLn2Hi - r;   // -(ed kLn2Hi + r)
 }
 
 // Quantised track length: q = round-half-even(s * 2^56) for 0 <= s < 2^7.

@@ -83,16 +83,20 @@ __device__ __forceinline__ int step_particle(EventParticle<F32>& e, const Global
         e.need_tau = false;
     }
     e.events++;
-    const GeomOut o = geom_pass<F32, TIMED>(e.p, C, wave_mask(true), tally);
-    const uint64_t absorbed = collide_pass<F32>(e.p, C, L, o.coll);
+    uint64_t up = wave_mask(e.p.mu > 0);
+    const GeomOut o = geom_pass<F32, TIMED>(e.p, C, wave_mask(true), up, tally);
     int end = END_NONE;
+    if (in_mask(o.leak)) {
+        end = in_mask(up) ? END_LEAK_RIGHT : END_LEAK_LEFT;
+        e.p.off = 0;   // a cell of the problem again: collide_pass reads every lane's cell from HBM
+    }
+    const uint64_t absorbed = o.coll & ~collide_pass<F32>(e.p, C, L, o.coll, up);
     if (in_mask(o.coll)) {
         e.colls++;
         e.draws += in_mask(absorbed) ? 1u : 2u;
         e.need_tau = !in_mask(absorbed);
     }
     if (in_mask(absorbed)) end = END_ABSORBED;
-    if (in_mask(o.leak)) end = in_mask(o.right) ? END_LEAK_RIGHT : END_LEAK_LEFT;
     if (TIMED && in_mask(o.census)) end = END_CENSUS;
     return end;
 }
@@ -110,6 +114,7 @@ __device__ __forceinline__ void load_particle(const EventBank& b, uint32_t i, Ev
     e.p.x = v.x[i];
     e.p.mu = v.mu[i];
     e.p.rmu = recip_refined(e.p.mu);
+    set_step<F32>(e.p);
     e.p.t = TIMED ? v.t[i] : 0;
     e.p.tau = v.tau[i];
     e.p.Z = b.X[i];

@@ -38,6 +38,7 @@ struct Particle {
     R rmu;              // refined reciprocal of mu; NaN when mu == 0 (no edge distance compares below a flight's)
     uint64_t Z;         // top-aligned LCG state
     uint32_t off;       // cell index times sizeof(R)
+    int32_t step;       // sizeof(R) with the sign of mu
     int32_t tb;
 };
 
@@ -152,17 +153,18 @@ struct LimbTally {
 template <bool F32>
 __device__ __forceinline__ void sample_tau(Particle<F32>& p, const LcgDev& L) {
     p.Z = lcg_next_z(L, p.Z);
-    p.tau = -fixed_log(uniform_z(p.Z));
+    p.tau = fixed_neg_log(uniform_z(p.Z));
 }
 
 // Outcomes of a geometry pass, subsets of the lanes it advanced: at a
-// collision site; out of the slab (right: of those, past the right face);
+// collision site; out of the slab (through the face they were heading for);
 // past the last time edge.  The others go on with their flight.
 struct GeomOut {
-    uint64_t coll, leak, right, census;
+    uint64_t coll, leak, census;
 };
 
-// One geometry step of the lanes in G.  FP64, global coordinates:
+// One geometry step of the lanes in G; up: the lanes with mu > 0 (kept from
+// the collision that drew mu).  FP64, global coordinates:
 //   s = tau / sig[c]                                          -> collision
 //   se = (E[c+1] - x) / mu if mu > 0, (E[c] - x) / mu if mu < 0, +inf if
 //   mu == 0;  if se < s: s = se                               -> edge
@@ -184,42 +186,37 @@ struct GeomOut {
 //   tau = tau - double(sig) double(s) (exact product), clamped at 0
 //   edge: mu > 0: c + 1, x = 0;  mu < 0: c - 1, x = W[c - 1]
 //   other: x = x + mu s clamped to [0, W[c]];  time: tb + 1, t = 0
-// Every lane computes (lanes outside G on whatever their registers hold: any
-// offset in them is a cell's); only the lanes in G score and change state.
+// Every lane computes, lanes outside G on whatever their registers hold (an
+// ended history's offset may be one cell outside the problem, where the LDS
+// arrays have neighbours; with cells in HBM the caller sets it back); only the
+// lanes in G score and change state.
 template <bool F32, bool TIMED, class Cells, class Tally>
-__device__ __forceinline__ GeomOut geom_pass(Particle<F32>& p, const Cells& C, uint64_t G, const Tally& tally) {
+__device__ __forceinline__ GeomOut geom_pass(Particle<F32>& p, const Cells& C, uint64_t G, uint64_t up,
+                                             const Tally& tally) {
     using R = typename Particle<F32>::R;
-    constexpr int kStep = static_cast<int>(sizeof(R));
     const uint32_t off = p.off;
     const R* const ed = C.edge(off);
     // FP64: the cell's edges; FP32: the widths of the cell before and of the cell
-    R e0, e1;
-    if constexpr (F32 && !std::is_same<Cells, GlobalCells<true>>::value) {
-        e0 = ed[0];
-        e1 = ed[1];
-    } else if constexpr (F32) {
+    R e0, e1 = ed[1];
+    if constexpr (std::is_same<Cells, GlobalCells<true>>::value)
         e0 = off != 0 ? ed[0] : R(0);
-        e1 = ed[1];
-    } else {
+    else
         e0 = ed[0];
-        e1 = ed[1];
-    }
     const R e_lo = F32 ? R(0) : e0, e_hi = e1;
     const R sig = C.sig(off);
     const R depth = static_cast<R>(p.tau);
-    const uint64_t up = wave_mask(p.mu > R(0));
-    const R e_to = F32 ? static_cast<R>(sel(up, e_hi, R(0))) : sel(up, e_hi, e_lo);
+    const R e_to = in_mask(up) ? e_hi : e_lo;
     const R num = e_to - p.x;
     const R sc = quot(depth, sig, C.rsig(off, sig));
     const R se = quot(num, p.mu, p.rmu);
     uint64_t edge = wave_mask(se < sc);
-    R s = sel(edge, se, sc);
-    if ((wave_mask(!(s >= QuotMin<R>::v)) & G) != 0) {
+    R s = min_num(se, sc);   // sc when se is NaN
+    if ((wave_mask(below_quot_min(s)) & G) != 0) {
         // a distance below the refined quotients' range: plain divisions
         const R pc = depth / sig;
         const R pe = p.mu == R(0) ? static_cast<R>(__builtin_huge_val()) : num / p.mu;
         edge = wave_mask(pe < pc);
-        s = sel(edge, pe, pc);
+        s = min_num(pe, pc);
     }
     // a set may mix steady and timed problems, an event schedule's wave too
     const uint64_t timed = TIMED ? wave_mask(C.n_time_bins > 0) : 0ull;
@@ -229,31 +226,29 @@ __device__ __forceinline__ GeomOut geom_pass(Particle<F32>& p, const Cells& C, u
         if (C.n_time_bins > 0) tnext = F32 ? C.tedge[p.tb] : C.tedge[p.tb + 1];
         const R st = tnext - p.t;
         time = timed & wave_mask(st < s);
-        s = sel(time, st, s);
+        s = sel(time, st, s);   // (steady lanes of a mixed wave keep theirs)
         edge &= ~time;
     }
-    const uint32_t noff = off + sel_or_zero(edge, sel_const<kStep, -kStep>(up));
-    const uint64_t out = edge & wave_mask(noff >= C.n_off);   // -1 wraps past n_off
+    edge &= G;
+    const uint32_t noff = off + sel_or_zero(edge, static_cast<uint32_t>(p.step));
     GeomOut o;
-    o.coll = G & ~(edge | time);
-    o.leak = G & out;
-    o.right = o.leak & up;
+    o.leak = G & wave_mask(noff >= C.n_off);   // -1 wraps past n_off
     o.census = 0;
     uint64_t last = 0;
     if (timed != 0) {
         last = wave_mask(p.tb + 1 == C.n_time_bins);
         o.census = G & time & last;
     }
-    const uint64_t stay = ~out;
+    o.coll = G & ~(edge | time);
     if (in_mask(G)) {
         tally.add((TIMED ? __umul24(static_cast<uint32_t>(p.tb), 8u * static_cast<uint32_t>(C.n_space_bins)) : 0u) +
                       C.bin8(off),
                   static_cast<double>(s));
         p.tau = __builtin_fmax(p.tau - static_cast<double>(sig) * static_cast<double>(s), 0.0);
         const R moved = min_num(max_num(p.x + p.mu * s, e_lo), e_hi);
-        const R entry = F32 ? sel(up, R(0), e0) : e_to;
+        const R entry = F32 ? (in_mask(up) ? R(0) : e0) : e_to;
         p.x = sel(edge, entry, moved);
-        p.off = sel(stay, noff, off);
+        p.off = noff;
         if (timed != 0) {
             p.t = sel(time, F32 ? R(0) : tnext, min_num(p.t + s, tnext));
             p.tb += static_cast<int32_t>(sel_const<1, 0>(time & ~last));
@@ -262,21 +257,40 @@ __device__ __forceinline__ GeomOut geom_pass(Particle<F32>& p, const Cells& C, u
     return o;
 }
 
+// The cell step of the direction: sizeof(R) with the sign bit of mu (of no
+// meaning when mu == 0, which meets no edge).
+template <bool F32>
+__device__ __forceinline__ void set_step(Particle<F32>& p) {
+    int32_t top;
+    if constexpr (F32)
+        top = static_cast<int32_t>(__float_as_uint(p.mu));
+    else
+        top = static_cast<int32_t>(static_cast<uint64_t>(__double_as_longlong(p.mu)) >> 32);
+    p.step = static_cast<int32_t>(sizeof(typename Particle<F32>::R)) ^ (top >> 31);
+    p.step -= top >> 31;
+}
+
 // Collision of the lanes in W at their sites: u1 decides absorption (the
 // state against the cell's bound), u2 the new direction mu = R(2 u2 - 1)
-// (computed in double, exact, then rounded once).  Returns the absorbed
-// lanes; the others sample their next flight with sample_tau.
+// (computed in double, exact, then rounded once).  Returns the scattered
+// lanes, which sample their next flight with sample_tau (the others of W are
+// absorbed), and updates the lanes with mu > 0.
 template <bool F32, class Cells>
-__device__ __forceinline__ uint64_t collide_pass(Particle<F32>& p, const Cells& C, const LcgDev& L, uint64_t W) {
+__device__ __forceinline__ uint64_t collide_pass(Particle<F32>& p, const Cells& C, const LcgDev& L, uint64_t W,
+                                                 uint64_t& up) {
     using R = typename Particle<F32>::R;
     const uint64_t z1 = lcg_next_z(L, p.Z);
     const uint64_t go = wave_mask(z1 < C.below(p.off)) & W;
+    const uint64_t z2 = lcg_next_z(L, z1);
+    const R mu = static_cast<R>(__builtin_fma(uniform_z(z2), 2.0, -1.0));
+    up = (up & ~go) | (go & wave_mask(mu > R(0)));
     if (in_mask(go)) {
-        p.Z = lcg_next_z(L, z1);
-        p.mu = static_cast<R>(__builtin_fma(uniform_z(p.Z), 2.0, -1.0));
-        p.rmu = recip_refined(p.mu);
+        p.Z = z2;
+        p.mu = mu;
+        p.rmu = recip_refined(mu);
+        set_step<F32>(p);
     }
-    return W & ~go;
+    return go;
 }
 
 // A new history whose stream starts at state Z: source at the left face
@@ -297,6 +311,7 @@ __device__ __forceinline__ void init_particle_at(Particle<F32>& p, const Cells& 
     p.rmu = R(1);   // recip_refined(1) is exactly 1
     p.tau = 0.0;
     p.off = 0;
+    p.step = static_cast<int32_t>(sizeof(R));
     p.tb = 0;
 }
 

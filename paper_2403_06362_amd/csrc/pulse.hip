@@ -93,7 +93,7 @@ __device__ __forceinline__ uint32_t pulse_flight(const PulseParams& P, PParticle
         *draws += 1;
     }
     p.Z = lcg_next_z(L, p.Z);
-    const double tau = -fixed_log(uniform_z(p.Z));
+    const double tau = fixed_neg_log(uniform_z(p.Z));
     *draws += 1;
     const double s = quot(tau, P.sigma_t, recip_refined(P.sigma_t));   // the reciprocal is loop-invariant
     const double tn = p.t + s;

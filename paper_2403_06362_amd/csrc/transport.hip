@@ -22,6 +22,8 @@
 // The per-history arithmetic (flight sampling, cell / time marching,
 // collision, scoring) follows the same fixed IEEE operation sequence in FP64
 // mode and in FP32-flight mode; it is spelled out in step_particle (particle.hpp).
+#include <algorithm>
+
 #include "particle.hpp"
 
 namespace mcrng {
@@ -77,6 +79,21 @@ size_t transport_static_lds_bytes(int block) {
     // skip table, rings, ring slice tags (k_transport_chain), block words
     return static_cast<size_t>(kStrideDigits) * kStrideRadix * 2 * sizeof(uint64_t) +
            static_cast<size_t>(block / 64) * 128 * (sizeof(uint64_t) + 1) + 512;
+}
+
+// A record that is the same on every lane, in scalar registers: the compiler
+// loads one through an address it cannot prove unchanged into vector registers
+// (24 of them here, and one wave per SIMD fewer).
+template <class T>
+__device__ __forceinline__ T uniform_record(const T& v) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    uint32_t w[sizeof(T) / 4];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (uint32_t& x : w) x = __builtin_amdgcn_readfirstlane(x);
+    T r;
+    __builtin_memcpy(&r, w, sizeof(T));
+    return r;
 }
 
 // The block's LDS arrays after the tally slices.
@@ -194,10 +211,23 @@ __device__ __forceinline__ uint32_t mask_rank(uint64_t m) {
                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
 }
 
+// Waiting lanes at which a wave's collision pass runs: `full` of `all` slots,
+// and the same share of the live ones once lanes stay empty (a wave's last
+// histories would otherwise wait for each other at every collision), at
+// least one and at most all of them.
+__device__ __forceinline__ uint32_t wave_batch(uint32_t full, uint32_t live, uint32_t all) {
+    const uint32_t b = (live * full + all - 1u) / all;
+    return b < live ? b : live;
+}
+
+// Empty lanes at which a wave takes new histories (about one history ends per
+// collision pass of the long-chain slab, and a refill costs a seventh of one).
+constexpr uint32_t kRefill = 3;
+
 // A lane's history slot is flying (its bit in G: takes geometry steps),
 // waiting at a collision site (W), or empty.
 template <bool F32, bool TIMED, bool ONE, int H, int BLOCK>
-__global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 1) k_transport(TransportParams P) {
+__global__ void __launch_bounds__(BLOCK, (H == 1) ? 7 : 1) k_transport(TransportParams P) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_unit;
     __shared__ uint32_t s_next;
@@ -228,9 +258,9 @@ __global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 
         __syncthreads();
         const uint32_t pos = __builtin_amdgcn_readfirstlane(s_unit);
         if (pos >= P.n_units) break;
-        const uint32_t ui = P.order[pos];
-        const WorkUnit U = P.units[ui];
-        const DevProblem PR = P.problems[U.problem];
+        const uint32_t ui = __builtin_amdgcn_readfirstlane(P.order[pos]);
+        const WorkUnit U = uniform_record(P.units[ui]);
+        const DevProblem PR = uniform_record(P.problems[U.problem]);
         const uint32_t slice = PR.slice_bins;
 
         for (uint32_t c = 0; c < P.tally_copies; ++c) {
@@ -251,12 +281,13 @@ __global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 
 
         Particle<F32> p[H];
         uint32_t draws[H];   // numbers drawn by the lane's history, before an absorption's one
-        uint64_t G[H], W[H];
+        uint64_t G[H], W[H], up[H];
 #pragma unroll
         for (int h = 0; h < H; ++h) {
             init_particle_at<F32, TIMED>(p[h], C, 0ull);
             draws[h] = 0;
             G[h] = W[h] = 0;
+            up[h] = ~0ull;
         }
         // wave-uniform counts of the unit (scalar registers)
         uint64_t w_events = 0, w_colls = 0;
@@ -277,36 +308,13 @@ __global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 
             }
         };
 
-        // Each iteration: one geometry step for every lane with a flight;
-        // then, once enough lanes wait at a collision site (or stand empty
-        // while histories remain), or none can move, the collision pass:
-        // empty lanes take new histories, and every waiting particle runs its
-        // collision draws and samples its next flight.  Every particle still
-        // runs its own operations in its own order.
+        // Geometry steps for every lane with a flight until enough lanes wait
+        // at a collision site (or stand empty while histories remain), or
+        // none can move; then the collision pass: empty lanes take new
+        // histories, and every waiting particle runs its collision draws and
+        // samples its next flight.  Every particle still runs its own
+        // operations in its own order.
         for (;;) {
-            uint32_t nwait = 0;
-            uint64_t flying = 0;
-#pragma unroll
-            for (int h = 0; h < H; ++h) {
-                if (G[h] != 0) {
-                    w_events += mask_count(G[h]);
-                    const GeomOut o = geom_pass<F32, TIMED>(p[h], C, G[h], tally);
-                    const uint64_t end = o.leak | o.census;
-                    G[h] &= ~(o.coll | end);
-                    W[h] |= o.coll;
-                    if (end != 0) {
-                        w_leak += mask_count(o.leak);
-                        w_lr += mask_count(o.right);
-                        if (TIMED) w_cen += mask_count(o.census);
-                        ended(end, draws[h]);
-                    }
-                }
-                flying |= G[h];
-                nwait += mask_count(exhausted ? W[h] : ~G[h]);
-            }
-            if (nwait < P.coll_batch && flying != 0) continue;
-
-            // collision pass: refill the empty lanes first
             uint64_t fresh[H], live = 0;
 #pragma unroll
             for (int h = 0; h < H; ++h) {
@@ -334,6 +342,7 @@ __global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 
                         init_particle_at<F32, TIMED>(p[h], C, ring[(r_next + rank) & 127u]);
                         draws[h] = 1;
                     }
+                    up[h] |= fresh[h];
                     r_next += take;
                     if (unit_taken && r_next == r_filled) exhausted = true;
                     __builtin_amdgcn_wave_barrier();
@@ -346,10 +355,10 @@ __global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 
                 uint64_t fly = fresh[h];
                 if (W[h] != 0) {
                     w_colls += mask_count(W[h]);
-                    const uint64_t absorbed = collide_pass<F32>(p[h], C, P.lcg, W[h]);
+                    const uint64_t scat = collide_pass<F32>(p[h], C, P.lcg, W[h], up[h]);
+                    const uint64_t absorbed = W[h] & ~scat;
                     w_abs += mask_count(absorbed);
                     ended(absorbed, draws[h] + 1u);
-                    const uint64_t scat = W[h] & ~absorbed;
                     draws[h] += sel_const<3, 0>(scat);
                     fly |= scat;
                     W[h] = 0;
@@ -357,6 +366,44 @@ __global__ void __launch_bounds__(BLOCK, (H == 1) ? ((F32 || !TIMED) ? 7 : 6) : 
                 if (in_mask(fly)) sample_tau<F32>(p[h], P.lcg);
                 G[h] |= fly;
             }
+            // idle[h]: the lanes that stay empty; at `batch` waiting lanes the
+            // geometry steps end (all live ones wait then at the latest)
+            uint64_t idle[H];
+            uint32_t nidle = 0, batch = 0, nwait = 0;
+            auto set_batch = [&]() {
+                nidle = 0;
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    idle[h] = exhausted ? ~(G[h] | W[h]) : 0ull;
+                    nidle += mask_count(idle[h]);
+                }
+                batch = wave_batch(P.coll_batch, 64u * H - nidle, 64u * H);
+            };
+            set_batch();
+            do {
+                nwait = 0;
+                uint64_t any_end = 0;
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    if (H == 1 || G[h] != 0) {
+                        w_events += mask_count(G[h]);
+                        const GeomOut o = geom_pass<F32, TIMED>(p[h], C, G[h], up[h], tally);
+                        const uint64_t end = o.leak | o.census;
+                        G[h] &= ~(o.coll | end);
+                        W[h] |= o.coll;
+                        if (end != 0) {
+                            w_leak += mask_count(o.leak);
+                            w_lr += mask_count(o.leak & up[h]);
+                            if (TIMED) w_cen += mask_count(o.census);
+                            ended(end, draws[h]);
+                        }
+                        any_end |= end;
+                    }
+                }
+                if (any_end != 0) set_batch();
+#pragma unroll
+                for (int h = 0; h < H; ++h) nwait += mask_count(~(G[h] | idle[h]));
+            } while (nwait < batch);
         }
 
         // unit diagnostics: the wave's counts and the lanes' into LDS
@@ -447,7 +494,7 @@ struct Slot {
 #define CH_ACQ_REL(op, p, v) __hip_atomic_##op((p), (v), __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP)
 
 template <bool F32, bool TIMED, bool ONE, int BLOCK>
-__global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_chain(TransportParams P) {
+__global__ void __launch_bounds__(BLOCK, 7) k_transport_chain(TransportParams P) {
     using chain::kNone;
     using chain::kNoMore;
     using chain::kWant;
@@ -619,11 +666,13 @@ __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_ch
     init_particle_at<F32, TIMED>(p, C, 0ull);
     uint32_t draws = 0;         // numbers drawn by the lane's history, before an absorption's one
     uint64_t G = 0, W = 0;      // flying, waiting (`live` also covers them)
+    uint64_t up = ~0ull;        // lanes with mu > 0
     uint32_t tl = 0;            // byte offset of the slice of the lane's history
     uint64_t w_events = 0, w_colls = 0;
     uint32_t w_leak = 0, w_lr = 0, w_abs = 0, w_cen = 0;
     uint32_t l_maxd = 0, l_over = 0;
     bool starved = false;   // wave-uniform: the last refill found no history to take
+    uint64_t done = 0;      // lanes whose ended histories are not reported yet
     auto note_end = [&](uint64_t m, uint32_t d) {
         if (in_mask(m)) {
             l_maxd = d > l_maxd ? d : l_maxd;
@@ -632,30 +681,16 @@ __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_ch
     };
 
     for (;;) {
-        if (G != 0) {
-            w_events += mask_count(G);
-            LimbTally tally;
-            tally.lo = reinterpret_cast<char*>(smem) + tl;
-            tally.hi_off = P.max_slice * 8u;
-            const GeomOut o = geom_pass<F32, TIMED>(p, C, G, tally);
-            const uint64_t end = o.leak | o.census;
-            G &= ~(o.coll | end);
-            W |= o.coll;
-            if (end != 0) {
-                w_leak += mask_count(o.leak);
-                w_lr += mask_count(o.right);
-                if (TIMED) w_cen += mask_count(o.census);
-                note_end(end, draws);
-                ends(end);
-            }
+        // report the histories that ended since the last pass (here only: one
+        // copy of that code keeps the scalar registers of the loops below)
+        if (done != 0) {
+            ends(done);
+            done = 0;
         }
-        const uint32_t nwait = mask_count(starved ? W : ~G);
-        if (nwait < P.coll_batch && G != 0) continue;
-
         // collision pass: refill the empty lanes first
         uint64_t fresh = 0;
         const uint64_t need = ~(G | W);
-        if (need != 0) {
+        if (mask_count(need) >= kRefill || (G | W) == 0) {
             const uint32_t nneed = mask_count(need);
             starved = false;
             while (r_filled - r_next < nneed) {
@@ -675,6 +710,7 @@ __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_ch
                 tl = sel_or_zero(in1, slice1_off);
                 draws = 1;
             }
+            up |= fresh;
             s1mask |= in1;
             live = G | W | fresh;
             r_next += take;
@@ -688,23 +724,51 @@ __global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_ch
             w = __builtin_amdgcn_readfirstlane(w);
             if ((w & kNoMore) && r_next == r_filled) break;
             __builtin_amdgcn_s_sleep(4);
+            continue;
         }
         uint64_t fly = fresh;
         if (W != 0) {
             w_colls += mask_count(W);
-            const uint64_t absorbed = collide_pass<F32>(p, C, P.lcg, W);
-            const uint64_t scat = W & ~absorbed;
+            const uint64_t scat = collide_pass<F32>(p, C, P.lcg, W, up);
+            const uint64_t absorbed = W & ~scat;
             W = 0;
+            draws += sel_const<3, 0>(scat);
             if (absorbed != 0) {
                 w_abs += mask_count(absorbed);
                 note_end(absorbed, draws + 1u);
-                ends(absorbed);
+                done |= absorbed;
             }
-            draws += sel_const<3, 0>(scat);
             fly |= scat;
         }
         if (in_mask(fly)) sample_tau<F32>(p, P.lcg);
         G |= fly;
+        if (G == 0) continue;
+
+        // geometry steps until `batch` lanes wait (empty lanes count while
+        // there may be histories for them)
+        uint64_t idle = starved ? ~(G | W) : 0ull;
+        uint32_t batch = wave_batch(P.coll_batch, 64u - mask_count(idle), 64u);
+        LimbTally tally;
+        tally.lo = reinterpret_cast<char*>(smem) + tl;
+        tally.hi_off = P.max_slice * 8u;
+        do {
+            w_events += mask_count(G);
+            const GeomOut o = geom_pass<F32, TIMED>(p, C, G, up, tally);
+            const uint64_t end = o.leak | o.census;
+            G &= ~(o.coll | end);
+            W |= o.coll;
+            if (end != 0) {
+                w_leak += mask_count(o.leak);
+                w_lr += mask_count(o.leak & up);
+                if (TIMED) w_cen += mask_count(o.census);
+                note_end(end, draws);
+                done |= end;
+                if (starved) {
+                    idle |= end;
+                    batch = wave_batch(P.coll_batch, 64u - mask_count(idle), 64u);
+                }
+            }
+        } while (mask_count(~(G | idle)) < batch);
     }
 
     // the problem's diagnostics: the block's sums, into its last unit's words
@@ -828,7 +892,10 @@ static hipError_t chain_fits_t(const TransportParams& a, const TransportParams& 
     e = blocks_per_cu(reinterpret_cast<const void*>(k_transport_chain<F32, TIMED, ONE, BLOCK>), BLOCK,
                       transport_lds_bytes(b, f32), &nb);
     if (e != hipSuccess) return e;
-    *fits = nb >= 1 && nb >= na;
+    // seven waves per SIMD are as many as help (eight measured 3% slower on
+    // the long-chain slab: 28.2 against 27.3 ms), so fewer are not missed
+    const int enough = std::max(1, 7 * 4 / (BLOCK / 64));
+    *fits = nb >= 1 && nb >= std::min(na, enough);
     return hipSuccess;
 }
 
