@@ -12,6 +12,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "internal.hpp"
@@ -360,6 +361,7 @@ struct mcrng_ctx {
     DevBuf units, order, partial, unit_diag, counter, groups, dx, dt, pu_begin;
     DevBuf bank_a, bank_b, records, rec_begin;   // event schedule
     DevBuf pulse_tedges, pulse_misc, pulse_diag, pulse_bank[2], pulse_stack;   // pulse problem
+    DevBuf pulse_left;                                                        // unused item ranges
     DevBuf pulse_census, pulse_copies, pulse_pop;                             // population control
     std::vector<double> h_pulse_tedges;
     uint64_t* h_pinned = nullptr;   // pinned host words for per-generation readbacks
@@ -458,7 +460,7 @@ extern "C" int mcrng_ctx_destroy(mcrng_ctx* ctx) {
                       &ctx->unit_diag, &ctx->counter, &ctx->groups, &ctx->dx, &ctx->dt, &ctx->pu_begin,
                       &ctx->bank_a, &ctx->bank_b, &ctx->records, &ctx->rec_begin, &ctx->pulse_tedges,
                       &ctx->pulse_misc, &ctx->pulse_diag, &ctx->pulse_bank[0], &ctx->pulse_bank[1],
-                      &ctx->pulse_stack, &ctx->pulse_census, &ctx->pulse_copies, &ctx->pulse_pop};
+                      &ctx->pulse_stack, &ctx->pulse_left, &ctx->pulse_census, &ctx->pulse_copies, &ctx->pulse_pop};
     for (DevBuf* b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (ctx->h_pinned) (void)hipHostFree(ctx->h_pinned);
@@ -1457,20 +1459,9 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     if (!d_counts) return fail(MCRNG_EINVAL, "d_counts is NULL");
     HIP_TRY(hipSetDevice(ctx->device));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // hash seeding lets every particle run anywhere: generation banks, or
-    // depth-first families once there are enough of them to fill every lane
-    // many times over (measured crossover on the 1000-source batches: about
-    // 16 families per resident lane); stride families must run depth first
-    // on one lane; population control needs the banks
-    if (o.schedule == MCRNG_PULSE_AUTO) {
-        const uint64_t lanes = static_cast<uint64_t>(pulse_family_grid(static_cast<int>(o.block))) * o.block;
-        if (!hash)
-            o.schedule = MCRNG_PULSE_FAMILY;
-        else if (!pc && n_src >= 16 * lanes)
-            o.schedule = MCRNG_PULSE_FAMILY;
-        else
-            o.schedule = MCRNG_PULSE_BANK;
-    }
+    // hash seeding lets every particle run anywhere: the waves' pools; stride
+    // families must run depth first on one lane
+    if (o.schedule == MCRNG_PULSE_AUTO) o.schedule = hash ? MCRNG_PULSE_BANK : MCRNG_PULSE_FAMILY;
 
     PulseParams pp;
     std::memset(&pp, 0, sizeof pp);
@@ -1513,10 +1504,35 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     pp.counts = d_counts;
     const uint64_t n_counters = static_cast<uint64_t>(P->n_batches) * P->n_time_bins;
     pp.n_counters = static_cast<uint32_t>(std::min<uint64_t>(n_counters, 0xffffffffu));
-    pp.lds_tally = n_counters <= kPulseLdsCounters ? 1u : 0u;
+    const bool event = o.schedule == MCRNG_PULSE_EVENT;
+    pp.lds_tally = n_counters <= (o.schedule == MCRNG_PULSE_BANK ? kPulsePoolLdsCounters : kPulseLdsCounters) ? 1u : 0u;
+    // the pool kernel's LDS: time edges up to 512 bins, and (counters not in
+    // LDS) 2 to 8 tally rows per wave within 1 KiB, up to 4 KiB for two
+    pp.edges_lds = P->n_time_bins <= 512 ? 1u : 0u;
+    pp.rows = 0;
+    if (!pp.lds_tally && P->n_time_bins <= 512) {
+        pp.rows = 8;
+        while (pp.rows > 2 && pp.rows * P->n_time_bins > 256) pp.rows /= 2;
+    }
+    pp.priv_cap = 1024;
+    pp.tail_iters = 256;
+    uint64_t pool_budget = 0;
+    if (const char* env = getenv("MCRNG_PULSE_PRIVATE")) pp.priv_cap = static_cast<uint32_t>(std::max(0, atoi(env)));
+    if (const char* env = getenv("MCRNG_PULSE_TAIL")) pp.tail_iters = static_cast<uint32_t>(std::max(1, atoi(env)));
+    if (const char* env = getenv("MCRNG_PULSE_BUDGET")) pool_budget = static_cast<uint64_t>(std::max(1, atoi(env)));
+    {
+        // edges near a uniform grid: the bin of a time is its grid cell or a neighbour
+        const uint32_t nt = P->n_time_bins;
+        pp.t0 = P->time_edges[0];
+        pp.inv_dt = nt / (P->time_edges[nt] - P->time_edges[0]);
+        bool uniform = std::isfinite(pp.inv_dt);
+        for (uint32_t i = 0; i <= nt && uniform; ++i)
+            uniform = std::fabs((P->time_edges[i] - pp.t0) * pp.inv_dt - i) < 0.25;
+        pp.grid_uniform = uniform ? 1u : 0u;
+    }
     pp.diag = static_cast<uint64_t*>(ctx->pulse_diag.p);
     // misc words: out_count, item_counter (reset per bank launch), family_counter, overflow,
-    // census arrivals, census copies
+    // census arrivals, census copies, unused item ranges
     uint64_t* misc = static_cast<uint64_t*>(ctx->pulse_misc.p);
     pp.out_count = misc;
     pp.item_counter = misc + 1;
@@ -1524,6 +1540,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     pp.overflow = reinterpret_cast<uint32_t*>(misc + 3);
     pp.cen_count = misc + 4;
     pp.copy_count = misc + 5;
+    pp.n_left = misc + 6;
     const uint32_t K = pc ? pc->census_every : 0;
     const uint32_t n_census = pc ? (P->n_time_bins - 1) / K : 0;
     const uint64_t n_pop = static_cast<uint64_t>(P->n_batches) * n_census * 2;
@@ -1542,12 +1559,96 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     HIP_TRY(hipEventRecord(ctx->ev0, st));
     ctx->timing_valid = false;
 
-    // Generations: a launch runs the lines of descent of its input items
-    // (their first emerging particles inline) and banks the siblings for
-    // the next launch.  Capacity per launch: the continue budget (2 per
-    // input item), n_max per input item, and one LDS stage plus one
-    // iteration's appends per wave.  With `pcen` (a census of population
-    // control ends the epoch) every line ends at most once at the census, so
+    // Pool launches (bank schedule): a launch runs its items and all they give
+    // rise to, except what its waves hand over to the output bank: entries
+    // beyond a wave's LDS pool and private stack, and what a wave still holds
+    // some iterations after the items have been taken.  The bank is the next
+    // launch's input, until none is left; then come the item ranges a wave
+    // took but handed back.  Capacities: a wave that has seen out_budget
+    // entries in the output bank (cen_budget census arrivals) hands over what
+    // it holds and ends, so it appends at most its slack after that; items
+    // not taken then (of a bank) are copied behind the output.
+    auto pool_run = [&](int kind, uint64_t begin, uint64_t end, bool pcen, uint64_t* cen_used) -> int {
+        const int block = static_cast<int>(o.block);
+        std::vector<std::pair<uint64_t, uint64_t>> ranges;
+        if (end > begin) ranges.emplace_back(begin, end);
+        int cur = 0, nxt = 1;   // banks: cur is the launch's input (kind BANK), nxt its output
+        uint64_t in_cap = 0, n_bank = 0;
+        while (n_bank > 0 || !ranges.empty()) {
+            const int k = n_bank > 0 ? static_cast<int>(PULSE_ITEMS_BANK) : kind;
+            if (n_bank > 0) {
+                pp.item_begin = 0;
+                pp.item_end = n_bank;
+                pp.in = carve_pulse_bank(ctx->pulse_bank[cur].p, in_cap);
+            } else {
+                pp.item_begin = ranges.back().first;
+                pp.item_end = ranges.back().second;
+                ranges.pop_back();
+            }
+            const uint64_t n = pp.item_end - pp.item_begin;
+            const uint32_t grid = pulse_pool_grid(pp, k, pcen, block, n);
+            const uint64_t waves = static_cast<uint64_t>(grid) * o.block / 64;
+            // half of a wave's share per atomic, so that the waves end together
+            pp.chunk = static_cast<uint32_t>(std::min<uint64_t>(64, std::max<uint64_t>(1, n / (2 * waves))));
+            if (o.chunk) pp.chunk = 64;
+            pp.out_budget = pool_budget ? pool_budget : std::min<uint64_t>(std::max<uint64_t>(2 * n, 1u << 16), 1u << 24);
+            const uint64_t ocap = pp.out_budget + waves * pulse_pool_slack(pp, n_max) + (n_bank > 0 ? n : 0);
+            int r;
+            if ((r = ensure(ctx->pulse_bank[nxt], ocap * 32, st)) < 0) return r;
+            if ((r = ensure(ctx->pulse_stack, waves * pp.priv_cap * sizeof(PulsePoolEntry), st)) < 0) return r;
+            if ((r = ensure(ctx->pulse_left, waves * 16, st)) < 0) return r;
+            pp.priv = static_cast<PulsePoolEntry*>(ctx->pulse_stack.p);
+            pp.left = static_cast<uint64_t*>(ctx->pulse_left.p);
+            if (pcen) {
+                pp.cen_budget = *cen_used + (pool_budget ? pool_budget : std::max<uint64_t>(4 * n, 1u << 20));
+                r = ensure_keep(ctx->pulse_census, *cen_used * sizeof(PulseCensusEntry),
+                                (pp.cen_budget + waves * kPulsePoolCensusSlack) * sizeof(PulseCensusEntry), st);
+                if (r < 0) return r;
+                pp.cen = static_cast<PulseCensusEntry*>(ctx->pulse_census.p);
+                pp.cen_cap = ctx->pulse_census.cap / sizeof(PulseCensusEntry);
+            }
+            pp.out = carve_pulse_bank(ctx->pulse_bank[nxt].p, ocap);
+            pp.out_cap = ocap;
+            HIP_TRY(launch_fill_u64(misc, 3, 0ull, st));
+            HIP_TRY(launch_pulse_pool(pp, k, pcen, block, grid, st));
+            uint64_t w[7];
+            if ((r = read_words(ctx, misc, 7, w, st)) < 0) return r;
+            // a bank that ran out of room (never, by the capacities above)
+            // ends the run before any launch reads past it
+            if (w[3] & 0xffffffffull) return fail(MCRNG_ERANGE, "a particle bank ran out of room");
+            if (pcen) *cen_used = w[4];
+            uint64_t n_out = w[0];
+            const uint64_t taken = std::min(pp.item_begin + w[1], pp.item_end);
+            if (k == PULSE_ITEMS_BANK && taken < pp.item_end) {
+                const uint64_t rest = pp.item_end - taken;
+                const PulseBankView &a = pp.in, &b = pp.out;
+                HIP_TRY(hipMemcpyAsync(b.x + n_out, a.x + taken, rest * 8, hipMemcpyDeviceToDevice, st));
+                HIP_TRY(hipMemcpyAsync(b.t + n_out, a.t + taken, rest * 8, hipMemcpyDeviceToDevice, st));
+                HIP_TRY(hipMemcpyAsync(b.X + n_out, a.X + taken, rest * 8, hipMemcpyDeviceToDevice, st));
+                HIP_TRY(hipMemcpyAsync(b.batch + n_out, a.batch + taken, rest * 4, hipMemcpyDeviceToDevice, st));
+                HIP_TRY(hipMemcpyAsync(b.tb + n_out, a.tb + taken, rest * 4, hipMemcpyDeviceToDevice, st));
+                n_out += rest;
+            } else if (taken < pp.item_end) {
+                ranges.emplace_back(taken, pp.item_end);
+            }
+            if (w[6] != 0) {   // ranges handed back
+                std::vector<uint64_t> l(2 * w[6]);
+                HIP_TRY(hipMemcpyAsync(l.data(), pp.left, l.size() * 8, hipMemcpyDeviceToHost, st));
+                HIP_TRY(hipStreamSynchronize(st));
+                for (size_t i = 0; i < l.size(); i += 2) ranges.emplace_back(l[i], l[i + 1]);
+                HIP_TRY(launch_fill_u64(pp.n_left, 1, 0ull, st));
+            }
+            n_bank = n_out;
+            std::swap(cur, nxt);
+            in_cap = ocap;
+        }
+        return MCRNG_OK;
+    };
+
+    // Event schedule: a launch advances its input items by one flight each and
+    // banks all emerging particles for the next launch.  Capacity per launch:
+    // n_max per input item, and one LDS stage plus one iteration's appends
+    // per wave.  With `pcen` (a census of population control ends the epoch)
     // the census bank grows by at most the launch's items.
     // The tail of a chain (a generation that shrank to at most 1/finish_div
     // of the largest, and to at most kFinishItems) is finished by one launch
@@ -1598,12 +1699,9 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             }
             const uint32_t grid = pulse_bank_grid(pp, kind, pcen, static_cast<int>(o.block), n);
             const uint64_t waves = static_cast<uint64_t>(grid) * o.block / 64;
-            // event schedule: no line runs on within a launch (one flight
-            // and collision per particle and launch)
-            const uint64_t budget = o.schedule == MCRNG_PULSE_EVENT ? 0 : 2 * n;
             const uint64_t slack =
                 (waves + 1) * (pulse_bank_stage(static_cast<int>(o.block)) + 64 * static_cast<uint64_t>(n_max));
-            const uint64_t ocap = budget + static_cast<uint64_t>(n_max) * n + slack;
+            const uint64_t ocap = static_cast<uint64_t>(n_max) * n + slack;
             int r = ensure(ctx->pulse_bank[nxt], ocap * 32, st, 8);
             if (r < 0) return r;
             if (pcen) {
@@ -1617,7 +1715,6 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             pp.n_in = kind == PULSE_ITEMS_SOURCES ? 0 : n;
             pp.out = carve_pulse_bank(ctx->pulse_bank[nxt].p, ocap);
             pp.out_cap = ocap;
-            pp.cont_budget = budget;
             HIP_TRY(launch_fill_u64(misc, 2, 0ull, st));
             HIP_TRY(launch_pulse_bank(pp, kind, pcen, static_cast<int>(o.block), grid, st));
             uint64_t w[5];
@@ -1653,12 +1750,14 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
                 uint64_t cen_used = 0;
                 HIP_TRY(launch_fill_u64(pp.cen_count, 1, 0ull, st));
                 if (e == 0) {
-                    rc = generations(PULSE_ITEMS_SOURCES, pp.src_end - pp.src_begin, pcen, &cen_used);
+                    rc = event ? generations(PULSE_ITEMS_SOURCES, pp.src_end - pp.src_begin, pcen, &cen_used)
+                               : pool_run(PULSE_ITEMS_SOURCES, pp.src_begin, pp.src_end, pcen, &cen_used);
                 } else {
                     pp.copies = static_cast<const PulseCensusEntry*>(ctx->pulse_copies.p);
                     pp.t_start = P->time_edges[static_cast<size_t>(e) * K];
                     pp.tb_start = static_cast<int32_t>(e * K);
-                    rc = generations(PULSE_ITEMS_COPIES, n_copies, pcen, &cen_used);
+                    rc = event ? generations(PULSE_ITEMS_COPIES, n_copies, pcen, &cen_used)
+                               : pool_run(PULSE_ITEMS_COPIES, 0, n_copies, pcen, &cen_used);
                 }
                 if (rc < 0) return rc;
                 if (!pcen) break;
@@ -1678,7 +1777,9 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
                 n_copies = w[5];
             }
         }
-    } else if (o.schedule == MCRNG_PULSE_BANK || o.schedule == MCRNG_PULSE_EVENT) {
+    } else if (o.schedule == MCRNG_PULSE_BANK) {
+        if ((rc = pool_run(PULSE_ITEMS_SOURCES, 0, n_src, false, nullptr)) < 0) return rc;
+    } else if (event) {
         // Sources go in chunks so that the banks stay within tens of GB.
         const uint64_t chunk = 1ull << 23;
         for (uint64_t c0 = 0; c0 < n_src; c0 += chunk) {

@@ -91,6 +91,14 @@ __host__ __device__ __forceinline__ uint64_t uniform_below(double c) {
 __device__ __forceinline__ uint64_t wave_mask(bool c) { return __builtin_amdgcn_ballot_w64(c); }
 __device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
+__device__ __forceinline__ uint32_t mask_count(uint64_t m) { return static_cast<uint32_t>(__popcll(m)); }
+
+// A lane's rank among the lanes of a mask.
+__device__ __forceinline__ uint32_t mask_rank(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+}
+
 // A value that is the same on every lane, in scalar registers.
 __device__ __forceinline__ uint64_t uniform_value(uint64_t v) {
     const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));

@@ -285,10 +285,9 @@ __device__ __forceinline__ void bank_store(const PulseParams& P, uint64_t o, dou
     }
 }
 
-// Copies the wave's staged entries to the output bank (one atomic) and
-// returns the output count just after them.
+// Copies the wave's staged entries to the output bank (one atomic).
 template <class Stage>
-__device__ __forceinline__ uint64_t bank_flush(const PulseParams& P, Stage& S, uint32_t count,
+__device__ __forceinline__ void bank_flush(const PulseParams& P, Stage& S, uint32_t count,
                                                uint32_t lane) {
     __builtin_amdgcn_wave_barrier();
     uint64_t base = 0;
@@ -296,20 +295,24 @@ __device__ __forceinline__ uint64_t bank_flush(const PulseParams& P, Stage& S, u
     base = lane_value(base, 0);
     for (uint32_t i = lane; i < count; i += 64) bank_store(P, base + i, S.x[i], S.t[i], S.X[i], S.batch[i], S.tb[i]);
     __builtin_amdgcn_wave_barrier();
-    return base + count;
 }
 
 // Per-wave staging of census arrivals (population control), flushed to
 // P.cen with one atomic per flush.
-struct CensusStage {
-    static constexpr uint32_t kCap = 128;   // 28 B per entry: 3.5 KiB per wave
+template <uint32_t CAP>
+struct CensusStageOf {
+    static constexpr uint32_t kCap = CAP;   // 28 B per entry
     double x[kCap];
     double mu[kCap];
     uint64_t X[kCap];
     uint32_t batch[kCap];
 };
 
-__device__ __forceinline__ void census_flush(const PulseParams& P, CensusStage& S, uint32_t count, uint32_t lane) {
+using CensusStage = CensusStageOf<128>;   // 3.5 KiB per wave
+
+// Returns the arrival count just after the flushed entries.
+template <class Stage>
+__device__ __forceinline__ uint64_t census_flush(const PulseParams& P, Stage& S, uint32_t count, uint32_t lane) {
     __builtin_amdgcn_wave_barrier();
     uint64_t base = 0;
     if (lane == 0) base = atomicAdd(reinterpret_cast<unsigned long long*>(P.cen_count), count);
@@ -329,6 +332,7 @@ __device__ __forceinline__ void census_flush(const PulseParams& P, CensusStage& 
         }
     }
     __builtin_amdgcn_wave_barrier();
+    return base + count;
 }
 
 // Stages the wave's census arrivals (lanes with at_census) in CS: the point
@@ -399,7 +403,6 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_bank(PulseParams P) {
     uint64_t wnext = 0, wend = 0;      // wave-uniform: the wave's unassigned items [wnext, wend)
     bool exhausted = false;            // wave-uniform
     uint32_t staged = 0;               // wave-uniform: entries in S
-    uint64_t seen = 0;                 // wave-uniform: output count after this wave's last flush
     PParticle p;
     p.x = p.t = 0.0;
     p.Z = 0;
@@ -445,29 +448,19 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_bank(PulseParams P) {
             uint32_t draws = 0;
             n = pulse_particle<DIR>(P, p, c, &draws, &tally, &at_census);
             note_stream(P, c, draws);   // every particle has its own stream
-            if (n == 0) active = false;
         }
         wave_tally(P, tally, lane, lds_counts);
         if (PC) census_stage(P, CS, cstaged, at_census, p, lane);
-        // siblings (keys 2..n) are banked and the line runs on with key 1
-        // while this wave's view of the output count (last flush + staged)
-        // is within the budget; past it (or with no budget: the event
-        // schedule), a scattering banks all n and ends the line
-        uint32_t sib_total = 0;
-        wave_prefix16(n > 1 ? n - 1 : 0, &sib_total);
-        const bool keep = P.cont_budget != 0 && seen + staged + sib_total <= P.cont_budget;   // 0: event based
-        const uint32_t k0 = keep ? 2u : 1u;
-        const uint32_t npush = n >= k0 ? n - k0 + 1 : 0;
         uint32_t total = 0;
-        const uint32_t off = wave_prefix16(npush, &total);
+        const uint32_t off = wave_prefix16(n, &total);
         if (total != 0) {
             if (staged + total > Stage::kCap) {
-                seen = bank_flush(P, S, staged, lane);
+                bank_flush(P, S, staged, lane);
                 staged = 0;
             }
             if (total <= Stage::kCap) {
-                for (uint32_t k = k0; k <= n; ++k) {
-                    const uint32_t e = staged + off + (k - k0);
+                for (uint32_t k = 1; k <= n; ++k) {
+                    const uint32_t e = staged + off + (k - 1);
                     S.x[e] = p.x;
                     S.t[e] = p.t;
                     S.X[e] = murmur_hash(k, p.Z >> P.lcg.up) << P.lcg.up;
@@ -480,24 +473,430 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_bank(PulseParams P) {
                 uint64_t base = 0;
                 if (lane == 0) base = atomicAdd(reinterpret_cast<unsigned long long*>(P.out_count), total);
                 base = lane_value(base, 0);
-                for (uint32_t k = k0; k <= n; ++k)
-                    bank_store(P, base + off + (k - k0), p.x, p.t, murmur_hash(k, p.Z >> P.lcg.up) << P.lcg.up, p.batch, p.tb);
-                seen = base + total;
+                for (uint32_t k = 1; k <= n; ++k)
+                    bank_store(P, base + off + (k - 1), p.x, p.t, murmur_hash(k, p.Z >> P.lcg.up) << P.lcg.up, p.batch, p.tb);
             }
         }
-        if (n > 0) {
-            if (keep) {
-                p.Z = murmur_hash(1ull, p.Z >> P.lcg.up) << P.lcg.up;   // the first emerging particle runs on here
-                p.has_mu = false;
-            } else {
-                active = false;
-            }
-        }
+        active = false;
     }
     if (staged != 0) bank_flush(P, S, staged, lane);
     if (PC && cstaged != 0) census_flush(P, CS, cstaged, lane);
     tally_lds_end<BLOCK>(P, lds_counts);
     flush_lane_counters<BLOCK>(P, c);
+}
+
+// A source of a wave's chunk, seeded when the chunk is taken.
+struct __align__(16) FamilySource {
+    uint64_t X;
+    uint32_t batch;
+    uint32_t pad;
+};
+
+// ------------------------------------------------------------ pool kernel (bank schedule)
+
+// Hash seeding lets any lane run any particle, so a wave works as one
+// depth-first walker with 64 hands: a lane runs a line of descent (the first
+// particle emerging from each scattering) in registers, the siblings go to the
+// wave's pool in LDS, and a lane whose line ended takes the newest particle
+// of the pool; new items only when the pool is empty.  All lanes fly in every
+// iteration, and no particle touches HBM while the pool fits (one iteration
+// adds about 7 entries net on the paper's problem, a particle lives about
+// `census time` iterations, so about 140 wait at a time).
+//   The kernel is bound by vector issue (about 190 instructions per flight at
+// full lanes).  Generations in HBM (the schedule's former kernel: one launch
+// and one read-back per generation, 32 B each way per banked particle, waves
+// waiting on the append counter) took 5.9 ms for the paper's 1000 x 1000
+// sources, 5.6 ms for 4096 sources to t = 60.
+//   Where particles go when the LDS pool is full: its older half to the wave's
+// private HBM stack (priv_cap entries, read back when the pool is empty); when
+// that is full too, to the launch's output bank; and once the wave has seen
+// more than out_budget entries there (or cen_budget census arrivals), it hands
+// over everything it holds and ends, so that appends stay within
+// out_budget + slack per wave.  A wave also hands over what is left tail_iters
+// iterations after the launch's items are taken: families are heavy-tailed,
+// and the next launch spreads the rest over all waves.
+template <int BLOCK, bool PC>
+constexpr uint32_t pool_entries() {
+    return (PC || BLOCK >= 1024) ? 128u : 256u;   // a 256-thread block stays within 40 KiB: four per CU
+}
+constexpr uint32_t kPoolCensusStage = 64;
+constexpr uint32_t kPoolFlushMask = (1u << 25) - 1u;   // iterations between forced row flushes (32-bit counters)
+
+// (k M ^ (k M >> 47)) M: the part of hash(k, s) that depends on k only.
+__device__ __forceinline__ uint64_t child_part(uint64_t k) {
+    const uint64_t y = k * kMurmurM;
+    return (y ^ (y >> 47)) * kMurmurM;
+}
+// Start state (top-aligned) of child k of a parent that ended in state X (eq. 5).
+__device__ __forceinline__ uint64_t child_state(const LcgDev& L, uint64_t X, uint64_t part) {
+    return murmur_sub(murmur_seed_part(X) ^ part) << L.up;
+}
+
+template <int ITEMS, bool PC, int BLOCK>
+__global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
+    constexpr bool SOURCES = ITEMS == PULSE_ITEMS_SOURCES;
+    constexpr bool COPIES = ITEMS == PULSE_ITEMS_COPIES;
+    constexpr uint32_t CAP = pool_entries<BLOCK, PC>();
+    constexpr uint32_t kWaves = BLOCK / 64;
+    __shared__ PulsePoolEntry s_pool[kWaves][CAP];
+    __shared__ FamilySource s_src[SOURCES ? kWaves : 1][SOURCES ? 64 : 1];
+    __shared__ uint32_t s_tag[kWaves][8];
+    __shared__ CensusStageOf<kPoolCensusStage> s_cen[PC ? kWaves : 1];
+    __shared__ uint64_t s_part[16];
+    __shared__ unsigned long long s_acc[kNDiag];
+    extern __shared__ unsigned long long dyn[];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t nt = P.n_time_bins;
+    // dynamic LDS: time edges, the block's counters or the waves' tally rows
+    double* const l_edges = reinterpret_cast<double*>(dyn);
+    unsigned long long* const counters = dyn + (P.edges_lds ? nt + 1 : 0u);
+    if (P.edges_lds)
+        for (uint32_t i = threadIdx.x; i <= nt; i += BLOCK) l_edges[i] = P.t_edges[i];
+    auto edge_at = [&](int32_t i) -> double { return P.edges_lds ? l_edges[i] : P.t_edges[i]; };
+    uint32_t* const rows = reinterpret_cast<uint32_t*>(counters) + wid * P.rows * nt;
+    if (P.rows != 0) {
+        for (uint32_t i = lane; i < P.rows * nt; i += 64u) rows[i] = 0u;
+        if (lane < 8u) s_tag[wid][lane] = 0xffffffffu;
+    }
+    if (threadIdx.x < 16) s_part[threadIdx.x] = child_part(threadIdx.x);
+    if (threadIdx.x < kNDiag) s_acc[threadIdx.x] = 0;
+    tally_lds_begin<BLOCK>(P, counters);   // and the barrier for the above
+
+    PulsePoolEntry* const pool = s_pool[wid];
+    FamilySource* const src = s_src[SOURCES ? wid : 0];
+    uint32_t* const tags = s_tag[wid];
+    auto& cen = s_cen[PC ? wid : 0];
+    const uint64_t wave = static_cast<uint64_t>(blockIdx.x) * kWaves + wid;
+    PulsePoolEntry* const priv = P.priv + wave * P.priv_cap;
+    const uint64_t part1 = uniform_value(child_part(1));
+    const double sigma = P.sigma_t;
+    const double rsigma = uniform_value(recip_refined(sigma));
+
+    // wave-uniform state
+    uint64_t A = 0;                     // lanes holding a particle at the start of its flight
+    uint64_t dir = 0;                   // COPIES: lanes whose particle keeps its direction
+    uint32_t bot = 0, top = 0;          // the pool holds entries [bot, top) (mod CAP)
+    uint32_t npriv = 0;
+    uint64_t wnext = 0, wend = 0;       // the wave's untaken items
+    uint32_t src_off = 0;               // item wnext's place in src
+    bool exhausted = false, hand_over = false;
+    uint64_t seen = 0;                  // output count after this wave's last append
+    uint32_t cstaged = 0, tail = 0, iter = 0;
+    uint64_t n_src = 0, n_fly = 0, n_dir = 0, n_coll = 0, n_tal = 0, n_scat = 0, n_extra = 0;
+    uint32_t max_draws = 0;
+    // the lane's particle
+    double x = 0.0, t = 0.0, mu0 = 0.0;
+    uint64_t Z = 0;
+    uint32_t batch = 0;
+    int32_t tb = -1;
+
+    auto flush_row = [&](uint32_t r) {
+        const uint32_t tag = __builtin_amdgcn_readfirstlane(tags[r]);
+        if (tag == 0xffffffffu) return;
+        unsigned long long* c = reinterpret_cast<unsigned long long*>(P.counts) + static_cast<uint64_t>(tag) * nt;
+        for (uint32_t i = lane; i < nt; i += 64u) {
+            const uint32_t v = rows[r * nt + i];
+            if (v != 0u) {
+                atomicAdd(c + i, static_cast<unsigned long long>(v));
+                rows[r * nt + i] = 0u;
+            }
+        }
+    };
+    // gives the batches of the lanes in m a tally row each (another batch's row
+    // with the same index goes to HBM first; particles of a batch without a
+    // row count in HBM)
+    auto claim_rows = [&](uint64_t m) {
+        while (m != 0) {
+            const uint32_t b = __builtin_amdgcn_readlane(batch, __builtin_ctzll(m));
+            const uint32_t r = b & (P.rows - 1u);
+            if (__builtin_amdgcn_readfirstlane(tags[r]) != b) {
+                flush_row(r);
+                if (lane == 0) tags[r] = b;
+                __builtin_amdgcn_wave_barrier();
+            }
+            m &= ~wave_mask(batch == b);
+        }
+    };
+    // reserves n entries of the output bank (n uniform)
+    auto reserve = [&](uint32_t n) -> uint64_t {
+        uint64_t base = 0;
+        if (lane == 0) base = atomicAdd(reinterpret_cast<unsigned long long*>(P.out_count), static_cast<unsigned long long>(n));
+        base = lane_value(base, 0);
+        seen = base + n;
+        return base;
+    };
+    auto store_entry = [&](uint64_t o, const PulsePoolEntry& e) {
+        bank_store(P, o, e.x, e.t, child_state(P.lcg, e.key, s_part[(e.meta >> 16) & 15u]), e.batch,
+                   static_cast<int32_t>(e.meta & 0xffffu) - 1);
+    };
+
+    for (;;) {
+        uint64_t need = ~A;
+        if (need != 0) {
+            if (top == bot && npriv != 0) {
+                // the newest entries of the private stack
+                const uint32_t cnt = npriv < CAP / 2 ? npriv : CAP / 2;
+                npriv -= cnt;
+                for (uint32_t i = lane; i < cnt; i += 64u) pool[(top + i) & (CAP - 1)] = priv[npriv + i];
+                top += cnt;
+                __builtin_amdgcn_wave_barrier();
+            }
+            uint32_t k = mask_count(need);
+            if (top != bot) {
+                const uint32_t take = top - bot < k ? top - bot : k;
+                const uint32_t rank = mask_rank(need);
+                const uint64_t m = need & wave_mask(rank < take);
+                if (in_mask(m)) {
+                    const PulsePoolEntry e = pool[(top - 1u - rank) & (CAP - 1)];
+                    x = e.x;
+                    t = e.t;
+                    batch = e.batch;
+                    tb = static_cast<int32_t>(e.meta & 0xffffu) - 1;
+                    Z = child_state(P.lcg, e.key, s_part[e.meta >> 16]);
+                }
+                top -= take;
+                k -= take;
+                A |= m;
+                need &= ~m;
+                __builtin_amdgcn_wave_barrier();
+            }
+            if (k != 0 && wnext == wend && !exhausted) {
+                uint64_t b = 0;
+                if (lane == 0)
+                    b = atomicAdd(reinterpret_cast<unsigned long long*>(P.item_counter), static_cast<unsigned long long>(P.chunk));
+                b = P.item_begin + lane_value(b, 0);
+                if (b + P.chunk >= P.item_end) exhausted = true;
+                wnext = b < P.item_end ? b : P.item_end;
+                wend = b + P.chunk < P.item_end ? b + P.chunk : P.item_end;
+                if (SOURCES) {
+                    const uint64_t j = wnext + lane;
+                    if (j < wend) {
+                        FamilySource e;
+                        e.X = pulse_source_state(P, j, &e.batch);
+                        e.pad = 0;
+                        src[lane] = e;
+                    }
+                    src_off = 0;
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
+            if (k != 0 && wnext != wend) {
+                const uint64_t avail = wend - wnext;
+                const uint32_t take = avail < k ? static_cast<uint32_t>(avail) : k;
+                const uint32_t rank = mask_rank(need);
+                const uint64_t m = need & wave_mask(rank < take);
+                if (in_mask(m)) {
+                    if (SOURCES) {
+                        const FamilySource e = src[src_off + rank];
+                        Z = e.X;
+                        batch = e.batch;
+                        x = 0.0;
+                        t = 0.0;
+                        tb = P.tb0;
+                    } else {
+                        PParticle q;
+                        load_item<ITEMS>(P, wnext + rank, q);
+                        x = q.x;
+                        t = q.t;
+                        Z = q.Z;
+                        batch = q.batch;
+                        tb = q.tb;
+                        if (COPIES) mu0 = q.mu;
+                    }
+                }
+                if (SOURCES) n_src += take;
+                if (COPIES) dir |= m;
+                wnext += take;
+                src_off += take;
+                A |= m;
+                if (P.rows != 0) claim_rows(m);
+            }
+        }
+        if (A == 0) break;   // no pool, no items
+        if (exhausted && wnext == wend && ++tail > P.tail_iters) {
+            hand_over = true;
+            break;
+        }
+        if (P.rows != 0 && (++iter & kPoolFlushMask) == 0)
+            for (uint32_t r = 0; r < P.rows; ++r) flush_row(r);
+
+        // one flight of every lane in A (the others compute on what their registers hold)
+        const uint64_t z1 = lcg_next_z(P.lcg, Z);
+        double mu = __builtin_fma(uniform_z(z1), 2.0, -1.0);   // exact
+        uint64_t z = z1;
+        if (COPIES && (dir & A) != 0) {
+            mu = sel(dir, mu0, mu);
+            z = sel(dir, Z, z1);
+        }
+        const uint64_t drew = COPIES ? A & ~dir : A;
+        z = lcg_next_z(P.lcg, z);
+        const double s = quot(fixed_neg_log(uniform_z(z)), sigma, rsigma);
+        const double tn = t + s;
+        const uint64_t coll = A & wave_mask(tn < P.t_end);
+        const uint64_t census = A & ~coll;
+        if (PC && census != 0) {
+            const uint32_t cnt = mask_count(census);
+            if (cstaged + cnt > kPoolCensusStage) {
+                if (census_flush(P, cen, cstaged, lane) > P.cen_budget) hand_over = true;
+                cstaged = 0;
+            }
+            if (in_mask(census)) {
+                const uint32_t e = cstaged + mask_rank(census);
+                const double rest = P.t_end - t;
+                const double step = mu * rest;
+                cen.x[e] = x + step;
+                cen.mu[e] = mu;
+                cen.X[e] = z >> P.lcg.up;
+                cen.batch[e] = batch;
+            }
+            cstaged += cnt;
+        }
+        const double step = mu * s;
+        const double xn = x + step;
+        int32_t bin = tb;
+        if (P.grid_uniform) {
+            int32_t g;   // (the instruction saturates, whatever idle lanes hold)
+            asm("v_cvt_i32_f64 %0, %1" : "=v"(g) : "v"((tn - P.t0) * P.inv_dt));
+            g = g < 0 ? 0 : g;
+            g = g < static_cast<int32_t>(nt) ? g : static_cast<int32_t>(nt) - 1;
+            const uint64_t before = wave_mask(tn < edge_at(g)), after = wave_mask(edge_at(g + 1) <= tn);
+            bin = g - static_cast<int32_t>(sel_const<1, 0>(before)) + static_cast<int32_t>(sel_const<1, 0>(after));
+        } else if (in_mask(coll)) {
+            while (bin + 1 < static_cast<int32_t>(nt) && edge_at(bin + 1) <= tn) bin++;
+        }
+        const uint64_t scored = coll & wave_mask(bin >= 0) & wave_mask(P.x_lo <= xn) & wave_mask(xn <= P.x_hi);
+        if (in_mask(scored)) {
+            const uint64_t counter = static_cast<uint64_t>(batch) * nt + static_cast<uint32_t>(bin);
+            if (P.lds_tally) {
+                atomicAdd(counters + counter, 1ull);
+            } else {
+                const uint32_t r = P.rows != 0 ? batch & (P.rows - 1u) : 0u;
+                if (P.rows != 0 && tags[r] == batch)
+                    atomicAdd(rows + r * nt + static_cast<uint32_t>(bin), 1u);
+                else
+                    atomicAdd(reinterpret_cast<unsigned long long*>(P.counts) + counter, 1ull);
+            }
+        }
+        const uint64_t z3 = lcg_next_z(P.lcg, z);
+        const uint64_t go = coll & wave_mask(z3 < P.scatter_below);
+        const uint64_t z4 = lcg_next_z(P.lcg, z3);
+        const uint64_t extra = go & wave_mask(z4 < P.frac_below);
+        const uint64_t key = z4 >> P.lcg.up;
+
+        n_fly += mask_count(A);
+        n_dir += mask_count(drew);
+        n_coll += mask_count(coll);
+        n_tal += mask_count(scored);
+        n_scat += mask_count(go);
+        n_extra += mask_count(extra);
+        {
+            // draws of the longest stream: direction, flight, absorption test, multiplicity
+            const uint64_t keep = A & ~drew;
+            uint32_t d = (drew & go) != 0 ? 4u : (((drew & coll) | (keep & go)) != 0 ? 3u : (((drew | (keep & coll)) != 0) ? 2u : 1u));
+            if (max_draws < d) max_draws = d;
+        }
+        if (COPIES) dir &= ~A;
+
+        // the first emerging particle runs on here, the others go to the pool:
+        // n_floor - 1 for every scattering, one more for `extra` (n_floor = 0: none)
+        if (in_mask(go)) {
+            x = xn;
+            t = tn;
+            tb = bin;
+        }
+        const uint32_t n_more = P.n_floor != 0 ? (P.n_floor - 1u) * mask_count(go) + mask_count(extra) : 0u;
+        if (n_more != 0) {
+            const uint32_t off = (P.n_floor - 1u) * mask_rank(go) + mask_rank(extra);
+            const uint32_t n = P.n_floor + sel_const<1, 0>(extra);
+            bool direct = n_more > CAP;   // large multiplicities
+            while (!direct && top - bot + n_more > CAP) {
+                const uint32_t cnt = top - bot < CAP / 2 ? top - bot : CAP / 2;
+                if (npriv + cnt <= P.priv_cap) {
+                    for (uint32_t i = lane; i < cnt; i += 64u) priv[npriv + i] = pool[(bot + i) & (CAP - 1)];
+                    npriv += cnt;
+                } else if (seen <= P.out_budget) {
+                    const uint64_t base = reserve(cnt);
+                    for (uint32_t i = lane; i < cnt; i += 64u) store_entry(base + i, pool[(bot + i) & (CAP - 1)]);
+                } else {
+                    direct = hand_over = true;
+                    break;
+                }
+                bot += cnt;
+                __builtin_amdgcn_wave_barrier();
+            }
+            if (direct) {
+                const uint64_t base = reserve(n_more);
+                if (seen > P.out_budget) hand_over = true;
+                if (in_mask(go))
+                    for (uint32_t c = 2; c <= n; ++c)
+                        bank_store(P, base + off + (c - 2u), x, t, child_state(P.lcg, key, s_part[c]), batch, tb);
+            } else {
+                if (in_mask(go))
+                    for (uint32_t c = 2; c <= n; ++c) {
+                        PulsePoolEntry e;
+                        e.x = x;
+                        e.t = t;
+                        e.key = key;
+                        e.batch = batch;
+                        e.meta = (c << 16) | static_cast<uint32_t>(tb + 1);
+                        pool[(top + off + (c - 2u)) & (CAP - 1)] = e;
+                    }
+                top += n_more;
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        A = P.n_floor != 0 ? go : extra;
+        if (in_mask(A)) Z = child_state(P.lcg, key, part1);
+        if (hand_over) break;
+    }
+
+    if (hand_over) {
+        // everything the wave holds goes to the output bank (every lane in A
+        // is past its first flight here, so no direction is lost); items
+        // taken but not started go there too, or back to the host as a range
+        const uint32_t nl = mask_count(A), np = top - bot;
+        uint32_t ni = 0;
+        if (ITEMS == PULSE_ITEMS_BANK) ni = static_cast<uint32_t>(wend - wnext);
+        if (ITEMS != PULSE_ITEMS_BANK && wend != wnext && lane == 0) {
+            const uint64_t o = atomicAdd(reinterpret_cast<unsigned long long*>(P.n_left), 1ull);
+            P.left[2 * o] = wnext;
+            P.left[2 * o + 1] = wend;
+        }
+        const uint64_t base = reserve(nl + np + npriv + ni);
+        if (in_mask(A)) bank_store(P, base + mask_rank(A), x, t, Z, batch, tb);
+        for (uint32_t i = lane; i < np; i += 64u) store_entry(base + nl + i, pool[(bot + i) & (CAP - 1)]);
+        for (uint32_t i = lane; i < npriv; i += 64u) store_entry(base + nl + np + i, priv[i]);
+        if (ITEMS == PULSE_ITEMS_BANK)
+            for (uint32_t i = lane; i < ni; i += 64u) {
+                const uint64_t j = wnext + i;
+                bank_store(P, base + nl + np + npriv + i, P.in.x[j], P.in.t[j], P.in.X[j], P.in.batch[j], P.in.tb[j]);
+            }
+    }
+    if (PC && cstaged != 0) census_flush(P, cen, cstaged, lane);
+    if (P.rows != 0)
+        for (uint32_t r = 0; r < P.rows; ++r) flush_row(r);
+    if (lane == 0) {
+        auto add = [&](int w, uint64_t v) { atomicAdd(&s_acc[w], static_cast<unsigned long long>(v)); };
+        add(PD_SOURCES, n_src);
+        add(PD_COLLISIONS, n_coll);
+        add(PD_TALLIED, n_tal);
+        add(PD_SCATTERS, n_scat);
+        add(PD_ABSORBED, n_coll - n_scat);
+        add(PD_CENSUS, n_fly - n_coll);
+        add(PD_SECONDARIES, n_scat * P.n_floor + n_extra);
+        add(PD_DRAWS, n_dir + n_fly + n_coll + n_scat);
+        atomicMax(&s_acc[PD_MAX_DRAWS], static_cast<unsigned long long>(max_draws));
+    }
+    tally_lds_end<BLOCK>(P, counters);
+    __syncthreads();
+    if (threadIdx.x < kNDiag && s_acc[threadIdx.x] != 0) {
+        unsigned long long* d = reinterpret_cast<unsigned long long*>(P.diag) + threadIdx.x;
+        if (threadIdx.x == PD_MAX_DRAWS)
+            atomicMax(d, s_acc[threadIdx.x]);
+        else
+            atomicAdd(d, s_acc[threadIdx.x]);
+    }
 }
 
 // ------------------------------------------------------------ family schedule
@@ -521,13 +920,6 @@ __device__ __forceinline__ void spill(const PulseParams& P, double x, double t, 
 // launch appends at most (budget + stack_depth + 1) n_max particles and
 // banks at most `budget` census arrivals per input particle.
 constexpr uint32_t kFamilyChunk = 64;   // items a wave of the family kernel takes per atomic
-
-// A source of the family schedule, seeded when its wave takes the chunk.
-struct __align__(16) FamilySource {
-    uint64_t X;
-    uint32_t batch;
-    uint32_t pad;
-};
 
 // A family of a chunk with a tally slot has ended: the lane whose end leaves
 // the chunk with no family marks the slot for its wave's flush.
@@ -1014,6 +1406,65 @@ hipError_t launch_pulse_bank(const PulseParams& p, int items_kind, bool pc, int 
     void* args[] = {&arg};
     return hipLaunchKernel(bank_kernel(block, items_kind, pc), dim3(grid), dim3(block), args,
                            pulse_tally_lds_bytes(p), st);
+}
+
+template <int BLOCK>
+static const void* pool_kernel_b(int items, bool pc) {
+    switch (items) {
+        case PULSE_ITEMS_SOURCES:
+            return pc ? reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_SOURCES, true, BLOCK>)
+                      : reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_SOURCES, false, BLOCK>);
+        case PULSE_ITEMS_COPIES:
+            return pc ? reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_COPIES, true, BLOCK>)
+                      : reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_COPIES, false, BLOCK>);
+        default:
+            return pc ? reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_BANK, true, BLOCK>)
+                      : reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_BANK, false, BLOCK>);
+    }
+}
+
+static const void* pool_kernel(int block, int items, bool pc) {
+    switch (block) {
+        case 64: return pool_kernel_b<64>(items, pc);
+        case 128: return pool_kernel_b<128>(items, pc);
+        case 512: return pool_kernel_b<512>(items, pc);
+        case 1024: return pool_kernel_b<1024>(items, pc);
+        default: return pool_kernel_b<256>(items, pc);
+    }
+}
+
+static size_t pool_lds_bytes(const PulseParams& p, int block) {
+    size_t b = p.edges_lds ? 8ull * (p.n_time_bins + 1) : 0;
+    b += pulse_tally_lds_bytes(p);
+    return b + static_cast<size_t>(block / 64) * p.rows * p.n_time_bins * 4u;
+}
+
+uint32_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int block, uint64_t items) {
+    block = bank_block(block);
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pool_kernel(block, items_kind, pc), block,
+                                                     pool_lds_bytes(p, block)) != hipSuccess ||
+        per_cu < 1)
+        per_cu = 1;
+    const uint64_t waves = static_cast<uint64_t>(block / 64);
+    uint64_t blocks = (items + waves - 1) / waves;   // an item per wave at least
+    const uint64_t cap = static_cast<uint64_t>(device_cus()) * static_cast<uint64_t>(per_cu);
+    if (blocks > cap) blocks = cap;
+    return static_cast<uint32_t>(blocks < 1 ? 1 : blocks);
+}
+
+uint64_t pulse_pool_slack(const PulseParams& p, uint32_t n_max) {
+    // the pool, the private stack, the lanes, a chunk and two iterations' appends
+    return 2ull * 256 + p.priv_cap + 64 + 64 + 2ull * 64 * n_max;
+}
+
+hipError_t launch_pulse_pool(const PulseParams& p, int items_kind, bool pc, int block, uint32_t grid, hipStream_t st) {
+    if (p.item_end == p.item_begin) return hipSuccess;
+    block = bank_block(block);
+    PulseParams arg = p;
+    void* args[] = {&arg};
+    return hipLaunchKernel(pool_kernel(block, items_kind, pc), dim3(grid), dim3(block), args,
+                           pool_lds_bytes(p, block), st);
 }
 
 static uint32_t stream_grid(uint64_t work, uint64_t per_block) {

@@ -38,6 +38,15 @@ struct PulseCensusEntry {
     uint32_t pad;
 };
 
+// A particle waiting in a wave's pool (k_pulse_pool): child k of a scattering
+// at (x, t) whose parent ended in state key.
+struct __align__(16) PulsePoolEntry {
+    double x, t;
+    uint64_t key;        // X_p, the parent's state
+    uint32_t batch;
+    uint32_t meta;       // k << 16 | time bin + 1
+};
+
 struct PulseParams {
     LcgDev lcg;
     SeedDev seed;            // hash: base = the global seed s; stride: skip table etc.
@@ -67,7 +76,18 @@ struct PulseParams {
     uint64_t out_cap;
     uint64_t* item_counter;  // bank schedule: next input particle (taken `chunk` per wave)
     uint32_t chunk;          // bank schedule: input particles a wave takes per atomic
-    uint64_t cont_budget;    // bank schedule: appends of continuing lines stay within this
+    uint64_t out_budget;     // pool: a wave that sees more entries in the output bank hands over its particles
+    uint64_t cen_budget;     // pool: the same for census arrivals
+    uint64_t item_begin, item_end;   // pool: the launch's items (sources of the run, copies or bank entries)
+    uint64_t* left;          // pool: ranges of taken but unused items (pairs), n_left of them
+    uint64_t* n_left;
+    PulsePoolEntry* priv;    // pool: priv_cap entries per wave behind the LDS pool
+    uint32_t priv_cap;
+    uint32_t tail_iters;     // pool: iterations of a wave after the launch's items are taken
+    uint32_t rows;           // pool: LDS tally rows per wave (a power of two; 0: HBM atomics)
+    uint32_t edges_lds;      // pool: time edges staged in LDS
+    uint32_t grid_uniform;   // pool: time edge i is within a quarter of a bin of t0 + i / inv_dt
+    double t0, inv_dt;
     uint32_t* overflow;      // set if an append or a stack push found no room
     uint64_t* family_counter;
     PulseStackEntry* stack;  // family schedule: stack_depth entries per lane of the launch,
@@ -95,17 +115,25 @@ struct PulseParams {
 enum PulseItems : int { PULSE_ITEMS_SOURCES = 0, PULSE_ITEMS_BANK = 1, PULSE_ITEMS_COPIES = 2 };
 constexpr uint32_t kPulsePcChunkBatches = 4096;   // batches per chunk of a population-controlled run
 
-// Bank launches: the grid (resident blocks, at most one chunk of items per
+// Event launches: the grid (resident blocks, at most one chunk of items per
 // wave) is chosen first, so that the caller can size the output for it.
 // `items` is a PulseItems value; `pc`: the launch's census is a census of
 // population control (arrivals are banked in p.cen).
 uint32_t pulse_bank_grid(const PulseParams& p, int items_kind, bool pc, int block, uint64_t items);
 constexpr uint32_t kPulseLdsCounters = 2048;   // block-local tally copies up to this many counters (16 KiB)
+constexpr uint32_t kPulsePoolLdsCounters = 512;   // the same for k_pulse_pool, whose pools need the LDS
 constexpr uint32_t kPulseTallySlots = 16;      // most tally slots per wave of the family kernel
 // Entries of a wave's LDS stage of appends in k_pulse_bank (output slack).
 uint32_t pulse_bank_stage(int block);
 hipError_t launch_pulse_bank(const PulseParams& p, int items_kind, bool pc, int block, uint32_t grid,
                              hipStream_t st);
+// Pool launches (bank schedule).  The grid is chosen first (buffers are sized
+// for its waves); pulse_pool_slack: entries a wave may append to the output
+// bank after it has seen out_budget passed, and census arrivals likewise.
+uint32_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int block, uint64_t items);
+uint64_t pulse_pool_slack(const PulseParams& p, uint32_t n_max);
+constexpr uint64_t kPulsePoolCensusSlack = 256;
+hipError_t launch_pulse_pool(const PulseParams& p, int items_kind, bool pc, int block, uint32_t grid, hipStream_t st);
 // Population control at census p.census: arrival counts per batch into
 // p.pop, then the copies of every arrival into p.copies_out.
 hipError_t launch_pulse_census_count(const PulseParams& p, uint64_t n_arrivals, hipStream_t st);

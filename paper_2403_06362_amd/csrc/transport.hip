@@ -203,14 +203,6 @@ __device__ __forceinline__ void add_limbs(uint64_t lo, uint64_t hi, uint64_t* pl
     *phi += hi + static_cast<uint64_t>(static_cast<int64_t>(lo) >> 32);
 }
 
-__device__ __forceinline__ uint32_t mask_count(uint64_t m) { return static_cast<uint32_t>(__popcll(m)); }
-
-// A lane's rank among the lanes of a mask.
-__device__ __forceinline__ uint32_t mask_rank(uint64_t m) {
-    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
-                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
-}
-
 // Waiting lanes at which a wave's collision pass runs: `full` of `all` slots,
 // and the same share of the live ones once lanes stay empty (a wave's last
 // histories would otherwise wait for each other at every collision), at
