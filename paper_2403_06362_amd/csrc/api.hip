@@ -349,6 +349,12 @@ struct DevBuf {
     Arena* arena = nullptr;   // set: carved from the arena, never hipMalloc'd or freed
 };
 
+// Pinned host words of a context: the event schedule's and the pulse
+// problem's counters (16 words, then the item parts' and the census parts').
+constexpr uint32_t kPulseItemWords = 16, kPulseCenWords = kPulseItemWords + kPulseItemParts * kPulseCounterStride;
+constexpr uint32_t kPulseMiscWords = kPulseCenWords + kPulseCensusParts * kPulseCounterStride;
+constexpr size_t kPinnedBytes = kPulseMiscWords * sizeof(uint64_t);
+
 struct mcrng_ctx {
     int device = 0;
     hipStream_t capture_stream = nullptr;
@@ -1025,7 +1031,7 @@ static int run_event_schedule(mcrng_ctx* ctx, const LcgDev& L, const mcrng_run_o
     const int f32 = o.precision == MCRNG_FP32;
     const int timed = ctx->any_timed;
     HIP_TRY(launch_fill_u64(ep.tp.partial, ctx->partial_words, 0ull, st));
-    if (!ctx->h_pinned) HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&ctx->h_pinned), 64, hipHostMallocDefault));
+    if (!ctx->h_pinned) HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&ctx->h_pinned), kPinnedBytes, hipHostMallocDefault));
     const uint32_t nu = static_cast<uint32_t>(ctx->h_units.size());
     uint32_t u0 = 0;
     while (u0 < nu) {
@@ -1380,8 +1386,6 @@ static PulseBankView carve_pulse_bank(void* base, uint64_t cap) {
     return v;
 }
 
-// Reads n <= 8 device words (through a pinned host buffer) after the work
-// queued on st.
 // Input particles a wave of the bank kernel takes per atomic on the item
 // counter: small launches keep many waves busy, large ones need few atomics
 // on that one counter (its same-address atomics serialise across the GPU).
@@ -1391,8 +1395,10 @@ static uint32_t pulse_auto_chunk(uint64_t n) {
     return c;
 }
 
+// Reads n <= kPulseMiscWords device words (through a pinned host buffer)
+// after the work queued on st.
 static int read_words(mcrng_ctx* ctx, const uint64_t* d, uint32_t n, uint64_t* h, hipStream_t st) {
-    if (!ctx->h_pinned) HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&ctx->h_pinned), 64, hipHostMallocDefault));
+    if (!ctx->h_pinned) HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&ctx->h_pinned), kPinnedBytes, hipHostMallocDefault));
     HIP_TRY(hipMemcpyAsync(ctx->h_pinned, d, n * sizeof *h, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     for (uint32_t i = 0; i < n; ++i) h[i] = ctx->h_pinned[i];
@@ -1401,22 +1407,6 @@ static int read_words(mcrng_ctx* ctx, const uint64_t* d, uint32_t n, uint64_t* h
 
 static int read_u64(mcrng_ctx* ctx, const uint64_t* d, uint64_t* h, hipStream_t st) {
     return read_words(ctx, d, 1, h, st);
-}
-
-// Grows b to at least `bytes`, keeping its first `used` bytes.
-static int ensure_keep(DevBuf& b, size_t used, size_t bytes, hipStream_t st) {
-    if (bytes <= b.cap) return MCRNG_OK;
-    const size_t want = std::max<size_t>(std::max<size_t>(bytes + bytes / 4, 2 * b.cap), 256);
-    void* np = nullptr;
-    HIP_TRY(hipMalloc(&np, want));
-    if (used) HIP_TRY(hipMemcpyAsync(np, b.p, used, hipMemcpyDeviceToDevice, st));
-    if (b.p) {
-        HIP_TRY(hipStreamSynchronize(st));
-        HIP_TRY(hipFree(b.p));
-    }
-    b.p = np;
-    b.cap = want;
-    return MCRNG_OK;
 }
 
 static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_problem* P, const mcrng_pulse_pc* pc,
@@ -1498,7 +1488,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
 
     ctx->h_pulse_tedges.assign(P->time_edges, P->time_edges + P->n_time_bins + 1);
     if ((rc = upload(ctx->pulse_tedges, ctx->h_pulse_tedges, st)) < 0) return rc;
-    if ((rc = ensure(ctx->pulse_misc, 64, st)) < 0) return rc;
+    if ((rc = ensure(ctx->pulse_misc, kPulseMiscWords * sizeof(uint64_t), st)) < 0) return rc;
     if ((rc = ensure(ctx->pulse_diag, kNDiag * sizeof(uint64_t), st)) < 0) return rc;
     pp.t_edges = static_cast<const double*>(ctx->pulse_tedges.p);
     pp.counts = d_counts;
@@ -1532,13 +1522,15 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     }
     pp.diag = static_cast<uint64_t*>(ctx->pulse_diag.p);
     // misc words: out_count, item_counter (reset per bank launch), family_counter, overflow,
-    // census arrivals, census copies, unused item ranges
+    // (unused), census copies, unused item ranges; then the item parts' and
+    // the census parts' counters
     uint64_t* misc = static_cast<uint64_t*>(ctx->pulse_misc.p);
     pp.out_count = misc;
-    pp.item_counter = misc + 1;
+    pp.item_counter = o.schedule == MCRNG_PULSE_BANK ? misc + kPulseItemWords : misc + 1;
     pp.family_counter = misc + 2;
     pp.overflow = reinterpret_cast<uint32_t*>(misc + 3);
-    pp.cen_count = misc + 4;
+    pp.cen_count = misc + kPulseCenWords;
+    pp.cen_parts = event ? 1 : kPulseCensusParts;
     pp.copy_count = misc + 5;
     pp.n_left = misc + 6;
     const uint32_t K = pc ? pc->census_every : 0;
@@ -1553,11 +1545,43 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
         pp.pop = static_cast<uint64_t*>(ctx->pulse_pop.p);
         if (n_pop) HIP_TRY(launch_fill_u64(pp.pop, n_pop, 0ull, st));
     }
-    HIP_TRY(launch_fill_u64(misc, 8, 0ull, st));
+    HIP_TRY(launch_fill_u64(misc, kPulseMiscWords, 0ull, st));
     HIP_TRY(launch_fill_u64(pp.diag, kNDiag, 0ull, st));
     HIP_TRY(launch_fill_u64(d_counts, static_cast<uint64_t>(P->n_batches) * P->n_time_bins, 0ull, st));
     HIP_TRY(hipEventRecord(ctx->ev0, st));
     ctx->timing_valid = false;
+
+    // Room for `cap` arrivals in each of `parts` census parts, keeping the first
+    // used[s] of part s.
+    uint64_t cen_cap = 0;
+    auto census_room = [&](uint64_t cap, const uint64_t* used, uint32_t parts) -> int {
+        if (cap > cen_cap) {
+            cap = std::max(cap + cap / 4, 2 * cen_cap);
+            const size_t bytes = static_cast<size_t>(cap) * parts * sizeof(PulseCensusEntry);
+            DevBuf nb;
+            nb.p = ctx->pulse_census.p;
+            uint64_t any = 0;
+            for (uint32_t i = 0; i < parts; ++i) any |= used[i];
+            if (any != 0 || bytes > ctx->pulse_census.cap) {
+                nb.p = nullptr;
+                HIP_TRY(hipMalloc(&nb.p, bytes));
+                nb.cap = bytes;
+                const PulseCensusEntry* from = static_cast<const PulseCensusEntry*>(ctx->pulse_census.p);
+                PulseCensusEntry* to = static_cast<PulseCensusEntry*>(nb.p);
+                for (uint32_t i = 0; i < parts; ++i)
+                    if (used[i])
+                        HIP_TRY(hipMemcpyAsync(to + i * cap, from + i * cen_cap, used[i] * sizeof(PulseCensusEntry),
+                                               hipMemcpyDeviceToDevice, st));
+                HIP_TRY(hipStreamSynchronize(st));
+                if (ctx->pulse_census.p) HIP_TRY(hipFree(ctx->pulse_census.p));
+                ctx->pulse_census = nb;
+            }
+            cen_cap = cap;
+        }
+        pp.cen = static_cast<PulseCensusEntry*>(ctx->pulse_census.p);
+        pp.cen_cap = cen_cap;
+        return MCRNG_OK;
+    };
 
     // Pool launches (bank schedule): a launch runs its items and all they give
     // rise to, except what its waves hand over to the output bank: entries
@@ -1569,6 +1593,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     // it holds and ends, so it appends at most its slack after that; items
     // not taken then (of a bank) are copied behind the output.
     auto pool_run = [&](int kind, uint64_t begin, uint64_t end, bool pcen, uint64_t* cen_used) -> int {
+        std::vector<uint64_t> part(kPulseCensusParts, 0);   // arrivals per census part
         const int block = static_cast<int>(o.block);
         std::vector<std::pair<uint64_t, uint64_t>> ranges;
         if (end > begin) ranges.emplace_back(begin, end);
@@ -1588,9 +1613,15 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             const uint64_t n = pp.item_end - pp.item_begin;
             const uint32_t grid = pulse_pool_grid(pp, k, pcen, block, n);
             const uint64_t waves = static_cast<uint64_t>(grid) * o.block / 64;
-            // half of a wave's share per atomic, so that the waves end together
-            pp.chunk = static_cast<uint32_t>(std::min<uint64_t>(64, std::max<uint64_t>(1, n / (2 * waves))));
-            if (o.chunk) pp.chunk = 64;
+            // few items: each wave its share.  Many: half of them so, the rest
+            // an eighth of a share at a time, so that the waves end together
+            const uint64_t share = (n + waves - 1) / waves;
+            pp.first_chunk = static_cast<uint32_t>(share <= 32 && !o.chunk ? share : std::min<uint64_t>(n / (2 * waves), 1u << 20));
+            const uint64_t dynamic = std::min(pp.item_begin + pp.first_chunk * waves, pp.item_end);
+            pp.item_parts = grid >= kPulseItemParts ? kPulseItemParts : 1;
+            for (uint32_t i = 0; i <= kPulseItemParts; ++i)
+                pp.item_part[i] = dynamic + (pp.item_end - dynamic) * std::min(i, pp.item_parts) / pp.item_parts;
+            pp.chunk = o.chunk ? o.chunk : static_cast<uint32_t>(std::min<uint64_t>(256, std::max<uint64_t>(1, share / 8)));
             pp.out_budget = pool_budget ? pool_budget : std::min<uint64_t>(std::max<uint64_t>(2 * n, 1u << 16), 1u << 24);
             const uint64_t ocap = pp.out_budget + waves * pulse_pool_slack(pp, n_max) + (n_bank > 0 ? n : 0);
             int r;
@@ -1600,37 +1631,49 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             pp.priv = static_cast<PulsePoolEntry*>(ctx->pulse_stack.p);
             pp.left = static_cast<uint64_t*>(ctx->pulse_left.p);
             if (pcen) {
-                pp.cen_budget = *cen_used + (pool_budget ? pool_budget : std::max<uint64_t>(4 * n, 1u << 20));
-                r = ensure_keep(ctx->pulse_census, *cen_used * sizeof(PulseCensusEntry),
-                                (pp.cen_budget + waves * kPulsePoolCensusSlack) * sizeof(PulseCensusEntry), st);
-                if (r < 0) return r;
-                pp.cen = static_cast<PulseCensusEntry*>(ctx->pulse_census.p);
-                pp.cen_cap = ctx->pulse_census.cap / sizeof(PulseCensusEntry);
+                const uint64_t add = pool_budget ? pool_budget : std::max<uint64_t>(4 * n, 1u << 20);
+                pp.cen_budget = *std::max_element(part.begin(), part.end()) + add / kPulseCensusParts + 1;
+                const uint64_t part_waves = (grid / kPulseCensusParts + 1) * o.block / 64;
+                if ((r = census_room(pp.cen_budget + part_waves * kPulsePoolCensusSlack, part.data(), kPulseCensusParts)) < 0)
+                    return r;
             }
             pp.out = carve_pulse_bank(ctx->pulse_bank[nxt].p, ocap);
             pp.out_cap = ocap;
+            // (n_left and the census counts stay)
             HIP_TRY(launch_fill_u64(misc, 3, 0ull, st));
+            if (dynamic != pp.item_end)
+                HIP_TRY(launch_fill_u64(pp.item_counter, kPulseItemParts * kPulseCounterStride, 0ull, st));
             HIP_TRY(launch_pulse_pool(pp, k, pcen, block, grid, st));
-            uint64_t w[7];
-            if ((r = read_words(ctx, misc, 7, w, st)) < 0) return r;
+            uint64_t w[kPulseMiscWords];
+            if ((r = read_words(ctx, misc, pcen ? kPulseMiscWords : kPulseCenWords, w, st)) < 0) return r;
             // a bank that ran out of room (never, by the capacities above)
             // ends the run before any launch reads past it
             if (w[3] & 0xffffffffull) return fail(MCRNG_ERANGE, "a particle bank ran out of room");
-            if (pcen) *cen_used = w[4];
-            uint64_t n_out = w[0];
-            const uint64_t taken = std::min(pp.item_begin + w[1], pp.item_end);
-            if (k == PULSE_ITEMS_BANK && taken < pp.item_end) {
-                const uint64_t rest = pp.item_end - taken;
-                const PulseBankView &a = pp.in, &b = pp.out;
-                HIP_TRY(hipMemcpyAsync(b.x + n_out, a.x + taken, rest * 8, hipMemcpyDeviceToDevice, st));
-                HIP_TRY(hipMemcpyAsync(b.t + n_out, a.t + taken, rest * 8, hipMemcpyDeviceToDevice, st));
-                HIP_TRY(hipMemcpyAsync(b.X + n_out, a.X + taken, rest * 8, hipMemcpyDeviceToDevice, st));
-                HIP_TRY(hipMemcpyAsync(b.batch + n_out, a.batch + taken, rest * 4, hipMemcpyDeviceToDevice, st));
-                HIP_TRY(hipMemcpyAsync(b.tb + n_out, a.tb + taken, rest * 4, hipMemcpyDeviceToDevice, st));
-                n_out += rest;
-            } else if (taken < pp.item_end) {
-                ranges.emplace_back(taken, pp.item_end);
+            if (pcen) {
+                *cen_used = 0;
+                for (uint32_t i = 0; i < kPulseCensusParts; ++i)
+                    *cen_used += part[i] = w[kPulseCenWords + i * kPulseCounterStride];
             }
+            uint64_t n_out = w[0];
+            // dynamic items that no wave has taken (its waves handed over early)
+            if (dynamic != pp.item_end)
+                for (uint32_t i = 0; i < kPulseItemParts; ++i) {
+                    const uint64_t e = pp.item_part[i + 1];
+                    const uint64_t taken = std::min(pp.item_part[i] + w[kPulseItemWords + i * kPulseCounterStride], e);
+                    const uint64_t rest = e - taken;
+                    if (rest == 0) continue;
+                    if (k != PULSE_ITEMS_BANK) {
+                        ranges.emplace_back(taken, e);
+                        continue;
+                    }
+                    const PulseBankView &a = pp.in, &b = pp.out;
+                    HIP_TRY(hipMemcpyAsync(b.x + n_out, a.x + taken, rest * 8, hipMemcpyDeviceToDevice, st));
+                    HIP_TRY(hipMemcpyAsync(b.t + n_out, a.t + taken, rest * 8, hipMemcpyDeviceToDevice, st));
+                    HIP_TRY(hipMemcpyAsync(b.X + n_out, a.X + taken, rest * 8, hipMemcpyDeviceToDevice, st));
+                    HIP_TRY(hipMemcpyAsync(b.batch + n_out, a.batch + taken, rest * 4, hipMemcpyDeviceToDevice, st));
+                    HIP_TRY(hipMemcpyAsync(b.tb + n_out, a.tb + taken, rest * 4, hipMemcpyDeviceToDevice, st));
+                    n_out += rest;
+                }
             if (w[6] != 0) {   // ranges handed back
                 std::vector<uint64_t> l(2 * w[6]);
                 HIP_TRY(hipMemcpyAsync(l.data(), pp.left, l.size() * 8, hipMemcpyDeviceToHost, st));
@@ -1673,11 +1716,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
                 const uint64_t ocap = n * (kFinishBudget + kFinishDepth + 1) * static_cast<uint64_t>(n_max) + 64;
                 if ((r = ensure(ctx->pulse_bank[nxt], ocap * 32, st, 8)) < 0) return r;
                 if (pcen) {
-                    r = ensure_keep(ctx->pulse_census, *cen_used * sizeof(PulseCensusEntry),
-                                    (*cen_used + n * kFinishBudget) * sizeof(PulseCensusEntry), st);
-                    if (r < 0) return r;
-                    pp.cen = static_cast<PulseCensusEntry*>(ctx->pulse_census.p);
-                    pp.cen_cap = ctx->pulse_census.cap / sizeof(PulseCensusEntry);
+                    if ((r = census_room(*cen_used + n * kFinishBudget, cen_used, 1)) < 0) return r;
                 }
                 pp.in = carve_pulse_bank(ctx->pulse_bank[cur].p, in_cap);
                 pp.n_in = n;
@@ -1688,11 +1727,11 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
                 pp.lane_budget = kFinishBudget;
                 HIP_TRY(launch_fill_u64(misc, 3, 0ull, st));
                 HIP_TRY(launch_pulse_finish(pp, pcen, grid, st));
-                uint64_t w[5];
-                if ((r = read_words(ctx, misc, 5, w, st)) < 0) return r;
+                uint64_t w[kPulseCenWords + 1];
+                if ((r = read_words(ctx, misc, kPulseCenWords + 1, w, st)) < 0) return r;
                 if (w[3] & 0xffffffffull) return fail(MCRNG_ERANGE, "a particle bank ran out of room");
                 n = w[0];
-                if (pcen) *cen_used = w[4];
+                if (pcen) *cen_used = w[kPulseCenWords];
                 std::swap(cur, nxt);
                 in_cap = ocap;
                 continue;
@@ -1705,11 +1744,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             int r = ensure(ctx->pulse_bank[nxt], ocap * 32, st, 8);
             if (r < 0) return r;
             if (pcen) {
-                r = ensure_keep(ctx->pulse_census, *cen_used * sizeof(PulseCensusEntry),
-                                (*cen_used + n) * sizeof(PulseCensusEntry), st);
-                if (r < 0) return r;
-                pp.cen = static_cast<PulseCensusEntry*>(ctx->pulse_census.p);
-                pp.cen_cap = ctx->pulse_census.cap / sizeof(PulseCensusEntry);
+                if ((r = census_room(*cen_used + n, cen_used, 1)) < 0) return r;
             }
             if (kind == PULSE_ITEMS_BANK) pp.in = carve_pulse_bank(ctx->pulse_bank[cur].p, in_cap);
             pp.n_in = kind == PULSE_ITEMS_SOURCES ? 0 : n;
@@ -1717,13 +1752,13 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             pp.out_cap = ocap;
             HIP_TRY(launch_fill_u64(misc, 2, 0ull, st));
             HIP_TRY(launch_pulse_bank(pp, kind, pcen, static_cast<int>(o.block), grid, st));
-            uint64_t w[5];
-            if ((r = read_words(ctx, misc, 5, w, st)) < 0) return r;
+            uint64_t w[kPulseCenWords + 1];
+            if ((r = read_words(ctx, misc, kPulseCenWords + 1, w, st)) < 0) return r;
             // a bank that ran out of room (never, by the capacities above)
             // ends the run before any launch reads past it
             if (w[3] & 0xffffffffull) return fail(MCRNG_ERANGE, "a particle bank ran out of room");
             n = w[0];
-            if (pcen) *cen_used = w[4];
+            if (pcen) *cen_used = w[kPulseCenWords];
             std::swap(cur, nxt);
             in_cap = ocap;
             kind = PULSE_ITEMS_BANK;
@@ -1748,7 +1783,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
                 const bool pcen = e < n_census;
                 pp.t_end = pcen ? P->time_edges[static_cast<size_t>(e + 1) * K] : P->time_edges[P->n_time_bins];
                 uint64_t cen_used = 0;
-                HIP_TRY(launch_fill_u64(pp.cen_count, 1, 0ull, st));
+                HIP_TRY(launch_fill_u64(pp.cen_count, kPulseCensusParts * kPulseCounterStride, 0ull, st));
                 if (e == 0) {
                     rc = event ? generations(PULSE_ITEMS_SOURCES, pp.src_end - pp.src_begin, pcen, &cen_used)
                                : pool_run(PULSE_ITEMS_SOURCES, pp.src_begin, pp.src_end, pcen, &cen_used);

@@ -310,12 +310,15 @@ struct CensusStageOf {
 
 using CensusStage = CensusStageOf<128>;   // 3.5 KiB per wave
 
-// Returns the arrival count just after the flushed entries.
+// Returns the arrival count of the block's part just after the flushed entries.
 template <class Stage>
 __device__ __forceinline__ uint64_t census_flush(const PulseParams& P, Stage& S, uint32_t count, uint32_t lane) {
     __builtin_amdgcn_wave_barrier();
+    const uint32_t part = blockIdx.x & (P.cen_parts - 1u);
+    PulseCensusEntry* const cen = P.cen + part * P.cen_cap;
     uint64_t base = 0;
-    if (lane == 0) base = atomicAdd(reinterpret_cast<unsigned long long*>(P.cen_count), count);
+    if (lane == 0)
+        base = atomicAdd(reinterpret_cast<unsigned long long*>(P.cen_count + part * kPulseCounterStride), count);
     base = lane_value(base, 0);
     for (uint32_t i = lane; i < count; i += 64) {
         const uint64_t o = base + i;
@@ -326,7 +329,7 @@ __device__ __forceinline__ uint64_t census_flush(const PulseParams& P, Stage& S,
             e.X = S.X[i];
             e.batch = S.batch[i];
             e.pad = 0;
-            P.cen[o] = e;
+            cen[o] = e;
         } else {
             atomicOr(P.overflow, 1u);
         }
@@ -532,6 +535,16 @@ __device__ __forceinline__ uint64_t child_state(const LcgDev& L, uint64_t X, uin
     return murmur_sub(murmur_seed_part(X) ^ part) << L.up;
 }
 
+// The launch's parameters, read again where they are used: for code that runs
+// rarely (a chunk taken, a pool spilled), so that its pointers and sizes do not
+// sit in (or spill from) the scalar registers of the flight loop.
+__device__ __forceinline__ const PulseParams& rare_params() {
+    using Arg = const __attribute__((address_space(4))) PulseParams*;
+    uint64_t p = reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr());
+    asm volatile("" : "+s"(p));
+    return *(const PulseParams*)(Arg)p;
+}
+
 template <int ITEMS, bool PC, int BLOCK>
 __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
     constexpr bool SOURCES = ITEMS == PULSE_ITEMS_SOURCES;
@@ -568,33 +581,38 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
     uint32_t* const tags = s_tag[wid];
     auto& cen = s_cen[PC ? wid : 0];
     const uint64_t wave = static_cast<uint64_t>(blockIdx.x) * kWaves + wid;
-    PulsePoolEntry* const priv = P.priv + wave * P.priv_cap;
-    const uint64_t part1 = uniform_value(child_part(1));
+    const uint64_t part1 = child_part(1);
     const double sigma = P.sigma_t;
     const double rsigma = uniform_value(recip_refined(sigma));
 
     // wave-uniform state
     uint64_t A = 0;                     // lanes holding a particle at the start of its flight
+    uint64_t child = 0;                 // of those, lanes whose Z is its parent's final state (start state: eq. 5 with part)
     uint64_t dir = 0;                   // COPIES: lanes whose particle keeps its direction
     uint32_t bot = 0, top = 0;          // the pool holds entries [bot, top) (mod CAP)
     uint32_t npriv = 0;
-    uint64_t wnext = 0, wend = 0;       // the wave's untaken items
+    // the wave's untaken items [wnext, gend); of sources [wnext, wend) are seeded in src
+    uint64_t wnext = P.item_begin + wave * P.first_chunk;
+    if (wnext > P.item_part[0]) wnext = P.item_part[0];
+    uint64_t gend = wnext + P.first_chunk < P.item_part[0] ? wnext + P.first_chunk : P.item_part[0];
+    uint64_t wend = SOURCES ? wnext : gend;
     uint32_t src_off = 0;               // item wnext's place in src
-    bool exhausted = false, hand_over = false;
+    bool exhausted = P.item_part[0] == P.item_end && wnext == gend, hand_over = false;   // no items left to take
     uint64_t seen = 0;                  // output count after this wave's last append
     uint32_t cstaged = 0, tail = 0, iter = 0;
     uint64_t n_src = 0, n_fly = 0, n_dir = 0, n_coll = 0, n_tal = 0, n_scat = 0, n_extra = 0;
-    uint32_t max_draws = 0;
+    uint64_t any3 = 0, any4 = 0;        // COPIES: lanes that drew 3 and 4 numbers in a flight with a direction draw
     // the lane's particle
     double x = 0.0, t = 0.0, mu0 = 0.0;
-    uint64_t Z = 0;
+    uint64_t Z = 0, part = part1;
     uint32_t batch = 0;
     int32_t tb = -1;
 
     auto flush_row = [&](uint32_t r) {
+        const PulseParams& R = rare_params();
         const uint32_t tag = __builtin_amdgcn_readfirstlane(tags[r]);
         if (tag == 0xffffffffu) return;
-        unsigned long long* c = reinterpret_cast<unsigned long long*>(P.counts) + static_cast<uint64_t>(tag) * nt;
+        unsigned long long* c = reinterpret_cast<unsigned long long*>(R.counts) + static_cast<uint64_t>(tag) * nt;
         for (uint32_t i = lane; i < nt; i += 64u) {
             const uint32_t v = rows[r * nt + i];
             if (v != 0u) {
@@ -619,15 +637,15 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
         }
     };
     // reserves n entries of the output bank (n uniform)
-    auto reserve = [&](uint32_t n) -> uint64_t {
+    auto reserve = [&](const PulseParams& R, uint32_t n) -> uint64_t {
         uint64_t base = 0;
-        if (lane == 0) base = atomicAdd(reinterpret_cast<unsigned long long*>(P.out_count), static_cast<unsigned long long>(n));
+        if (lane == 0) base = atomicAdd(reinterpret_cast<unsigned long long*>(R.out_count), static_cast<unsigned long long>(n));
         base = lane_value(base, 0);
         seen = base + n;
         return base;
     };
-    auto store_entry = [&](uint64_t o, const PulsePoolEntry& e) {
-        bank_store(P, o, e.x, e.t, child_state(P.lcg, e.key, s_part[(e.meta >> 16) & 15u]), e.batch,
+    auto store_entry = [&](const PulseParams& R, uint64_t o, const PulsePoolEntry& e) {
+        bank_store(R, o, e.x, e.t, child_state(R.lcg, e.key, s_part[(e.meta >> 16) & 15u]), e.batch,
                    static_cast<int32_t>(e.meta & 0xffffu) - 1);
     };
 
@@ -636,6 +654,8 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
         if (need != 0) {
             if (top == bot && npriv != 0) {
                 // the newest entries of the private stack
+                const PulseParams& R = rare_params();
+                const PulsePoolEntry* const priv = R.priv + wave * R.priv_cap;
                 const uint32_t cnt = npriv < CAP / 2 ? npriv : CAP / 2;
                 npriv -= cnt;
                 for (uint32_t i = lane; i < cnt; i += 64u) pool[(top + i) & (CAP - 1)] = priv[npriv + i];
@@ -653,27 +673,39 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
                     t = e.t;
                     batch = e.batch;
                     tb = static_cast<int32_t>(e.meta & 0xffffu) - 1;
-                    Z = child_state(P.lcg, e.key, s_part[e.meta >> 16]);
+                    Z = e.key;
+                    part = s_part[e.meta >> 16];
                 }
                 top -= take;
                 k -= take;
                 A |= m;
+                child |= m;
                 need &= ~m;
                 __builtin_amdgcn_wave_barrier();
             }
             if (k != 0 && wnext == wend && !exhausted) {
-                uint64_t b = 0;
-                if (lane == 0)
-                    b = atomicAdd(reinterpret_cast<unsigned long long*>(P.item_counter), static_cast<unsigned long long>(P.chunk));
-                b = P.item_begin + lane_value(b, 0);
-                if (b + P.chunk >= P.item_end) exhausted = true;
-                wnext = b < P.item_end ? b : P.item_end;
-                wend = b + P.chunk < P.item_end ? b + P.chunk : P.item_end;
-                if (SOURCES) {
+                const PulseParams& R = rare_params();
+                if (wnext == gend) {
+                    // (no taking from other blocks' parts: the parts are alike,
+                    // and every look at a counter costs as much as a take)
+                    const uint32_t s = blockIdx.x & (R.item_parts - 1u);
+                    const uint64_t e = R.item_part[s + 1u];
+                    uint64_t b = 0;
+                    if (lane == 0)
+                        b = atomicAdd(reinterpret_cast<unsigned long long*>(R.item_counter + s * kPulseCounterStride),
+                                      static_cast<unsigned long long>(R.chunk));
+                    b = R.item_part[s] + lane_value(b, 0);
+                    wnext = b < e ? b : e;
+                    gend = b + R.chunk < e ? b + R.chunk : e;
+                    exhausted = wnext == gend;
+                    wend = SOURCES ? wnext : gend;
+                }
+                if (SOURCES && wnext != gend) {
+                    wend = gend - wnext < 64u ? gend : wnext + 64u;
                     const uint64_t j = wnext + lane;
                     if (j < wend) {
                         FamilySource e;
-                        e.X = pulse_source_state(P, j, &e.batch);
+                        e.X = pulse_source_state(R, j, &e.batch);
                         e.pad = 0;
                         src[lane] = e;
                     }
@@ -687,16 +719,17 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
                 const uint32_t rank = mask_rank(need);
                 const uint64_t m = need & wave_mask(rank < take);
                 if (in_mask(m)) {
+                    const PulseParams& R = rare_params();
                     if (SOURCES) {
                         const FamilySource e = src[src_off + rank];
                         Z = e.X;
                         batch = e.batch;
                         x = 0.0;
                         t = 0.0;
-                        tb = P.tb0;
+                        tb = R.tb0;
                     } else {
                         PParticle q;
-                        load_item<ITEMS>(P, wnext + rank, q);
+                        load_item<ITEMS>(R, wnext + rank, q);
                         x = q.x;
                         t = q.t;
                         Z = q.Z;
@@ -714,7 +747,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
             }
         }
         if (A == 0) break;   // no pool, no items
-        if (exhausted && wnext == wend && ++tail > P.tail_iters) {
+        if (exhausted && ++tail > P.tail_iters) {
             hand_over = true;
             break;
         }
@@ -722,6 +755,8 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
             for (uint32_t r = 0; r < P.rows; ++r) flush_row(r);
 
         // one flight of every lane in A (the others compute on what their registers hold)
+        if (in_mask(child)) Z = child_state(P.lcg, Z, part);
+        child = 0;
         const uint64_t z1 = lcg_next_z(P.lcg, Z);
         double mu = __builtin_fma(uniform_z(z1), 2.0, -1.0);   // exact
         uint64_t z = z1;
@@ -738,7 +773,8 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
         if (PC && census != 0) {
             const uint32_t cnt = mask_count(census);
             if (cstaged + cnt > kPoolCensusStage) {
-                if (census_flush(P, cen, cstaged, lane) > P.cen_budget) hand_over = true;
+                const PulseParams& R = rare_params();
+                if (census_flush(R, cen, cstaged, lane) > R.cen_budget) hand_over = true;
                 cstaged = 0;
             }
             if (in_mask(census)) {
@@ -766,17 +802,19 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
             while (bin + 1 < static_cast<int32_t>(nt) && edge_at(bin + 1) <= tn) bin++;
         }
         const uint64_t scored = coll & wave_mask(bin >= 0) & wave_mask(P.x_lo <= xn) & wave_mask(xn <= P.x_hi);
-        if (in_mask(scored)) {
-            const uint64_t counter = static_cast<uint64_t>(batch) * nt + static_cast<uint32_t>(bin);
-            if (P.lds_tally) {
-                atomicAdd(counters + counter, 1ull);
-            } else {
-                const uint32_t r = P.rows != 0 ? batch & (P.rows - 1u) : 0u;
-                if (P.rows != 0 && tags[r] == batch)
-                    atomicAdd(rows + r * nt + static_cast<uint32_t>(bin), 1u);
-                else
-                    atomicAdd(reinterpret_cast<unsigned long long*>(P.counts) + counter, 1ull);
+        if (P.lds_tally) {
+            if (in_mask(scored)) atomicAdd(counters + (batch * nt + static_cast<uint32_t>(bin)), 1ull);
+        } else {
+            uint64_t far = scored;
+            if (P.rows != 0) {
+                const uint32_t r = batch & (P.rows - 1u);
+                const uint64_t near = scored & wave_mask(tags[r] == batch);
+                if (in_mask(near)) atomicAdd(rows + (__umul24(r, nt) + static_cast<uint32_t>(bin)), 1u);
+                far &= ~near;
             }
+            if (far != 0 && in_mask(far))
+                atomicAdd(reinterpret_cast<unsigned long long*>(P.counts) +
+                              (static_cast<uint64_t>(batch) * nt + static_cast<uint32_t>(bin)), 1ull);
         }
         const uint64_t z3 = lcg_next_z(P.lcg, z);
         const uint64_t go = coll & wave_mask(z3 < P.scatter_below);
@@ -785,18 +823,16 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
         const uint64_t key = z4 >> P.lcg.up;
 
         n_fly += mask_count(A);
-        n_dir += mask_count(drew);
         n_coll += mask_count(coll);
         n_tal += mask_count(scored);
         n_scat += mask_count(go);
         n_extra += mask_count(extra);
-        {
-            // draws of the longest stream: direction, flight, absorption test, multiplicity
-            const uint64_t keep = A & ~drew;
-            uint32_t d = (drew & go) != 0 ? 4u : (((drew & coll) | (keep & go)) != 0 ? 3u : (((drew | (keep & coll)) != 0) ? 2u : 1u));
-            if (max_draws < d) max_draws = d;
+        if (COPIES) {
+            n_dir += mask_count(drew);
+            any4 |= drew & go;
+            any3 |= (drew & coll) | (go & dir);
+            dir &= ~A;
         }
-        if (COPIES) dir &= ~A;
 
         // the first emerging particle runs on here, the others go to the pool:
         // n_floor - 1 for every scattering, one more for `extra` (n_floor = 0: none)
@@ -804,33 +840,40 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
             x = xn;
             t = tn;
             tb = bin;
+            Z = key;
+            part = part1;
         }
         const uint32_t n_more = P.n_floor != 0 ? (P.n_floor - 1u) * mask_count(go) + mask_count(extra) : 0u;
         if (n_more != 0) {
             const uint32_t off = (P.n_floor - 1u) * mask_rank(go) + mask_rank(extra);
             const uint32_t n = P.n_floor + sel_const<1, 0>(extra);
             bool direct = n_more > CAP;   // large multiplicities
-            while (!direct && top - bot + n_more > CAP) {
-                const uint32_t cnt = top - bot < CAP / 2 ? top - bot : CAP / 2;
-                if (npriv + cnt <= P.priv_cap) {
-                    for (uint32_t i = lane; i < cnt; i += 64u) priv[npriv + i] = pool[(bot + i) & (CAP - 1)];
-                    npriv += cnt;
-                } else if (seen <= P.out_budget) {
-                    const uint64_t base = reserve(cnt);
-                    for (uint32_t i = lane; i < cnt; i += 64u) store_entry(base + i, pool[(bot + i) & (CAP - 1)]);
-                } else {
-                    direct = hand_over = true;
-                    break;
+            if (!direct && top - bot + n_more > CAP) {
+                const PulseParams& R = rare_params();
+                while (!direct && top - bot + n_more > CAP) {
+                    const uint32_t cnt = top - bot < CAP / 2 ? top - bot : CAP / 2;
+                    if (npriv + cnt <= R.priv_cap) {
+                        PulsePoolEntry* const priv = R.priv + wave * R.priv_cap;
+                        for (uint32_t i = lane; i < cnt; i += 64u) priv[npriv + i] = pool[(bot + i) & (CAP - 1)];
+                        npriv += cnt;
+                    } else if (seen <= R.out_budget) {
+                        const uint64_t base = reserve(R, cnt);
+                        for (uint32_t i = lane; i < cnt; i += 64u) store_entry(R, base + i, pool[(bot + i) & (CAP - 1)]);
+                    } else {
+                        direct = hand_over = true;
+                        break;
+                    }
+                    bot += cnt;
+                    __builtin_amdgcn_wave_barrier();
                 }
-                bot += cnt;
-                __builtin_amdgcn_wave_barrier();
             }
             if (direct) {
-                const uint64_t base = reserve(n_more);
-                if (seen > P.out_budget) hand_over = true;
+                const PulseParams& R = rare_params();
+                const uint64_t base = reserve(R, n_more);
+                if (seen > R.out_budget) hand_over = true;
                 if (in_mask(go))
                     for (uint32_t c = 2; c <= n; ++c)
-                        bank_store(P, base + off + (c - 2u), x, t, child_state(P.lcg, key, s_part[c]), batch, tb);
+                        bank_store(R, base + off + (c - 2u), x, t, child_state(R.lcg, key, s_part[c]), batch, tb);
             } else {
                 if (in_mask(go))
                     for (uint32_t c = 2; c <= n; ++c) {
@@ -847,33 +890,36 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
             }
         }
         A = P.n_floor != 0 ? go : extra;
-        if (in_mask(A)) Z = child_state(P.lcg, key, part1);
+        child = A;
         if (hand_over) break;
     }
 
+    const PulseParams& R = rare_params();
     if (hand_over) {
         // everything the wave holds goes to the output bank (every lane in A
         // is past its first flight here, so no direction is lost); items
         // taken but not started go there too, or back to the host as a range
+        const PulsePoolEntry* const priv = R.priv + wave * R.priv_cap;
         const uint32_t nl = mask_count(A), np = top - bot;
         uint32_t ni = 0;
-        if (ITEMS == PULSE_ITEMS_BANK) ni = static_cast<uint32_t>(wend - wnext);
-        if (ITEMS != PULSE_ITEMS_BANK && wend != wnext && lane == 0) {
-            const uint64_t o = atomicAdd(reinterpret_cast<unsigned long long*>(P.n_left), 1ull);
-            P.left[2 * o] = wnext;
-            P.left[2 * o + 1] = wend;
+        if (ITEMS == PULSE_ITEMS_BANK) ni = static_cast<uint32_t>(gend - wnext);
+        if (ITEMS != PULSE_ITEMS_BANK && gend != wnext && lane == 0) {
+            const uint64_t o = atomicAdd(reinterpret_cast<unsigned long long*>(R.n_left), 1ull);
+            R.left[2 * o] = wnext;
+            R.left[2 * o + 1] = gend;
         }
-        const uint64_t base = reserve(nl + np + npriv + ni);
-        if (in_mask(A)) bank_store(P, base + mask_rank(A), x, t, Z, batch, tb);
-        for (uint32_t i = lane; i < np; i += 64u) store_entry(base + nl + i, pool[(bot + i) & (CAP - 1)]);
-        for (uint32_t i = lane; i < npriv; i += 64u) store_entry(base + nl + np + i, priv[i]);
+        const uint64_t base = reserve(R, nl + np + npriv + ni);
+        if (in_mask(child)) Z = child_state(R.lcg, Z, part);
+        if (in_mask(A)) bank_store(R, base + mask_rank(A), x, t, Z, batch, tb);
+        for (uint32_t i = lane; i < np; i += 64u) store_entry(R, base + nl + i, pool[(bot + i) & (CAP - 1)]);
+        for (uint32_t i = lane; i < npriv; i += 64u) store_entry(R, base + nl + np + i, priv[i]);
         if (ITEMS == PULSE_ITEMS_BANK)
             for (uint32_t i = lane; i < ni; i += 64u) {
                 const uint64_t j = wnext + i;
-                bank_store(P, base + nl + np + npriv + i, P.in.x[j], P.in.t[j], P.in.X[j], P.in.batch[j], P.in.tb[j]);
+                bank_store(R, base + nl + np + npriv + i, R.in.x[j], R.in.t[j], R.in.X[j], R.in.batch[j], R.in.tb[j]);
             }
     }
-    if (PC && cstaged != 0) census_flush(P, cen, cstaged, lane);
+    if (PC && cstaged != 0) census_flush(R, cen, cstaged, lane);
     if (P.rows != 0)
         for (uint32_t r = 0; r < P.rows; ++r) flush_row(r);
     if (lane == 0) {
@@ -885,13 +931,16 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
         add(PD_ABSORBED, n_coll - n_scat);
         add(PD_CENSUS, n_fly - n_coll);
         add(PD_SECONDARIES, n_scat * P.n_floor + n_extra);
-        add(PD_DRAWS, n_dir + n_fly + n_coll + n_scat);
-        atomicMax(&s_acc[PD_MAX_DRAWS], static_cast<unsigned long long>(max_draws));
+        add(PD_DRAWS, (COPIES ? n_dir : n_fly) + n_fly + n_coll + n_scat);
+        // numbers of the longest stream: direction, flight, absorption test, multiplicity
+        uint32_t d = n_scat != 0 ? 4u : (n_coll != 0 ? 3u : (n_fly != 0 ? 2u : 0u));
+        if (COPIES) d = any4 != 0 ? 4u : (any3 != 0 ? 3u : ((n_dir | n_coll) != 0 ? 2u : (n_fly != 0 ? 1u : 0u)));
+        atomicMax(&s_acc[PD_MAX_DRAWS], static_cast<unsigned long long>(d));
     }
     tally_lds_end<BLOCK>(P, counters);
     __syncthreads();
     if (threadIdx.x < kNDiag && s_acc[threadIdx.x] != 0) {
-        unsigned long long* d = reinterpret_cast<unsigned long long*>(P.diag) + threadIdx.x;
+        unsigned long long* d = reinterpret_cast<unsigned long long*>(R.diag) + threadIdx.x;
         if (threadIdx.x == PD_MAX_DRAWS)
             atomicMax(d, s_acc[threadIdx.x]);
         else
@@ -1194,15 +1243,37 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
 
 // ------------------------------------------------------------ population control
 
+// Where arrival i of all parts, in part order, lies in P.cen.
+struct CensusIndex {
+    uint64_t first[kPulseCensusParts + 1];   // arrivals before part s
+    __device__ __forceinline__ void load(const PulseParams& P) {   // one thread; the caller synchronises
+        uint64_t n = 0;
+        for (uint32_t s = 0; s < P.cen_parts; ++s) {
+            first[s] = n;
+            n += P.cen_count[s * kPulseCounterStride];
+        }
+        for (uint32_t s = P.cen_parts; s <= kPulseCensusParts; ++s) first[s] = n;
+    }
+    __device__ __forceinline__ const PulseCensusEntry& at(const PulseParams& P, uint64_t i) const {
+        uint32_t s = 0;   // the last part with first[s] <= i among the first cen_parts
+#pragma unroll
+        for (uint32_t step = kPulseCensusParts / 2; step != 0; step /= 2)
+            if (first[s + step] <= i) s += step;
+        return P.cen[s * P.cen_cap + (i - first[s])];
+    }
+};
+
 // Arrivals per batch at census P.census: a block-local histogram over the
 // chunk's batches, added to P.pop once per block.
 __global__ void __launch_bounds__(256) k_pulse_census_count(PulseParams P, uint64_t n) {
     __shared__ uint32_t hist[kPulsePcChunkBatches];
+    __shared__ CensusIndex idx;
+    if (threadIdx.x == 0) idx.load(P);
     for (uint32_t i = threadIdx.x; i < P.n_chunk_batches; i += 256) hist[i] = 0;
     __syncthreads();
     for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * 256 + threadIdx.x; i < n;
          i += static_cast<uint64_t>(gridDim.x) * 256) {
-        const uint32_t k = P.cen[i].batch - P.batch_lo;
+        const uint32_t k = idx.at(P, i).batch - P.batch_lo;
         if (k < P.n_chunk_batches)
             atomicAdd(&hist[k], 1u);
         else
@@ -1263,6 +1334,8 @@ __global__ void __launch_bounds__(256) k_pulse_split(PulseParams P, uint64_t n) 
     __shared__ unsigned long long hist[kPulsePcChunkBatches];
     __shared__ uint64_t s_wave[4];
     __shared__ uint64_t s_base;
+    __shared__ CensusIndex idx;
+    if (threadIdx.x == 0) idx.load(P);
     for (uint32_t i = threadIdx.x; i < P.n_chunk_batches; i += 256) hist[i] = 0;
     __syncthreads();
     const uint64_t tile = 256ull * kPer;
@@ -1270,7 +1343,7 @@ __global__ void __launch_bounds__(256) k_pulse_split(PulseParams P, uint64_t n) 
         uint64_t mine = 0;
         for (uint32_t t = 0; t < kPer; ++t) {
             const uint64_t i = t0 + t * 256ull + threadIdx.x;
-            if (i < n) mine += split_copies(P, P.cen[i]);
+            if (i < n) mine += split_copies(P, idx.at(P, i));
         }
         uint64_t total = 0;
         uint64_t o = block_scan256(mine, &total, s_wave);
@@ -1280,7 +1353,7 @@ __global__ void __launch_bounds__(256) k_pulse_split(PulseParams P, uint64_t n) 
         for (uint32_t t = 0; t < kPer; ++t) {
             const uint64_t i = t0 + t * 256ull + threadIdx.x;
             if (i >= n) continue;
-            const PulseCensusEntry a = P.cen[i];
+            const PulseCensusEntry a = idx.at(P, i);
             const uint64_t nk = split_copies(P, a);
             for (uint64_t k = 1; k <= nk; ++k, ++o) {
                 if (o < P.copy_cap) {
@@ -1454,8 +1527,9 @@ uint32_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int bloc
 }
 
 uint64_t pulse_pool_slack(const PulseParams& p, uint32_t n_max) {
-    // the pool, the private stack, the lanes, a chunk and two iterations' appends
-    return 2ull * 256 + p.priv_cap + 64 + 64 + 2ull * 64 * n_max;
+    // the pool, the private stack, the lanes and two iterations' appends (a
+    // bank's items that a wave has taken but not started have room of their own)
+    return 2ull * 256 + p.priv_cap + 64 + 2ull * 64 * n_max;
 }
 
 hipError_t launch_pulse_pool(const PulseParams& p, int items_kind, bool pc, int block, uint32_t grid, hipStream_t st) {

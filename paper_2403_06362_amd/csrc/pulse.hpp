@@ -47,6 +47,12 @@ struct __align__(16) PulsePoolEntry {
     uint32_t meta;       // k << 16 | time bin + 1
 };
 
+// One counter takes about 15 ns per atomic, whoever adds (26000 appends of 64
+// census arrivals made a 0.3 ms epoch of the paper's problem 0.68 ms, 20000
+// takes of items 0.36): a pool launch's census arrivals and the items its
+// waves take dynamically go by 16 counters each, 128 bytes apart.
+constexpr uint32_t kPulseCensusParts = 16, kPulseItemParts = 16, kPulseCounterStride = 16;
+
 struct PulseParams {
     LcgDev lcg;
     SeedDev seed;            // hash: base = the global seed s; stride: skip table etc.
@@ -78,7 +84,10 @@ struct PulseParams {
     uint32_t chunk;          // bank schedule: input particles a wave takes per atomic
     uint64_t out_budget;     // pool: a wave that sees more entries in the output bank hands over its particles
     uint64_t cen_budget;     // pool: the same for census arrivals
-    uint64_t item_begin, item_end;   // pool: the launch's items (sources of the run, copies or bank entries)
+    uint64_t item_begin, item_end;   // pool: the launch's items (sources of the run, copies or bank entries):
+    uint32_t first_chunk;            // wave w starts with [item_begin + w first_chunk, ...) up to item_part[0];
+    uint64_t item_part[kPulseItemParts + 1];        // part s of the rest, [item_part[s], item_part[s + 1]), is taken `chunk` at a time
+    uint32_t item_parts;             // by the blocks b with b mod item_parts = s (a power of two)
     uint64_t* left;          // pool: ranges of taken but unused items (pairs), n_left of them
     uint64_t* n_left;
     PulsePoolEntry* priv;    // pool: priv_cap entries per wave behind the LDS pool
@@ -94,8 +103,9 @@ struct PulseParams {
                              // depth-major (entry d of lane l at d * lanes + l)
     // population control (t_end is then the census time of the epoch)
     PulseCensusEntry* cen;   // census arrivals of the epoch
-    uint64_t* cen_count;
-    uint64_t cen_cap;
+    uint64_t* cen_count;     // arrivals of part s at cen_count[s kPulseCounterStride]
+    uint64_t cen_cap;        // capacity of a part: part s starts at cen[s cen_cap]
+    uint32_t cen_parts;      // 1, or kPulseCensusParts (block b appends to part b mod cen_parts)
     const PulseCensusEntry* copies;   // copies starting the epoch (taken as items)
     double t_start;          // the census time the copies start at
     int32_t tb_start;        // its time bin
