@@ -1505,7 +1505,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
         while (pp.rows > 2 && pp.rows * P->n_time_bins > 256) pp.rows /= 2;
     }
     pp.priv_cap = 1024;
-    pp.tail_iters = 256;
+    pp.tail_iters = 32;
     uint64_t pool_budget = 0;
     if (const char* env = getenv("MCRNG_PULSE_PRIVATE")) pp.priv_cap = static_cast<uint32_t>(std::max(0, atoi(env)));
     if (const char* env = getenv("MCRNG_PULSE_TAIL")) pp.tail_iters = static_cast<uint32_t>(std::max(1, atoi(env)));

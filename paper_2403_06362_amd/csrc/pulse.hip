@@ -516,12 +516,41 @@ struct __align__(16) FamilySource {
 // more than out_budget entries there (or cen_budget census arrivals), it hands
 // over everything it holds and ends, so that appends stay within
 // out_budget + slack per wave.  A wave also hands over what is left tail_iters
-// iterations after the launch's items are taken: families are heavy-tailed,
+// (32) iterations after the launch's items are taken: families are heavy-tailed,
 // and the next launch spreads the rest over all waves.
-template <int BLOCK, bool PC>
-constexpr uint32_t pool_entries() {
-    return (PC || BLOCK >= 1024) ? 128u : 256u;   // a 256-thread block stays within 40 KiB: four per CU
-}
+// LDS entries of a wave's pool.  256 entries leave four 256-thread blocks per
+// CU, 128 six: 1000 x 1000 sources 827 against 881 us (more goes through the
+// private stack), 4096 sources to t = 60 821 against 659 (more waves in
+// flight where each one waits on its own chain).
+constexpr uint32_t kPoolEntries = 128;
+// Two planes of 16 bytes per entry: consecutive lanes touch consecutive banks
+// (entries of 32 bytes side by side conflict two ways).
+template <uint32_t CAP>
+struct PoolPlanes {
+    struct __align__(16) Half {
+        uint64_t a, b;
+    };
+    Half xt[CAP], kb[CAP];
+    __device__ __forceinline__ PulsePoolEntry get(uint32_t i) const {
+        const Half p = xt[i & (CAP - 1)], q = kb[i & (CAP - 1)];
+        PulsePoolEntry e;
+        e.x = __longlong_as_double(static_cast<long long>(p.a));
+        e.t = __longlong_as_double(static_cast<long long>(p.b));
+        e.key = q.a;
+        e.batch = static_cast<uint32_t>(q.b);
+        e.meta = static_cast<uint32_t>(q.b >> 32);
+        return e;
+    }
+    __device__ __forceinline__ void put(uint32_t i, const PulsePoolEntry& e) {
+        Half p, q;
+        p.a = static_cast<uint64_t>(__double_as_longlong(e.x));
+        p.b = static_cast<uint64_t>(__double_as_longlong(e.t));
+        q.a = e.key;
+        q.b = (static_cast<uint64_t>(e.meta) << 32) | e.batch;
+        xt[i & (CAP - 1)] = p;
+        kb[i & (CAP - 1)] = q;
+    }
+};
 constexpr uint32_t kPoolCensusStage = 64;
 constexpr uint32_t kPoolFlushMask = (1u << 25) - 1u;   // iterations between forced row flushes (32-bit counters)
 
@@ -549,9 +578,9 @@ template <int ITEMS, bool PC, int BLOCK>
 __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
     constexpr bool SOURCES = ITEMS == PULSE_ITEMS_SOURCES;
     constexpr bool COPIES = ITEMS == PULSE_ITEMS_COPIES;
-    constexpr uint32_t CAP = pool_entries<BLOCK, PC>();
+    constexpr uint32_t CAP = kPoolEntries;
     constexpr uint32_t kWaves = BLOCK / 64;
-    __shared__ PulsePoolEntry s_pool[kWaves][CAP];
+    __shared__ PoolPlanes<CAP> s_pool[kWaves];
     __shared__ FamilySource s_src[SOURCES ? kWaves : 1][SOURCES ? 64 : 1];
     __shared__ uint32_t s_tag[kWaves][8];
     __shared__ CensusStageOf<kPoolCensusStage> s_cen[PC ? kWaves : 1];
@@ -576,7 +605,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
     if (threadIdx.x < kNDiag) s_acc[threadIdx.x] = 0;
     tally_lds_begin<BLOCK>(P, counters);   // and the barrier for the above
 
-    PulsePoolEntry* const pool = s_pool[wid];
+    PoolPlanes<CAP>& pool = s_pool[wid];
     FamilySource* const src = s_src[SOURCES ? wid : 0];
     uint32_t* const tags = s_tag[wid];
     auto& cen = s_cen[PC ? wid : 0];
@@ -658,7 +687,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
                 const PulsePoolEntry* const priv = R.priv + wave * R.priv_cap;
                 const uint32_t cnt = npriv < CAP / 2 ? npriv : CAP / 2;
                 npriv -= cnt;
-                for (uint32_t i = lane; i < cnt; i += 64u) pool[(top + i) & (CAP - 1)] = priv[npriv + i];
+                for (uint32_t i = lane; i < cnt; i += 64u) pool.put(top + i, priv[npriv + i]);
                 top += cnt;
                 __builtin_amdgcn_wave_barrier();
             }
@@ -668,7 +697,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
                 const uint32_t rank = mask_rank(need);
                 const uint64_t m = need & wave_mask(rank < take);
                 if (in_mask(m)) {
-                    const PulsePoolEntry e = pool[(top - 1u - rank) & (CAP - 1)];
+                    const PulsePoolEntry e = pool.get(top - 1u - rank);
                     x = e.x;
                     t = e.t;
                     batch = e.batch;
@@ -854,11 +883,11 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
                     const uint32_t cnt = top - bot < CAP / 2 ? top - bot : CAP / 2;
                     if (npriv + cnt <= R.priv_cap) {
                         PulsePoolEntry* const priv = R.priv + wave * R.priv_cap;
-                        for (uint32_t i = lane; i < cnt; i += 64u) priv[npriv + i] = pool[(bot + i) & (CAP - 1)];
+                        for (uint32_t i = lane; i < cnt; i += 64u) priv[npriv + i] = pool.get(bot + i);
                         npriv += cnt;
                     } else if (seen <= R.out_budget) {
                         const uint64_t base = reserve(R, cnt);
-                        for (uint32_t i = lane; i < cnt; i += 64u) store_entry(R, base + i, pool[(bot + i) & (CAP - 1)]);
+                        for (uint32_t i = lane; i < cnt; i += 64u) store_entry(R, base + i, pool.get(bot + i));
                     } else {
                         direct = hand_over = true;
                         break;
@@ -883,7 +912,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
                         e.key = key;
                         e.batch = batch;
                         e.meta = (c << 16) | static_cast<uint32_t>(tb + 1);
-                        pool[(top + off + (c - 2u)) & (CAP - 1)] = e;
+                        pool.put(top + off + (c - 2u), e);
                     }
                 top += n_more;
                 __builtin_amdgcn_wave_barrier();
@@ -911,7 +940,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
         const uint64_t base = reserve(R, nl + np + npriv + ni);
         if (in_mask(child)) Z = child_state(R.lcg, Z, part);
         if (in_mask(A)) bank_store(R, base + mask_rank(A), x, t, Z, batch, tb);
-        for (uint32_t i = lane; i < np; i += 64u) store_entry(R, base + nl + i, pool[(bot + i) & (CAP - 1)]);
+        for (uint32_t i = lane; i < np; i += 64u) store_entry(R, base + nl + i, pool.get(bot + i));
         for (uint32_t i = lane; i < npriv; i += 64u) store_entry(R, base + nl + np + i, priv[i]);
         if (ITEMS == PULSE_ITEMS_BANK)
             for (uint32_t i = lane; i < ni; i += 64u) {
