@@ -1495,7 +1495,8 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     const uint64_t n_counters = static_cast<uint64_t>(P->n_batches) * P->n_time_bins;
     pp.n_counters = static_cast<uint32_t>(std::min<uint64_t>(n_counters, 0xffffffffu));
     const bool event = o.schedule == MCRNG_PULSE_EVENT;
-    pp.lds_tally = n_counters <= (o.schedule == MCRNG_PULSE_BANK ? kPulsePoolLdsCounters : kPulseLdsCounters) ? 1u : 0u;
+    const bool pooled = o.schedule == MCRNG_PULSE_BANK || !hash;   // k_pulse_pool or k_pulse_stride
+    pp.lds_tally = n_counters <= (pooled ? kPulsePoolLdsCounters : kPulseLdsCounters) ? 1u : 0u;
     // the pool kernel's LDS: time edges up to 512 bins, and (counters not in
     // LDS) 2 to 8 tally rows per wave within 1 KiB, up to 4 KiB for two
     pp.edges_lds = P->n_time_bins <= 512 ? 1u : 0u;
@@ -1526,7 +1527,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     // the census parts' counters
     uint64_t* misc = static_cast<uint64_t*>(ctx->pulse_misc.p);
     pp.out_count = misc;
-    pp.item_counter = o.schedule == MCRNG_PULSE_BANK ? misc + kPulseItemWords : misc + 1;
+    pp.item_counter = pooled ? misc + kPulseItemWords : misc + 1;
     pp.family_counter = misc + 2;
     pp.overflow = reinterpret_cast<uint32_t*>(misc + 3);
     pp.cen_count = misc + kPulseCenWords;
@@ -1583,6 +1584,21 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
         return MCRNG_OK;
     };
 
+    // How the waves of a pool or stride launch come by its items.  Few: each
+    // wave its share.  Many: half of them so, the rest an eighth of a share at
+    // a time, so that the waves end together (1000 x 1000 sources: 866 us; a
+    // sixteenth 878, a thirty-second 962; three quarters without an atomic 926).
+    auto split_items = [&](uint32_t grid, uint32_t chunk, uint32_t waves) {
+        const uint64_t n = pp.item_end - pp.item_begin;
+        const uint64_t share = (n + waves - 1) / waves;
+        pp.first_chunk = static_cast<uint32_t>(share <= 32 && !chunk ? share : std::min<uint64_t>(n / (2 * waves), 1u << 20));
+        pp.chunk = chunk ? chunk : static_cast<uint32_t>(std::min<uint64_t>(256, std::max<uint64_t>(1, share / 8)));
+        const uint64_t dynamic = std::min<uint64_t>(pp.item_begin + static_cast<uint64_t>(pp.first_chunk) * waves, pp.item_end);
+        pp.item_parts = grid >= kPulseItemParts ? kPulseItemParts : 1;
+        for (uint32_t i = 0; i <= kPulseItemParts; ++i)
+            pp.item_part[i] = dynamic + (pp.item_end - dynamic) * std::min(i, pp.item_parts) / pp.item_parts;
+    };
+
     // Pool launches (bank schedule): a launch runs its items and all they give
     // rise to, except what its waves hand over to the output bank: entries
     // beyond a wave's LDS pool and private stack, and what a wave still holds
@@ -1613,15 +1629,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             const uint64_t n = pp.item_end - pp.item_begin;
             const uint32_t grid = pulse_pool_grid(pp, k, pcen, block, n);
             const uint64_t waves = static_cast<uint64_t>(grid) * o.block / 64;
-            // few items: each wave its share.  Many: half of them so, the rest
-            // an eighth of a share at a time, so that the waves end together
-            const uint64_t share = (n + waves - 1) / waves;
-            pp.first_chunk = static_cast<uint32_t>(share <= 32 && !o.chunk ? share : std::min<uint64_t>(n / (2 * waves), 1u << 20));
-            const uint64_t dynamic = std::min(pp.item_begin + pp.first_chunk * waves, pp.item_end);
-            pp.item_parts = grid >= kPulseItemParts ? kPulseItemParts : 1;
-            for (uint32_t i = 0; i <= kPulseItemParts; ++i)
-                pp.item_part[i] = dynamic + (pp.item_end - dynamic) * std::min(i, pp.item_parts) / pp.item_parts;
-            pp.chunk = o.chunk ? o.chunk : static_cast<uint32_t>(std::min<uint64_t>(256, std::max<uint64_t>(1, share / 8)));
+            split_items(grid, o.chunk, static_cast<uint32_t>(waves));
             pp.out_budget = pool_budget ? pool_budget : std::min<uint64_t>(std::max<uint64_t>(2 * n, 1u << 16), 1u << 24);
             const uint64_t ocap = pp.out_budget + waves * pulse_pool_slack(pp, n_max) + (n_bank > 0 ? n : 0);
             int r;
@@ -1641,7 +1649,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             pp.out_cap = ocap;
             // (n_left and the census counts stay)
             HIP_TRY(launch_fill_u64(misc, 3, 0ull, st));
-            if (dynamic != pp.item_end)
+            if (pp.item_part[0] != pp.item_end)
                 HIP_TRY(launch_fill_u64(pp.item_counter, kPulseItemParts * kPulseCounterStride, 0ull, st));
             HIP_TRY(launch_pulse_pool(pp, k, pcen, block, grid, st));
             uint64_t w[kPulseMiscWords];
@@ -1656,7 +1664,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             }
             uint64_t n_out = w[0];
             // dynamic items that no wave has taken (its waves handed over early)
-            if (dynamic != pp.item_end)
+            if (pp.item_part[0] != pp.item_end)
                 for (uint32_t i = 0; i < kPulseItemParts; ++i) {
                     const uint64_t e = pp.item_part[i + 1];
                     const uint64_t taken = std::min(pp.item_part[i] + w[kPulseItemWords + i * kPulseCounterStride], e);
@@ -1822,6 +1830,15 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             pp.src_end = std::min(n_src, c0 + chunk);
             if ((rc = generations(PULSE_ITEMS_SOURCES, pp.src_end - pp.src_begin, false, nullptr)) < 0) return rc;
         }
+    } else if (!hash) {
+        pp.item_begin = 0;
+        pp.item_end = n_src;
+        const uint32_t grid = pulse_stride_grid(pp, static_cast<int>(o.block), n_src);
+        const uint64_t lanes = static_cast<uint64_t>(grid) * o.block;
+        split_items(grid, 0, grid * (o.block / 64));
+        if ((rc = ensure(ctx->pulse_stack, lanes * o.stack_depth * sizeof(PulseStackEntry), st)) < 0) return rc;
+        pp.stack = static_cast<PulseStackEntry*>(ctx->pulse_stack.p);
+        HIP_TRY(launch_pulse_stride(pp, static_cast<int>(o.block), grid, st));
     } else {
         const uint32_t grid = pulse_family_grid(static_cast<int>(o.block));
         const uint64_t lanes = static_cast<uint64_t>(grid) * o.block;

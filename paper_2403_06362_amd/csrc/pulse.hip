@@ -552,7 +552,7 @@ struct PoolPlanes {
     }
 };
 constexpr uint32_t kPoolCensusStage = 64;
-constexpr uint32_t kPoolFlushMask = (1u << 25) - 1u;   // iterations between forced row flushes (32-bit counters)
+constexpr uint32_t kRowFlushMask = (1u << 25) - 1u;   // iterations between forced row flushes (32-bit counters)
 
 // (k M ^ (k M >> 47)) M: the part of hash(k, s) that depends on k only.
 __device__ __forceinline__ uint64_t child_part(uint64_t k) {
@@ -574,6 +574,97 @@ __device__ __forceinline__ const PulseParams& rare_params() {
     return *(const PulseParams*)(Arg)p;
 }
 
+// Tallies of a wave of the pool and stride kernels.  All counters in the
+// block's LDS copy when they fit; else rows of n_time_bins counters in LDS, one
+// per batch the wave works on (row b mod P.rows, tagged); collisions of a batch
+// without a row count in HBM.
+struct WaveTally {
+    unsigned long long* counters;   // the block's copy (P.lds_tally)
+    uint32_t* rows;
+    uint32_t* tags;
+    uint32_t nt, lane;
+    __device__ __forceinline__ void begin(const PulseParams& P) {
+        if (P.rows != 0) {
+            for (uint32_t i = lane; i < P.rows * nt; i += 64u) rows[i] = 0u;
+            if (lane < 8u) tags[lane] = 0xffffffffu;
+        }
+    }
+    __device__ __forceinline__ void flush_row(uint32_t r) {
+        const PulseParams& R = rare_params();
+        const uint32_t tag = __builtin_amdgcn_readfirstlane(tags[r]);
+        if (tag == 0xffffffffu) return;
+        unsigned long long* c = reinterpret_cast<unsigned long long*>(R.counts) + static_cast<uint64_t>(tag) * nt;
+        for (uint32_t i = lane; i < nt; i += 64u) {
+            const uint32_t v = rows[r * nt + i];
+            if (v != 0u) {
+                atomicAdd(c + i, static_cast<unsigned long long>(v));
+                rows[r * nt + i] = 0u;
+            }
+        }
+    }
+    __device__ __forceinline__ void flush(const PulseParams& P) {
+        for (uint32_t r = 0; r < P.rows; ++r) flush_row(r);
+    }
+    // gives the batches of the lanes in m a row each (another batch's row with
+    // the same index goes to HBM first)
+    __device__ __forceinline__ void claim(const PulseParams& P, uint64_t m, uint32_t batch) {
+        while (m != 0) {
+            const uint32_t b = __builtin_amdgcn_readlane(batch, __builtin_ctzll(m));
+            const uint32_t r = b & (P.rows - 1u);
+            if (__builtin_amdgcn_readfirstlane(tags[r]) != b) {
+                flush_row(r);
+                if (lane == 0) tags[r] = b;
+                __builtin_amdgcn_wave_barrier();
+            }
+            m &= ~wave_mask(batch == b);
+        }
+    }
+    __device__ __forceinline__ void add(const PulseParams& P, uint64_t scored, uint32_t batch, int32_t bin) {
+        if (P.lds_tally) {
+            if (in_mask(scored)) atomicAdd(counters + (batch * nt + static_cast<uint32_t>(bin)), 1ull);
+            return;
+        }
+        uint64_t far = scored;
+        if (P.rows != 0) {
+            const uint32_t r = batch & (P.rows - 1u);
+            const uint64_t near = scored & wave_mask(tags[r] == batch);
+            if (in_mask(near)) atomicAdd(rows + (__umul24(r, nt) + static_cast<uint32_t>(bin)), 1u);
+            far &= ~near;
+        }
+        if (far != 0 && in_mask(far))
+            atomicAdd(reinterpret_cast<unsigned long long*>(P.counts) +
+                          (static_cast<uint64_t>(batch) * nt + static_cast<uint32_t>(bin)), 1ull);
+    }
+};
+
+// Time bin (-1 before the first edge) of the end times tn of the lanes in m
+// (tn below the last edge), whose flights started in bin tb.
+__device__ __forceinline__ int32_t flight_bin(const PulseParams& P, const double* l_edges, uint64_t m, double tn, int32_t tb) {
+    const uint32_t nt = P.n_time_bins;
+    auto edge_at = [&](int32_t i) -> double { return P.edges_lds ? l_edges[i] : P.t_edges[i]; };
+    int32_t bin = tb;
+    if (P.grid_uniform) {
+        int32_t g;   // (the instruction saturates, whatever idle lanes hold)
+        asm("v_cvt_i32_f64 %0, %1" : "=v"(g) : "v"((tn - P.t0) * P.inv_dt));
+        g = g < 0 ? 0 : g;
+        g = g < static_cast<int32_t>(nt) ? g : static_cast<int32_t>(nt) - 1;
+        const uint64_t before = wave_mask(tn < edge_at(g)), after = wave_mask(edge_at(g + 1) <= tn);
+        bin = g - static_cast<int32_t>(sel_const<1, 0>(before)) + static_cast<int32_t>(sel_const<1, 0>(after));
+    } else if (in_mask(m)) {
+        while (bin + 1 < static_cast<int32_t>(nt) && edge_at(bin + 1) <= tn) bin++;
+    }
+    return bin;
+}
+
+// Dynamic LDS of both kernels: time edges, the block's counters, the waves' rows.
+template <int BLOCK>
+__device__ __forceinline__ double* stage_edges(const PulseParams& P, unsigned long long* dyn) {
+    double* const l_edges = reinterpret_cast<double*>(dyn);
+    if (P.edges_lds)
+        for (uint32_t i = threadIdx.x; i <= P.n_time_bins; i += BLOCK) l_edges[i] = P.t_edges[i];
+    return l_edges;
+}
+
 template <int ITEMS, bool PC, int BLOCK>
 __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
     constexpr bool SOURCES = ITEMS == PULSE_ITEMS_SOURCES;
@@ -589,25 +680,20 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
     extern __shared__ unsigned long long dyn[];
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t nt = P.n_time_bins;
-    // dynamic LDS: time edges, the block's counters or the waves' tally rows
-    double* const l_edges = reinterpret_cast<double*>(dyn);
-    unsigned long long* const counters = dyn + (P.edges_lds ? nt + 1 : 0u);
-    if (P.edges_lds)
-        for (uint32_t i = threadIdx.x; i <= nt; i += BLOCK) l_edges[i] = P.t_edges[i];
-    auto edge_at = [&](int32_t i) -> double { return P.edges_lds ? l_edges[i] : P.t_edges[i]; };
-    uint32_t* const rows = reinterpret_cast<uint32_t*>(counters) + wid * P.rows * nt;
-    if (P.rows != 0) {
-        for (uint32_t i = lane; i < P.rows * nt; i += 64u) rows[i] = 0u;
-        if (lane < 8u) s_tag[wid][lane] = 0xffffffffu;
-    }
+    double* const l_edges = stage_edges<BLOCK>(P, dyn);
+    WaveTally tally;
+    tally.nt = P.n_time_bins;
+    tally.lane = lane;
+    tally.counters = dyn + (P.edges_lds ? P.n_time_bins + 1 : 0u);
+    tally.rows = reinterpret_cast<uint32_t*>(tally.counters) + wid * P.rows * P.n_time_bins;
+    tally.tags = s_tag[wid];
+    tally.begin(P);
     if (threadIdx.x < 16) s_part[threadIdx.x] = child_part(threadIdx.x);
     if (threadIdx.x < kNDiag) s_acc[threadIdx.x] = 0;
-    tally_lds_begin<BLOCK>(P, counters);   // and the barrier for the above
+    tally_lds_begin<BLOCK>(P, tally.counters);   // and the barrier for the above
 
     PoolPlanes<CAP>& pool = s_pool[wid];
     FamilySource* const src = s_src[SOURCES ? wid : 0];
-    uint32_t* const tags = s_tag[wid];
     auto& cen = s_cen[PC ? wid : 0];
     const uint64_t wave = static_cast<uint64_t>(blockIdx.x) * kWaves + wid;
     const uint64_t part1 = child_part(1);
@@ -637,34 +723,6 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
     uint32_t batch = 0;
     int32_t tb = -1;
 
-    auto flush_row = [&](uint32_t r) {
-        const PulseParams& R = rare_params();
-        const uint32_t tag = __builtin_amdgcn_readfirstlane(tags[r]);
-        if (tag == 0xffffffffu) return;
-        unsigned long long* c = reinterpret_cast<unsigned long long*>(R.counts) + static_cast<uint64_t>(tag) * nt;
-        for (uint32_t i = lane; i < nt; i += 64u) {
-            const uint32_t v = rows[r * nt + i];
-            if (v != 0u) {
-                atomicAdd(c + i, static_cast<unsigned long long>(v));
-                rows[r * nt + i] = 0u;
-            }
-        }
-    };
-    // gives the batches of the lanes in m a tally row each (another batch's row
-    // with the same index goes to HBM first; particles of a batch without a
-    // row count in HBM)
-    auto claim_rows = [&](uint64_t m) {
-        while (m != 0) {
-            const uint32_t b = __builtin_amdgcn_readlane(batch, __builtin_ctzll(m));
-            const uint32_t r = b & (P.rows - 1u);
-            if (__builtin_amdgcn_readfirstlane(tags[r]) != b) {
-                flush_row(r);
-                if (lane == 0) tags[r] = b;
-                __builtin_amdgcn_wave_barrier();
-            }
-            m &= ~wave_mask(batch == b);
-        }
-    };
     // reserves n entries of the output bank (n uniform)
     auto reserve = [&](const PulseParams& R, uint32_t n) -> uint64_t {
         uint64_t base = 0;
@@ -772,7 +830,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
                 wnext += take;
                 src_off += take;
                 A |= m;
-                if (P.rows != 0) claim_rows(m);
+                if (P.rows != 0) tally.claim(P, m, batch);
             }
         }
         if (A == 0) break;   // no pool, no items
@@ -780,8 +838,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
             hand_over = true;
             break;
         }
-        if (P.rows != 0 && (++iter & kPoolFlushMask) == 0)
-            for (uint32_t r = 0; r < P.rows; ++r) flush_row(r);
+        if ((++iter & kRowFlushMask) == 0) tally.flush(P);
 
         // one flight of every lane in A (the others compute on what their registers hold)
         if (in_mask(child)) Z = child_state(P.lcg, Z, part);
@@ -819,32 +876,9 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
         }
         const double step = mu * s;
         const double xn = x + step;
-        int32_t bin = tb;
-        if (P.grid_uniform) {
-            int32_t g;   // (the instruction saturates, whatever idle lanes hold)
-            asm("v_cvt_i32_f64 %0, %1" : "=v"(g) : "v"((tn - P.t0) * P.inv_dt));
-            g = g < 0 ? 0 : g;
-            g = g < static_cast<int32_t>(nt) ? g : static_cast<int32_t>(nt) - 1;
-            const uint64_t before = wave_mask(tn < edge_at(g)), after = wave_mask(edge_at(g + 1) <= tn);
-            bin = g - static_cast<int32_t>(sel_const<1, 0>(before)) + static_cast<int32_t>(sel_const<1, 0>(after));
-        } else if (in_mask(coll)) {
-            while (bin + 1 < static_cast<int32_t>(nt) && edge_at(bin + 1) <= tn) bin++;
-        }
+        const int32_t bin = flight_bin(P, l_edges, coll, tn, tb);
         const uint64_t scored = coll & wave_mask(bin >= 0) & wave_mask(P.x_lo <= xn) & wave_mask(xn <= P.x_hi);
-        if (P.lds_tally) {
-            if (in_mask(scored)) atomicAdd(counters + (batch * nt + static_cast<uint32_t>(bin)), 1ull);
-        } else {
-            uint64_t far = scored;
-            if (P.rows != 0) {
-                const uint32_t r = batch & (P.rows - 1u);
-                const uint64_t near = scored & wave_mask(tags[r] == batch);
-                if (in_mask(near)) atomicAdd(rows + (__umul24(r, nt) + static_cast<uint32_t>(bin)), 1u);
-                far &= ~near;
-            }
-            if (far != 0 && in_mask(far))
-                atomicAdd(reinterpret_cast<unsigned long long*>(P.counts) +
-                              (static_cast<uint64_t>(batch) * nt + static_cast<uint32_t>(bin)), 1ull);
-        }
+        tally.add(P, scored, batch, bin);
         const uint64_t z3 = lcg_next_z(P.lcg, z);
         const uint64_t go = coll & wave_mask(z3 < P.scatter_below);
         const uint64_t z4 = lcg_next_z(P.lcg, z3);
@@ -949,8 +983,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
             }
     }
     if (PC && cstaged != 0) census_flush(R, cen, cstaged, lane);
-    if (P.rows != 0)
-        for (uint32_t r = 0; r < P.rows; ++r) flush_row(r);
+    tally.flush(P);
     if (lane == 0) {
         auto add = [&](int w, uint64_t v) { atomicAdd(&s_acc[w], static_cast<unsigned long long>(v)); };
         add(PD_SOURCES, n_src);
@@ -966,7 +999,249 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
         if (COPIES) d = any4 != 0 ? 4u : (any3 != 0 ? 3u : ((n_dir | n_coll) != 0 ? 2u : (n_fly != 0 ? 1u : 0u)));
         atomicMax(&s_acc[PD_MAX_DRAWS], static_cast<unsigned long long>(d));
     }
-    tally_lds_end<BLOCK>(P, counters);
+    tally_lds_end<BLOCK>(P, tally.counters);
+    __syncthreads();
+    if (threadIdx.x < kNDiag && s_acc[threadIdx.x] != 0) {
+        unsigned long long* d = reinterpret_cast<unsigned long long*>(R.diag) + threadIdx.x;
+        if (threadIdx.x == PD_MAX_DRAWS)
+            atomicMax(d, s_acc[threadIdx.x]);
+        else
+            atomicAdd(d, s_acc[threadIdx.x]);
+    }
+}
+
+// ------------------------------------------------------------ stride kernel
+
+// Families of stride seeding: one source family per lane, depth first on the
+// source's one stream.  Every lane flies in every iteration: a line that ends
+// goes on with the stack's newest sibling, a family that ends with the wave's
+// next source.  A lane's stack entry holds the siblings of one scattering
+// still to start (x, t, their number and the time bin); its newest
+// kStrideDepth entries lie in LDS, one plane per depth (entry d of every lane
+// side by side), the older ones in HBM planes (entry d of lane l of the launch
+// at d * lanes + l): when the LDS part is full its oldest entry moves out, and
+// back when the lane runs out of newer ones.
+//   The kernel is bound by vector issue and the chains of one wave's flight
+// (about 190 instructions).  Against the walk it replaces (every entry below
+// the top in HBM, the phases of a family as branches: 358 instructions per
+// flight, 108 GB of stack traffic) the 3e7-source study went from 36.7 ms to
+// 13.3.
+constexpr uint32_t kStrideDepth = 6;   // a 256-thread block stays within 40 KiB of LDS: four per CU
+
+template <int BLOCK>
+__global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
+    constexpr uint32_t kWaves = BLOCK / 64;
+    __shared__ double s_x[kWaves][kStrideDepth][64], s_t[kWaves][kStrideDepth][64];
+    __shared__ uint32_t s_m[kWaves][kStrideDepth][64];   // siblings left << 16 | time bin + 1
+    __shared__ FamilySource s_src[kWaves][64];
+    __shared__ uint32_t s_tag[kWaves][8];
+    __shared__ unsigned long long s_acc[kNDiag];
+    extern __shared__ unsigned long long dyn[];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double* const l_edges = stage_edges<BLOCK>(P, dyn);
+    WaveTally tally;
+    tally.nt = P.n_time_bins;
+    tally.lane = lane;
+    tally.counters = dyn + (P.edges_lds ? P.n_time_bins + 1 : 0u);
+    tally.rows = reinterpret_cast<uint32_t*>(tally.counters) + wid * P.rows * P.n_time_bins;
+    tally.tags = s_tag[wid];
+    tally.begin(P);
+    if (threadIdx.x < kNDiag) s_acc[threadIdx.x] = 0;
+    tally_lds_begin<BLOCK>(P, tally.counters);   // and the barrier for the above
+
+    double* const sx = &s_x[wid][0][lane];
+    double* const st = &s_t[wid][0][lane];
+    uint32_t* const sm = &s_m[wid][0][lane];
+    FamilySource* const src = s_src[wid];
+    const uint64_t lanes = static_cast<uint64_t>(gridDim.x) * BLOCK;
+    const uint64_t gl = static_cast<uint64_t>(blockIdx.x) * BLOCK + threadIdx.x;
+    const uint64_t wave = static_cast<uint64_t>(blockIdx.x) * kWaves + wid;
+    const double sigma = P.sigma_t;
+    const double rsigma = uniform_value(recip_refined(sigma));
+
+    uint64_t A = 0;                     // lanes with a family
+    uint64_t wnext = P.item_begin + wave * P.first_chunk;   // the wave's untaken sources [wnext, gend), seeded up to wend
+    if (wnext > P.item_part[0]) wnext = P.item_part[0];
+    uint64_t gend = wnext + P.first_chunk < P.item_part[0] ? wnext + P.first_chunk : P.item_part[0];
+    uint64_t wend = wnext;
+    uint32_t src_off = 0;
+    bool exhausted = P.item_part[0] == P.item_end && wnext == gend;
+    uint32_t iter = 0;
+    uint64_t n_src = 0, n_fly = 0, n_coll = 0, n_tal = 0, n_scat = 0, n_extra = 0;
+    uint64_t max_draws = 0, over = 0;   // per lane
+    double x = 0.0, t = 0.0;
+    uint64_t Z = 0, draws = 0;
+    uint32_t batch = 0, depth = 0, low = 0;   // entries of the lane's stack, and those of them in HBM
+    uint32_t slot = 0;                  // (depth mod kStrideDepth) x 64: the next entry's place in LDS
+    int32_t tb = -1;
+
+    for (;;) {
+        const uint64_t need = ~A;
+        if (need != 0 && !exhausted) {
+            if (wnext == wend) {
+                const PulseParams& R = rare_params();
+                if (wnext == gend) {
+                    const uint32_t s = blockIdx.x & (R.item_parts - 1u);
+                    const uint64_t e = R.item_part[s + 1u];
+                    uint64_t b = 0;
+                    if (lane == 0)
+                        b = atomicAdd(reinterpret_cast<unsigned long long*>(R.item_counter + s * kPulseCounterStride),
+                                      static_cast<unsigned long long>(R.chunk));
+                    b = R.item_part[s] + lane_value(b, 0);
+                    wnext = b < e ? b : e;
+                    gend = b + R.chunk < e ? b + R.chunk : e;
+                    exhausted = wnext == gend;
+                }
+                wend = gend - wnext < 64u ? gend : wnext + 64u;
+                const uint64_t j = wnext + lane;
+                if (j < wend) {
+                    FamilySource e;
+                    e.X = pulse_source_state(R, j, &e.batch);
+                    e.pad = 0;
+                    src[lane] = e;
+                }
+                src_off = 0;
+                __builtin_amdgcn_wave_barrier();
+            }
+            const uint64_t avail = wend - wnext;
+            const uint32_t k = mask_count(need);
+            const uint32_t take = avail < k ? static_cast<uint32_t>(avail) : k;
+            const uint32_t rank = mask_rank(need);
+            const uint64_t m = need & wave_mask(rank < take);
+            if (in_mask(m)) {
+                const FamilySource e = src[src_off + rank];
+                Z = e.X;
+                batch = e.batch;
+                x = 0.0;
+                t = 0.0;
+                tb = P.tb0;
+                draws = 0;
+            }
+            n_src += take;
+            wnext += take;
+            src_off += take;
+            A |= m;
+            if (P.rows != 0 && m != 0) tally.claim(P, m, batch);
+        }
+        if (A == 0) {
+            if (exhausted) break;
+            continue;
+        }
+        if ((++iter & kRowFlushMask) == 0) tally.flush(P);
+
+        // one flight of every lane in A (the others compute on what their registers hold)
+        const uint64_t z1 = lcg_next_z(P.lcg, Z);
+        const double mu = __builtin_fma(uniform_z(z1), 2.0, -1.0);   // exact
+        const uint64_t z2 = lcg_next_z(P.lcg, z1);
+        const double s = quot(fixed_neg_log(uniform_z(z2)), sigma, rsigma);
+        const double tn = t + s;
+        const uint64_t coll = A & wave_mask(tn < P.t_end);
+        const double step = mu * s;
+        const double xn = x + step;
+        const int32_t bin = flight_bin(P, l_edges, coll, tn, tb);
+        const uint64_t scored = coll & wave_mask(bin >= 0) & wave_mask(P.x_lo <= xn) & wave_mask(xn <= P.x_hi);
+        tally.add(P, scored, batch, bin);
+        const uint64_t z3 = lcg_next_z(P.lcg, z2);
+        const uint64_t go = coll & wave_mask(z3 < P.scatter_below);
+        const uint64_t z4 = lcg_next_z(P.lcg, z3);
+        const uint64_t extra = go & wave_mask(z4 < P.frac_below);
+        // the stream goes on from the last number drawn: two of a flight that
+        // reached the end, three of an absorption, four of a scattering
+        Z = sel(go, z4, sel(coll, z3, z2));
+        draws += 2u + sel_const<1, 0>(coll) + sel_const<1, 0>(go);
+        n_fly += mask_count(A);
+        n_coll += mask_count(coll);
+        n_tal += mask_count(scored);
+        n_scat += mask_count(go);
+        n_extra += mask_count(extra);
+
+        // the first emerging particle runs on; its siblings wait on the stack
+        const uint64_t on = P.n_floor != 0 ? go : extra;
+        const uint64_t push = P.n_floor >= 2u ? go : (P.n_floor == 1u ? extra : 0ull);
+        if (in_mask(go)) {
+            x = xn;
+            t = tn;
+            tb = bin;
+        }
+        uint64_t lost = 0;   // lanes whose stack would grow past stack_depth: the family is abandoned
+        if (push != 0) {
+            lost = push & wave_mask(depth == P.stack_depth);
+            const uint64_t full = push & ~lost & wave_mask(depth - low == kStrideDepth);
+            if (full != 0 && in_mask(full)) {
+                const PulseParams& R = rare_params();
+                PulseStackEntry e;
+                e.x = sx[slot];
+                e.t = st[slot];
+                e.key = sm[slot];
+                R.stack[low * lanes + gl] = e;
+                low++;
+            }
+            if (in_mask(push & ~lost)) {
+                sx[slot] = x;
+                st[slot] = t;
+                sm[slot] = ((P.n_floor - 1u + sel_const<1, 0>(extra)) << 16) | static_cast<uint32_t>(tb + 1);
+                depth++;
+                slot = slot == (kStrideDepth - 1u) * 64u ? 0u : slot + 64u;
+            }
+        }
+        // lines that ended: the newest sibling, or the end of the family
+        const uint64_t ended = A & ~on;
+        const uint64_t back = ended & wave_mask(depth != 0);
+        const uint64_t dry = back & wave_mask(depth == low);
+        if (dry != 0 && in_mask(dry)) {
+            const PulseParams& R = rare_params();
+            low--;
+            const PulseStackEntry e = R.stack[low * lanes + gl];
+            const uint32_t o = slot == 0u ? (kStrideDepth - 1u) * 64u : slot - 64u;
+            sx[o] = e.x;
+            st[o] = e.t;
+            sm[o] = static_cast<uint32_t>(e.key);
+        }
+        if (in_mask(back)) {
+            const uint32_t o = slot == 0u ? (kStrideDepth - 1u) * 64u : slot - 64u;
+            const uint32_t m = sm[o];
+            x = sx[o];
+            t = st[o];
+            tb = static_cast<int32_t>(m & 0xffffu) - 1;
+            const uint64_t last = wave_mask(m < (2u << 16));
+            sm[o] = m - (1u << 16);
+            depth -= sel_const<1, 0>(last);
+            slot = sel(last, o, slot);
+        }
+        const uint64_t end = (ended & ~back) | lost;
+        if (end != 0) {
+            if (in_mask(end)) {
+                max_draws = draws > max_draws ? draws : max_draws;
+                if (draws > P.stride_q) over++;
+                depth = 0;
+                low = 0;
+                slot = 0;
+            }
+            A &= ~end;
+            if (lost != 0) {
+                const PulseParams& R = rare_params();
+                if (lane == 0) atomicOr(R.overflow, 1u);
+            }
+        }
+    }
+
+    const PulseParams& R = rare_params();
+    tally.flush(P);
+    atomicMax(&s_acc[PD_MAX_DRAWS], static_cast<unsigned long long>(max_draws));
+    atomicAdd(&s_acc[PD_OVER_STRIDE], static_cast<unsigned long long>(over));
+    if (lane == 0) {
+        auto add = [&](int w, uint64_t v) { atomicAdd(&s_acc[w], static_cast<unsigned long long>(v)); };
+        add(PD_SOURCES, n_src);
+        add(PD_COLLISIONS, n_coll);
+        add(PD_TALLIED, n_tal);
+        add(PD_SCATTERS, n_scat);
+        add(PD_ABSORBED, n_coll - n_scat);
+        add(PD_CENSUS, n_fly - n_coll);
+        add(PD_SECONDARIES, n_scat * P.n_floor + n_extra);
+        add(PD_DRAWS, 2 * n_fly + n_coll + n_scat);
+    }
+    tally_lds_end<BLOCK>(P, tally.counters);
     __syncthreads();
     if (threadIdx.x < kNDiag && s_acc[threadIdx.x] != 0) {
         unsigned long long* d = reinterpret_cast<unsigned long long*>(R.diag) + threadIdx.x;
@@ -1652,6 +1927,38 @@ hipError_t launch_pulse_finish(const PulseParams& p, bool pc, uint32_t grid, hip
         hipLaunchKernelGGL((k_pulse_family<true, PULSE_ITEMS_BANK, false, 256, false, false>), dim3(grid), dim3(256),
                            pulse_tally_lds_bytes(p), st, p);
     return hipGetLastError();
+}
+
+static const void* stride_kernel(int block) {
+    switch (block) {
+        case 64: return reinterpret_cast<const void*>(k_pulse_stride<64>);
+        case 128: return reinterpret_cast<const void*>(k_pulse_stride<128>);
+        case 512: return reinterpret_cast<const void*>(k_pulse_stride<512>);
+        case 1024: return reinterpret_cast<const void*>(k_pulse_stride<1024>);
+        default: return reinterpret_cast<const void*>(k_pulse_stride<256>);
+    }
+}
+
+uint32_t pulse_stride_grid(const PulseParams& p, int block, uint64_t sources) {
+    block = bank_block(block);
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stride_kernel(block), block, pool_lds_bytes(p, block)) !=
+            hipSuccess ||
+        per_cu < 1)
+        per_cu = 1;
+    // a family per wave at least: few families spread over the whole chip
+    uint64_t blocks = (sources + block / 64 - 1) / (block / 64);
+    const uint64_t cap = static_cast<uint64_t>(device_cus()) * static_cast<uint64_t>(per_cu);
+    if (blocks > cap) blocks = cap;
+    return static_cast<uint32_t>(blocks < 1 ? 1 : blocks);
+}
+
+hipError_t launch_pulse_stride(const PulseParams& p, int block, uint32_t grid, hipStream_t st) {
+    if (p.item_end == p.item_begin) return hipSuccess;
+    block = bank_block(block);
+    PulseParams arg = p;
+    void* args[] = {&arg};
+    return hipLaunchKernel(stride_kernel(block), dim3(grid), dim3(block), args, pool_lds_bytes(p, block), st);
 }
 
 uint32_t pulse_family_grid(int block) {

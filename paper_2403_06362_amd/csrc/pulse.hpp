@@ -149,6 +149,11 @@ hipError_t launch_pulse_pool(const PulseParams& p, int items_kind, bool pc, int 
 hipError_t launch_pulse_census_count(const PulseParams& p, uint64_t n_arrivals, hipStream_t st);
 hipError_t launch_pulse_split(const PulseParams& p, uint64_t n_arrivals, hipStream_t st);
 uint32_t pulse_family_grid(int block);
+// Families of stride seeding: the grid (p.stack holds stack_depth entries per
+// lane of it), then the launch over items [item_begin, item_end) taken as by
+// the pool.
+uint32_t pulse_stride_grid(const PulseParams& p, int block, uint64_t sources);
+hipError_t launch_pulse_stride(const PulseParams& p, int block, uint32_t grid, hipStream_t st);
 // Finish launch (hash seeding): the generation bank p.in (p.n_in particles)
 // run depth first per lane with p.stack (p.stack_depth entries per lane),
 // at most p.lane_budget particles per input particle, the rest banked in
