@@ -1020,13 +1020,15 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
 // kStrideDepth entries lie in LDS, one plane per depth (entry d of every lane
 // side by side), the older ones in HBM planes (entry d of lane l of the launch
 // at d * lanes + l): when the LDS part is full its oldest entry moves out, and
-// back when the lane runs out of newer ones.
+// back when the lane runs out of newer ones (read one flight ahead: some lane
+// of a wave needs one in nearly every iteration).
 //   The kernel is bound by vector issue and the chains of one wave's flight
 // (about 190 instructions).  Against the walk it replaces (every entry below
 // the top in HBM, the phases of a family as branches: 358 instructions per
 // flight, 108 GB of stack traffic) the 3e7-source study went from 36.7 ms to
 // 13.3.
 constexpr uint32_t kStrideDepth = 6;   // a 256-thread block stays within 40 KiB of LDS: four per CU
+constexpr uint32_t kStrideRefill = 3;  // idle lanes at which a wave takes sources (a family ends in 60% of its iterations)
 
 template <int BLOCK>
 __global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
@@ -1073,12 +1075,14 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
     double x = 0.0, t = 0.0;
     uint64_t Z = 0, draws = 0;
     uint32_t batch = 0, depth = 0, low = 0;   // entries of the lane's stack, and those of them in HBM
+    PulseStackEntry ahead{};            // entry ahead_of - 1, read ahead from HBM
+    uint32_t ahead_of = 0;
     uint32_t slot = 0;                  // (depth mod kStrideDepth) x 64: the next entry's place in LDS
     int32_t tb = -1;
 
     for (;;) {
         const uint64_t need = ~A;
-        if (need != 0 && !exhausted) {
+        if ((mask_count(need) >= kStrideRefill || A == 0) && !exhausted) {
             if (wnext == wend) {
                 const PulseParams& R = rare_params();
                 if (wnext == gend) {
@@ -1190,13 +1194,12 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
         const uint64_t back = ended & wave_mask(depth != 0);
         const uint64_t dry = back & wave_mask(depth == low);
         if (dry != 0 && in_mask(dry)) {
-            const PulseParams& R = rare_params();
-            low--;
-            const PulseStackEntry e = R.stack[low * lanes + gl];
             const uint32_t o = slot == 0u ? (kStrideDepth - 1u) * 64u : slot - 64u;
-            sx[o] = e.x;
-            st[o] = e.t;
-            sm[o] = static_cast<uint32_t>(e.key);
+            low--;
+            sx[o] = ahead.x;
+            st[o] = ahead.t;
+            sm[o] = static_cast<uint32_t>(ahead.key);
+            ahead_of = 0;
         }
         if (in_mask(back)) {
             const uint32_t o = slot == 0u ? (kStrideDepth - 1u) * 64u : slot - 64u;
@@ -1209,6 +1212,14 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
             depth -= sel_const<1, 0>(last);
             slot = sel(last, o, slot);
         }
+        // a lane whose next sibling is in HBM reads it now: it flies at least
+        // once before it needs it
+        const uint64_t fetch = A & wave_mask(depth == low) & wave_mask(low != 0) & wave_mask(ahead_of != low);
+        if (fetch != 0 && in_mask(fetch)) {
+            const PulseParams& R = rare_params();
+            ahead = R.stack[(low - 1u) * lanes + gl];
+            ahead_of = low;
+        }
         const uint64_t end = (ended & ~back) | lost;
         if (end != 0) {
             if (in_mask(end)) {
@@ -1217,6 +1228,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
                 depth = 0;
                 low = 0;
                 slot = 0;
+                ahead_of = 0;
             }
             A &= ~end;
             if (lost != 0) {
