@@ -156,10 +156,8 @@ enum { MCRNG_SCHED_HISTORY = 0, MCRNG_SCHED_EVENT = 1 };
  *   block           threads per block: 64, 128, 256, 512 or 1024
  *   hist_per_lane   histories each lane carries at once: 1, 2 or 4
  *   unit_histories  histories per work unit (the scheduling grain), at most
- *                   2^18 (0 = automatic, at most 2^16: total / 4096, or
- *                   total / 10240 when that takes the chained kernel
- *                   below).  A unit's partial
- *                   tally is exact while fewer than 2^32 of its scores fall
+ *                   2^18 (0 = automatic, 64 .. 2^16, growing with the square
+ *                   root of the total).  A unit's partial tally is exact while fewer than 2^32 of its scores fall
  *                   in one bin (2^14 per history on average at 2^18
  *                   histories); the event schedule's slots that collect a
  *                   whole slice carry and have no such limit.

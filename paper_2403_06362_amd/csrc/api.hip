@@ -571,8 +571,6 @@ static uint64_t signature(const mcrng_lcg* lcg, const mcrng_problem* P, uint32_t
     return h;
 }
 
-// Work units of a chained run by default (total histories / kChainUnits).
-constexpr uint64_t kChainUnits = 10240;
 // The chained kernel holds two units per block, so the block waits whenever
 // a unit is handed out before the one before it has ended; on the long-chain
 // slab (heavy-tailed history lengths) that costs little from about 20
@@ -594,15 +592,13 @@ static int chain_mode() {
 }
 static bool chain_enabled() { return chain_mode() != 0; }
 
-// Whether a run of these problems with these options will take the chained
+// Whether a run of these problems with these options can take the chained
 // kernel (estimated from the problem's sizes: the merged cells are at most
 // regions + bins; the launch decides on the exact tables).
-static bool chain_planned(const mcrng_problem* P, uint32_t n, const mcrng_run_opts& o) {
+static bool chain_possible(const mcrng_problem* P, uint32_t n, const mcrng_run_opts& o) {
     if (n != 1 || o.schedule != MCRNG_SCHED_HISTORY || o.hist_per_lane != 1 || o.tally_copies != 1 ||
         !chain_enabled())
         return false;
-    const uint64_t unit = o.unit_histories ? o.unit_histories : P[0].n_histories / kChainUnits;
-    if (chain_mode() != 2 && unit < static_cast<uint64_t>(kChainMinPerLane) * o.block) return false;
     TransportParams a{};
     a.max_slice = std::max<uint32_t>(P[0].n_time_bins, 1) * P[0].n_space_bins;
     a.max_cells = P[0].n_regions + P[0].n_space_bins;
@@ -620,17 +616,57 @@ static bool chain_planned(const mcrng_problem* P, uint32_t n, const mcrng_run_op
     return transport_chain_fits(a, b, s, &fits) == hipSuccess && fits;
 }
 
-// Histories per work unit.  The per-unit kernel pays a pause at the end of
-// each unit, so its units are few (a few per resident block); the chained
-// kernel pauses only at the end of the launch, where small units even out
-// the blocks' finishing times.
-static uint32_t default_unit_histories(const mcrng_problem* P, uint32_t n, bool chained) {
+// Histories per work unit.  Large units pay at the end of the launch (blocks
+// idle while the last units run), small ones at every unit's end (a block's
+// lanes idle while the unit's longest histories run, then the slice goes out),
+// so the best size grows like the square root of the total.  Measured best,
+// 256-thread blocks: 1e5 histories 512 .. 1024, 1e6 2048, 3e6 4096, 1e7 4096 on
+// a thick (50 mean free paths, c = 0.99) and a thin slab alike (1e6 thick: 1.47 ms,
+// 1.94 at 512; 3e6 thin: 0.24, 0.37 at 1024); time-dependent tallies 2e7 8192,
+// 6e7 16384; 512 slabs of 1.35e8 histories 12288 (12.0 ms, 18.2 at 32768), 128
+// of 1.3e7 4096.  The chained kernel pays at the ends of launches only, where
+// units of 32 histories per lane even out the blocks; it wins from about
+// 1.5e7 histories on (2e7 thick: 7.5 ms, 7.8 per unit; 1e7: 5.1 against 4.7).
+static uint32_t default_unit_histories(const mcrng_problem* P, uint32_t n, const mcrng_run_opts& o) {
     uint64_t total = 0;
     for (uint32_t i = 0; i < n; ++i) total += P[i].n_histories;
-    uint64_t u = total / (chained ? kChainUnits : 4096);
-    u = std::max<uint64_t>(u, 512);
-    u = std::min<uint64_t>(u, 65536);
-    return static_cast<uint32_t>(u);
+    const double lanes = o.block / 256.0 * o.hist_per_lane;
+    const double root = std::sqrt(static_cast<double>(total));
+    double u;
+    if (n > 1)
+        u = std::min(1.25 * root, 16384.0) * lanes;
+    else if (chain_possible(P, n, o))
+        u = (2 * root >= 7680 ? std::min(2 * root, 8192.0) : std::min(2 * root, 4096.0)) * lanes;
+    else
+        u = std::min(2 * root, 16384.0) * lanes;
+    u = std::max(u, static_cast<double>(total / 16384));
+    return static_cast<uint32_t>(std::min<uint64_t>(std::max<uint64_t>((static_cast<uint64_t>(u) + 63) & ~63ull, 64), 65536));
+}
+
+// Units of the event schedule, and of a run whose units by the rule above
+// exceed the static scratch: at most about 4096 per problem set.
+static uint32_t coarse_unit_histories(const mcrng_problem* P, uint32_t n) {
+    uint64_t total = 0;
+    for (uint32_t i = 0; i < n; ++i) total += P[i].n_histories;
+    return static_cast<uint32_t>(std::min<uint64_t>(std::max<uint64_t>(total / 4096, 512), 65536));
+}
+
+// Relative time of one history of a problem, for the schedule's order only:
+// expected events and (three times the work of an event) collisions of a
+// homogeneous slab of the problem's mean scattering ratio and optical width,
+// with the collisions from the half-space albedo (two-stream approximation).
+static double history_cost(const mcrng_problem& P) {
+    double w = 0, sw = 0;
+    for (uint32_t r = 0; r < P.n_regions; ++r) {
+        const double d = P.sigma_t[r] * (P.region_edges[r + 1] - P.region_edges[r]);
+        w += d;
+        sw += P.scatter[r] * d;
+    }
+    const double c = w > 0 ? sw / w : 0.0;
+    const double q = std::sqrt(std::max(1.0 - c, 1e-12)), h = std::sqrt(3.0);
+    const double coll = std::min((1 + h) / ((1 + h * q) * q), 1 + w * (1 + w / 2));
+    const double cells = P.n_regions + P.n_space_bins;
+    return (coll + 1) * (1 + 0.5 * cells / std::max(w, 1e-3)) + 3 * coll;
 }
 
 // Builds every table of the problem set on the host and uploads them.
@@ -751,11 +787,14 @@ static int build_tables(mcrng_ctx* ctx, const LcgDev& L, const mcrng_problem* P,
     if (ctx->h_units.size() > 0xffffffffull) return fail(MCRNG_EINVAL, "too many work units");
     if (ctx->h_groups.size() > 65535)
         return fail(MCRNG_EINVAL, "more than 65535 (problem, batch) tally groups in one run");
-    // schedule: largest units first (stable), so short units fill the tail
+    // schedule: the units that take longest first (stable), so short units fill the tail
     ctx->h_order.resize(ctx->h_units.size());
     for (uint32_t i = 0; i < ctx->h_order.size(); ++i) ctx->h_order[i] = i;
+    std::vector<double> cost(n);
+    for (uint32_t p = 0; p < n; ++p) cost[p] = history_cost(P[p]);
     std::stable_sort(ctx->h_order.begin(), ctx->h_order.end(), [&](uint32_t x, uint32_t y) {
-        return ctx->h_units[x].count > ctx->h_units[y].count;
+        const WorkUnit &a = ctx->h_units[x], &b = ctx->h_units[y];
+        return cost[a.problem] * a.count > cost[b.problem] * b.count;
     });
     // FP32 flight tables, each rounded once from a double: per problem the
     // cell widths (n_cells, then a 0 to keep the edge offsets) and the
@@ -908,7 +947,9 @@ extern "C" int mcrng_run_histories(mcrng_ctx* ctx, const mcrng_lcg* lcg, const m
     HIP_TRY(hipSetDevice(ctx->device));
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint32_t unit_hist =
-        o.unit_histories ? o.unit_histories : default_unit_histories(problems, n_problems, chain_planned(problems, n_problems, o));
+        o.unit_histories                          ? o.unit_histories
+        : o.schedule == MCRNG_SCHED_EVENT ? coarse_unit_histories(problems, n_problems)
+                                          : default_unit_histories(problems, n_problems, o);
     o.unit_histories = unit_hist;
     const uint64_t sig = signature(lcg, problems, n_problems, unit_hist);
     int warn = MCRNG_OK;
@@ -1229,20 +1270,33 @@ extern "C" int mcrng_run_histories_noalloc(const mcrng_lcg* lcg, const mcrng_pro
     if ((rc = static_device(dev, &sd)) < 0) return rc;
     std::lock_guard<std::mutex> lk(sd->mu);
     mcrng_ctx* ctx = &sd->ctx;
-    sd->arena.reset();
-    DevBuf* bufs[] = {&ctx->problems, &ctx->edges64, &ctx->sig64, &ctx->scat64, &ctx->cbin, &ctx->edges32,
-                      &ctx->sig32, &ctx->tedges64, &ctx->tedges32, &ctx->units, &ctx->order, &ctx->partial,
-                      &ctx->unit_diag, &ctx->counter, &ctx->groups, &ctx->dx, &ctx->dt, &ctx->pu_begin,
-                      &ctx->rec_begin};
-    for (DevBuf* b : bufs) {
-        b->p = nullptr;
-        b->cap = 0;
-    }
+    auto reset = [&]() {
+        sd->arena.reset();
+        DevBuf* bufs[] = {&ctx->problems, &ctx->edges64, &ctx->sig64, &ctx->scat64, &ctx->cbin, &ctx->edges32,
+                          &ctx->sig32, &ctx->tedges64, &ctx->tedges32, &ctx->units, &ctx->order, &ctx->partial,
+                          &ctx->unit_diag, &ctx->counter, &ctx->groups, &ctx->dx, &ctx->dt, &ctx->pu_begin,
+                          &ctx->rec_begin};
+        for (DevBuf* b : bufs) {
+            b->p = nullptr;
+            b->cap = 0;
+        }
+    };
+    reset();
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (!o.unit_histories)
-        o.unit_histories = default_unit_histories(problems, n_problems, chain_planned(problems, n_problems, o));
+    const bool automatic = o.unit_histories == 0;
+    if (automatic) o.unit_histories = default_unit_histories(problems, n_problems, o);
     int warn = MCRNG_OK;
-    if ((rc = build_tables(ctx, L, problems, n_problems, o.unit_histories, st, &warn)) < 0) return rc;
+    rc = build_tables(ctx, L, problems, n_problems, o.unit_histories, st, &warn);
+    if (rc == MCRNG_EINVAL && automatic) {
+        // (nothing is enqueued before everything fits)
+        const uint32_t coarse = coarse_unit_histories(problems, n_problems);
+        if (coarse > o.unit_histories) {
+            o.unit_histories = coarse;
+            reset();
+            rc = build_tables(ctx, L, problems, n_problems, o.unit_histories, st, &warn);
+        }
+    }
+    if (rc < 0) return rc;
     if ((rc = enqueue_run(ctx, L, o, st)) < 0) return rc;
     if ((rc = enqueue_reduce(ctx, d_raw, d_flux, d_diag, st)) < 0) return rc;
     return warn;
@@ -1313,7 +1367,8 @@ extern "C" int mcrng_autotune(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_
     if ((rc = try_field(&mcrng_run_opts::tally_copies, {1, 2})) < 0) return rc;
     if (cur.schedule == MCRNG_SCHED_HISTORY)
         if ((rc = try_field(&mcrng_run_opts::coll_batch, {1, 16, 24, 32, 36, 40, 48})) < 0) return rc;
-    const uint32_t u0 = default_unit_histories(problems, n_problems, chain_planned(problems, n_problems, cur));
+    const uint32_t u0 = cur.schedule == MCRNG_SCHED_EVENT ? coarse_unit_histories(problems, n_problems)
+                                                               : default_unit_histories(problems, n_problems, cur);
     if ((rc = try_field(&mcrng_run_opts::unit_histories, {u0 / 4 > 256 ? u0 / 4 : 256, u0, u0 * 4})) < 0) return rc;
     if (cur.unit_histories == 0) cur.unit_histories = u0;
     cur.use_graph = b0.use_graph;
