@@ -950,27 +950,41 @@ __device__ __forceinline__ double u128_to_double(uint64_t lo, uint64_t hi) {
     return __builtin_ldexp(static_cast<double>(static_cast<uint64_t>(mant)), sh);
 }
 
-// Block = (group, tile of 32 bins); 8 unit lanes per bin.  A group's units
-// are consecutive with consecutive partial slots (2 x slice_bins words each),
-// so unit u's words for bin i sit at slot0 + (u - u0) 2 slice + 2 i.  Unit
-// lane l sums units u0 + l, u0 + l + 8, ...; the 8 partial sums are then
-// added in lane order (integers: any order gives the same bits).
-constexpr int kRedBins = 32, kRedLanes = 8;
+// One launch: blocks (tile, group) reduce a group's bins, blocks (0, n_groups +
+// p) problem p's diagnostics.
+// Bins: a tile of 8 bins, 32 unit lanes per bin.  A group's units are
+// consecutive with consecutive partial slots (2 x slice_bins words each), so
+// unit u's words for bin i sit at slot0 + (u - u0) 2 slice + 2 i.  Unit lane l
+// sums units u0 + l, u0 + l + 32, ..., several loads in flight; the partial sums
+// are then added in lane order (integers: any order gives the same bits).  The
+// kernel waits for HBM: with 32 bins per tile and 8 unit lanes a group of 1000
+// bins and 4096 units was 32 blocks of 512 dependent steps, 169 us.
+constexpr int kRedBins = 8, kRedLanes = 32, kRedAhead = 8;
 
-__global__ void __launch_bounds__(256) k_reduce_bins(ReduceParams P) {
+__device__ __forceinline__ void reduce_bins(const ReduceParams& P) {
     typedef unsigned __int128 u128;
     __shared__ uint64_t part[kRedLanes][kRedBins][2];
     const ReduceGroup G = P.groups[blockIdx.y];
     const uint32_t bl = threadIdx.x % kRedBins, ul = threadIdx.x / kRedBins;
     const uint32_t i = blockIdx.x * kRedBins + bl;
+    if (blockIdx.x * kRedBins >= G.slice_bins) return;
     u128 acc = 0;
     if (i < G.slice_bins && G.unit_end > G.unit_begin) {
-        const uint64_t slot0 = P.units[G.unit_begin].slot;
         const uint64_t stride = 2ull * G.slice_bins;
-        for (uint32_t u = ul; u < G.unit_end - G.unit_begin; u += kRedLanes) {
-            const uint64_t* s = P.partial + slot0 + u * stride + 2ull * i;
-            acc += static_cast<u128>(s[0]);
-            acc += static_cast<u128>(s[1]) << 32;
+        const uint64_t* s = P.partial + P.units[G.unit_begin].slot + 2ull * i;
+        const uint32_t n = G.unit_end - G.unit_begin;
+        uint32_t u = ul;
+        for (; u + (kRedAhead - 1) * kRedLanes < n; u += kRedAhead * kRedLanes) {
+            ulonglong2 v[kRedAhead];
+#pragma unroll
+            for (int k = 0; k < kRedAhead; ++k)
+                v[k] = *reinterpret_cast<const ulonglong2*>(s + (u + k * kRedLanes) * stride);
+#pragma unroll
+            for (int k = 0; k < kRedAhead; ++k) acc += static_cast<u128>(v[k].x) + (static_cast<u128>(v[k].y) << 32);
+        }
+        for (; u < n; u += kRedLanes) {
+            const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(s + u * stride);
+            acc += static_cast<u128>(v.x) + (static_cast<u128>(v.y) << 32);
         }
     }
     part[ul][bl][0] = static_cast<uint64_t>(acc);
@@ -978,7 +992,6 @@ __global__ void __launch_bounds__(256) k_reduce_bins(ReduceParams P) {
     __syncthreads();
     if (ul != 0 || i >= G.slice_bins) return;
     u128 tot = 0;
-#pragma unroll
     for (int l = 0; l < kRedLanes; ++l)
         tot += (static_cast<u128>(part[l][bl][1]) << 64) | part[l][bl][0];
     const uint64_t lo = static_cast<uint64_t>(tot), hi = static_cast<uint64_t>(tot >> 64);
@@ -993,16 +1006,15 @@ __global__ void __launch_bounds__(256) k_reduce_bins(ReduceParams P) {
     P.flux[o] = (d != 0.0) ? r / d : 0.0;
 }
 
-__global__ void __launch_bounds__(256) k_reduce_diag(ReduceParams P) {
-    const uint32_t pb = blockIdx.x;
-    __shared__ unsigned long long acc[kNDiag];
-    if (threadIdx.x < kNDiag) acc[threadIdx.x] = 0;
-    __syncthreads();
+// The words of a problem's units, each thread's units first, then across the
+// wave by exchanges, then across the waves in LDS.
+__device__ __forceinline__ void reduce_diag(const ReduceParams& P, uint32_t pb) {
+    __shared__ unsigned long long acc[4][kNDiag];
     const uint32_t u0 = P.pu_begin[pb], u1 = P.pu_begin[pb + 1];
     unsigned long long loc[kNDiag];
 #pragma unroll
     for (int k = 0; k < kNDiag; ++k) loc[k] = 0;
-    for (uint32_t u = u0 + threadIdx.x; u < u1; u += blockDim.x) {
+    for (uint32_t u = u0 + threadIdx.x; u < u1; u += 256) {
 #pragma unroll
         for (int k = 0; k < kNDiag; ++k) {
             const unsigned long long v = P.unit_diag[static_cast<size_t>(u) * kNDiag + k];
@@ -1013,26 +1025,49 @@ __global__ void __launch_bounds__(256) k_reduce_diag(ReduceParams P) {
         }
     }
 #pragma unroll
-    for (int k = 0; k < kNDiag; ++k) {
-        if (k == D_MAX_DRAWS)
-            atomicMax(&acc[k], loc[k]);
-        else
-            atomicAdd(&acc[k], loc[k]);
-    }
+    for (int m = 32; m != 0; m >>= 1)
+#pragma unroll
+        for (int k = 0; k < kNDiag; ++k) {
+            const unsigned long long v = __shfl_xor(loc[k], m);
+            loc[k] = k == D_MAX_DRAWS ? (v > loc[k] ? v : loc[k]) : loc[k] + v;
+        }
+    if ((threadIdx.x & 63u) == 0)
+#pragma unroll
+        for (int k = 0; k < kNDiag; ++k) acc[threadIdx.x >> 6][k] = loc[k];
     __syncthreads();
-    if (threadIdx.x < kNDiag) P.diag[static_cast<size_t>(pb) * kNDiag + threadIdx.x] = acc[threadIdx.x];
+    if (threadIdx.x < kNDiag) {
+        unsigned long long v = acc[0][threadIdx.x];
+        for (int w = 1; w < 4; ++w) {
+            const unsigned long long o = acc[w][threadIdx.x];
+            v = threadIdx.x == D_MAX_DRAWS ? (o > v ? o : v) : v + o;
+        }
+        P.diag[static_cast<size_t>(pb) * kNDiag + threadIdx.x] = v;
+    }
 }
 
+__global__ void __launch_bounds__(256) k_reduce(ReduceParams P) {
+    if (blockIdx.y < P.n_groups)
+        reduce_bins(P);
+    else if (blockIdx.x == 0)
+        reduce_diag(P, blockIdx.y - P.n_groups);
+}
+
+__global__ void __launch_bounds__(256) k_reduce_diag(ReduceParams P) { reduce_diag(P, blockIdx.x); }
+
 hipError_t launch_reduce(const ReduceParams& p, hipStream_t st) {
-    if (p.n_groups > 0) {
-        uint32_t bx = (p.max_slice + kRedBins - 1) / kRedBins;
-        if (bx < 1) bx = 1;
-        hipLaunchKernelGGL(k_reduce_bins, dim3(bx, p.n_groups), dim3(kRedBins * kRedLanes), 0, st, p);
-        hipError_t e = hipGetLastError();
+    uint32_t bx = (p.max_slice + kRedBins - 1) / kRedBins;
+    if (bx < 1) bx = 1;
+    const uint32_t nd = p.diag != nullptr ? p.n_problems : 0;
+    // (a grid's second extent is at most 65535)
+    const bool one = static_cast<uint64_t>(p.n_groups) + nd <= 65535;
+    const uint32_t rows = p.n_groups + (one ? nd : 0);
+    if (rows > 0) {
+        hipLaunchKernelGGL(k_reduce, dim3(bx, rows), dim3(256), 0, st, p);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (p.diag != nullptr && p.n_problems > 0) {
-        hipLaunchKernelGGL(k_reduce_diag, dim3(p.n_problems), dim3(256), 0, st, p);
+    if (!one) {
+        hipLaunchKernelGGL(k_reduce_diag, dim3(nd), dim3(256), 0, st, p);
         return hipGetLastError();
     }
     return hipSuccess;
