@@ -1,0 +1,216 @@
+"""GPU parity of the kernels' rarer paths against the CPU oracle: pools that
+spill and waves that hand over (bank schedule), stacks that leave LDS and time
+grids that are not uniform (both seedings), generators of every size, distances
+below the refined quotients' range, rows of uniforms that start inside lines,
+and automatic work units.  Integer tallies and bits throughout, so every
+comparison is exact."""
+import sys
+
+import numpy as np
+import pytest
+
+import workloads as W
+from helpers import diag_dict, raw_ints, u64_np
+
+pytestmark = pytest.mark.gpu
+LCG = W.Lcg()
+
+
+def say(*a):
+    print("[gpu]", *a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def M():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    import paper_2403_06362_amd as M
+    M.lib()
+    return M
+
+
+@pytest.fixture(scope="module")
+def ctx(M):
+    c = M.Context(0)
+    yield c
+    c.close()
+
+
+def slab(M, ctx, probs, lcg=LCG, **opts):
+    import torch
+    raw, flux, diag = M.transport(probs, lcg, ctx=ctx, opts=M.make_opts(**opts))
+    torch.cuda.synchronize()
+    return raw_ints(raw), flux.cpu().numpy(), diag_dict(diag, M.DIAG_NAMES)
+
+
+def pulse(M, ctx, prob, lcg=LCG, **opts):
+    import torch
+    counts, flux, diag = M.pulse(prob, lcg, ctx=ctx, opts=M.make_pulse_opts(**opts))
+    torch.cuda.synchronize()
+    return u64_np(counts).reshape(prob.n_batches, -1), dict(zip(M.PULSE_DIAG_NAMES, (int(v) for v in u64_np(diag))))
+
+
+GROWING = W.pulse(W.hash_seeding(), n_batches=3, per_batch=90).with_(time_edges=np.arange(31, dtype=np.float64))
+WIDE = W.pulse(W.hash_seeding(), n_batches=2, per_batch=50).with_(
+    nu=13.5, scatter=0.3, time_edges=np.array([0.0, 0.5, 1.0, 1.5]))
+
+
+@pytest.mark.parametrize("prob", [GROWING, WIDE], ids=["growing", "wide"])
+@pytest.mark.parametrize("private,budget,tail", [(1024, 0, 1), (0, 0, 32), (64, 1, 32), (0, 1, 1), (128, 500, 100000)])
+def test_pool_spills_and_hand_over(M, ctx, orc, monkeypatch, prob, private, budget, tail):
+    """Every place a full pool's particles go: the private stack, the output
+    bank, a hand-over of all a wave holds (with items not taken yet), after one
+    iteration or never."""
+    monkeypatch.setenv("MCRNG_PULSE_PRIVATE", str(private))
+    monkeypatch.setenv("MCRNG_PULSE_TAIL", str(tail))
+    if budget:
+        monkeypatch.setenv("MCRNG_PULSE_BUDGET", str(budget))
+    ref = orc.pulse(prob, LCG, threads=8)
+    say("pool", prob.nu, private, budget, tail)
+    c, d = pulse(M, ctx, prob, schedule=M.PULSE_BANK)
+    assert np.array_equal(c, ref.counts) and d == ref.diag
+
+
+@pytest.mark.parametrize("budget,tail", [(0, 1), (1, 32), (300, 3)])
+def test_pool_hand_over_with_population_control(M, ctx, orc, monkeypatch, budget, tail):
+    """Census arrivals past their budget end a launch too; copies and sources
+    not taken by then are taken by a later launch."""
+    import torch
+    monkeypatch.setenv("MCRNG_PULSE_TAIL", str(tail))
+    if budget:
+        monkeypatch.setenv("MCRNG_PULSE_BUDGET", str(budget))
+    p = W.pulse_pc(n_batches=40, per_batch=300, census_every=4)
+    ref = orc.pulse_pc(p, LCG, threads=8)
+    say("pool with population control", budget, tail)
+    counts, flux, diag, pop = M.pulse_pc(p, LCG, ctx=ctx)
+    torch.cuda.synchronize()
+    assert np.array_equal(u64_np(counts).reshape(p.n_batches, -1), ref.counts)
+    assert np.array_equal(u64_np(pop.contiguous()).reshape(ref.pop.shape), ref.pop)
+    assert dict(zip(M.PULSE_DIAG_NAMES, (int(v) for v in u64_np(diag)))) == ref.diag
+
+
+@pytest.mark.parametrize("kind", ["hash", "stride"])
+@pytest.mark.parametrize("edges", [np.array([0.0, 1.0]), np.array([0.5, 0.75, 7.0, 7.125, 12.0]),
+                                   np.linspace(2.0, 9.0, 600), np.array([0.0, 0.9, 2.1, 3.0, 4.2, 5.0]) * 3.0],
+                         ids=["one", "uneven", "many", "nearly-uniform"])
+def test_pulse_time_grids(M, ctx, orc, kind, edges):
+    """One bin, bins of very different widths, more bins than are staged in
+    LDS, edges off a uniform grid by up to a fifth of a bin; a first edge
+    after the pulse."""
+    sd = W.hash_seeding() if kind == "hash" else W.stride_seeding()
+    p = W.pulse(sd, n_batches=31, per_batch=70).with_(time_edges=edges)
+    ref = orc.pulse(p, LCG, threads=8)
+    say("time grid", kind, len(edges))
+    for block in (64, 256):
+        c, d = pulse(M, ctx, p, block=block)
+        assert np.array_equal(c, ref.counts) and d == ref.diag, block
+
+
+@pytest.mark.parametrize("nu", [0.7, 1.0, 1.6, 3.0])
+def test_stride_multiplicities(M, ctx, orc, nu):
+    """At most one particle, exactly one, one or two, always three emerging:
+    lines without siblings and stacks deeper than their LDS part."""
+    p = W.pulse(W.stride_seeding(), n_batches=9, per_batch=64).with_(
+        nu=nu, scatter=min(0.95, 1.1 / nu), time_edges=np.arange(16, dtype=np.float64))
+    ref = orc.pulse(p, LCG, threads=8)
+    say("stride multiplicity", nu)
+    c, d = pulse(M, ctx, p)
+    assert np.array_equal(c, ref.counts) and d == ref.diag
+
+
+@pytest.mark.parametrize("m", [53, 60, 64])
+def test_generator_sizes(M, ctx, orc, m):
+    """Top-aligned states of generators of 53, 60 and 64 bits: slab in both
+    precisions and seedings, pulse in both seedings, uniforms."""
+    import torch
+    lcg = W.Lcg(m=m)
+    for kind in ("hash", "stride"):
+        sd = W.hash_seeding() if kind == "hash" else W.stride_seeding()
+        p = W.homogeneous(10.0, 1.3, 0.9, 11, 3001, sd, n_batches=2)
+        for precision in (0, 1):
+            say("generator", m, kind, precision)
+            ref = orc.transport(p, lcg, float_mode=bool(precision), threads=8)
+            raw, _, diag = slab(M, ctx, [p], lcg, precision=precision)
+            assert raw == ref.raw and diag[0] == ref.diag
+        q = W.pulse(sd, n_batches=3, per_batch=100)
+        ref = orc.pulse(q, lcg, threads=8)
+        c, d = pulse(M, ctx, q, lcg)
+        assert np.array_equal(c, ref.counts) and d == ref.diag
+        u = torch.empty((5, 1003), dtype=torch.float64, device="cuda:0")
+        M.uniforms(lcg, sd, u)
+        torch.cuda.synchronize()
+        assert np.array_equal(u.cpu().numpy(), orc.uniforms(lcg, sd, 1003, 5))
+
+
+@pytest.mark.parametrize("c", [0.0, 2.0 ** -53, 0.5, 1.0 - 2.0 ** -53, 1.0])
+def test_absorption_bounds(M, ctx, orc, c):
+    """The absorption test as an integer bound, at its ends."""
+    p = W.homogeneous(3.0, 1.0, c, 7, 4001, W.hash_seeding())
+    ref = orc.transport(p, LCG, threads=8)
+    say("absorption", c)
+    raw, _, diag = slab(M, ctx, [p])
+    assert raw == ref.raw and diag[0] == ref.diag
+
+
+@pytest.mark.parametrize("precision,width", [(0, 1e-213), (1, 1e-10), (1, 3e-30)])
+@pytest.mark.parametrize("regions", [1, 2])
+def test_distances_below_the_quotients_range(M, ctx, orc, precision, width, regions):
+    """Cells so thin that flight distances lie below the range of the refined
+    quotients (2^-700, single 2^-36): plain divisions, the oracle's bits."""
+    p = W.homogeneous(1.0, 1.0, 0.9, 8, 2003, W.hash_seeding())
+    edges = np.linspace(0.0, width, 9)
+    re = edges[[0, 8]] if regions == 1 else edges[[0, 4, 8]]
+    p = p.with_(region_edges=re, sigma_t=np.full(regions, 1.5), scatter=np.full(regions, 0.9), bin_edges=edges)
+    ref = orc.transport(p, LCG, float_mode=bool(precision), threads=8)
+    say("thin cells", precision, width, regions)
+    raw, _, diag = slab(M, ctx, [p], precision=precision)
+    assert raw == ref.raw and diag[0] == ref.diag
+
+
+def test_automatic_units_of_sets(M, ctx, orc):
+    """Problems of very different sizes and costs in one set, one of them of no
+    histories, steady and time-dependent, one and several regions: scheduled by
+    expected time, reduced in one launch."""
+    probs = [W.homogeneous(20.0, 1.0, 0.99, 40, 30_011, W.hash_seeding(group_key=1), n_batches=3),
+             W.homogeneous(2.0, 0.5, 0.3, 9, 5, W.hash_seeding(group_key=2)),
+             W.homogeneous(5.0, 2.0, 0.5, 200, 0, W.stride_seeding()),
+             W.multi_region(n_histories=9_001, n_space_bins=8, n_time_bins=4)]
+    say("automatic units")
+    raw, _, diag = slab(M, ctx, probs)
+    off = 0
+    for p, d in zip(probs, diag):
+        ref = orc.transport(p, LCG, threads=8)
+        n = len(ref.raw)
+        assert raw[off:off + n] == ref.raw and d == ref.diag
+        off += n
+
+
+@pytest.mark.parametrize("mode", ["hash", "stride", "load"])
+@pytest.mark.parametrize("n,k", [(1_000_003, 3), (3_000_017, 17), (65_537, 800)])
+def test_uniforms_rows_inside_lines(M, orc, mode, n, k):
+    """Rows that start inside a 128-byte line, below and above the size where
+    they are stored by runs; final states."""
+    import torch
+    sd = W.hash_seeding(5) if mode == "hash" else W.stride_seeding(5)
+    st = torch.empty(n, dtype=torch.uint64, device="cuda:0")
+    u = torch.empty((k, n), dtype=torch.float64, device="cuda:0")
+    u.fill_(-1.0)
+    say("uniforms rows", mode, n, k)
+    if mode == "load":
+        M.init_streams(LCG, sd, n, st)
+    M.uniforms(LCG, None if mode == "load" else sd, u, st)
+    torch.cuda.synchronize()
+    assert float(u.min()) > 0.0 and float(u.max()) <= 1.0
+    idx = np.concatenate([np.arange(40), np.arange(1000, 1050), np.arange(n - 40, n),
+                          np.random.default_rng(3).integers(0, n, 150)])
+    got = u[:, torch.from_numpy(idx).to("cuda:0")].cpu().numpy()
+    end = u64_np(st)
+    for c, i in enumerate(idx):
+        one = W.hash_seeding(5 + int(i)) if mode == "hash" else W.stride_seeding(5 + int(i))
+        assert np.array_equal(got[:, c], orc.uniforms(LCG, one, 1, k)[:, 0]), i
+        x = orc.stream_start(LCG, one, 0)
+        if c < 5:
+            for _ in range(k):
+                x = (LCG.g * x + LCG.c) % (1 << 63)
+            assert int(end[i]) == x
