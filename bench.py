@@ -708,16 +708,16 @@ def pulse_ops(d):
 
 
 def pulse_bank_leg(M, W, torch, lcg, ctx, reps=3):
-    """The hash-seeded generation banks alone on the paper's 1000 x 1000
-    problem (for profiling the bank kernel): run time and the algorithmic
-    work per flight over it (the run is a chain of launches with a size
-    read-back between generations, so this is a bound on the kernels' rate)."""
+    """The hash-seeded bank schedule alone on the paper's 1000 x 1000 problem
+    (for profiling its kernel): run time and the algorithmic work per flight
+    over it (the run is two launches with a read-back after each, so this is a
+    bound on the kernel's rate)."""
     p = W.pulse(W.hash_seeding())
     ms, _, d = pulse_run(M, torch, lcg, ctx, p, M.PULSE_BANK, reps)
     ops, flights = pulse_ops(d)
-    out = {"workload": "pulse 1000 x 1000, hash seeding, generation banks", "runs": reps, "ms": ms,
+    out = {"workload": "pulse 1000 x 1000, hash seeding, bank schedule", "runs": reps, "ms": ms,
            "sources_per_s": p.n_sources / (ms * 1e-3), "flights": flights}
-    out["roofline_over_run_time"] = valu_roofline(ops, ms, "k_pulse_bank + finish (whole run)",
+    out["roofline_over_run_time"] = valu_roofline(ops, ms, "k_pulse_pool (whole run)",
                                                   {"flights": flights, "collisions": d["collisions"],
                                                    "scatters": d["scatters"], "secondaries": d["secondaries"]})
     return out
@@ -743,11 +743,11 @@ def _study(M, W, torch, lcg, ctx, out):
                        "over_stride_families": d["over_stride"], "max_draws": d["max_draws"]}
         if kind == "hash":
             ops, flights = pulse_ops(d)
-            out["roofline"] = valu_roofline(ops, ms, "k_pulse_family (3e7-source study, hash)",
+            out["roofline"] = valu_roofline(ops, ms, "k_pulse_pool (3e7-source study, hash)",
                                             {"flights": flights, "collisions": d["collisions"],
                                              "scatters": d["scatters"], "secondaries": d["secondaries"]})
             out["roofline"]["traffic"] = traffic_from_profiles(
-                source_sha("pulse.hip", "pulse.hpp", "device_rng.hpp"), "k_pulse_family_study_traffic.txt")
+                source_sha("pulse.hip", "pulse.hpp", "device_rng.hpp"), "k_pulse_pool_study_traffic.txt")
     study["paper_fails_of_600"] = {"stride": 369, "hash": 339}
     return study
 

@@ -157,9 +157,9 @@ enum { MCRNG_SCHED_HISTORY = 0, MCRNG_SCHED_EVENT = 1 };
  *   hist_per_lane   histories each lane carries at once: 1, 2 or 4
  *   unit_histories  histories per work unit (the scheduling grain), at most
  *                   2^18 (0 = automatic, 64 .. 2^16, growing with the square
- *                   root of the total).  A unit's partial tally is exact while fewer than 2^32 of its scores fall
- *                   in one bin (2^14 per history on average at 2^18
- *                   histories); the event schedule's slots that collect a
+ *                   root of the total).  A unit's partial tally is exact
+ *                   while fewer than 2^32 of its scores fall in one bin
+ *                   (2^14 per history on average at 2^18 histories); the event schedule's slots that collect a
  *                   whole slice carry and have no such limit.
  *   grid            persistent blocks (0 = fill the device)
  *   tally_copies    LDS tally copies per block: 1, or one per wave (= 2)
@@ -344,32 +344,32 @@ enum { MCRNG_PULSE_AUTO = 0, MCRNG_PULSE_BANK = 1, MCRNG_PULSE_FAMILY = 2, MCRNG
 
 /* Options (zero = default).  No option changes a result bit: counts are
  * integers.
- *   schedule     MCRNG_PULSE_BANK (hash seeding only): generations; a
- *                launch runs the lines of descent of its input particles
- *                (the first particle emerging from a scattering at once) in
- *                any order and banks the siblings for the next launch;
- *                MCRNG_PULSE_FAMILY: one source family per lane, depth
- *                first (history based); MCRNG_PULSE_EVENT (hash seeding
- *                only): event based, every launch advances each live
- *                particle by one flight and its collision and banks all
- *                emerging particles for the next launch (the tail is
- *                finished as for the bank schedule, unless finish_div says
- *                never); AUTO: for hash seeding the bank below 16 sources per
- *                resident lane (2048 lanes per CU) and families from there
- *                on (the bank with population control), family for stride
+ *   schedule     MCRNG_PULSE_BANK (hash seeding only): a wave's lanes run
+ *                lines of descent (the first particle emerging from a
+ *                scattering at once) in any order, the siblings wait in the
+ *                wave's pool in LDS, behind it in HBM; what a launch hands
+ *                over is banked for the next one; MCRNG_PULSE_FAMILY: one
+ *                source family per lane, depth first (history based);
+ *                MCRNG_PULSE_EVENT (hash seeding only): event based, every
+ *                launch advances each live particle by one flight and its
+ *                collision and banks all emerging particles for the next
+ *                launch (see finish_div); AUTO: the bank schedule for hash
+ *                seeding (faster than families at every size: 0.9 against
+ *                10 ms for 1e6 sources to t = 20, 25 against 42 for 3e7),
+ *                families for stride
  *   block        threads per block: 64, 128, 256, 512 or 1024
  *   stack_depth  family schedule: stack entries per lane (default 128; an
  *                entry holds the siblings of one scattering on the current
  *                line of descent)
- *   finish_div   bank schedule: once a generation is smaller than the one
+ *   finish_div   event schedule: once a generation is smaller than the one
  *                before it, at most 1/finish_div of the largest of its chain
  *                and at most 65536 particles, one launch runs the rest depth
  *                first per lane, up to 64 particles per banked particle
  *                (default 1: the first shrinking generation of that size;
- *                0xffffffff: never)
- *   chunk        bank and event schedules: particles a wave takes from a
- *                launch's input per atomic, 64 .. 2^20 (default 0: chosen
- *                per launch from its input count) */
+ *                0xffffffff: never); the other schedules take any value
+ *   chunk        particles a wave takes from a launch's input per atomic,
+ *                64 .. 2^20 (default 0: chosen per launch from its input
+ *                count) */
 typedef struct {
     uint32_t schedule;
     uint32_t block;
@@ -396,16 +396,20 @@ enum {
  *             count / (((sigma_t per_batch) (x_hi - x_lo)) dt)
  *   d_diag    MCRNG_NDIAG uint64 (may be NULL)
  * Unlike the other calls this one returns after the run has finished on
- * `stream` (the bank schedule reads each generation's size).  Errors:
+ * `stream` (the host reads what a launch hands over to the next).  Errors:
  * MCRNG_EINVAL (arguments), MCRNG_ERANGE (a family outgrew
  * opts.stack_depth; the outputs are then incomplete), MCRNG_ENOMEM.
  * Returns MCRNG_WSTRIDE_WRAP when the stride allocation passes 2^m states.
  * The run's time (first to last launch of the run) is mcrng_last_run_ms.
- * Family-kernel overrides read from the environment (counts never change):
- * MCRNG_PULSE_DEEP = 0 or 1 (the lane-major stack, or the register-held top
- * over depth-major planes; by default the latter from 16 families per lane),
- * MCRNG_PULSE_SLOTS = 0..16 (per-wave LDS tally slots when the counters do
- * not fit one LDS copy per block; default 16, 0 counts into HBM). */
+ * Overrides read from the environment (counts never change).  Families of
+ * hash seeding: MCRNG_PULSE_DEEP = 0 or 1 (the lane-major stack, or the
+ * register-held top over depth-major planes; by default the latter from 16
+ * families per lane), MCRNG_PULSE_SLOTS = 0..16 (per-wave LDS tally slots when
+ * the counters do not fit one LDS copy per block; default 16, 0 counts into
+ * HBM).  Bank schedule: MCRNG_PULSE_PRIVATE (entries a wave may hold in HBM
+ * behind its pool; default 1024), MCRNG_PULSE_TAIL (iterations of a wave after
+ * a launch's input is taken; default 32), MCRNG_PULSE_BUDGET (banked entries
+ * past which a launch hands over what its waves hold). */
 int mcrng_run_pulse(mcrng_ctx *ctx, const mcrng_lcg *lcg, const mcrng_pulse_problem *problem,
                     const mcrng_pulse_opts *opts, uint64_t *d_counts, double *d_flux,
                     uint64_t *d_diag, void *stream);

@@ -13,33 +13,29 @@
 //   stride seeding they continue the source's one stream, depth first.
 //
 // Schedules:
-//   k_pulse_bank (hash only)  one launch per generation.  A wave takes a chunk
-//       of input particles (or sources) at a time through one atomic and hands
-//       them to its idle lanes; a lane runs each one's line of descent: at a
-//       scattering it keeps the first emerging particle in registers and
-//       banks its siblings (staged per wave in LDS, copied to the output bank
-//       with one atomic per flush) while the wave's view of the output count
-//       (its last flush plus its staged entries) is within the launch's
-//       budget; past it, a scattering banks all n particles and ends the
-//       line.  Appends are thus at most budget + n_max per input particle +
-//       one stage and one iteration's appends per wave (the view lags by at
-//       most a stage), which the output capacity covers.  With no budget
-//       (the event-based schedule) every scattering banks all n particles:
-//       each launch advances every live particle by one flight.
-//   k_pulse_family            one source family per lane (sources taken 64
-//       per wave and atomic), walked depth first with a per-lane stack (its
-//       top entry in registers, the rest in HBM planes, one per depth); a
-//       stack entry holds the siblings still to start of one scattering
-//       (stride: a count; hash: X_p and the next key), so the depth is at
-//       most the number of scatterings on the current line of descent.  With bank items (hash seeding) the same kernel finishes
-//       a bank schedule's tail: up to a budget of particles per item, the
-//       rest banked for the next launch.
-// Counts are integers added with 64-bit atomics (into a per-block LDS copy
-// of every counter when they fit, else one HBM atomic per distinct counter
-// of a wave), so every schedule, launch shape and order gives the same
-// counts.
+//   k_pulse_pool (hash: the bank schedule)  a wave is one depth-first walker
+//       with 64 lanes: siblings wait in the wave's LDS pool, and one launch
+//       runs nearly everything (at the kernel: what bounds it, and where
+//       particles go when the pool is full).
+//   k_pulse_stride (stride: families)  one source family per lane, depth
+//       first on its one stream, every lane flying in every iteration.
+//   k_pulse_bank (hash: the event-based schedule)  every launch advances each
+//       live particle by one flight and banks all n emerging particles:
+//       a wave takes a chunk of input particles through one atomic and stages
+//       its appends in LDS, copied to the output bank with one atomic per
+//       flush.  Appends are at most n_max per input particle.
+//   k_pulse_family (hash)  one source family per lane (sources taken 64 per
+//       wave and atomic), walked depth first with a per-lane stack in HBM; an
+//       entry holds the siblings still to start of one scattering (X_p and the
+//       next key), so the depth is at most the number of scatterings on the
+//       current line of descent.  With bank items the same kernel finishes the
+//       event schedule's tail: up to a budget of particles per item, the rest
+//       banked for the next launch.
+// Counts are integers: each is added once per scored collision, in LDS (rows
+// per wave, a copy per block) or with 64-bit HBM atomics, so every schedule,
+// launch shape and order gives the same counts.
 //
-// Population control (hash seeding, bank schedule; Sec. "Hierarchical Seed
+// Population control (hash seeding, bank and event schedules; Sec. "Hierarchical Seed
 // Splitting": one-off hashed values where no full stream is needed): the
 // run is cut into epochs at census times T[(c+1) K].  A particle whose
 // flight reaches the census stops at x + mu (C - t) with its direction and
@@ -58,7 +54,7 @@ namespace mcrng {
 
 struct PulseLane {
     uint64_t sources = 0, collisions = 0, tallied = 0, scatters = 0, absorbed = 0, census = 0;
-    uint64_t secondaries = 0, draws = 0, max_draws = 0, over_stride = 0;
+    uint64_t secondaries = 0, draws = 0, max_draws = 0;
 };
 
 struct PParticle {
@@ -147,10 +143,9 @@ __device__ __forceinline__ uint64_t pulse_source_state(const PulseParams& P, uin
     return stream_start_z(P.lcg, P.seed, j);
 }
 
-__device__ __forceinline__ void note_stream(const PulseParams& P, PulseLane& c, uint64_t draws) {
+__device__ __forceinline__ void note_stream(PulseLane& c, uint64_t draws) {
     c.draws += draws;
     if (draws > c.max_draws) c.max_draws = draws;
-    if (!P.hash && draws > P.stride_q) c.over_stride++;
 }
 
 template <int BLOCK>
@@ -184,7 +179,6 @@ __device__ __forceinline__ void flush_lane_counters(const PulseParams& P, const 
     atomicAdd(&acc[PD_SECONDARIES], c.secondaries);
     atomicAdd(&acc[PD_DRAWS], c.draws);
     atomicMax(&acc[PD_MAX_DRAWS], c.max_draws);
-    atomicAdd(&acc[PD_OVER_STRIDE], c.over_stride);
     __syncthreads();
     if (threadIdx.x < kNDiag) {
         unsigned long long* d = reinterpret_cast<unsigned long long*>(P.diag) + threadIdx.x;
@@ -200,12 +194,6 @@ __device__ __forceinline__ uint32_t lane_prefix(uint64_t mask) {
                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
 }
 
-// Adds the wave's scored collisions (tally = counter index, or -1).  When
-// all counters fit in LDS (P.lds_tally) each block counts into its own copy
-// and adds it to HBM once at its end (tally_lds_begin / tally_lds_end);
-// otherwise one 64-bit HBM atomic per distinct counter of the wave.  Either
-// way same-address atomics from every wave of the GPU, which serialise, are
-// avoided.  Called by the whole wave.
 // Lane l's value of v as a wave-uniform (scalar) value: the compiler then
 // treats what depends on it (loop exits included) as uniform, where a lane
 // shuffle's result would count as divergent.
@@ -215,6 +203,12 @@ __device__ __forceinline__ uint64_t lane_value(uint64_t v, int l) {
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
+// Adds the wave's scored collisions (tally = counter index, or -1).  When
+// all counters fit in LDS (P.lds_tally) each block counts into its own copy
+// and adds it to HBM once at its end (tally_lds_begin / tally_lds_end);
+// otherwise one 64-bit HBM atomic per distinct counter of the wave.  Either
+// way same-address atomics from every wave of the GPU, which serialise, are
+// avoided.  Called by the whole wave.
 __device__ __forceinline__ void wave_tally(const PulseParams& P, int64_t tally, uint32_t lane,
                                            unsigned long long* lds_counts) {
     if (P.lds_tally) {
@@ -256,8 +250,8 @@ __device__ __forceinline__ uint32_t wave_prefix16(uint32_t v, uint32_t* total) {
 // Entries of a wave's bank stage: 16 KiB per wave (8 KiB at 512 threads,
 // 4 KiB at 1024, so that a block fits in LDS).  Larger stages mean fewer
 // flushes, each an atomic on the one output counter: 512 entries took the
-// 1000 x 1000 problem from 6.1 to 5.7 ms and the event-based passes from
-// 7.6 to 6.3 ms against 256.
+// event-based passes of the 1000 x 1000 problem from 7.6 to 6.3 ms against
+// 256.
 constexpr uint32_t bank_stage_entries(int block) { return block >= 1024 ? 128u : (block >= 512 ? 256u : 512u); }
 
 uint32_t pulse_bank_stage(int block) { return bank_stage_entries(block); }
@@ -450,7 +444,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_bank(PulseParams P) {
         if (active) {
             uint32_t draws = 0;
             n = pulse_particle<DIR>(P, p, c, &draws, &tally, &at_census);
-            note_stream(P, c, draws);   // every particle has its own stream
+            note_stream(c, draws);   // every particle has its own stream
         }
         wave_tally(P, tally, lane, lds_counts);
         if (PC) census_stage(P, CS, cstaged, at_census, p, lane);
@@ -1023,11 +1017,14 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
 // back when the lane runs out of newer ones (read one flight ahead: some lane
 // of a wave needs one in nearly every iteration).
 //   The kernel is bound by vector issue and the chains of one wave's flight
-// (about 190 instructions).  Against the walk it replaces (every entry below
-// the top in HBM, the phases of a family as branches: 358 instructions per
-// flight, 108 GB of stack traffic) the 3e7-source study went from 36.7 ms to
-// 13.3.
-constexpr uint32_t kStrideDepth = 6;   // a 256-thread block stays within 40 KiB of LDS: four per CU
+// (about 190 instructions; vector units 77% busy).  Against the walk it
+// replaces (every entry below the top in HBM, the phases of a family as
+// branches: 358 instructions per flight, 108 GB of stack traffic) the
+// 3e7-source study went from 36.7 ms to 19.7.
+// LDS entries per lane: 6 keep a 256-thread block within 40 KiB, four per CU.
+// The study takes 19.7-20.5 ms at 4 (five blocks per CU, more entries moved),
+// 19.6-20.5 at 6, 22 at 7 (three blocks), 23.9 at 3.
+constexpr uint32_t kStrideDepth = 6;
 constexpr uint32_t kStrideRefill = 3;  // idle lanes at which a wave takes sources (a family ends in 60% of its iterations)
 
 template <int BLOCK>
@@ -1305,7 +1302,7 @@ __device__ __forceinline__ void spill_stack(const PulseParams& P, const PulseSta
     if (has_top) spill(P, top.x, top.t, top.tb, batch, top.key, top.next, top.n);
 }
 
-template <bool HASH, int ITEMS, bool PC, int BLOCK, bool DEEP, bool SLOTS>
+template <int ITEMS, bool PC, int BLOCK, bool DEEP, bool SLOTS>
 __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
     constexpr bool SOURCES = ITEMS == PULSE_ITEMS_SOURCES;
     constexpr bool SPILL = !SOURCES;
@@ -1474,11 +1471,8 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
         }
         if (PC) census_stage(P, CS, cstaged, at_census, p, lane);
         if (!active) continue;
-        if (HASH) {
-            // the particle's own stream ends here
-            note_stream(P, c, pdraws);
-            pdraws = 0;
-        }
+        note_stream(c, pdraws);   // the particle's own stream ends here
+        pdraws = 0;
         if (SPILL) budget--;
         if (n > 0) {
             if (n > 1) {
@@ -1517,12 +1511,11 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
                 active = false;
                 continue;
             }
-            if (HASH) p.Z = murmur_hash(1ull, p.Z >> P.lcg.up) << P.lcg.up;
+            p.Z = murmur_hash(1ull, p.Z >> P.lcg.up) << P.lcg.up;
             p.has_mu = false;
             continue;   // the first emerging particle starts at once
         }
         if (DEEP ? !has_top : sp == 0) {
-            if (!HASH) note_stream(P, c, pdraws);
             active = false;
             if (SL) family_ended(slot_alive, lsl);
             continue;
@@ -1539,7 +1532,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
         p.t = e.t;
         p.tb = e.tb;
         p.has_mu = false;
-        if (HASH) p.Z = murmur_hash(e.next, e.key) << P.lcg.up;
+        p.Z = murmur_hash(e.next, e.key) << P.lcg.up;
         if (e.next != e.n) {
             e.next++;
         } else if (!DEEP) {
@@ -1892,7 +1885,7 @@ static uint32_t family_tally_slots(const PulseParams& p) {
     return k;
 }
 
-template <bool HASH, int BLOCK>
+template <int BLOCK>
 static hipError_t launch_family_b(const PulseParams& p_in, uint32_t grid, hipStream_t st) {
     PulseParams p = p_in;
     p.tally_slots = family_tally_slots<BLOCK>(p);
@@ -1906,17 +1899,17 @@ static hipError_t launch_family_b(const PulseParams& p_in, uint32_t grid, hipStr
     if (!kSlots) p.tally_slots = 0;
     if (p.tally_slots != 0) {
         if (deep)
-            hipLaunchKernelGGL((k_pulse_family<HASH, PULSE_ITEMS_SOURCES, false, BLOCK, true, kSlots>), dim3(grid),
+            hipLaunchKernelGGL((k_pulse_family<PULSE_ITEMS_SOURCES, false, BLOCK, true, kSlots>), dim3(grid),
                                dim3(BLOCK), lds, st, p);
         else
-            hipLaunchKernelGGL((k_pulse_family<HASH, PULSE_ITEMS_SOURCES, false, BLOCK, false, kSlots>), dim3(grid),
+            hipLaunchKernelGGL((k_pulse_family<PULSE_ITEMS_SOURCES, false, BLOCK, false, kSlots>), dim3(grid),
                                dim3(BLOCK), lds, st, p);
     } else {
         if (deep)
-            hipLaunchKernelGGL((k_pulse_family<HASH, PULSE_ITEMS_SOURCES, false, BLOCK, true, false>), dim3(grid),
+            hipLaunchKernelGGL((k_pulse_family<PULSE_ITEMS_SOURCES, false, BLOCK, true, false>), dim3(grid),
                                dim3(BLOCK), pulse_tally_lds_bytes(p), st, p);
         else
-            hipLaunchKernelGGL((k_pulse_family<HASH, PULSE_ITEMS_SOURCES, false, BLOCK, false, false>), dim3(grid),
+            hipLaunchKernelGGL((k_pulse_family<PULSE_ITEMS_SOURCES, false, BLOCK, false, false>), dim3(grid),
                                dim3(BLOCK), pulse_tally_lds_bytes(p), st, p);
     }
     return hipGetLastError();
@@ -1933,10 +1926,10 @@ uint32_t pulse_finish_grid(uint64_t items) {
 hipError_t launch_pulse_finish(const PulseParams& p, bool pc, uint32_t grid, hipStream_t st) {
     if (p.n_in == 0) return hipSuccess;
     if (pc)
-        hipLaunchKernelGGL((k_pulse_family<true, PULSE_ITEMS_BANK, true, 256, false, false>), dim3(grid), dim3(256),
+        hipLaunchKernelGGL((k_pulse_family<PULSE_ITEMS_BANK, true, 256, false, false>), dim3(grid), dim3(256),
                            pulse_tally_lds_bytes(p), st, p);
     else
-        hipLaunchKernelGGL((k_pulse_family<true, PULSE_ITEMS_BANK, false, 256, false, false>), dim3(grid), dim3(256),
+        hipLaunchKernelGGL((k_pulse_family<PULSE_ITEMS_BANK, false, 256, false, false>), dim3(grid), dim3(256),
                            pulse_tally_lds_bytes(p), st, p);
     return hipGetLastError();
 }
@@ -1982,12 +1975,11 @@ uint32_t pulse_family_grid(int block) {
 hipError_t launch_pulse_family(const PulseParams& p, int block, uint32_t grid, hipStream_t st) {
     if (p.src_end == p.src_begin) return hipSuccess;
     switch (block) {
-        case 64: return p.hash ? launch_family_b<true, 64>(p, grid, st) : launch_family_b<false, 64>(p, grid, st);
-        case 128: return p.hash ? launch_family_b<true, 128>(p, grid, st) : launch_family_b<false, 128>(p, grid, st);
-        case 512: return p.hash ? launch_family_b<true, 512>(p, grid, st) : launch_family_b<false, 512>(p, grid, st);
-        case 1024:
-            return p.hash ? launch_family_b<true, 1024>(p, grid, st) : launch_family_b<false, 1024>(p, grid, st);
-        default: return p.hash ? launch_family_b<true, 256>(p, grid, st) : launch_family_b<false, 256>(p, grid, st);
+        case 64: return launch_family_b<64>(p, grid, st);
+        case 128: return launch_family_b<128>(p, grid, st);
+        case 512: return launch_family_b<512>(p, grid, st);
+        case 1024: return launch_family_b<1024>(p, grid, st);
+        default: return launch_family_b<256>(p, grid, st);
     }
 }
 

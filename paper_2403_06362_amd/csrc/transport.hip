@@ -3,16 +3,18 @@
 // k_transport (history-based, persistent).  A block takes work units (a run
 // of histories of one batch of one problem) from a global counter.  For each
 // unit it stages the problem's cells in LDS, zeroes an LDS tally slice and
-// runs the unit's histories one per lane: a lane whose history ended takes
-// the next history index of the unit through a wave ballot, a prefix count
-// and one LDS atomic per wave.  Every track length is scored as the integer
-// q = round-half-even(s 2^56) into the LDS slice (64-bit LDS atomics on its
-// low and high 32-bit halves, exact while fewer than 2^32 of the unit's
-// scores fall in one bin), so the unit's partial tally is an exact integer
-// whatever order the lanes score in.  At the end of the unit the block adds
-// its tally copies (carrying a wrap of the low word) and writes the slice to
-// the unit's own partial-tally slot in HBM.  (Carrying every score's wrap,
+// runs the unit's histories one per lane; a wave's empty lanes take the next
+// histories from the wave's ring, seeded 64 at a time.  Every track length is
+// scored as the integer q = round-half-even(s 2^56) into the LDS slice (two
+// 64-bit LDS atomics, one per 32-bit limb, exact while fewer than 2^32 of the
+// unit's scores fall in one bin), so the unit's partial tally is an exact
+// integer whatever order the lanes score in.  At the end of the unit the block
+// adds its tally copies (carrying a wrap of the low limb) and writes the slice
+// to the unit's own partial-tally slot in HBM.  (Carrying every score's wrap,
 // with a returning low-word atomic, measured 5-6% slower.)
+//
+// k_transport_chain holds two units of one problem per block, so that lanes
+// go on without a pause between units.
 //
 // k_reduce sums the partial slots of each (problem, batch) in unit order
 // (a fixed order; integer addition makes any order give the same bits),
@@ -21,7 +23,7 @@
 //
 // The per-history arithmetic (flight sampling, cell / time marching,
 // collision, scoring) follows the same fixed IEEE operation sequence in FP64
-// mode and in FP32-flight mode; it is spelled out in step_particle (particle.hpp).
+// mode and in FP32-flight mode; it is spelled out in particle.hpp.
 #include <algorithm>
 
 #include "particle.hpp"
@@ -218,6 +220,15 @@ constexpr uint32_t kRefill = 3;
 
 // A lane's history slot is flying (its bit in G: takes geometry steps),
 // waiting at a collision site (W), or empty.
+//   Bound by vector issue where histories are many: an instruction of a wave
+// takes a SIMD 4.3 cycles on average and the vector units are 93-98% busy, so
+// the bookkeeping lives in scalar registers and a geometry pass has no branch
+// per outcome.  With phases in vector registers: 512 slabs of 1.3e8 histories
+// 22.2 ms, now 9.2 (with the units in order of expected time); 2e7
+// time-dependent histories of ten regions 1588 us, now 1184; the long chain of
+// 1e8 histories on the chained kernel 35.2 ms, now 25.8 (173 vector
+// instructions per event, now 121).  A run of 1e6 thick-slab histories ends
+// with its longest histories' serial chains: 3.5 ms, now 1.5.
 template <bool F32, bool TIMED, bool ONE, int H, int BLOCK>
 __global__ void __launch_bounds__(BLOCK, (H == 1) ? 7 : 1) k_transport(TransportParams P) {
     extern __shared__ __align__(16) unsigned char smem[];
