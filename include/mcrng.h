@@ -355,7 +355,7 @@ enum { MCRNG_PULSE_AUTO = 0, MCRNG_PULSE_BANK = 1, MCRNG_PULSE_FAMILY = 2, MCRNG
  *                collision and banks all emerging particles for the next
  *                launch (see finish_div); AUTO: the bank schedule for hash
  *                seeding (faster than families at every size: 0.9 against
- *                10 ms for 1e6 sources to t = 20, 25 against 42 for 3e7),
+ *                10 ms for 1e6 sources to t = 20, 15 against 42 for 3e7),
  *                families for stride
  *   block        threads per block: 64, 128, 256, 512 or 1024
  *   stack_depth  family schedule: stack entries per lane (default 128; an

@@ -395,7 +395,7 @@ struct mcrng_ctx {
     DevBuf partial, unit_diag, counter;
     DevBuf bank_a, bank_b, records;   // event schedule
     DevBuf pulse_tedges, pulse_misc, pulse_diag, pulse_bank[2], pulse_stack;   // pulse problem
-    DevBuf pulse_left;                                                        // unused item ranges
+    DevBuf pulse_left, pulse_ranges;                                          // unused item ranges, and those a launch takes
     DevBuf pulse_census, pulse_copies, pulse_pop;                             // population control
     std::vector<double> h_pulse_tedges;
     uint64_t* h_pinned = nullptr;   // pinned host words for per-generation readbacks
@@ -493,7 +493,7 @@ extern "C" int mcrng_ctx_destroy(mcrng_ctx* ctx) {
     DevBuf* bufs[] = {&ctx->tables, &ctx->partial, &ctx->unit_diag, &ctx->counter,
                       &ctx->bank_a, &ctx->bank_b, &ctx->records, &ctx->pulse_tedges,
                       &ctx->pulse_misc, &ctx->pulse_diag, &ctx->pulse_bank[0], &ctx->pulse_bank[1],
-                      &ctx->pulse_stack, &ctx->pulse_left, &ctx->pulse_census, &ctx->pulse_copies, &ctx->pulse_pop};
+                      &ctx->pulse_stack, &ctx->pulse_left, &ctx->pulse_ranges, &ctx->pulse_census, &ctx->pulse_copies, &ctx->pulse_pop};
     for (DevBuf* b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (ctx->h_pinned) (void)hipHostFree(ctx->h_pinned);
@@ -1659,10 +1659,13 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     // wave its share.  Many: half of them so, the rest an eighth of a share at
     // a time, so that the waves end together (1000 x 1000 sources: 866 us; a
     // sixteenth 878, a thirty-second 962; three quarters without an atomic 926).
+    // (waves = 0: nothing in advance.)
     auto split_items = [&](uint32_t grid, uint32_t chunk, uint32_t waves) {
         const uint64_t n = pp.item_end - pp.item_begin;
-        const uint64_t share = (n + waves - 1) / waves;
-        pp.first_chunk = static_cast<uint32_t>(share <= 32 && !chunk ? share : std::min<uint64_t>(n / (2 * waves), 1u << 20));
+        const uint64_t share = waves ? (n + waves - 1) / waves : 0;
+        pp.first_chunk = waves == 0 ? 0u
+                                    : static_cast<uint32_t>(share <= 32 && !chunk ? share
+                                                                                  : std::min<uint64_t>(n / (2 * waves), 1u << 20));
         pp.chunk = chunk ? chunk : static_cast<uint32_t>(std::min<uint64_t>(256, std::max<uint64_t>(1, share / 8)));
         const uint64_t dynamic = std::min<uint64_t>(pp.item_begin + static_cast<uint64_t>(pp.first_chunk) * waves, pp.item_end);
         pp.item_parts = grid >= kPulseItemParts ? kPulseItemParts : 1;
@@ -1674,8 +1677,9 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     // rise to, except what its waves hand over to the output bank: entries
     // beyond a wave's LDS pool and private stack, and what a wave still holds
     // some iterations after the items have been taken.  The bank is the next
-    // launch's input, until none is left; then come the item ranges a wave
-    // took but handed back.  Capacities: a wave that has seen out_budget
+    // launch's input, until none is left; then come the items that waves took
+    // but handed back or that no wave took, all in one launch, cut into pieces
+    // (an eighth of a wave's share).  Capacities: a wave that has seen out_budget
     // entries in the output bank (cen_budget census arrivals) hands over what
     // it holds and ends, so it appends at most its slack after that; items
     // not taken then (of a bank) are copied behind the output.
@@ -1683,27 +1687,44 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
         std::vector<uint64_t> part(kPulseCensusParts, 0);   // arrivals per census part
         const int block = static_cast<int>(o.block);
         std::vector<std::pair<uint64_t, uint64_t>> ranges;
+        std::vector<uint64_t> pieces;   // of the launch's ranges, if more than one
         if (end > begin) ranges.emplace_back(begin, end);
         int cur = 0, nxt = 1;   // banks: cur is the launch's input (kind BANK), nxt its output
         uint64_t in_cap = 0, n_bank = 0;
         while (n_bank > 0 || !ranges.empty()) {
             const int k = n_bank > 0 ? static_cast<int>(PULSE_ITEMS_BANK) : kind;
+            uint64_t n = n_bank;
             if (n_bank > 0) {
-                pp.item_begin = 0;
-                pp.item_end = n_bank;
                 pp.in = carve_pulse_bank(ctx->pulse_bank[cur].p, in_cap);
             } else {
-                pp.item_begin = ranges.back().first;
-                pp.item_end = ranges.back().second;
-                ranges.pop_back();
+                for (const auto& g : ranges) n += g.second - g.first;
             }
-            const uint64_t n = pp.item_end - pp.item_begin;
             const uint32_t grid = pulse_pool_grid(pp, k, pcen, block, n);
             const uint64_t waves = static_cast<uint64_t>(grid) * o.block / 64;
-            split_items(grid, o.chunk, static_cast<uint32_t>(waves));
+            int r;
+            pp.ranges = nullptr;
+            pieces.clear();
+            if (n_bank > 0 || ranges.size() == 1) {
+                pp.item_begin = n_bank > 0 ? 0 : ranges[0].first;
+                pp.item_end = pp.item_begin + n;
+                split_items(grid, o.chunk, static_cast<uint32_t>(waves));
+            } else {
+                const uint64_t per = std::max<uint64_t>(1, n / (8 * waves));
+                for (const auto& g : ranges)
+                    for (uint64_t i = g.first; i < g.second; i += std::min(per, g.second - i)) {
+                        pieces.push_back(i);
+                        pieces.push_back(i + std::min(per, g.second - i));
+                    }
+                if ((r = ensure(ctx->pulse_ranges, pieces.size() * 8, st)) < 0) return r;
+                HIP_TRY(hipMemcpyAsync(ctx->pulse_ranges.p, pieces.data(), pieces.size() * 8, hipMemcpyHostToDevice, st));
+                pp.ranges = static_cast<const uint64_t*>(ctx->pulse_ranges.p);
+                pp.item_begin = 0;
+                pp.item_end = pieces.size() / 2;
+                split_items(grid, 1, 0);
+            }
+            if (n_bank == 0) ranges.clear();
             pp.out_budget = pool_budget ? pool_budget : std::min<uint64_t>(std::max<uint64_t>(2 * n, 1u << 16), 1u << 24);
             const uint64_t ocap = pp.out_budget + waves * pulse_pool_slack(pp, n_max) + (n_bank > 0 ? n : 0);
-            int r;
             if ((r = ensure(ctx->pulse_bank[nxt], ocap * 32, st)) < 0) return r;
             if ((r = ensure(ctx->pulse_stack, waves * pp.priv_cap * sizeof(PulsePoolEntry), st)) < 0) return r;
             if ((r = ensure(ctx->pulse_left, waves * 16, st)) < 0) return r;
@@ -1742,7 +1763,9 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
                     const uint64_t rest = e - taken;
                     if (rest == 0) continue;
                     if (k != PULSE_ITEMS_BANK) {
-                        ranges.emplace_back(taken, e);
+                        if (pieces.empty()) ranges.emplace_back(taken, e);
+                        for (uint64_t i = taken; i < e && !pieces.empty(); ++i)
+                            ranges.emplace_back(pieces[2 * i], pieces[2 * i + 1]);
                         continue;
                     }
                     const PulseBankView &a = pp.in, &b = pp.out;

@@ -779,6 +779,10 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
                     wnext = b < e ? b : e;
                     gend = b + R.chunk < e ? b + R.chunk : e;
                     exhausted = wnext == gend;
+                    if (ITEMS != PULSE_ITEMS_BANK && R.ranges != nullptr && !exhausted) {
+                        gend = uniform_value(R.ranges[2 * b + 1]);
+                        wnext = uniform_value(R.ranges[2 * b]);
+                    }
                     wend = SOURCES ? wnext : gend;
                 }
                 if (SOURCES && wnext != gend) {

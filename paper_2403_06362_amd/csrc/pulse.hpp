@@ -90,6 +90,7 @@ struct PulseParams {
     uint32_t item_parts;             // by the blocks b with b mod item_parts = s (a power of two)
     uint64_t* left;          // pool: ranges of taken but unused items (pairs), n_left of them
     uint64_t* n_left;
+    const uint64_t* ranges;  // pool: the items are ranges of sources or copies (pairs, none empty), taken one at a time (null: no)
     PulsePoolEntry* priv;    // pool: priv_cap entries per wave behind the LDS pool
     uint32_t priv_cap;
     uint32_t tail_iters;     // pool: iterations of a wave after the launch's items are taken

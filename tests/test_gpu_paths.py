@@ -72,6 +72,28 @@ def test_pool_spills_and_hand_over(M, ctx, orc, monkeypatch, prob, private, budg
     assert np.array_equal(c, ref.counts) and d == ref.diag
 
 
+@pytest.mark.parametrize("budget,private", [(1, 0), (3000, 64)])
+def test_pool_many_ranges_handed_back(M, ctx, orc, monkeypatch, budget, private):
+    """Every wave hands back the rest of its share at its first full pool: the
+    next launch takes thousands of ranges of sources, or of census copies."""
+    import torch
+    monkeypatch.setenv("MCRNG_PULSE_PRIVATE", str(private))
+    monkeypatch.setenv("MCRNG_PULSE_BUDGET", str(budget))
+    p = W.pulse(W.hash_seeding(), n_batches=211, per_batch=1003)
+    ref = orc.pulse(p, LCG, threads=8)
+    say("ranges of sources", budget, private)
+    c, d = pulse(M, ctx, p)
+    assert np.array_equal(c, ref.counts) and d == ref.diag
+    p = W.pulse_pc(n_batches=300, per_batch=1000, census_every=8)
+    ref = orc.pulse_pc(p, LCG, threads=8)
+    say("ranges of copies", budget, private)
+    counts, flux, diag, pop = M.pulse_pc(p, LCG, ctx=ctx)
+    torch.cuda.synchronize()
+    assert np.array_equal(u64_np(counts).reshape(p.n_batches, -1), ref.counts)
+    assert np.array_equal(u64_np(pop.contiguous()).reshape(ref.pop.shape), ref.pop)
+    assert dict(zip(M.PULSE_DIAG_NAMES, (int(v) for v in u64_np(diag)))) == ref.diag
+
+
 @pytest.mark.parametrize("budget,tail", [(0, 1), (1, 32), (300, 3)])
 def test_pool_hand_over_with_population_control(M, ctx, orc, monkeypatch, budget, tail):
     """Census arrivals past their budget end a launch too; copies and sources
