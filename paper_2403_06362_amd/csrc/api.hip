@@ -599,11 +599,13 @@ static uint64_t signature(const mcrng_lcg* lcg, const mcrng_problem* P, uint32_t
 }
 
 // The chained kernel holds two units per block, so the block waits whenever
-// a unit is handed out before the one before it has ended; on the long-chain
-// slab (heavy-tailed history lengths) that costs little from about 20
-// histories per lane per unit up (block 256: 34.5-35.2 ms at 5425-12207
-// histories per unit, 44 ms at 3051, 67 ms at 1525; the per-unit kernel
-// 38.1 ms).  Smaller units run on the per-unit kernel.
+// a unit is handed out before the one before it has ended, and pays at the end
+// of a launch.  On the long-chain slab (heavy-tailed history lengths) with 1e8
+// histories it wins at every unit size (block 256: 26.1 ms at 5425 histories
+// per unit, 25.5 at 16384, 30.2 at 3051, against 32.1, 25.6 and 39.2 on the
+// per-unit kernel), with fewer histories it loses (1e6: 1.90 against 1.63 ms at
+// 1024 per unit, 4e6: 3.34 against 2.98 at 2048; 3e7: 9.70 against 9.82 at
+// 8192).  Units of 20 histories per lane belong to large runs.
 constexpr uint32_t kChainMinPerLane = 20;
 
 // MCRNG_TRANSPORT_CHAIN: 0 keeps one-problem runs on the per-unit kernel;

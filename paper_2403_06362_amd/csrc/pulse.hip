@@ -499,11 +499,13 @@ struct __align__(16) FamilySource {
 // iteration, and no particle touches HBM while the pool fits (one iteration
 // adds about 7 entries net on the paper's problem, a particle lives about
 // `census time` iterations, so about 140 wait at a time).
-//   The kernel is bound by vector issue (about 190 instructions per flight at
-// full lanes).  Generations in HBM (the schedule's former kernel: one launch
-// and one read-back per generation, 32 B each way per banked particle, waves
-// waiting on the append counter) took 5.9 ms for the paper's 1000 x 1000
-// sources, 5.6 ms for 4096 sources to t = 60.
+//   The kernel is bound by vector issue where sources are many (about 190
+// instructions per flight at full lanes), by the chains of the longest
+// families where they are few.  Generations in HBM (the schedule's former
+// kernel: one launch and one read-back per generation, 32 B each way per
+// banked particle, waves waiting on the append counter) took 5.9 ms for the
+// paper's 1000 x 1000 sources, now 0.89; 5.6 ms for 4096 sources to t = 60, now
+// 0.70; 3e7 sources took 101 ms (41.5 as families), now 15.2.
 //   Where particles go when the LDS pool is full: its older half to the wave's
 // private HBM stack (priv_cap entries, read back when the pool is empty); when
 // that is full too, to the launch's output bank; and once the wave has seen
