@@ -21,7 +21,7 @@ Also reported, each timed separately after the headline loop:
                 precision, reported under "opts")
   pulse         the paper's test problem (pulse in an infinite multiplying
                 medium, secondaries seeded on demand), 1000 x 1000 sources:
-                hash-seeded generation banks, event-based passes and
+                hash-seeded bank schedule, event-based passes and
                 depth-first families against stride-seeded families, and
                 the paper's normality study at full size (30 x 1000 batches)
   pulse_population_control
@@ -344,7 +344,7 @@ def main():
     ap.add_argument("--only", default="",
                     help="comma-separated subset of the legs after the draw legs: long_chain, batched, "
                          "multi_region, pulse (schedules), study (the normality study), pulse_pc, "
-                         "pulse_bank (the hash-seeded generation banks on 1000 x 1000 alone)")
+                         "pulse_bank (the hash-seeded bank schedule on 1000 x 1000 alone)")
     ap.add_argument("--no-autotune", action="store_true",
                     help="long-chain legs with the default launch options (no autotuner runs)")
     ap.add_argument("--copy-probe", action="store_true",

@@ -1,7 +1,7 @@
 // Host side of the C ABI declared in include/mcrng.h: argument validation,
 // slab geometry (merged cells), stride skip-ahead tables, work units, device
 // buffers of a context, hipGraph capture, the launch-option autotuner and the
-// generation loop of the pulse problem.
+// launch loops of the pulse problem.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -398,7 +398,7 @@ struct mcrng_ctx {
     DevBuf pulse_left, pulse_ranges;                                          // unused item ranges, and those a launch takes
     DevBuf pulse_census, pulse_copies, pulse_pop;                             // population control
     std::vector<double> h_pulse_tedges;
-    uint64_t* h_pinned = nullptr;   // pinned host words for per-generation readbacks
+    uint64_t* h_pinned = nullptr;   // pinned host words for read-backs between launches
     std::vector<uint64_t> h_rec_begin;
     std::vector<uint32_t> h_group_first;   // per unit: the first unit of its (problem, batch) (host only)
 

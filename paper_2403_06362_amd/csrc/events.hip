@@ -2,7 +2,7 @@
 //
 // The live particles sit in a structure-of-arrays bank in HBM.  One launch of
 // k_event_step advances every live particle by exactly one event (the same
-// step_particle as the history-based kernel, so the per-particle operation
+// passes of particle.hpp as the history-based kernel, so the per-particle operation
 // sequence is identical); survivors are appended to the other bank through
 // one atomic per 1024-thread block, so each launch compacts the bank.  A
 // particle scores into the partial-tally slot of its score unit: its own work
