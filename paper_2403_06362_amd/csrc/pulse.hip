@@ -1023,20 +1023,21 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
 // back when the lane runs out of newer ones (read one flight ahead: some lane
 // of a wave needs one in nearly every iteration).
 //   The kernel is bound by vector issue and the chains of one wave's flight
-// (about 190 instructions; vector units 77% busy).  Against the walk it
+// (about 210 instructions; vector units 77% busy).  Against the walk it
 // replaces (every entry below the top in HBM, the phases of a family as
 // branches: 358 instructions per flight, 108 GB of stack traffic) the
-// 3e7-source study went from 36.7 ms to 19.7.
-// LDS entries per lane: 6 keep a 256-thread block within 40 KiB, four per CU.
-// The study takes 19.7-20.5 ms at 4 (five blocks per CU, more entries moved),
-// 19.6-20.5 at 6, 22 at 7 (three blocks), 23.9 at 3.
-constexpr uint32_t kStrideDepth = 6;
+// 3e7-source study went from 36.7 ms to 18.8.
+// LDS entries per lane: a power of two, so that an entry's place is its depth
+// masked (with 6 entries, a running place and stack addresses computed where
+// they are used the study took 19.7 ms at 237 instructions per flight, now 18.8
+// at 211; that form took 23.9 ms at 3 entries and 22 at 7, three blocks per CU).
+constexpr uint32_t kStrideDepth = 4;   // a power of two
 constexpr uint32_t kStrideRefill = 3;  // idle lanes at which a wave takes sources (a family ends in 60% of its iterations)
 
 template <int BLOCK>
 __global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
     constexpr uint32_t kWaves = BLOCK / 64;
-    __shared__ double s_x[kWaves][kStrideDepth][64], s_t[kWaves][kStrideDepth][64];
+    __shared__ double s_xt[kWaves][2][kStrideDepth][64];   // x and t planes
     __shared__ uint32_t s_m[kWaves][kStrideDepth][64];   // siblings left << 16 | time bin + 1
     __shared__ FamilySource s_src[kWaves][64];
     __shared__ uint32_t s_tag[kWaves][8];
@@ -1055,8 +1056,8 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
     if (threadIdx.x < kNDiag) s_acc[threadIdx.x] = 0;
     tally_lds_begin<BLOCK>(P, tally.counters);   // and the barrier for the above
 
-    double* const sx = &s_x[wid][0][lane];
-    double* const st = &s_t[wid][0][lane];
+    constexpr uint32_t kT = kStrideDepth * 64u;
+    double* const sx = &s_xt[wid][0][0][lane];   // entry d at [d mod kStrideDepth x 64], its t at + kT
     uint32_t* const sm = &s_m[wid][0][lane];
     FamilySource* const src = s_src[wid];
     const uint64_t lanes = static_cast<uint64_t>(gridDim.x) * BLOCK;
@@ -1080,7 +1081,12 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
     uint32_t batch = 0, depth = 0, low = 0;   // entries of the lane's stack, and those of them in HBM
     PulseStackEntry ahead{};            // entry ahead_of - 1, read ahead from HBM
     uint32_t ahead_of = 0;
-    uint32_t slot = 0;                  // (depth mod kStrideDepth) x 64: the next entry's place in LDS
+    // the next entry's place in HBM (entry `low`), and the first one's
+    PulseStackEntry* const hbm0 = P.stack + gl;
+    PulseStackEntry* hbm = hbm0;
+    uint32_t max_depth;                 // in a vector register: the loop's scalar ones are full
+    asm("v_mov_b32 %0, %1" : "=v"(max_depth) : "s"(P.stack_depth));
+    auto place = [](uint32_t d) { return (d & (kStrideDepth - 1u)) * 64u; };
     int32_t tb = -1;
 
     for (;;) {
@@ -1173,54 +1179,52 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
         }
         uint64_t lost = 0;   // lanes whose stack would grow past stack_depth: the family is abandoned
         if (push != 0) {
-            lost = push & wave_mask(depth == P.stack_depth);
+            lost = push & wave_mask(depth == max_depth);
             const uint64_t full = push & ~lost & wave_mask(depth - low == kStrideDepth);
+            const uint32_t o = place(depth);   // of the oldest entry in LDS too when they fill it
             if (full != 0 && in_mask(full)) {
-                const PulseParams& R = rare_params();
                 PulseStackEntry e;
-                e.x = sx[slot];
-                e.t = st[slot];
-                e.key = sm[slot];
-                R.stack[low * lanes + gl] = e;
+                e.x = sx[o];
+                e.t = sx[o + kT];
+                e.key = sm[o];
+                *hbm = e;
+                hbm += lanes;
                 low++;
             }
             if (in_mask(push & ~lost)) {
-                sx[slot] = x;
-                st[slot] = t;
-                sm[slot] = ((P.n_floor - 1u + sel_const<1, 0>(extra)) << 16) | static_cast<uint32_t>(tb + 1);
+                sx[o] = x;
+                sx[o + kT] = t;
+                sm[o] = ((P.n_floor - 1u + sel_const<1, 0>(extra)) << 16) | static_cast<uint32_t>(tb + 1);
                 depth++;
-                slot = slot == (kStrideDepth - 1u) * 64u ? 0u : slot + 64u;
             }
         }
         // lines that ended: the newest sibling, or the end of the family
         const uint64_t ended = A & ~on;
         const uint64_t back = ended & wave_mask(depth != 0);
         const uint64_t dry = back & wave_mask(depth == low);
+        const uint32_t o = place(depth - 1u);
         if (dry != 0 && in_mask(dry)) {
-            const uint32_t o = slot == 0u ? (kStrideDepth - 1u) * 64u : slot - 64u;
             low--;
+            hbm -= lanes;
             sx[o] = ahead.x;
-            st[o] = ahead.t;
+            sx[o + kT] = ahead.t;
             sm[o] = static_cast<uint32_t>(ahead.key);
             ahead_of = 0;
         }
         if (in_mask(back)) {
-            const uint32_t o = slot == 0u ? (kStrideDepth - 1u) * 64u : slot - 64u;
             const uint32_t m = sm[o];
             x = sx[o];
-            t = st[o];
+            t = sx[o + kT];
             tb = static_cast<int32_t>(m & 0xffffu) - 1;
             const uint64_t last = wave_mask(m < (2u << 16));
             sm[o] = m - (1u << 16);
             depth -= sel_const<1, 0>(last);
-            slot = sel(last, o, slot);
         }
         // a lane whose next sibling is in HBM reads it now: it flies at least
         // once before it needs it
         const uint64_t fetch = A & wave_mask(depth == low) & wave_mask(low != 0) & wave_mask(ahead_of != low);
         if (fetch != 0 && in_mask(fetch)) {
-            const PulseParams& R = rare_params();
-            ahead = R.stack[(low - 1u) * lanes + gl];
+            ahead = *(hbm - lanes);
             ahead_of = low;
         }
         const uint64_t end = (ended & ~back) | lost;
@@ -1230,7 +1234,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
                 if (draws > P.stride_q) over++;
                 depth = 0;
                 low = 0;
-                slot = 0;
+                hbm = hbm0;
                 ahead_of = 0;
             }
             A &= ~end;
