@@ -1023,14 +1023,14 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
 // back when the lane runs out of newer ones (read one flight ahead: some lane
 // of a wave needs one in nearly every iteration).
 //   The kernel is bound by vector issue and the chains of one wave's flight
-// (about 210 instructions; vector units 77% busy).  Against the walk it
+// (about 230 instructions; vector units 77% busy).  Against the walk it
 // replaces (every entry below the top in HBM, the phases of a family as
 // branches: 358 instructions per flight, 108 GB of stack traffic) the
 // 3e7-source study went from 36.7 ms to 18.8.
 // LDS entries per lane: a power of two, so that an entry's place is its depth
 // masked (with 6 entries, a running place and stack addresses computed where
 // they are used the study took 19.7 ms at 237 instructions per flight, now 18.8
-// at 211; that form took 23.9 ms at 3 entries and 22 at 7, three blocks per CU).
+// at 227; that form took 23.9 ms at 3 entries and 22 at 7, three blocks per CU).
 constexpr uint32_t kStrideDepth = 4;   // a power of two
 constexpr uint32_t kStrideRefill = 3;  // idle lanes at which a wave takes sources (a family ends in 60% of its iterations)
 
