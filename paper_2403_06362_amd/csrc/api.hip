@@ -394,7 +394,7 @@ struct mcrng_ctx {
     DevBuf units, order, groups, dx, dt, pu_begin, rec_begin;
     DevBuf partial, unit_diag, counter;
     DevBuf bank_a, bank_b, records;   // event schedule
-    DevBuf pulse_tedges, pulse_misc, pulse_diag, pulse_bank[2], pulse_stack;   // pulse problem
+    DevBuf pulse_tedges, pulse_misc, pulse_bank[2], pulse_stack;   // pulse problem
     DevBuf pulse_left, pulse_ranges;                                          // unused item ranges, and those a launch takes
     DevBuf pulse_census, pulse_copies, pulse_pop;                             // population control
     std::vector<double> h_pulse_tedges;
@@ -492,7 +492,7 @@ extern "C" int mcrng_ctx_destroy(mcrng_ctx* ctx) {
     clear_graphs(ctx);
     DevBuf* bufs[] = {&ctx->tables, &ctx->partial, &ctx->unit_diag, &ctx->counter,
                       &ctx->bank_a, &ctx->bank_b, &ctx->records, &ctx->pulse_tedges,
-                      &ctx->pulse_misc, &ctx->pulse_diag, &ctx->pulse_bank[0], &ctx->pulse_bank[1],
+                      &ctx->pulse_misc, &ctx->pulse_bank[0], &ctx->pulse_bank[1],
                       &ctx->pulse_stack, &ctx->pulse_left, &ctx->pulse_ranges, &ctx->pulse_census, &ctx->pulse_copies, &ctx->pulse_pop};
     for (DevBuf* b : bufs)
         if (b->p) (void)hipFree(b->p);
@@ -1561,8 +1561,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
 
     ctx->h_pulse_tedges.assign(P->time_edges, P->time_edges + P->n_time_bins + 1);
     if ((rc = upload(ctx->pulse_tedges, ctx->h_pulse_tedges, st)) < 0) return rc;
-    if ((rc = ensure(ctx->pulse_misc, kPulseMiscWords * sizeof(uint64_t), st)) < 0) return rc;
-    if ((rc = ensure(ctx->pulse_diag, kNDiag * sizeof(uint64_t), st)) < 0) return rc;
+    if ((rc = ensure(ctx->pulse_misc, (kPulseMiscWords + kNDiag) * sizeof(uint64_t), st)) < 0) return rc;
     pp.t_edges = static_cast<const double*>(ctx->pulse_tedges.p);
     pp.counts = d_counts;
     const uint64_t n_counters = static_cast<uint64_t>(P->n_batches) * P->n_time_bins;
@@ -1594,11 +1593,11 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             uniform = std::fabs((P->time_edges[i] - pp.t0) * pp.inv_dt - i) < 0.25;
         pp.grid_uniform = uniform ? 1u : 0u;
     }
-    pp.diag = static_cast<uint64_t*>(ctx->pulse_diag.p);
     // misc words: out_count, item_counter (reset per bank launch), family_counter, overflow,
     // (unused), census copies, unused item ranges; then the item parts' and
-    // the census parts' counters
+    // the census parts' counters; then the diagnostics
     uint64_t* misc = static_cast<uint64_t*>(ctx->pulse_misc.p);
+    pp.diag = misc + kPulseMiscWords;
     pp.out_count = misc;
     pp.item_counter = pooled ? misc + kPulseItemWords : misc + 1;
     pp.family_counter = misc + 2;
@@ -1619,8 +1618,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
         pp.pop = static_cast<uint64_t*>(ctx->pulse_pop.p);
         if (n_pop) HIP_TRY(launch_fill_u64(pp.pop, n_pop, 0ull, st));
     }
-    HIP_TRY(launch_fill_u64(misc, kPulseMiscWords, 0ull, st));
-    HIP_TRY(launch_fill_u64(pp.diag, kNDiag, 0ull, st));
+    HIP_TRY(launch_fill_u64(misc, kPulseMiscWords + kNDiag, 0ull, st));
     HIP_TRY(launch_fill_u64(d_counts, static_cast<uint64_t>(P->n_batches) * P->n_time_bins, 0ull, st));
     HIP_TRY(hipEventRecord(ctx->ev0, st));
     ctx->timing_valid = false;
@@ -1685,6 +1683,9 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     // entries in the output bank (cen_budget census arrivals) hands over what
     // it holds and ends, so it appends at most its slack after that; items
     // not taken then (of a bank) are copied behind the output.
+    // A launch's counters, all read back after it, are cleared by one fill
+    // before the next (each small launch costs 5 to 10 us).
+    uint32_t stale = 0;   // the words of misc to clear before a pool launch
     auto pool_run = [&](int kind, uint64_t begin, uint64_t end, bool pcen, uint64_t* cen_used) -> int {
         std::vector<uint64_t> part(kPulseCensusParts, 0);   // arrivals per census part
         const int block = static_cast<int>(o.block);
@@ -1741,10 +1742,8 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             }
             pp.out = carve_pulse_bank(ctx->pulse_bank[nxt].p, ocap);
             pp.out_cap = ocap;
-            // (n_left and the census counts stay)
-            HIP_TRY(launch_fill_u64(misc, 3, 0ull, st));
-            if (pp.item_part[0] != pp.item_end)
-                HIP_TRY(launch_fill_u64(pp.item_counter, kPulseItemParts * kPulseCounterStride, 0ull, st));
+            if (stale) HIP_TRY(launch_fill_u64(misc, stale, 0ull, st));
+            stale = kPulseCenWords;   // (an epoch's census counts go on)
             HIP_TRY(launch_pulse_pool(pp, k, pcen, block, grid, st));
             uint64_t w[kPulseMiscWords];
             if ((r = read_words(ctx, misc, pcen ? kPulseMiscWords : kPulseCenWords, w, st)) < 0) return r;
@@ -1783,7 +1782,6 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
                 HIP_TRY(hipMemcpyAsync(l.data(), pp.left, l.size() * 8, hipMemcpyDeviceToHost, st));
                 HIP_TRY(hipStreamSynchronize(st));
                 for (size_t i = 0; i < l.size(); i += 2) ranges.emplace_back(l[i], l[i + 1]);
-                HIP_TRY(launch_fill_u64(pp.n_left, 1, 0ull, st));
             }
             n_bank = n_out;
             std::swap(cur, nxt);
@@ -1887,7 +1885,10 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
                 const bool pcen = e < n_census;
                 pp.t_end = pcen ? P->time_edges[static_cast<size_t>(e + 1) * K] : P->time_edges[P->n_time_bins];
                 uint64_t cen_used = 0;
-                HIP_TRY(launch_fill_u64(pp.cen_count, kPulseCensusParts * kPulseCounterStride, 0ull, st));
+                if (event)
+                    HIP_TRY(launch_fill_u64(pp.cen_count, kPulseCensusParts * kPulseCounterStride, 0ull, st));
+                else if (stale)
+                    stale = kPulseMiscWords;
                 if (e == 0) {
                     rc = event ? generations(PULSE_ITEMS_SOURCES, pp.src_end - pp.src_begin, pcen, &cen_used)
                                : pool_run(PULSE_ITEMS_SOURCES, pp.src_begin, pp.src_end, pcen, &cen_used);
@@ -1908,7 +1909,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
                     return rc;
                 pp.copies_out = static_cast<PulseCensusEntry*>(ctx->pulse_copies.p);
                 pp.copy_cap = ccap;
-                HIP_TRY(launch_fill_u64(pp.copy_count, 1, 0ull, st));
+                if (event) HIP_TRY(launch_fill_u64(pp.copy_count, 1, 0ull, st));   // (else cleared before the pool launch)
                 HIP_TRY(launch_pulse_split(pp, cen_used, st));
                 uint64_t w[6];
                 if ((rc = read_words(ctx, misc, 6, w, st)) < 0) return rc;
