@@ -1569,14 +1569,8 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     const bool event = o.schedule == MCRNG_PULSE_EVENT;
     const bool pooled = o.schedule == MCRNG_PULSE_BANK || !hash;   // k_pulse_pool or k_pulse_stride
     pp.lds_tally = n_counters <= (pooled ? kPulsePoolLdsCounters : kPulseLdsCounters) ? 1u : 0u;
-    // the pool kernel's LDS: time edges up to 512 bins, and (counters not in
-    // LDS) 2 to 8 tally rows per wave within 1 KiB, up to 4 KiB for two
-    pp.edges_lds = P->n_time_bins <= 512 ? 1u : 0u;
-    pp.rows = 0;
-    if (!pp.lds_tally && P->n_time_bins <= 512) {
-        pp.rows = 8;
-        while (pp.rows > 2 && pp.rows * P->n_time_bins > 256) pp.rows /= 2;
-    }
+    pp.edges_lds = P->n_time_bins <= kPulseEdgeBins ? 1u : 0u;
+    if (pooled) HIP_TRY(pulse_fit_rows(&pp, pc != nullptr, static_cast<int>(o.block)));
     pp.priv_cap = 1024;
     pp.tail_iters = 32;
     uint64_t pool_budget = 0;
@@ -1702,7 +1696,8 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
             } else {
                 for (const auto& g : ranges) n += g.second - g.first;
             }
-            const uint32_t grid = pulse_pool_grid(pp, k, pcen, block, n);
+            uint32_t grid = 0;
+            HIP_TRY(pulse_pool_grid(pp, k, pcen, block, n, &grid));
             const uint64_t waves = static_cast<uint64_t>(grid) * o.block / 64;
             int r;
             pp.ranges = nullptr;
@@ -1930,7 +1925,8 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     } else if (!hash) {
         pp.item_begin = 0;
         pp.item_end = n_src;
-        const uint32_t grid = pulse_stride_grid(pp, static_cast<int>(o.block), n_src);
+        uint32_t grid = 0;
+        HIP_TRY(pulse_stride_grid(pp, static_cast<int>(o.block), n_src, &grid));
         const uint64_t lanes = static_cast<uint64_t>(grid) * o.block;
         split_items(grid, 0, grid * (o.block / 64));
         if ((rc = ensure(ctx->pulse_stack, lanes * o.stack_depth * sizeof(PulseStackEntry), st)) < 0) return rc;

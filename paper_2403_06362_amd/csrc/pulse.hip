@@ -1831,18 +1831,30 @@ static size_t pool_lds_bytes(const PulseParams& p, int block) {
     return b + static_cast<size_t>(block / 64) * p.rows * p.n_time_bins * 4u;
 }
 
-uint32_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int block, uint64_t items) {
+// Blocks of a pool or stride kernel that fit on one CU; above 64 KiB of dynamic
+// LDS the kernel is told so first, here and before its launch.
+static hipError_t tally_blocks_per_cu(const void* kern, const PulseParams& p, int block, int* per_cu) {
+    const size_t lds = pool_lds_bytes(p, block);
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+        if (e != hipSuccess) return e;
+    }
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, kern, block, lds);
+    if (e != hipSuccess) return e;
+    return *per_cu < 1 ? hipErrorInvalidConfiguration : hipSuccess;
+}
+
+hipError_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int block, uint64_t items, uint32_t* grid) {
     block = bank_block(block);
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pool_kernel(block, items_kind, pc), block,
-                                                     pool_lds_bytes(p, block)) != hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
+    const hipError_t e = tally_blocks_per_cu(pool_kernel(block, items_kind, pc), p, block, &per_cu);
+    if (e != hipSuccess) return e;
     const uint64_t waves = static_cast<uint64_t>(block / 64);
     uint64_t blocks = (items + waves - 1) / waves;   // an item per wave at least
     const uint64_t cap = static_cast<uint64_t>(device_cus()) * static_cast<uint64_t>(per_cu);
     if (blocks > cap) blocks = cap;
-    return static_cast<uint32_t>(blocks < 1 ? 1 : blocks);
+    *grid = static_cast<uint32_t>(blocks < 1 ? 1 : blocks);
+    return hipSuccess;
 }
 
 uint64_t pulse_pool_slack(const PulseParams& p, uint32_t n_max) {
@@ -1954,18 +1966,41 @@ static const void* stride_kernel(int block) {
     }
 }
 
-uint32_t pulse_stride_grid(const PulseParams& p, int block, uint64_t sources) {
+hipError_t pulse_stride_grid(const PulseParams& p, int block, uint64_t sources, uint32_t* grid) {
     block = bank_block(block);
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, stride_kernel(block), block, pool_lds_bytes(p, block)) !=
-            hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
+    const hipError_t e = tally_blocks_per_cu(stride_kernel(block), p, block, &per_cu);
+    if (e != hipSuccess) return e;
     // a family per wave at least: few families spread over the whole chip
     uint64_t blocks = (sources + block / 64 - 1) / (block / 64);
     const uint64_t cap = static_cast<uint64_t>(device_cus()) * static_cast<uint64_t>(per_cu);
     if (blocks > cap) blocks = cap;
-    return static_cast<uint32_t>(blocks < 1 ? 1 : blocks);
+    *grid = static_cast<uint32_t>(blocks < 1 ? 1 : blocks);
+    return hipSuccess;
+}
+
+// Tally rows per wave of the run's pool or stride launches when the counters
+// are not in LDS: 2 to 8 within 1 KiB, two up to 512 bins (4 KiB); fewer where
+// the block's rows would not fit beside the kernel's static LDS.  (1024 threads
+// with 512 bins: 64 KiB of rows beside 97 KiB in the stride kernel and 109 KiB
+// in the pool kernel with population control, of 160 KiB.)  The pool kernel
+// over sources has the most static LDS of those of a run.
+hipError_t pulse_fit_rows(PulseParams* p, bool pc, int block) {
+    p->rows = 0;
+    if (p->lds_tally || p->n_time_bins > kPulseEdgeBins) return hipSuccess;
+    block = bank_block(block);
+    int dev = 0, lds = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    if (e != hipSuccess) return e;
+    hipFuncAttributes a;
+    e = hipFuncGetAttributes(&a, p->hash ? pool_kernel(block, PULSE_ITEMS_SOURCES, pc) : stride_kernel(block));
+    if (e != hipSuccess) return e;
+    p->rows = 8;
+    while (p->rows > 2 && p->rows * p->n_time_bins > 256) p->rows /= 2;
+    while (p->rows > 0 && a.sharedSizeBytes + pool_lds_bytes(*p, block) > static_cast<size_t>(lds)) p->rows /= 2;
+    return hipSuccess;
 }
 
 hipError_t launch_pulse_stride(const PulseParams& p, int block, uint32_t grid, hipStream_t st) {

@@ -138,10 +138,14 @@ constexpr uint32_t kPulseTallySlots = 16;      // most tally slots per wave of t
 uint32_t pulse_bank_stage(int block);
 hipError_t launch_pulse_bank(const PulseParams& p, int items_kind, bool pc, int block, uint32_t grid,
                              hipStream_t st);
+constexpr uint32_t kPulseEdgeBins = 512;   // most time bins with edges (and tally rows) in LDS
+// Sets p->rows (hash: of the pool kernels, else of the stride kernel) for the
+// block size; p->edges_lds and p->lds_tally are set before.
+hipError_t pulse_fit_rows(PulseParams* p, bool pc, int block);
 // Pool launches (bank schedule).  The grid is chosen first (buffers are sized
 // for its waves); pulse_pool_slack: entries a wave may append to the output
 // bank after it has seen out_budget passed, and census arrivals likewise.
-uint32_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int block, uint64_t items);
+hipError_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int block, uint64_t items, uint32_t* grid);
 uint64_t pulse_pool_slack(const PulseParams& p, uint32_t n_max);
 constexpr uint64_t kPulsePoolCensusSlack = 256;
 hipError_t launch_pulse_pool(const PulseParams& p, int items_kind, bool pc, int block, uint32_t grid, hipStream_t st);
@@ -153,7 +157,7 @@ uint32_t pulse_family_grid(int block);
 // Families of stride seeding: the grid (p.stack holds stack_depth entries per
 // lane of it), then the launch over items [item_begin, item_end) taken as by
 // the pool.
-uint32_t pulse_stride_grid(const PulseParams& p, int block, uint64_t sources);
+hipError_t pulse_stride_grid(const PulseParams& p, int block, uint64_t sources, uint32_t* grid);
 hipError_t launch_pulse_stride(const PulseParams& p, int block, uint32_t grid, hipStream_t st);
 // Finish launch (hash seeding): the generation bank p.in (p.n_in particles)
 // run depth first per lane with p.stack (p.stack_depth entries per lane),

@@ -236,3 +236,29 @@ def test_uniforms_rows_inside_lines(M, orc, mode, n, k):
             for _ in range(k):
                 x = (LCG.g * x + LCG.c) % (1 << 63)
             assert int(end[i]) == x
+
+
+@pytest.mark.parametrize("block", [256, 1024])
+@pytest.mark.parametrize("bins", [50, 200, 400, 512])
+def test_pulse_tally_rows(M, ctx, orc, bins, block):
+    """Counters that are not in LDS, in 4 and 2 tally rows per wave, and in as
+    many as the largest block has LDS for: hash and stride seeding, population
+    control."""
+    import torch
+    edges = np.linspace(0.0, 12.0, bins + 1)
+    n_batches = 1024 // bins + 2
+    for kind in ("hash", "stride"):
+        sd = W.hash_seeding() if kind == "hash" else W.stride_seeding()
+        p = W.pulse(sd, n_batches=n_batches, per_batch=45).with_(time_edges=edges)
+        ref = orc.pulse(p, LCG, threads=8)
+        say("tally rows", kind, bins, block)
+        c, d = pulse(M, ctx, p, block=block)
+        assert np.array_equal(c, ref.counts) and d == ref.diag
+    p = W.pulse_pc(n_batches=n_batches, per_batch=45, census_every=bins // 3).with_(time_edges=edges)
+    ref = orc.pulse_pc(p, LCG, threads=8)
+    say("tally rows, population control", bins, block)
+    counts, flux, diag, pop = M.pulse_pc(p, LCG, ctx=ctx, opts=M.make_pulse_opts(block=block))
+    torch.cuda.synchronize()
+    assert np.array_equal(u64_np(counts).reshape(p.n_batches, -1), ref.counts)
+    assert np.array_equal(u64_np(pop.contiguous()).reshape(ref.pop.shape), ref.pop)
+    assert dict(zip(M.PULSE_DIAG_NAMES, (int(v) for v in u64_np(diag)))) == ref.diag
