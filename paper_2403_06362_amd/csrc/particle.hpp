@@ -42,6 +42,15 @@ struct Particle {
     int32_t tb;
 };
 
+// A cell offset as a signed distance.  A lane that left through the left face
+// keeps the offset of the cell before the first, 0 - sizeof(R) in 32 bits, and
+// geom_pass forms addresses from it (the arrays have neighbours there): as an
+// unsigned distance that address is right only where the compiler has proved
+// the pointer to be one into LDS, 32 bits wide, and else 4 GiB off.
+constexpr __host__ __device__ int32_t cell_distance(uint32_t off) { return static_cast<int32_t>(off); }
+static_assert(cell_distance(0u - 8u) == -8 && cell_distance(2u * (0u - 4u)) == -8 && (cell_distance(0u - 8u) >> 1) == -4,
+              "the offset before the first cell is a distance of one cell");
+
 // Cell data of the current problem.  FP64: edge c is the position of edge c
 // (n_cells + 1), tedge[t] the time edges.  FP32: entry c + 1 of the edge
 // array is the width of cell c (entry 0 is unused), tedge[t] the duration of
@@ -62,24 +71,24 @@ struct LdsCells {
     uint32_t n_off;        // n_cells * sizeof(R)
     int32_t n_time_bins;
     int32_t n_space_bins;
-    __device__ __forceinline__ const R* edge(uint32_t off) const { return reinterpret_cast<const R*>(edge_base + off); }
+    __device__ __forceinline__ const R* edge(uint32_t off) const { return reinterpret_cast<const R*>(edge_base + cell_distance(off)); }
     __device__ __forceinline__ R sig(uint32_t off) const {
         if constexpr (ONE) return sig1;
-        return *reinterpret_cast<const R*>(sig_base + off);
+        return *reinterpret_cast<const R*>(sig_base + cell_distance(off));
     }
     __device__ __forceinline__ R rsig(uint32_t off, R) const {
         if constexpr (ONE) return rsig1;
-        return *reinterpret_cast<const R*>(rsig_base + off);
+        return *reinterpret_cast<const R*>(rsig_base + cell_distance(off));
     }
     // the state bound of the absorption test (uniform_below of the cell's c)
     __device__ __forceinline__ uint64_t below(uint32_t off) const {
         if constexpr (ONE) return below1;
-        return *reinterpret_cast<const uint64_t*>(below_base + (F32 ? 2u * off : off));
+        return *reinterpret_cast<const uint64_t*>(below_base + cell_distance(F32 ? 2u * off : off));
     }
     // 8 x the cell's space bin
     __device__ __forceinline__ uint32_t bin8(uint32_t off) const {
         if constexpr (ONE) return F32 ? 2u * off : off;
-        return *reinterpret_cast<const uint32_t*>(bin_base + (F32 ? off : off >> 1));
+        return *reinterpret_cast<const uint32_t*>(bin_base + (F32 ? cell_distance(off) : cell_distance(off) >> 1));
     }
 };
 
