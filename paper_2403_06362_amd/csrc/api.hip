@@ -1568,7 +1568,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
     pp.n_counters = static_cast<uint32_t>(std::min<uint64_t>(n_counters, 0xffffffffu));
     const bool event = o.schedule == MCRNG_PULSE_EVENT;
     const bool pooled = o.schedule == MCRNG_PULSE_BANK || !hash;   // k_pulse_pool or k_pulse_stride
-    pp.lds_tally = n_counters <= (pooled ? kPulsePoolLdsCounters : kPulseLdsCounters) ? 1u : 0u;
+    pp.lds_tally = n_counters <= kPulseLdsCounters ? 1u : 0u;
     pp.edges_lds = P->n_time_bins <= kPulseEdgeBins ? 1u : 0u;
     if (pooled) HIP_TRY(pulse_fit_rows(&pp, pc != nullptr, static_cast<int>(o.block)));
     pp.priv_cap = 1024;

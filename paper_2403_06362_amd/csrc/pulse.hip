@@ -573,7 +573,11 @@ __device__ __forceinline__ const PulseParams& rare_params() {
 // Tallies of a wave of the pool and stride kernels.  All counters in the
 // block's LDS copy when they fit; else rows of n_time_bins counters in LDS, one
 // per batch the wave works on (row b mod P.rows, tagged); collisions of a batch
-// without a row count in HBM.
+// without a row count in HBM.  Atomics on one address pass one after another,
+// about 10 ns each: where few batches share the counters (P.merge_far) the lanes
+// of one counter go as one atomic.  With an atomic per lane 1e6 sources whose
+// collisions fall into one of 600 bins took 689 ms (now in LDS: 19), 4 x 200000
+// sources 200 ms (now 20); the former schedules, in LDS or merged, 41.
 struct WaveTally {
     unsigned long long* counters;   // the block's copy (P.lds_tally)
     uint32_t* rows;
@@ -626,6 +630,24 @@ struct WaveTally {
             const uint64_t near = scored & wave_mask(tags[r] == batch);
             if (in_mask(near)) atomicAdd(rows + (__umul24(r, nt) + static_cast<uint32_t>(bin)), 1u);
             far &= ~near;
+        }
+        if (far == 0) return;
+        if (__builtin_expect(P.merge_far != 0, 0)) {
+            // the first lane's counter, and on while at least four lanes share
+            // one: up to merge_far that fewer share (lanes spread over many
+            // counters then go one by one)
+            const PulseParams& R = rare_params();
+            unsigned long long* const counts = reinterpret_cast<unsigned long long*>(R.counts);
+            for (uint32_t few = R.merge_far; far != 0 && few != 0u;) {
+                const int l = __builtin_ctzll(far);
+                const uint32_t b = __builtin_amdgcn_readlane(batch, l), i = __builtin_amdgcn_readlane(bin, l);
+                const uint64_t same = far & wave_mask(batch == b) & wave_mask(static_cast<uint32_t>(bin) == i);
+                const uint32_t n = mask_count(same);
+                if (lane == static_cast<uint32_t>(l))
+                    atomicAdd(counts + (static_cast<uint64_t>(b) * nt + i), static_cast<unsigned long long>(n));
+                far &= ~same;
+                few -= n < 4u ? 1u : 0u;
+            }
         }
         if (far != 0 && in_mask(far))
             atomicAdd(reinterpret_cast<unsigned long long*>(P.counts) +
@@ -1987,6 +2009,12 @@ hipError_t pulse_stride_grid(const PulseParams& p, int block, uint64_t sources, 
 // over sources has the most static LDS of those of a run.
 hipError_t pulse_fit_rows(PulseParams* p, bool pc, int block) {
     p->rows = 0;
+    // Merging pays where few batches' counters may be hit by all waves, and
+    // costs up to 18% where the lanes' counters differ (128 batches of 600 bins:
+    // 1064 against 958 us spread, 15.1 against 18.6 ms all in one bin).  Without
+    // rows every lane's count comes here: more tries.
+    const uint32_t merge = p->n_batches <= kPulseMergeBatches ? 1u : 0u;
+    p->merge_far = 3u * merge;
     if (p->lds_tally || p->n_time_bins > kPulseEdgeBins) return hipSuccess;
     block = bank_block(block);
     int dev = 0, lds = 0;
@@ -2000,6 +2028,7 @@ hipError_t pulse_fit_rows(PulseParams* p, bool pc, int block) {
     p->rows = 8;
     while (p->rows > 2 && p->rows * p->n_time_bins > 256) p->rows /= 2;
     while (p->rows > 0 && a.sharedSizeBytes + pool_lds_bytes(*p, block) > static_cast<size_t>(lds)) p->rows /= 2;
+    if (p->rows != 0) p->merge_far = merge;
     return hipSuccess;
 }
 

@@ -95,6 +95,8 @@ struct PulseParams {
     uint32_t priv_cap;
     uint32_t tail_iters;     // pool: iterations of a wave after the launch's items are taken
     uint32_t rows;           // pool: LDS tally rows per wave (a power of two; 0: HBM atomics)
+    uint32_t merge_far;      // pool: counts in HBM: counters with few lanes of a wave before the rest go one by one
+                             // (0: all one by one)
     uint32_t edges_lds;      // pool: time edges staged in LDS
     uint32_t grid_uniform;   // pool: time edge i is within a quarter of a bin of t0 + i / inv_dt
     double t0, inv_dt;
@@ -131,13 +133,14 @@ constexpr uint32_t kPulsePcChunkBatches = 4096;   // batches per chunk of a popu
 // `items` is a PulseItems value; `pc`: the launch's census is a census of
 // population control (arrivals are banked in p.cen).
 uint32_t pulse_bank_grid(const PulseParams& p, int items_kind, bool pc, int block, uint64_t items);
-constexpr uint32_t kPulseLdsCounters = 2048;   // block-local tally copies up to this many counters (16 KiB)
-constexpr uint32_t kPulsePoolLdsCounters = 512;   // the same for k_pulse_pool, whose pools need the LDS
-constexpr uint32_t kPulseTallySlots = 16;      // most tally slots per wave of the family kernel
-// Entries of a wave's LDS stage of appends in k_pulse_bank (output slack).
-uint32_t pulse_bank_stage(int block);
-hipError_t launch_pulse_bank(const PulseParams& p, int items_kind, bool pc, int block, uint32_t grid,
-                             hipStream_t st);
+// Block-local tally copies up to this many counters (16 KiB).  In the pool and
+// stride kernels they leave four 256-thread blocks per CU, where tally rows
+// leave six, but no row changes hands and no count goes to HBM: 513 to 2048
+// counters are up to 3.4 times faster so (3 x 100000 sources in 200 bins 428
+// against 1440 us; 60 x 1000 in 20 bins 245 against 255; 100 x 300000 in 20
+// bins 15.2 against 14.9 ms).
+constexpr uint32_t kPulseLdsCounters = 2048;
+constexpr uint32_t kPulseMergeBatches = 128;   // most batches whose HBM counts are merged (WaveTally)
 constexpr uint32_t kPulseEdgeBins = 512;   // most time bins with edges (and tally rows) in LDS
 // Sets p->rows (hash: of the pool kernels, else of the stride kernel) for the
 // block size; p->edges_lds and p->lds_tally are set before.

@@ -262,3 +262,41 @@ def test_pulse_tally_rows(M, ctx, orc, bins, block):
     assert np.array_equal(u64_np(counts).reshape(p.n_batches, -1), ref.counts)
     assert np.array_equal(u64_np(pop.contiguous()).reshape(ref.pop.shape), ref.pop)
     assert dict(zip(M.PULSE_DIAG_NAMES, (int(v) for v in u64_np(diag)))) == ref.diag
+
+
+ONE_BIN = lambda bins: np.concatenate([[0.0], np.linspace(19.0, 20.0, bins)])   # all but a few collisions in bin 0
+
+
+@pytest.mark.parametrize("n_batches,bins", [(1, 600), (3, 682), (4, 512), (4, 600), (20, 300), (129, 17)])
+def test_pulse_counters_beyond_lds(M, ctx, orc, n_batches, bins):
+    """About as many counters as LDS holds and more, with and without rows, few
+    batches and more, the lanes of a wave in one counter or in many."""
+    for kind in ("hash", "stride"):
+        for spread in (False, True):
+            sd = W.hash_seeding() if kind == "hash" else W.stride_seeding()
+            p = W.pulse(sd, n_batches=n_batches, per_batch=900 // n_batches + 1)
+            p = p.with_(time_edges=np.linspace(0.0, 20.0, bins + 1) if spread else ONE_BIN(bins), x_lo=-30.0, x_hi=30.0)
+            ref = orc.pulse(p, LCG, threads=8)
+            say("counters", n_batches, bins, kind, spread)
+            c, d = pulse(M, ctx, p)
+            assert np.array_equal(c, ref.counts) and d == ref.diag
+
+
+@pytest.mark.parametrize("n_batches", [1, 4])
+def test_pulse_counts_in_one_bin_do_not_queue(M, ctx, n_batches):
+    """A run whose collisions nearly all fall into one of 600 bins against the
+    same run with none of them scored: 9e5 wave flights of at most four atomics
+    per batch, 10 ns each, at most double it; an atomic per collision on one
+    address takes 11 to 36 times as long."""
+    ms = {}
+    for scored in (False, True):
+        p = W.pulse(W.hash_seeding(), n_batches=n_batches, per_batch=800_000 // n_batches)
+        p = p.with_(time_edges=ONE_BIN(600), x_lo=-50.0 if scored else 1000.0, x_hi=50.0 if scored else 1001.0)
+        say("one bin", n_batches, scored)
+        t = []
+        for _ in range(3):
+            pulse(M, ctx, p)
+            t.append(ctx.last_run_ms())
+        ms[scored] = min(t)
+    say(ms)
+    assert ms[True] < 4 * ms[False]
