@@ -496,8 +496,12 @@ struct Slot {
 
 #define CH_ACQ_REL(op, p, v) __hip_atomic_##op((p), (v), __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP)
 
+// Seven waves per SIMD (72 VGPRs), six (80) with time bins in FP64, which would
+// spill: 20 x 20 space-time bins, units of 8192: 2e7 histories 1091 us at seven,
+// 1047 at six, 6e7 2746 and 2641.  k_transport holds seven there (952 and
+// 2468 us; six within 1%), so such runs stay on it (transport_chain_fits).
 template <bool F32, bool TIMED, bool ONE, int BLOCK>
-__global__ void __launch_bounds__(BLOCK, 7) k_transport_chain(TransportParams P) {
+__global__ void __launch_bounds__(BLOCK, (F32 || !TIMED) ? 7 : 6) k_transport_chain(TransportParams P) {
     using chain::kNone;
     using chain::kNoMore;
     using chain::kWant;

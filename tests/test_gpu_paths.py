@@ -300,3 +300,20 @@ def test_pulse_counts_in_one_bin_do_not_queue(M, ctx, n_batches):
         ms[scored] = min(t)
     say(ms)
     assert ms[True] < 4 * ms[False]
+
+
+@pytest.mark.parametrize("precision,kernel", [(0, "k_transport"), (1, "k_transport_chain")])
+def test_timed_runs_with_large_units(M, ctx, orc, monkeypatch, precision, kernel):
+    """Time-dependent runs with units large enough for the chained kernel: FP64
+    ones stay on the per-unit kernel, which has more waves per SIMD; both give
+    the oracle's bits."""
+    p = W.multi_region(n_histories=30_011, n_space_bins=20, n_time_bins=20)
+    ref = orc.transport(p, LCG, float_mode=bool(precision), threads=8)
+    say("timed, large units", precision)
+    raw, _, diag = slab(M, ctx, [p], precision=precision, unit_histories=5120)
+    assert ctx.last_run_kernel() == kernel
+    assert raw == ref.raw and diag[0] == ref.diag
+    monkeypatch.setenv("MCRNG_TRANSPORT_CHAIN", "2")
+    raw, _, diag = slab(M, ctx, [p], precision=precision, unit_histories=5120)
+    assert ctx.last_run_kernel() == "k_transport_chain"
+    assert raw == ref.raw and diag[0] == ref.diag
