@@ -140,6 +140,11 @@ uint32_t pulse_bank_grid(const PulseParams& p, int items_kind, bool pc, int bloc
 // against 1440 us; 60 x 1000 in 20 bins 245 against 255; 100 x 300000 in 20
 // bins 15.2 against 14.9 ms).
 constexpr uint32_t kPulseLdsCounters = 2048;
+constexpr uint32_t kPulseTallySlots = 16;      // most tally slots per wave of the family kernel
+// Entries of a wave's LDS stage of appends in k_pulse_bank (output slack).
+uint32_t pulse_bank_stage(int block);
+hipError_t launch_pulse_bank(const PulseParams& p, int items_kind, bool pc, int block, uint32_t grid,
+                             hipStream_t st);
 constexpr uint32_t kPulseMergeBatches = 128;   // most batches whose HBM counts are merged (WaveTally)
 constexpr uint32_t kPulseEdgeBins = 512;   // most time bins with edges (and tally rows) in LDS
 // Sets p->rows (hash: of the pool kernels, else of the stride kernel) for the
