@@ -600,12 +600,10 @@ static uint64_t signature(const mcrng_lcg* lcg, const mcrng_problem* P, uint32_t
 
 // The chained kernel holds two units per block, so the block waits whenever
 // a unit is handed out before the one before it has ended, and pays at the end
-// of a launch.  On the long-chain slab (heavy-tailed history lengths) with 1e8
-// histories it wins at every unit size (block 256: 26.1 ms at 5425 histories
-// per unit, 25.5 at 16384, 30.2 at 3051, against 32.1, 25.6 and 39.2 on the
-// per-unit kernel), with fewer histories it loses (1e6: 1.90 against 1.63 ms at
-// 1024 per unit, 4e6: 3.34 against 2.98 at 2048; 3e7: 9.70 against 9.82 at
-// 8192).  Units of 20 histories per lane belong to large runs.
+// of a launch: it needs large units.  On the long-chain slab (50 mean free
+// paths, c = 0.99, 200 bins) with 1e8 histories: block 256: 30.2 ms at 3051
+// histories per unit, 26.1 at 5425, 25.5 at 16384; per-unit kernel 39.2, 32.1 and
+// 25.6.  Units that a caller sets decide by this alone.
 constexpr uint32_t kChainMinPerLane = 20;
 
 // MCRNG_TRANSPORT_CHAIN: 0 keeps one-problem runs on the per-unit kernel;
@@ -645,42 +643,8 @@ static bool chain_possible(const mcrng_problem* P, uint32_t n, const mcrng_run_o
     return transport_chain_fits(a, b, s, &fits) == hipSuccess && fits;
 }
 
-// Histories per work unit.  Large units pay at the end of the launch (blocks
-// idle while the last units run), small ones at every unit's end (a block's
-// lanes idle while the unit's longest histories run, then the slice goes out),
-// so the best size grows like the square root of the total.  Measured best,
-// 256-thread blocks: 1e5 histories 512 .. 1024, 1e6 2048, 3e6 4096, 1e7 4096 on
-// a thick (50 mean free paths, c = 0.99) and a thin slab alike (1e6 thick: 1.47 ms,
-// 1.94 at 512; 3e6 thin: 0.24, 0.37 at 1024); time-dependent tallies 2e7 8192,
-// 6e7 16384; 512 slabs of 1.35e8 histories 12288 (12.0 ms, 18.2 at 32768), 128
-// of 1.3e7 4096.  The chained kernel pays at the ends of launches only, where
-// units of 32 histories per lane even out the blocks; it wins from about
-// 1.5e7 histories on (2e7 thick: 7.5 ms, 7.8 per unit; 1e7: 5.1 against 4.7).
-static uint32_t default_unit_histories(const mcrng_problem* P, uint32_t n, const mcrng_run_opts& o) {
-    uint64_t total = 0;
-    for (uint32_t i = 0; i < n; ++i) total += P[i].n_histories;
-    const double lanes = o.block / 256.0 * o.hist_per_lane;
-    const double root = std::sqrt(static_cast<double>(total));
-    double u;
-    if (n > 1)
-        u = std::min(1.25 * root, 16384.0) * lanes;
-    else if (chain_possible(P, n, o))
-        u = (2 * root >= 7680 ? std::min(2 * root, 8192.0) : std::min(2 * root, 4096.0)) * lanes;
-    else
-        u = std::min(2 * root, 16384.0) * lanes;
-    u = std::max(u, static_cast<double>(total / 16384));
-    return static_cast<uint32_t>(std::min<uint64_t>(std::max<uint64_t>((static_cast<uint64_t>(u) + 63) & ~63ull, 64), 65536));
-}
-
-// Units of the event schedule, and of a run whose units by the rule above
-// exceed the static scratch: at most about 4096 per problem set.
-static uint32_t coarse_unit_histories(const mcrng_problem* P, uint32_t n) {
-    uint64_t total = 0;
-    for (uint32_t i = 0; i < n; ++i) total += P[i].n_histories;
-    return static_cast<uint32_t>(std::min<uint64_t>(std::max<uint64_t>(total / 4096, 512), 65536));
-}
-
-// Relative time of one history of a problem, for the schedule's order only:
+// Relative time of one history of a problem, for the schedule's order and the
+// automatic units only:
 // expected events and (three times the work of an event) collisions of a
 // homogeneous slab of the problem's mean scattering ratio and optical width,
 // with the collisions from the half-space albedo (two-stream approximation).
@@ -696,6 +660,60 @@ static double history_cost(const mcrng_problem& P) {
     const double coll = std::min((1 + h) / ((1 + h * q) * q), 1 + w * (1 + w / 2));
     const double cells = P.n_regions + P.n_space_bins;
     return (coll + 1) * (1 + 0.5 * cells / std::max(w, 1e-3)) + 3 * coll;
+}
+
+// Histories per work unit.  Large units pay at the end of the launch (blocks
+// idle while the last units run), small ones at every unit's end (a block's
+// lanes idle while the unit's longest histories run, then the slice goes out),
+// so the best size grows like the square root of the total.  Measured best,
+// 256-thread blocks: 1e5 histories 512 .. 1024, 1e6 2048, 3e6 4096, 1e7 4096 on
+// a thick (50 mean free paths, c = 0.99) and a thin slab alike (1e6 thick: 1.47 ms,
+// 1.94 at 512; 3e6 thin: 0.24, 0.37 at 1024); time-dependent tallies 2e7 8192,
+// 6e7 16384; 512 slabs of 1.35e8 histories 12288 (12.0 ms, 18.2 at 32768), 128
+// of 1.3e7 4096.  The chained kernel pays at the ends of launches only, where
+// units of 32 histories per lane even out the blocks.
+//   Which of the two an automatic run of one problem takes: the pauses at the
+// ends of units weigh the more the longer histories are, the chained kernel's
+// large units the less the more histories there are.  The line lies at 1.47e7
+// histories and kChainMinWork for histories times history_cost.  Chained against
+// per-unit time on random slabs (5 to 50 mean free paths, c = 0.5 to 0.99, 20 to
+// 200 bins, both precisions): below 1.47e7 histories 1.06 to 1.35 (42 runs from
+// 6e6 on), from there to 8e7 histories below the line 0.98 to 1.21, on average
+// 1.09 (42 runs), above it 0.83 to 1.05, on average 0.95 (16 runs); 2e7
+// time-dependent histories of 20 x 20 bins 1.14, the long-chain slab of 3e7
+// histories 0.91, of 5e7 0.81.  The per-unit kernel has 19 histories per lane
+// there, below the chained kernel's 20 (4096 per block 2% slower; below 1.47e7
+// 1% faster); from 8e7 histories on, where that would make more than 16384
+// units, all are chained.
+constexpr double kChainMinWork = 1.8e9;
+static uint32_t default_unit_histories(const mcrng_problem* P, uint32_t n, const mcrng_run_opts& o) {
+    uint64_t total = 0;
+    for (uint32_t i = 0; i < n; ++i) total += P[i].n_histories;
+    const double lanes = o.block / 256.0 * o.hist_per_lane;
+    const double root = std::sqrt(static_cast<double>(total));
+    double u;
+    if (n > 1)
+        u = std::min(1.25 * root, 16384.0) * lanes;
+    else if (chain_possible(P, n, o)) {
+        constexpr double per_unit = (kChainMinPerLane - 1) * 256.0;
+        if (2 * root < 7680)
+            u = std::min(2 * root, 4096.0) * lanes;
+        else if (total * history_cost(P[0]) >= kChainMinWork || total / 16384 > per_unit * lanes)
+            u = std::min(2 * root, 8192.0) * lanes;
+        else
+            u = per_unit * lanes;
+    } else
+        u = std::min(2 * root, 16384.0) * lanes;
+    u = std::max(u, static_cast<double>(total / 16384));
+    return static_cast<uint32_t>(std::min<uint64_t>(std::max<uint64_t>((static_cast<uint64_t>(u) + 63) & ~63ull, 64), 65536));
+}
+
+// Units of the event schedule, and of a run whose units by the rule above
+// exceed the static scratch: at most about 4096 per problem set.
+static uint32_t coarse_unit_histories(const mcrng_problem* P, uint32_t n) {
+    uint64_t total = 0;
+    for (uint32_t i = 0; i < n; ++i) total += P[i].n_histories;
+    return static_cast<uint32_t>(std::min<uint64_t>(std::max<uint64_t>(total / 4096, 512), 65536));
 }
 
 // Builds every table of the problem set on the host and uploads them.

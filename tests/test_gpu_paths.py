@@ -317,3 +317,17 @@ def test_timed_runs_with_large_units(M, ctx, orc, monkeypatch, precision, kernel
     raw, _, diag = slab(M, ctx, [p], precision=precision, unit_histories=5120)
     assert ctx.last_run_kernel() == "k_transport_chain"
     assert raw == ref.raw and diag[0] == ref.diag
+
+
+@pytest.mark.parametrize("c,kernel", [(0.5, "k_transport"), (0.99, "k_transport_chain")])
+def test_automatic_units_choose_the_kernel(M, ctx, monkeypatch, c, kernel):
+    """A large run of one problem: long histories are chained, short ones run
+    per unit; the other kernel gives the same bits."""
+    p = W.homogeneous(30.0, 1.0, c, 100, 20_000_000, n_batches=2)
+    say("automatic units", c)
+    raw, flux, diag = slab(M, ctx, [p])
+    assert ctx.last_run_kernel() == kernel
+    monkeypatch.setenv("MCRNG_TRANSPORT_CHAIN", "0" if kernel == "k_transport_chain" else "2")
+    other = slab(M, ctx, [p])
+    assert ctx.last_run_kernel() != kernel
+    assert other[0] == raw and other[2] == diag and np.array_equal(other[1], flux)
