@@ -46,6 +46,7 @@
 // integers, and copy k starts the stream hash(k, X) (eq. 5).  All
 // particles of a batch share the epoch's weight, so counts stay integers
 // and the flux applies the weights.
+#include <algorithm>
 #include <cstdlib>
 
 #include "pulse.hpp"
@@ -1879,10 +1880,12 @@ hipError_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int bl
     return hipSuccess;
 }
 
+// A wave that last saw at most out_budget entries appends at most one spill more
+// (half a pool) before it sees the budget passed, then one iteration's siblings
+// (64 (n_max - 1)) and what it holds: its lanes, pool and private stack.  (A
+// bank's items that it has taken but not started have room of their own.)
 uint64_t pulse_pool_slack(const PulseParams& p, uint32_t n_max) {
-    // the pool, the private stack, the lanes and two iterations' appends (a
-    // bank's items that a wave has taken but not started have room of their own)
-    return 2ull * 256 + p.priv_cap + 64 + 2ull * 64 * n_max;
+    return kPoolEntries / 2 + 64ull * std::max(n_max, 1u) + kPoolEntries + p.priv_cap;
 }
 
 hipError_t launch_pulse_pool(const PulseParams& p, int items_kind, bool pc, int block, uint32_t grid, hipStream_t st) {

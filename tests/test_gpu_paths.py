@@ -331,3 +331,23 @@ def test_automatic_units_choose_the_kernel(M, ctx, monkeypatch, c, kernel):
     other = slab(M, ctx, [p])
     assert ctx.last_run_kernel() != kernel
     assert other[0] == raw and other[2] == diag and np.array_equal(other[1], flux)
+
+
+def test_pool_buffers_of_a_small_run(M):
+    """A new context's first run of 4096 sources: at most 4096 waves, each with
+    a private stack of 1024 entries and, in one full and one smaller bank, room
+    for 1408, 32 bytes each and a quarter more: 525 MiB."""
+    import torch
+    p = W.pulse(W.hash_seeding(), n_batches=1, per_batch=4096)
+    counts = torch.empty((1, 20), dtype=torch.uint64, device="cuda:0")
+    pulse(M, M.Context(0), p)   # code objects and tables of the process
+    torch.cuda.synchronize()
+    c = M.Context(0)
+    before = torch.cuda.mem_get_info()[0]
+    say("buffers of a small run")
+    c.run_pulse(LCG, p, counts)
+    torch.cuda.synchronize()
+    used = (before - torch.cuda.mem_get_info()[0]) >> 20
+    c.close()
+    say(used, "MiB")
+    assert used < 600
