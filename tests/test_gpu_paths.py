@@ -351,3 +351,26 @@ def test_pool_buffers_of_a_small_run(M):
     c.close()
     say(used, "MiB")
     assert used < 600
+
+
+@pytest.mark.parametrize("div", [0xFFFFFFFF, 1, 2, 3, 4, 16, 64])
+def test_event_schedule_finish_points(M, ctx, orc, div):
+    """The event schedule's tail, run depth first per lane by a finish launch
+    (with its budget per particle and spills to the next generation), switched
+    to at every point, never, and at the first shrinking generation of a growing
+    population; its census arrivals with population control."""
+    import torch
+    for p in (W.pulse(W.hash_seeding(), n_batches=8, per_batch=400), W.pulse_few_sources(n_sources=256, t_end=40)):
+        ref = orc.pulse(p, LCG, threads=8)
+        say("event finish", div, p.n_batches)
+        c, d = pulse(M, ctx, p, schedule=M.PULSE_EVENT, finish_div=div)
+        assert np.array_equal(c, ref.counts) and d == ref.diag
+    p = W.pulse_pc(n_batches=6, per_batch=500, census_every=4, target=700)
+    ref = orc.pulse_pc(p, LCG, threads=6)
+    say("event finish, population control", div)
+    counts, flux, diag, pop = M.pulse_pc(p, LCG, ctx=ctx,
+                                         opts=M.make_pulse_opts(schedule=M.PULSE_EVENT, finish_div=div))
+    torch.cuda.synchronize()
+    assert np.array_equal(u64_np(counts).reshape(p.n_batches, -1), ref.counts)
+    assert np.array_equal(u64_np(pop.contiguous()).reshape(ref.pop.shape), ref.pop)
+    assert dict(zip(M.PULSE_DIAG_NAMES, (int(v) for v in u64_np(diag)))) == ref.diag
