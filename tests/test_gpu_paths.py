@@ -4,6 +4,7 @@ grids that are not uniform (both seedings), generators of every size, distances
 below the refined quotients' range, rows of uniforms that start inside lines,
 and automatic work units.  Integer tallies and bits throughout, so every
 comparison is exact."""
+import math
 import sys
 
 import numpy as np
@@ -374,3 +375,55 @@ def test_event_schedule_finish_points(M, ctx, orc, div):
     assert np.array_equal(u64_np(counts).reshape(p.n_batches, -1), ref.counts)
     assert np.array_equal(u64_np(pop.contiguous()).reshape(ref.pop.shape), ref.pop)
     assert dict(zip(M.PULSE_DIAG_NAMES, (int(v) for v in u64_np(diag)))) == ref.diag
+
+
+def family_depth(orc, p):
+    """Most entries (scatterings with siblings still to start) that a family of
+    the stride-seeded problem holds at once."""
+    mask = (1 << LCG.m) - 1
+    deepest = 0
+    for j in range(p.n_sources):
+        x = orc.stream_start(LCG, p.seeding, j)
+
+        def draw():
+            nonlocal x
+            x = (LCG.g * x + LCG.c) & mask
+            return ((x >> (LCG.m - 53)) + 1) * 2.0 ** -53
+
+        t, stack = 0.0, []
+        while True:
+            draw()                                   # direction
+            t -= math.log(draw()) / p.sigma_t
+            n = 0
+            if t < p.time_edges[-1] and draw() < p.scatter:
+                n = int(p.nu) + (draw() < p.nu - int(p.nu))
+            if n > 1:
+                stack.append([t, n - 1])
+                deepest = max(deepest, len(stack))
+            if n == 0:
+                if not stack:
+                    break
+                t = stack[-1][0]
+                stack[-1][1] -= 1
+                if stack[-1][1] == 0:
+                    stack.pop()
+    return deepest
+
+
+@pytest.mark.parametrize("t_end,n,depth", [(1, 30, 1), (3, 30, 4), (6, 30, 5), (6, 60, 6), (10, 30, 13)])
+def test_stride_stack_depths(M, ctx, orc, t_end, n, depth):
+    """Families as deep as opts.stack_depth: less than the entries a lane keeps
+    in LDS, just as many, one and two more, and many more; one entry less is
+    reported."""
+    p = W.pulse(W.stride_seeding(), n_batches=1, per_batch=n).with_(time_edges=np.linspace(0.0, t_end, 5))
+    assert family_depth(orc, p) == depth
+    ref = orc.pulse(p, LCG, threads=4)
+    for block in (64, 256):
+        for extra in (0, 1, 40):
+            say("stride stack", depth, block, extra)
+            c, d = pulse(M, ctx, p, block=block, stack_depth=depth + extra)
+            assert np.array_equal(c, ref.counts) and d == ref.diag
+        if depth > 1:
+            with pytest.raises(M.McrngError) as e:
+                pulse(M, ctx, p, block=block, stack_depth=depth - 1)
+            assert e.value.code == -4
