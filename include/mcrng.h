@@ -367,9 +367,9 @@ enum { MCRNG_PULSE_AUTO = 0, MCRNG_PULSE_BANK = 1, MCRNG_PULSE_FAMILY = 2, MCRNG
  *                first per lane, up to 64 particles per banked particle
  *                (default 1: the first shrinking generation of that size;
  *                0xffffffff: never); the other schedules take any value
- *   chunk        particles a wave takes from a launch's input per atomic,
- *                64 .. 2^20 (default 0: chosen per launch from its input
- *                count) */
+ *   chunk        bank and event schedules: particles a wave takes from a
+ *                launch's input per atomic, 64 .. 2^20 (default 0: chosen per
+ *                launch from its input count); families take any value */
 typedef struct {
     uint32_t schedule;
     uint32_t block;
