@@ -369,7 +369,7 @@ enum { MCRNG_PULSE_AUTO = 0, MCRNG_PULSE_BANK = 1, MCRNG_PULSE_FAMILY = 2, MCRNG
  *                0xffffffff: never); the other schedules take any value
  *   chunk        bank and event schedules: particles a wave takes from a
  *                launch's input per atomic, 64 .. 2^20 (default 0: chosen per
- *                launch from its input count); families take any value */
+ *                launch from its input count); families do not use it */
 typedef struct {
     uint32_t schedule;
     uint32_t block;
