@@ -1339,7 +1339,7 @@ template <int ITEMS, bool PC, int BLOCK, bool DEEP, bool SLOTS>
 __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
     constexpr bool SOURCES = ITEMS == PULSE_ITEMS_SOURCES;
     constexpr bool SPILL = !SOURCES;
-    constexpr bool DIR = PC || ITEMS == PULSE_ITEMS_COPIES;
+    constexpr bool DIR = PC;   // census arrivals keep their direction
     __shared__ CensusStage cstage[PC ? BLOCK / 64 : 1];
     extern __shared__ unsigned long long lds_counts[];
     tally_lds_begin<BLOCK>(P, lds_counts);
@@ -1401,7 +1401,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_family(PulseParams P) {
     bool active = false;       // the lane holds a particle of a family
     bool exhausted = false;    // wave-uniform: the item counter has passed the end
     uint64_t wnext = 0, wend = 0;   // wave-uniform: the wave's untaken items [wnext, wend)
-    uint32_t pdraws = 0;       // draws of the current stream (hash: particle; stride: family)
+    uint32_t pdraws = 0;       // draws of the current particle
     uint32_t budget = 0;       // finish: particles the current item may still start
 
     for (;;) {

@@ -25,8 +25,8 @@ struct PulseBankView {
 // scattering that have not started yet (keys next .. n).
 struct PulseStackEntry {
     double x, t;
-    uint64_t key;        // hash seeding: the parent's state X_p
-    int32_t tb;
+    uint64_t key;        // hash seeding: the parent's state X_p; stride: siblings left << 16 | time bin + 1
+    int32_t tb;          // (hash seeding)
     uint16_t next, n;
 };
 
@@ -102,8 +102,9 @@ struct PulseParams {
     double t0, inv_dt;
     uint32_t* overflow;      // set if an append or a stack push found no room
     uint64_t* family_counter;
-    PulseStackEntry* stack;  // family schedule: stack_depth entries per lane of the launch,
-                             // depth-major (entry d of lane l at d * lanes + l)
+    PulseStackEntry* stack;  // families: stack_depth entries per lane of the launch.  Stride kernel and
+                             // the register-top form of the hash kernel: depth-major (entry d of lane l
+                             // at d * lanes + l); the other hash form: a lane's entries together
     // population control (t_end is then the census time of the epoch)
     PulseCensusEntry* cen;   // census arrivals of the epoch
     uint64_t* cen_count;     // arrivals of part s at cen_count[s kPulseCounterStride]
