@@ -48,6 +48,7 @@
 // and the flux applies the weights.
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "pulse.hpp"
 
@@ -620,6 +621,9 @@ struct WaveTally {
             m &= ~wave_mask(batch == b);
         }
     }
+    // MERGE: P.merge_far != 0 (forms of their own: the code costs the study 2%
+    // where it never runs)
+    template <bool MERGE>
     __device__ __forceinline__ void add(const PulseParams& P, uint64_t scored, uint32_t batch, int32_t bin) {
         if (P.lds_tally) {
             if (in_mask(scored)) atomicAdd(counters + (batch * nt + static_cast<uint32_t>(bin)), 1ull);
@@ -632,8 +636,7 @@ struct WaveTally {
             if (in_mask(near)) atomicAdd(rows + (__umul24(r, nt) + static_cast<uint32_t>(bin)), 1u);
             far &= ~near;
         }
-        if (far == 0) return;
-        if (__builtin_expect(P.merge_far != 0, 0)) {
+        if (MERGE && far != 0) {
             // the first lane's counter, and on while at least four lanes share
             // one: up to merge_far that fewer share (lanes spread over many
             // counters then go one by one)
@@ -684,7 +687,7 @@ __device__ __forceinline__ double* stage_edges(const PulseParams& P, unsigned lo
     return l_edges;
 }
 
-template <int ITEMS, bool PC, int BLOCK>
+template <int ITEMS, bool PC, int BLOCK, bool MERGE>
 __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
     constexpr bool SOURCES = ITEMS == PULSE_ITEMS_SOURCES;
     constexpr bool COPIES = ITEMS == PULSE_ITEMS_COPIES;
@@ -901,7 +904,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
         const double xn = x + step;
         const int32_t bin = flight_bin(P, l_edges, coll, tn, tb);
         const uint64_t scored = coll & wave_mask(bin >= 0) & wave_mask(P.x_lo <= xn) & wave_mask(xn <= P.x_hi);
-        tally.add(P, scored, batch, bin);
+        tally.add<MERGE>(P, scored, batch, bin);
         const uint64_t z3 = lcg_next_z(P.lcg, z);
         const uint64_t go = coll & wave_mask(z3 < P.scatter_below);
         const uint64_t z4 = lcg_next_z(P.lcg, z3);
@@ -1057,7 +1060,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
 constexpr uint32_t kStrideDepth = 4;   // a power of two
 constexpr uint32_t kStrideRefill = 3;  // idle lanes at which a wave takes sources (a family ends in 60% of its iterations)
 
-template <int BLOCK>
+template <int BLOCK, bool MERGE>
 __global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
     constexpr uint32_t kWaves = BLOCK / 64;
     __shared__ double s_xt[kWaves][2][kStrideDepth][64];   // x and t planes
@@ -1177,7 +1180,7 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_stride(PulseParams P) {
         const double xn = x + step;
         const int32_t bin = flight_bin(P, l_edges, coll, tn, tb);
         const uint64_t scored = coll & wave_mask(bin >= 0) & wave_mask(P.x_lo <= xn) & wave_mask(xn <= P.x_hi);
-        tally.add(P, scored, batch, bin);
+        tally.add<MERGE>(P, scored, batch, bin);
         const uint64_t z3 = lcg_next_z(P.lcg, z2);
         const uint64_t go = coll & wave_mask(z3 < P.scatter_below);
         const uint64_t z4 = lcg_next_z(P.lcg, z3);
@@ -1823,28 +1826,31 @@ hipError_t launch_pulse_bank(const PulseParams& p, int items_kind, bool pc, int 
                            pulse_tally_lds_bytes(p), st);
 }
 
-template <int BLOCK>
+template <int BLOCK, bool MERGE>
 static const void* pool_kernel_b(int items, bool pc) {
     switch (items) {
         case PULSE_ITEMS_SOURCES:
-            return pc ? reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_SOURCES, true, BLOCK>)
-                      : reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_SOURCES, false, BLOCK>);
+            return pc ? reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_SOURCES, true, BLOCK, MERGE>)
+                      : reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_SOURCES, false, BLOCK, MERGE>);
         case PULSE_ITEMS_COPIES:
-            return pc ? reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_COPIES, true, BLOCK>)
-                      : reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_COPIES, false, BLOCK>);
+            return pc ? reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_COPIES, true, BLOCK, MERGE>)
+                      : reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_COPIES, false, BLOCK, MERGE>);
         default:
-            return pc ? reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_BANK, true, BLOCK>)
-                      : reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_BANK, false, BLOCK>);
+            return pc ? reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_BANK, true, BLOCK, MERGE>)
+                      : reinterpret_cast<const void*>(k_pulse_pool<PULSE_ITEMS_BANK, false, BLOCK, MERGE>);
     }
 }
 
-static const void* pool_kernel(int block, int items, bool pc) {
+static const void* pool_kernel(const PulseParams& p, int block, int items, bool pc) {
+    auto form = [&](auto b) {
+        return p.merge_far != 0 ? pool_kernel_b<b.value, true>(items, pc) : pool_kernel_b<b.value, false>(items, pc);
+    };
     switch (block) {
-        case 64: return pool_kernel_b<64>(items, pc);
-        case 128: return pool_kernel_b<128>(items, pc);
-        case 512: return pool_kernel_b<512>(items, pc);
-        case 1024: return pool_kernel_b<1024>(items, pc);
-        default: return pool_kernel_b<256>(items, pc);
+        case 64: return form(std::integral_constant<int, 64>());
+        case 128: return form(std::integral_constant<int, 128>());
+        case 512: return form(std::integral_constant<int, 512>());
+        case 1024: return form(std::integral_constant<int, 1024>());
+        default: return form(std::integral_constant<int, 256>());
     }
 }
 
@@ -1870,7 +1876,7 @@ static hipError_t tally_blocks_per_cu(const void* kern, const PulseParams& p, in
 hipError_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int block, uint64_t items, uint32_t* grid) {
     block = bank_block(block);
     int per_cu = 0;
-    const hipError_t e = tally_blocks_per_cu(pool_kernel(block, items_kind, pc), p, block, &per_cu);
+    const hipError_t e = tally_blocks_per_cu(pool_kernel(p, block, items_kind, pc), p, block, &per_cu);
     if (e != hipSuccess) return e;
     const uint64_t waves = static_cast<uint64_t>(block / 64);
     uint64_t blocks = (items + waves - 1) / waves;   // an item per wave at least
@@ -1893,7 +1899,7 @@ hipError_t launch_pulse_pool(const PulseParams& p, int items_kind, bool pc, int 
     block = bank_block(block);
     PulseParams arg = p;
     void* args[] = {&arg};
-    return hipLaunchKernel(pool_kernel(block, items_kind, pc), dim3(grid), dim3(block), args,
+    return hipLaunchKernel(pool_kernel(p, block, items_kind, pc), dim3(grid), dim3(block), args,
                            pool_lds_bytes(p, block), st);
 }
 
@@ -1981,20 +1987,24 @@ hipError_t launch_pulse_finish(const PulseParams& p, bool pc, uint32_t grid, hip
     return hipGetLastError();
 }
 
-static const void* stride_kernel(int block) {
+static const void* stride_kernel(const PulseParams& p, int block) {
+    auto form = [&](auto b) {
+        return p.merge_far != 0 ? reinterpret_cast<const void*>(k_pulse_stride<b.value, true>)
+                                : reinterpret_cast<const void*>(k_pulse_stride<b.value, false>);
+    };
     switch (block) {
-        case 64: return reinterpret_cast<const void*>(k_pulse_stride<64>);
-        case 128: return reinterpret_cast<const void*>(k_pulse_stride<128>);
-        case 512: return reinterpret_cast<const void*>(k_pulse_stride<512>);
-        case 1024: return reinterpret_cast<const void*>(k_pulse_stride<1024>);
-        default: return reinterpret_cast<const void*>(k_pulse_stride<256>);
+        case 64: return form(std::integral_constant<int, 64>());
+        case 128: return form(std::integral_constant<int, 128>());
+        case 512: return form(std::integral_constant<int, 512>());
+        case 1024: return form(std::integral_constant<int, 1024>());
+        default: return form(std::integral_constant<int, 256>());
     }
 }
 
 hipError_t pulse_stride_grid(const PulseParams& p, int block, uint64_t sources, uint32_t* grid) {
     block = bank_block(block);
     int per_cu = 0;
-    const hipError_t e = tally_blocks_per_cu(stride_kernel(block), p, block, &per_cu);
+    const hipError_t e = tally_blocks_per_cu(stride_kernel(p, block), p, block, &per_cu);
     if (e != hipSuccess) return e;
     // a family per wave at least: few families spread over the whole chip
     uint64_t blocks = (sources + block / 64 - 1) / (block / 64);
@@ -2011,14 +2021,15 @@ hipError_t pulse_stride_grid(const PulseParams& p, int block, uint64_t sources, 
 // in the pool kernel with population control, of 160 KiB.)  The pool kernel
 // over sources has the most static LDS of those of a run.
 hipError_t pulse_fit_rows(PulseParams* p, bool pc, int block) {
-    p->rows = 0;
+    p->rows = p->merge_far = 0;
+    if (p->lds_tally) return hipSuccess;
     // Merging pays where few batches' counters may be hit by all waves, and
     // costs up to 18% where the lanes' counters differ (128 batches of 600 bins:
     // 1064 against 958 us spread, 15.1 against 18.6 ms all in one bin).  Without
     // rows every lane's count comes here: more tries.
     const uint32_t merge = p->n_batches <= kPulseMergeBatches ? 1u : 0u;
     p->merge_far = 3u * merge;
-    if (p->lds_tally || p->n_time_bins > kPulseEdgeBins) return hipSuccess;
+    if (p->n_time_bins > kPulseEdgeBins) return hipSuccess;
     block = bank_block(block);
     int dev = 0, lds = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -2026,7 +2037,7 @@ hipError_t pulse_fit_rows(PulseParams* p, bool pc, int block) {
     e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     if (e != hipSuccess) return e;
     hipFuncAttributes a;
-    e = hipFuncGetAttributes(&a, p->hash ? pool_kernel(block, PULSE_ITEMS_SOURCES, pc) : stride_kernel(block));
+    e = hipFuncGetAttributes(&a, p->hash ? pool_kernel(*p, block, PULSE_ITEMS_SOURCES, pc) : stride_kernel(*p, block));
     if (e != hipSuccess) return e;
     p->rows = 8;
     while (p->rows > 2 && p->rows * p->n_time_bins > 256) p->rows /= 2;
@@ -2040,7 +2051,7 @@ hipError_t launch_pulse_stride(const PulseParams& p, int block, uint32_t grid, h
     block = bank_block(block);
     PulseParams arg = p;
     void* args[] = {&arg};
-    return hipLaunchKernel(stride_kernel(block), dim3(grid), dim3(block), args, pool_lds_bytes(p, block), st);
+    return hipLaunchKernel(stride_kernel(p, block), dim3(grid), dim3(block), args, pool_lds_bytes(p, block), st);
 }
 
 uint32_t pulse_family_grid(int block) {
