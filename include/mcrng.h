@@ -157,7 +157,8 @@ enum { MCRNG_SCHED_HISTORY = 0, MCRNG_SCHED_EVENT = 1 };
  *   hist_per_lane   histories each lane carries at once: 1, 2 or 4
  *   unit_histories  histories per work unit (the scheduling grain), at most
  *                   2^18 (0 = automatic, 64 .. 2^16, growing with the square
- *                   root of the total).  A unit's partial tally is exact
+ *                   root of the total; one problem whose histories are short
+ *                   for their number stays below the chained kernel's units).  A unit's partial tally is exact
  *                   while fewer than 2^32 of its scores fall in one bin
  *                   (2^14 per history on average at 2^18 histories); the event schedule's slots that collect a
  *                   whole slice carry and have no such limit.
@@ -251,9 +252,10 @@ int mcrng_reduce_tallies(mcrng_ctx *ctx, uint64_t *d_raw, double *d_flux, uint64
  *     scheduling counter) comes from one static device array of 64 MiB per
  *     device, which the library allocates with its code object the first
  *     time this call runs on a device and keeps until the process ends;
- *     a run that needs more (about units x slice_bins x 16 bytes, e.g. the
- *     2e8-history multi-region slab takes 49 MB) returns MCRNG_EINVAL and
- *     enqueues nothing;
+ *     a run that needs more (about units x slice_bins x 16 bytes) returns
+ *     MCRNG_EINVAL and enqueues nothing; automatic units that do not fit
+ *     are first made coarser, at most about 4096 in all (the 2e8-history
+ *     multi-region slab with its 1000 bins then takes 66 MB);
  *   - history schedule only; opts.schedule = MCRNG_SCHED_EVENT or
  *     opts.use_graph = 1 return MCRNG_EINVAL;
  *   - every call on a device shares that device's array and leaves its

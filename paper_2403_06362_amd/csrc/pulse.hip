@@ -506,8 +506,8 @@ struct __align__(16) FamilySource {
 // families where they are few.  Generations in HBM (the schedule's former
 // kernel: one launch and one read-back per generation, 32 B each way per
 // banked particle, waves waiting on the append counter) took 5.9 ms for the
-// paper's 1000 x 1000 sources, now 0.89; 5.6 ms for 4096 sources to t = 60, now
-// 0.70; 3e7 sources took 101 ms (41.5 as families), now 15.2.
+// paper's 1000 x 1000 sources, now 0.86; 5.6 ms for 4096 sources to t = 60, now
+// 0.68; 3e7 sources took 101 ms (41.5 as families), now 14.7.
 //   Where particles go when the LDS pool is full: its older half to the wave's
 // private HBM stack (priv_cap entries, read back when the pool is empty); when
 // that is full too, to the launch's output bank; and once the wave has seen
@@ -1052,11 +1052,12 @@ __global__ void __launch_bounds__(BLOCK) k_pulse_pool(PulseParams P) {
 // (about 230 instructions; vector units 77% busy).  Against the walk it
 // replaces (every entry below the top in HBM, the phases of a family as
 // branches: 358 instructions per flight, 108 GB of stack traffic) the
-// 3e7-source study went from 36.7 ms to 18.8.
+// 3e7-source study went from 38 ms to 19 (18.1 to 19.6 from run to run).
 // LDS entries per lane: a power of two, so that an entry's place is its depth
 // masked (with 6 entries, a running place and stack addresses computed where
-// they are used the study took 19.7 ms at 237 instructions per flight, now 18.8
-// at 227; that form took 23.9 ms at 3 entries and 22 at 7, three blocks per CU).
+// they are used the study took 5% longer at 237 instructions per flight, now
+// 227; that form took 23.9 ms at 3 entries, 19.7 at 6 and 22 at 7, three blocks
+// per CU).
 constexpr uint32_t kStrideDepth = 4;   // a power of two
 constexpr uint32_t kStrideRefill = 3;  // idle lanes at which a wave takes sources (a family ends in 60% of its iterations)
 
