@@ -158,10 +158,11 @@ enum { MCRNG_SCHED_HISTORY = 0, MCRNG_SCHED_EVENT = 1 };
  *   unit_histories  histories per work unit (the scheduling grain), at most
  *                   2^18 (0 = automatic, 64 .. 2^16, growing with the square
  *                   root of the total; one problem whose histories are short
- *                   for their number stays below the chained kernel's units).  A unit's partial tally is exact
- *                   while fewer than 2^32 of its scores fall in one bin
- *                   (2^14 per history on average at 2^18 histories); the event schedule's slots that collect a
- *                   whole slice carry and have no such limit.
+ *                   for their number stays below the chained kernel's
+ *                   units).  A unit's partial tally is exact while fewer than
+ *                   2^32 of its scores fall in one bin (2^14 per history on
+ *                   average at 2^18 histories); the event schedule's slots
+ *                   that collect a whole slice carry and have no such limit.
  *   grid            persistent blocks (0 = fill the device)
  *   tally_copies    LDS tally copies per block: 1, or one per wave (= 2)
  *                   A set of one problem with one history per lane, one
