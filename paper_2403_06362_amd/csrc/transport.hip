@@ -934,6 +934,15 @@ static hipError_t with_flags(int f32, int timed, int one, F f) {
 hipError_t transport_chain_fits(const TransportParams& single, const TransportParams& chained, const LaunchShape& s,
                                 bool* fits) {
     *fits = false;
+    // (asking for more LDS than there is would leave an error behind for the
+    // next launch to report)
+    int dev = 0, lds = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    if (e != hipSuccess) return e;
+    if (transport_lds_bytes(chained, s.f32) + transport_static_lds_bytes(s.block) > static_cast<size_t>(lds))
+        return hipSuccess;
     return with_flags(s.f32, s.timed, static_cast<int>(single.one_region), [&](auto f, auto t, auto o) {
         return chain_fits_b<f.value, t.value, o.value>(single, chained, s, fits);
     });

@@ -427,3 +427,26 @@ def test_stride_stack_depths(M, ctx, orc, t_end, n, depth):
             with pytest.raises(M.McrngError) as e:
                 pulse(M, ctx, p, block=block, stack_depth=depth - 1)
             assert e.value.code == -4
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("space,time", [(50, 100), (20, 250), (4095, 0), (4, 2048)])
+def test_slices_that_fill_lds(M, ctx, orc, precision, space, time):
+    """Tally slices of which LDS holds one but not the chained kernel's two: with
+    automatic units, with units large enough for that kernel, and without
+    allocation."""
+    import torch
+    p = W.homogeneous(6.0, 1.0, 0.7, space, 1503, W.hash_seeding(), n_batches=2)
+    if time:
+        p = p.with_(time_edges=np.linspace(0.0, 40.0, time + 1))
+    ref = orc.transport(p, LCG, float_mode=bool(precision), threads=8)
+    for unit in (0, 6000):
+        say("large slice", precision, space, time, unit)
+        raw, _, diag = slab(M, ctx, [p], precision=precision, unit_histories=unit)
+        assert raw == ref.raw and diag[0] == ref.diag
+    nb = M.tally_bins([p])
+    raw = torch.zeros((nb, 2), dtype=torch.uint64, device="cuda:0")
+    flux = torch.zeros(nb, dtype=torch.float64, device="cuda:0")
+    M.run_histories_noalloc(LCG, [p], raw, flux, opts=M.make_opts(precision=precision))
+    torch.cuda.synchronize()
+    assert raw_ints(raw) == ref.raw
