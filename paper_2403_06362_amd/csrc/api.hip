@@ -672,6 +672,13 @@ static double history_cost(const mcrng_problem& P) {
 // 6e7 16384; 512 slabs of 1.35e8 histories 12288 (12.0 ms, 18.2 at 32768), 128
 // of 1.3e7 4096.  The chained kernel pays at the ends of launches only, where
 // units of 32 histories per lane even out the blocks.
+//   Larger blocks take proportionally larger units while there is one for each
+// CU (total / 256), more histories per lane the same: on slabs of 5e3 to 1e7
+// histories, blocks of 64 to 1024 threads, 1 to 4 histories per lane, such units
+// are 1 to 7% slower than the best size of a sweep by powers of two; scaled by
+// block and histories per lane without that bound 1 to 102% (2e4 thick
+// histories on 1024 threads x 4: 1087 us, 389 with it), total / 4096 but at
+// least 512 16 to 58%.
 //   Which of the two an automatic run of one problem takes: the pauses at the
 // ends of units weigh the more the longer histories are, the chained kernel's
 // large units the less the more histories there are.  The line lies at 1.47e7
@@ -689,21 +696,25 @@ constexpr double kChainMinWork = 1.8e9;
 static uint32_t default_unit_histories(const mcrng_problem* P, uint32_t n, const mcrng_run_opts& o) {
     uint64_t total = 0;
     for (uint32_t i = 0; i < n; ++i) total += P[i].n_histories;
-    const double lanes = o.block / 256.0 * o.hist_per_lane;
+    const double block = o.block / 256.0;
     const double root = std::sqrt(static_cast<double>(total));
+    // `best` for a 256-thread block, for this one
+    auto sized = [&](double best) {
+        return std::min(best * block, std::max(best * std::min(block, 1.0), static_cast<double>(total / 256)));
+    };
     double u;
     if (n > 1)
-        u = std::min(1.25 * root, 16384.0) * lanes;
+        u = sized(std::min(1.25 * root, 16384.0));
     else if (chain_possible(P, n, o)) {
         constexpr double per_unit = (kChainMinPerLane - 1) * 256.0;
         if (2 * root < 7680)
-            u = std::min(2 * root, 4096.0) * lanes;
-        else if (total * history_cost(P[0]) >= kChainMinWork || total / 16384 > per_unit * lanes)
-            u = std::min(2 * root, 8192.0) * lanes;
+            u = sized(std::min(2 * root, 4096.0));
+        else if (total * history_cost(P[0]) >= kChainMinWork || total / 16384 > per_unit * block)
+            u = sized(std::min(2 * root, 8192.0));
         else
-            u = per_unit * lanes;
+            u = sized(per_unit);
     } else
-        u = std::min(2 * root, 16384.0) * lanes;
+        u = sized(std::min(2 * root, 16384.0));
     u = std::max(u, static_cast<double>(total / 16384));
     return static_cast<uint32_t>(std::min<uint64_t>(std::max<uint64_t>((static_cast<uint64_t>(u) + 63) & ~63ull, 64), 65536));
 }

@@ -450,3 +450,21 @@ def test_slices_that_fill_lds(M, ctx, orc, precision, space, time):
     M.run_histories_noalloc(LCG, [p], raw, flux, opts=M.make_opts(precision=precision))
     torch.cuda.synchronize()
     assert raw_ints(raw) == ref.raw
+
+
+@pytest.mark.parametrize("hist_per_lane", [1, 4])
+def test_automatic_units_of_large_blocks(M, ctx, hist_per_lane):
+    """A small run on large blocks keeps a unit for each of many of them: about
+    the time of units of 256 histories (within the 1.3 of neighbouring sizes),
+    not the two to three times of a few large ones."""
+    p = W.homogeneous(42.0, 1.0, 0.95, 200, 50_000)
+    ms = {}
+    for unit in (0, 256):
+        say("units of large blocks", hist_per_lane, unit)
+        t = []
+        for _ in range(5):
+            slab(M, ctx, [p], block=1024, hist_per_lane=hist_per_lane, unit_histories=unit)
+            t.append(ctx.last_run_ms())
+        ms[unit] = min(t)
+    say(ms)
+    assert ms[0] < 1.6 * ms[256]
