@@ -90,13 +90,15 @@ __device__ __forceinline__ int step_particle(EventParticle<F32>& e, const Global
         end = in_mask(up) ? END_LEAK_RIGHT : END_LEAK_LEFT;
         e.p.off = 0;   // a cell of the problem again: collide_pass reads every lane's cell from HBM
     }
-    const uint64_t absorbed = o.coll & ~collide_pass<F32>(e.p, C, L, o.coll, up);
-    if (in_mask(o.coll)) {
-        e.colls++;
-        e.draws += in_mask(absorbed) ? 1u : 2u;
-        e.need_tau = !in_mask(absorbed);
+    if (o.coll != 0) {   // (a wave of thin cells seldom has a collision)
+        const uint64_t absorbed = o.coll & ~collide_pass<F32>(e.p, C, L, o.coll, up);
+        if (in_mask(o.coll)) {
+            e.colls++;
+            e.draws += in_mask(absorbed) ? 1u : 2u;
+            e.need_tau = !in_mask(absorbed);
+        }
+        if (in_mask(absorbed)) end = END_ABSORBED;
     }
-    if (in_mask(absorbed)) end = END_ABSORBED;
     if (TIMED && in_mask(o.census)) end = END_CENSUS;
     return end;
 }
