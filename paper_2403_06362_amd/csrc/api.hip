@@ -1715,6 +1715,10 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
         std::vector<std::pair<uint64_t, uint64_t>> ranges;
         std::vector<uint64_t> pieces;   // of the launch's ranges, if more than one
         if (end > begin) ranges.emplace_back(begin, end);
+        // flights of one item: the population grows or dies as e^{(k - 1) sigma t}
+        const double k1 = P->multiplicity * P->scatter - 1.0;
+        const double depth = P->sigma_t * (pp.t_end - (kind == PULSE_ITEMS_COPIES ? pp.t_start : 0.0));
+        const double flights = 1.0 + (k1 + 1.0) * (std::fabs(k1 * depth) < 1e-6 ? depth : std::expm1(k1 * depth) / k1);
         int cur = 0, nxt = 1;   // banks: cur is the launch's input (kind BANK), nxt its output
         uint64_t in_cap = 0, n_bank = 0;
         while (n_bank > 0 || !ranges.empty()) {
@@ -1726,7 +1730,7 @@ static int run_pulse(mcrng_ctx* ctx, const mcrng_lcg* lcg, const mcrng_pulse_pro
                 for (const auto& g : ranges) n += g.second - g.first;
             }
             uint32_t grid = 0;
-            HIP_TRY(pulse_pool_grid(pp, k, pcen, block, n, &grid));
+            HIP_TRY(pulse_pool_grid(pp, k, pcen, block, n, flights, &grid));
             const uint64_t waves = static_cast<uint64_t>(grid) * o.block / 64;
             int r;
             pp.ranges = nullptr;

@@ -154,7 +154,9 @@ hipError_t pulse_fit_rows(PulseParams* p, bool pc, int block);
 // Pool launches (bank schedule).  The grid is chosen first (buffers are sized
 // for its waves); pulse_pool_slack: entries a wave may append to the output
 // bank after it has seen out_budget passed, and census arrivals likewise.
-hipError_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int block, uint64_t items, uint32_t* grid);
+// `flights`: expected flights of an item and all it gives rise to.
+hipError_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int block, uint64_t items, double flights,
+                           uint32_t* grid);
 uint64_t pulse_pool_slack(const PulseParams& p, uint32_t n_max);
 constexpr uint64_t kPulsePoolCensusSlack = 256;
 hipError_t launch_pulse_pool(const PulseParams& p, int items_kind, bool pc, int block, uint32_t grid, hipStream_t st);

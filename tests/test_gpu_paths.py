@@ -468,3 +468,21 @@ def test_automatic_units_of_large_blocks(M, ctx, hist_per_lane):
         ms[unit] = min(t)
     say(ms)
     assert ms[0] < 1.6 * ms[256]
+
+
+def test_small_blocks_of_few_flights(M, ctx):
+    """Sources of little more than one flight each on 64-thread blocks: about as
+    fast as on 256-thread ones (a wave per block costs the ends of four times as
+    many blocks on the run's counters, which made it 1.6 times as long)."""
+    p = W.pulse(W.hash_seeding(), n_batches=1, per_batch=247_334).with_(
+        nu=0.5, scatter=0.5, time_edges=np.linspace(0.0, 5.0, 21))
+    ms = {}
+    for block in (64, 256):
+        say("few flights", block)
+        t = []
+        for _ in range(10):
+            pulse(M, ctx, p, block=block)
+            t.append(ctx.last_run_ms())
+        ms[block] = min(t)
+    say(ms)
+    assert ms[64] < 1.25 * ms[256]
