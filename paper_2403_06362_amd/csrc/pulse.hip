@@ -1877,8 +1877,9 @@ static hipError_t tally_blocks_per_cu(const void* kern, const PulseParams& p, in
 // At most an item per wave and the blocks that fit.  A block ends with atomics
 // on the run's counters and diagnostics, about 15 ns each on one address whoever
 // adds, so blocks of 64 and 128 threads are no more than six per CU (about as
-// many as fit of 256) unless each lane has 32 flights: 247334 sources of 1.3 flights
-// took 177 us on 6144 blocks of 64 threads, 88 on 1536.
+// many as fit of 256) unless each lane has 8 flights: 247334 sources of 1.3 flights
+// took 177 us on 6144 blocks of 64 threads, 88 on 1536 (626051 sources with more
+// flights and 700 uneven bins 1061 us on all that fit, 1313 on 1536).
 hipError_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int block, uint64_t items, double flights,
                            uint32_t* grid) {
     block = bank_block(block);
@@ -1889,7 +1890,7 @@ hipError_t pulse_pool_grid(const PulseParams& p, int items_kind, bool pc, int bl
     uint64_t blocks = (items + waves - 1) / waves;   // an item per wave at least
     const uint64_t cus = static_cast<uint64_t>(device_cus());
     uint64_t cap = cus * static_cast<uint64_t>(per_cu);
-    const double busy = static_cast<double>(items) * flights / (32.0 * block);
+    const double busy = static_cast<double>(items) * flights / (8.0 * block);
     if (block < 256 && busy < static_cast<double>(cap)) cap = std::min(cap, std::max(6 * cus, static_cast<uint64_t>(busy)));
     if (blocks > cap) blocks = cap;
     *grid = static_cast<uint32_t>(blocks < 1 ? 1 : blocks);
