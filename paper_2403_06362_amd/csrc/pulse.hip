@@ -585,7 +585,10 @@ struct WaveTally {
     uint32_t* rows;
     uint32_t* tags;
     uint32_t nt, lane;
+    uint32_t hot, cold;   // MERGE: wave-uniform, iterations to go on merging, iterations without
     __device__ __forceinline__ void begin(const PulseParams& P) {
+        hot = 16u;
+        cold = 0u;
         if (P.rows != 0) {
             for (uint32_t i = lane; i < P.rows * nt; i += 64u) rows[i] = 0u;
             if (lane < 8u) tags[lane] = 0xffffffffu;
@@ -636,12 +639,15 @@ struct WaveTally {
             if (in_mask(near)) atomicAdd(rows + (__umul24(r, nt) + static_cast<uint32_t>(bin)), 1u);
             far &= ~near;
         }
-        if (MERGE && far != 0) {
-            // the first lane's counter, and on while at least four lanes share
-            // one: up to merge_far that fewer share (lanes spread over many
-            // counters then go one by one)
+        // the first lane's counter, and on while at least four lanes share one:
+        // up to merge_far that fewer share.  A wave that met no counter of three
+        // lanes in its last 16 looks in every eighth of its iterations only: 20 x
+        // 5000 sources spread over 600 bins take 433 us (453 looking in each, 370
+        // never), 4 x 200000 in one bin 19 ms either way (197 never).
+        if (MERGE && far != 0 && (hot != 0u || (++cold & 7u) == 0u)) {
             const PulseParams& R = rare_params();
             unsigned long long* const counts = reinterpret_cast<unsigned long long*>(R.counts);
+            hot -= hot != 0u ? 1u : 0u;
             for (uint32_t few = R.merge_far; far != 0 && few != 0u;) {
                 const int l = __builtin_ctzll(far);
                 const uint32_t b = __builtin_amdgcn_readlane(batch, l), i = __builtin_amdgcn_readlane(bin, l);
@@ -651,6 +657,7 @@ struct WaveTally {
                     atomicAdd(counts + (static_cast<uint64_t>(b) * nt + i), static_cast<unsigned long long>(n));
                 far &= ~same;
                 few -= n < 4u ? 1u : 0u;
+                hot = n > 2u ? 16u : hot;
             }
         }
         if (far != 0 && in_mask(far))
@@ -2035,8 +2042,9 @@ hipError_t pulse_fit_rows(PulseParams* p, bool pc, int block) {
     p->rows = p->merge_far = 0;
     if (p->lds_tally) return hipSuccess;
     // Merging pays where few batches' counters may be hit by all waves, and
-    // costs up to 18% where the lanes' counters differ (128 batches of 600 bins:
-    // 1064 against 958 us spread, 15.1 against 18.6 ms all in one bin).  Without
+    // costs up to 18% where the lanes' counters differ (20 batches of 600 bins: 433
+    // against 370 us spread, 4.5 against 9.4 ms in one bin; 128 batches: 1045
+    // against 970 us, 14.7 against 18.6 ms).  Without
     // rows every lane's count comes here: more tries.
     const uint32_t merge = p->n_batches <= kPulseMergeBatches ? 1u : 0u;
     p->merge_far = 3u * merge;
