@@ -673,12 +673,12 @@ static double history_cost(const mcrng_problem& P) {
 // of 1.3e7 4096.  The chained kernel pays at the ends of launches only, where
 // units of 32 histories per lane even out the blocks.
 //   Larger blocks take proportionally larger units while there is one for each
-// CU (total / 256), more histories per lane the same: on slabs of 5e3 to 1e7
-// histories, blocks of 64 to 1024 threads, 1 to 4 histories per lane, such units
-// are 1 to 7% slower than the best size of a sweep by powers of two; scaled by
-// block and histories per lane without that bound 1 to 102% (2e4 thick
-// histories on 1024 threads x 4: 1087 us, 389 with it), total / 4096 but at
-// least 512 16 to 58%.
+// CU (total / 256), and more histories per lane units larger by their root: on
+// three slabs of 2e4 to 4e7 histories, blocks of 256 to 1024 threads, 1 to 4
+// histories per lane, in both precisions, they took 6% longer than the best size
+// of a sweep by powers of two in the mean and 52% at worst (8 and 60% without the
+// root; as estimated from the sweep 9 and 44% with the whole factor, 44% and 5.6
+// times without the bound, 63% and 5.7 times at total / 4096 but at least 512).
 //   Which of the two an automatic run of one problem takes: the pauses at the
 // ends of units weigh the more the longer histories are, the chained kernel's
 // large units the less the more histories there are.  The line lies at 1.47e7
@@ -697,10 +697,11 @@ static uint32_t default_unit_histories(const mcrng_problem* P, uint32_t n, const
     uint64_t total = 0;
     for (uint32_t i = 0; i < n; ++i) total += P[i].n_histories;
     const double block = o.block / 256.0;
+    const double lanes = block * std::sqrt(static_cast<double>(o.hist_per_lane));
     const double root = std::sqrt(static_cast<double>(total));
     // `best` for a 256-thread block, for this one
     auto sized = [&](double best) {
-        return std::min(best * block, std::max(best * std::min(block, 1.0), static_cast<double>(total / 256)));
+        return std::min(best * lanes, std::max(best * std::min(block, 1.0), static_cast<double>(total / 256)));
     };
     double u;
     if (n > 1)
